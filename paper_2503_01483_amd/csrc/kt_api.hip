@@ -143,7 +143,7 @@ static bool launch_gemm(const void* A, int64_t lda, int64_t bsa, int M, const vo
                         int64_t block_stride_a = 0, int64_t block_stride_b = 0, int k_valid = 0) {
   // ATN: A is [K][lda] with the M index along its rows (see gemm_mainloop); K blocking applies to B only
   auto kern = gemm_nt_kernel<TL, Epi, ATN>;
-  constexpr int lds_bytes = ATN ? 2 * (kAtnStageBytes + TL::B_BYTES) : TL::LDS_BYTES;
+  constexpr int lds_bytes = TL::LDS_BYTES;
   // the kernel addresses the rows of a tile with 32-bit byte offsets from the tile's first row
   const int64_t esz = (int64_t)sizeof(typename TL::T);
   if ((ATN ? 127 : TL::BM - 1) * lda * esz + 512 > (int64_t)UINT32_MAX || (TL::BN - 1) * ldb * esz + 128 > (int64_t)UINT32_MAX)

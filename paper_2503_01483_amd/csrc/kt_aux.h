@@ -50,7 +50,7 @@ __global__ __launch_bounds__(256) void transpose_kernel(const Tin* __restrict__ 
 // The token-minor, token-permuted, token-blocked copy of X for 2-byte elements, with
 // 16-byte global accesses on both sides (layout as described at EpiGrad; ldo = tokens per
 // block, a multiple of 128).
-// tile = 128 rows (one token group) x 64 cols; each thread moves four 16-byte chunks in
+// tile = 128 rows (two token groups) x 64 cols; each thread moves four 16-byte chunks in
 // and four out.  Needs cols % 64 == 0, rows_pad % 128 == 0, ldi % 8 == 0, ldo % 8 == 0.
 // grid = (ceil(rows_pad/128), cols/64, batch)
 __global__ __launch_bounds__(256) void transpose16_kernel(const uint16_t* __restrict__ in, int64_t ldi,
@@ -83,10 +83,11 @@ __global__ __launch_bounds__(256) void transpose16_kernel(const uint16_t* __rest
       uint32_t w[4];
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        // output position p of the group holds token (p & 3) * 32 + (p >> 2)
+        // output position p of a 64-token group holds token (p & 3) * 16 + (p & 63) / 4 of it; p is even
         const int p = t8 * 8 + 2 * e;
-        const uint32_t lo = t16[(((p & 3) << 5) + (p >> 2)) * (2 * PITCH) + f];
-        const uint32_t hi = t16[((((p + 1) & 3) << 5) + ((p + 1) >> 2)) * (2 * PITCH) + f];
+        const uint16_t* src = t16 + ((p & 64) + ((p & 3) << 4) + ((p & 63) >> 2)) * (2 * PITCH) + f;
+        const uint32_t lo = src[0];
+        const uint32_t hi = src[16 * (2 * PITCH)];
         w[e] = lo | (hi << 16);
       }
       intx4 v = {(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
@@ -197,7 +198,7 @@ __global__ __launch_bounds__(256) void finalize_rows_kernel(const floatx4* __res
 // dL/dY (chain rule through the kurtosis of Eq. 3; coefficients from finalize_rows_kernel) from a kept Y:
 // GT[i] = grad_value(YT[i], coef of i's token) for every entry of the token-minor
 // layout that EpiMomentsKeep / EpiGrad write (rows = features, blocks of tb tokens, tokens permuted inside
-// groups of 128: position 4 j + k of a group holds token j + 32 k).  A half wave takes one group of 128
+// groups of 64: position 4 j + k of a group holds token j + 16 k).  A half wave takes two groups, 128
 // positions (16 bytes of YT per lane), its four tokens' coefficients stay in registers while it walks
 // FEATS feature rows; the four waves of a workgroup take four runs of feature rows of the same two groups.
 // grid = (ceil(ldt / 256), ceil(d / (4 FEATS)), batch).  Padding tokens (>= n) get alpha = 0, as in EpiGrad.
@@ -213,7 +214,7 @@ __global__ __launch_bounds__(256) void grad_from_y_kernel(const float* __restric
   float alpha[4], mu[4], beta[4], m3[4];
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
-    const int64_t token = group0 + j + 32 * k;
+    const int64_t token = group0 + 64 * (j >> 4) + (j & 15) + 16 * k;
     floatx4 c4 = {0.f, 0.f, 0.f, 0.f};
     if (token < n) c4 = coef[(int64_t)batch * n + token];
     alpha[k] = c4[0]; mu[k] = c4[1]; beta[k] = c4[2]; m3[k] = c4[3];

@@ -50,7 +50,11 @@ __device__ __forceinline__ void c128_gemm_nt(const char* A, const char* B, float
 #pragma unroll
     for (int i = 0; i < 2; ++i)
 #pragma unroll
-      for (int j = 0; j < 2; ++j) Mma<float>::run(fa[i], fb[j], acc[i][j]);
+      for (int j = 0; j < 2; ++j) {
+        const floatx4 a = __builtin_bit_cast(floatx4, fa[i]), b = __builtin_bit_cast(floatx4, fb[j]);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) acc[i][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[e], b[e], acc[i][j], 0, 0, 0);
+      }
   }
 }
 

@@ -16,8 +16,48 @@ template <>
 __device__ __forceinline__ __bf16 from_float<__bf16>(float v) { return (__bf16)v; }
 
 struct EpiBase {
+  static constexpr bool kSwap = false;  // accumulator layout the epilogue takes (Frag)
   __device__ __forceinline__ bool skip(int) const { return false; }
 };
+
+// Sums over the four lane quarters of a wave (a column of a 16-row block is spread over them), on the vector ALU:
+// v_permlane32_swap exchanges the upper half of its first operand with the lower half of the second,
+// v_permlane16_swap the odd quarters of the first with the even ones of the second.
+__device__ __forceinline__ void swap_halves(float& a, float& b) {
+  const auto r = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  a = __uint_as_float(r[0]);
+  b = __uint_as_float(r[1]);
+}
+__device__ __forceinline__ void swap_quarters(float& a, float& b) {
+  const auto r = __builtin_amdgcn_permlane16_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  a = __uint_as_float(r[0]);
+  b = __uint_as_float(r[1]);
+}
+// the sum of the quarters, in every lane
+__device__ __forceinline__ float quarter_sum_all(float x) {
+  float y = x;
+  swap_halves(x, y);
+  x += y;
+  y = x;
+  swap_quarters(x, y);
+  return x + y;
+}
+struct OpAdd { static __device__ __forceinline__ float of(float a, float b) { return a + b; } };
+struct OpMax { static __device__ __forceinline__ float of(float a, float b) { return fmaxf(a, b); } };
+// four values v0..v3 per lane, reduced over the quarters: quarter k ends up with the total of v_k
+template <class Op>
+__device__ __forceinline__ float quarter_reduce4(float v0, float v1, float v2, float v3) {
+  swap_halves(v0, v2);
+  swap_halves(v1, v3);
+  float u0 = Op::of(v0, v2), u1 = Op::of(v1, v3);
+  swap_quarters(u0, u1);
+  return Op::of(u0, u1);
+}
+// v_q of the lane's quarter q
+__device__ __forceinline__ float quarter_pick(int q, float v0, float v1, float v2, float v3) {
+  const float a = (q & 1) ? v1 : v0, b = (q & 1) ? v3 : v2;
+  return (q & 2) ? b : a;
+}
 
 // ---- forward pass: per-token moments of y over the hidden dimension ---------------
 // m = output feature (reduced in registers), n = token (one per lane).
@@ -29,48 +69,52 @@ template <class TL>
 struct EpiMoments : EpiBase {
   floatx4* part;
   int n_tokens, d, P;
-  __device__ __forceinline__ void operator()(floatx16 (&acc)[TL::MB][TL::NB], int batch, int tm,
+  __device__ __forceinline__ void operator()(floatx4 (&acc)[TL::MB][TL::NB], int batch, int tm,
                                              int, int, int m0, int n0) const {
     const Frag<TL> f;
     const int p = tm * TL::WGM + f.wm;
     int blocks = 0;
 #pragma unroll
     for (int mb = 0; mb < TL::MB; ++mb) blocks += (m0 + f.m_block(mb) < d) ? 1 : 0;
-    const float inv_cnt = blocks > 0 ? 1.0f / (float)(32 * blocks) : 0.f;
+    const float inv_cnt = blocks > 0 ? 1.0f / (float)(16 * blocks) : 0.f;
+    // 64 tokens (four blocks of columns) at a time: quarter k of the wave ends up with the sums of block k, i.e.
+    // lane l with those of token l of the 64
 #pragma unroll
-    for (int nb = 0; nb < TL::NB; ++nb) {
-      float s1 = 0.f;
+    for (int g = 0; g < TL::NB / 4; ++g) {
+      float mean[4], s2[4], s3[4], s4[4];
 #pragma unroll
-      for (int mb = 0; mb < TL::MB; ++mb) {
-        if (m0 + f.m_block(mb) < d) {
+      for (int k = 0; k < 4; ++k) {
+        const int nb = 4 * g + k;
+        float s1 = 0.f;
 #pragma unroll
-          for (int r = 0; r < 16; ++r) s1 += acc[mb][nb][r];
+        for (int mb = 0; mb < TL::MB; ++mb) {
+          if (m0 + f.m_block(mb) < d) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) s1 += acc[mb][nb][r];
+          }
         }
-      }
-      s1 += __shfl_xor(s1, 32);
-      const float mean = s1 * inv_cnt;
-      float s2 = 0.f, s3 = 0.f, s4 = 0.f;
+        mean[k] = quarter_sum_all(s1) * inv_cnt;
+        s2[k] = 0.f; s3[k] = 0.f; s4[k] = 0.f;
 #pragma unroll
-      for (int mb = 0; mb < TL::MB; ++mb) {
-        if (m0 + f.m_block(mb) < d) {
+        for (int mb = 0; mb < TL::MB; ++mb) {
+          if (m0 + f.m_block(mb) < d) {
 #pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const float c = acc[mb][nb][r] - mean;
-            const float c2 = c * c;
-            s2 += c2;
-            s3 = fmaf(c2, c, s3);
-            s4 = fmaf(c2, c2, s4);
+            for (int r = 0; r < 4; ++r) {
+              const float c = acc[mb][nb][r] - mean[k];
+              const float c2 = c * c;
+              s2[k] += c2;
+              s3[k] = fmaf(c2, c, s3[k]);
+              s4[k] = fmaf(c2, c2, s4[k]);
+            }
           }
         }
       }
-      s2 += __shfl_xor(s2, 32);
-      s3 += __shfl_xor(s3, 32);
-      s4 += __shfl_xor(s4, 32);
-      const int token = n0 + f.n_of(nb);
-      if (f.half == 0 && token < n_tokens) {
-        floatx4 v = {mean, s2, s3, s4};
-        part[((int64_t)batch * P + p) * n_tokens + token] = v;
-      }
+      const int token = n0 + f.wn * TL::WTN + 64 * g + f.lane;
+      const floatx4 v = {quarter_pick(f.q, mean[0], mean[1], mean[2], mean[3]),
+                         quarter_reduce4<OpAdd>(s2[0], s2[1], s2[2], s2[3]),
+                         quarter_reduce4<OpAdd>(s3[0], s3[1], s3[2], s3[3]),
+                         quarter_reduce4<OpAdd>(s4[0], s4[1], s4[2], s4[3])};
+      if (token < n_tokens) part[((int64_t)batch * P + p) * n_tokens + token] = v;
     }
   }
 };
@@ -79,18 +123,19 @@ struct EpiMoments : EpiBase {
 // coef[token] = {alpha, mu, beta, m3};  g = alpha * (c (c^2 - beta) - m3), c = y - mu.
 //
 // Layout of GT (and of the token-minor copy of X that meets it in dR = X^T G): rows are
-// features, and inside every group of 128 tokens the tokens are PERMUTED,
-//     position(t) = (t & 31) * 4 + ((t & 127) >> 5),
+// features, and inside every group of 64 tokens the tokens are PERMUTED,
+//     position(t) = (t & 15) * 4 + ((t & 63) >> 4),
 // because the contraction over tokens does not care in which order the tokens come as
 // long as both operands agree.  In the accumulator layout a lane owns tokens
-// t, t+32, t+64, t+96 of a group, so with this order its values for one feature are
-// ADJACENT in memory: one 8-byte store per feature instead of four 2-byte ones, and 32
-// lanes cover 256 contiguous bytes.  Tokens in [n_tokens, ldt) are written as zero so the
-// padded K range contributes nothing; ldt is a multiple of 128.
+// t, t+16, t+32, t+48 of a group, so with this order its values for one feature are
+// ADJACENT in memory: one 8-byte store per feature instead of four 2-byte ones, and the 16
+// lanes of a quarter cover 128 contiguous bytes (256 of an fp32 copy).  Tokens in
+// [n_tokens, ldt) are written as zero so the padded K range contributes nothing; ldt is a
+// multiple of 128.
 // Rows are stored in blocks of tb tokens (tb a multiple of 128): position p of feature f
 // lives at  (p / tb) * d * tb + f * tb + p % tb  (one block, tb = ldt, is the plain layout).
 __host__ __device__ __forceinline__ int64_t token_position(int64_t t) {
-  return (t & ~(int64_t)127) + ((t & 31) << 2) + ((t & 127) >> 5);
+  return (t & ~(int64_t)63) + ((t & 15) << 2) + ((t & 63) >> 4);
 }
 
 // dL/dy of one entry from the row's coefficients {alpha, mu, beta, m3}; alpha = 0 (padding tokens, rows
@@ -108,37 +153,37 @@ struct EpiGrad : EpiBase {
   T* GT;
   int64_t ldt, tb, batch_stride;
   int n_tokens, d;
-  static_assert(TL::BN % 128 == 0 && (TL::WTN == 128 || TL::WTN == 64), "token groups are 128 wide");
-  __device__ __forceinline__ void operator()(floatx16 (&acc)[TL::MB][TL::NB], int batch, int,
+  __device__ __forceinline__ void operator()(floatx4 (&acc)[TL::MB][TL::NB], int batch, int,
                                              int, int, int m0, int n0) const {
-    typedef T vecT __attribute__((ext_vector_type(TL::NB)));
+    typedef T vecT __attribute__((ext_vector_type(4)));
     const Frag<TL> f;
-    const int wave_tok0 = n0 + f.wn * TL::WTN;            // first token of this wave
-    const int group0 = wave_tok0 & ~127;                   // its 128-token group
-    if (group0 >= ldt) return;
-    // lane's tokens: wave_tok0 + nb*32 + (lane & 31); positions are consecutive in nb
-    const int64_t pos0 = group0 + ((f.lane & 31) << 2) + ((wave_tok0 & 127) >> 5);
-    const int64_t blk = pos0 / tb;
-    T* out = GT + (int64_t)batch * batch_stride + blk * d * tb + (pos0 - blk * tb);
-    float alpha[TL::NB], mu[TL::NB], beta[TL::NB], m3[TL::NB];
 #pragma unroll
-    for (int nb = 0; nb < TL::NB; ++nb) {
-      const int token = n0 + f.n_of(nb);
-      floatx4 c4 = {0.f, 0.f, 0.f, 0.f};  // alpha = 0 zeroes the padding tokens
-      if (token < n_tokens) c4 = coef[(int64_t)batch * n_tokens + token];
-      alpha[nb] = c4[0]; mu[nb] = c4[1]; beta[nb] = c4[2]; m3[nb] = c4[3];
-    }
+    for (int g = 0; g < TL::NB / 4; ++g) {
+      const int group0 = n0 + f.wn * TL::WTN + 64 * g;  // the 64-token group
+      if (group0 >= ldt) return;
+      const int64_t pos0 = group0 + (f.l16 << 2);  // the lane's tokens group0 + 16 k + l16 lie at pos0 + k
+      const int64_t blk = pos0 / tb;
+      T* out = GT + (int64_t)batch * batch_stride + blk * d * tb + (pos0 - blk * tb);
+      float alpha[4], mu[4], beta[4], m3[4];
 #pragma unroll
-    for (int mb = 0; mb < TL::MB; ++mb) {
-      if (m0 + f.m_block(mb) < d) {
+      for (int k = 0; k < 4; ++k) {
+        const int token = group0 + 16 * k + f.l16;
+        floatx4 c4 = {0.f, 0.f, 0.f, 0.f};  // alpha = 0 zeroes the padding tokens
+        if (token < n_tokens) c4 = coef[(int64_t)batch * n_tokens + token];
+        alpha[k] = c4[0]; mu[k] = c4[1]; beta[k] = c4[2]; m3[k] = c4[3];
+      }
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          vecT v;
+      for (int mb = 0; mb < TL::MB; ++mb) {
+        if (m0 + f.m_block(mb) < d) {
 #pragma unroll
-          for (int nb = 0; nb < TL::NB; ++nb)  // (the accumulators of padding tokens come from re-read valid rows and are finite)
-            v[nb] = from_float<T>(grad_value(acc[mb][nb][r], alpha[nb], mu[nb], beta[nb], m3[nb]));
-          const int feat = m0 + f.m_of(mb, r);
-          *reinterpret_cast<vecT*>(out + (int64_t)feat * tb) = v;
+          for (int r = 0; r < 4; ++r) {
+            vecT v;
+#pragma unroll
+            for (int k = 0; k < 4; ++k)  // (the accumulators of padding tokens come from re-read valid rows and are finite)
+              v[k] = from_float<T>(grad_value(acc[mb][4 * g + k][r], alpha[k], mu[k], beta[k], m3[k]));
+            const int feat = m0 + f.m_of(mb, r);
+            *reinterpret_cast<vecT*>(out + (int64_t)feat * tb) = v;
+          }
         }
       }
     }
@@ -146,8 +191,8 @@ struct EpiGrad : EpiBase {
 };
 
 // ---- forward pass that also keeps Y = X R ("Learning the Rotations"): the moments of EpiMoments (Eq. 3), and the fp32 accumulators written
-// in the layout of GT above (features on the rows, tokens permuted inside groups of 128, blocks of tb
-// tokens): one 16-byte store per lane and feature.  grad_from_y_kernel then turns YT into GT entry by
+// in the layout of GT above (features on the rows, tokens permuted inside groups of 64, blocks of tb
+// tokens): one 16-byte store per lane, feature and group, 256 contiguous bytes per feature.  grad_from_y_kernel then turns YT into GT entry by
 // entry, which replaces the recompute GEMM of the backward pass (same accumulators, same arithmetic: the
 // gradient is bit-identical) at the price of n d 4 bytes of scratch, one write and one read of them.
 template <class TL>
@@ -155,27 +200,25 @@ struct EpiMomentsKeep : EpiBase {
   EpiMoments<TL> mom;
   float* YT;
   int64_t ldt, tb, batch_stride;  // batch_stride in elements of YT
-  static_assert(TL::BN % 128 == 0 && (TL::WTN == 128 || TL::WTN == 64), "token groups are 128 wide");
-  __device__ __forceinline__ void operator()(floatx16 (&acc)[TL::MB][TL::NB], int batch, int tm,
+  __device__ __forceinline__ void operator()(floatx4 (&acc)[TL::MB][TL::NB], int batch, int tm,
                                              int tn, int ks, int m0, int n0) const {
     mom(acc, batch, tm, tn, ks, m0, n0);
-    typedef float vecF __attribute__((ext_vector_type(TL::NB)));
     const Frag<TL> f;
-    const int wave_tok0 = n0 + f.wn * TL::WTN;
-    const int group0 = wave_tok0 & ~127;
-    if (group0 >= ldt) return;
-    const int64_t pos0 = group0 + ((f.lane & 31) << 2) + ((wave_tok0 & 127) >> 5);
-    const int64_t blk = pos0 / tb;
-    float* out = YT + (int64_t)batch * batch_stride + blk * mom.d * tb + (pos0 - blk * tb);
 #pragma unroll
-    for (int mb = 0; mb < TL::MB; ++mb) {
-      if (m0 + f.m_block(mb) < mom.d) {
+    for (int g = 0; g < TL::NB / 4; ++g) {
+      const int group0 = n0 + f.wn * TL::WTN + 64 * g;
+      if (group0 >= ldt) return;
+      const int64_t pos0 = group0 + (f.l16 << 2);
+      const int64_t blk = pos0 / tb;
+      float* out = YT + (int64_t)batch * batch_stride + blk * mom.d * tb + (pos0 - blk * tb);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          vecF v;
+      for (int mb = 0; mb < TL::MB; ++mb) {
+        if (m0 + f.m_block(mb) < mom.d) {
 #pragma unroll
-          for (int nb = 0; nb < TL::NB; ++nb) v[nb] = acc[mb][nb][r];
-          *reinterpret_cast<vecF*>(out + (int64_t)(m0 + f.m_of(mb, r)) * tb) = v;
+          for (int r = 0; r < 4; ++r) {
+            const floatx4 v = {acc[mb][4 * g][r], acc[mb][4 * g + 1][r], acc[mb][4 * g + 2][r], acc[mb][4 * g + 3][r]};
+            *reinterpret_cast<floatx4*>(out + (int64_t)(m0 + f.m_of(mb, r)) * tb) = v;
+          }
         }
       }
     }
@@ -190,55 +233,35 @@ struct EpiStore : EpiBase {
   int64_t ldc, batch_stride, split_stride;
   int M, N;
   float alpha = 1.f;  // C = alpha * acc
-  // An accumulator block leaves the matrix pipe with one COLUMN per lane (4 consecutive rows in 4 registers), so
-  // a direct store is a 4-byte store per lane, 256 of them per wave and tile, and the address path handles
-  // each at the same rate as a 16-byte one.  Here every 8 x 32 piece (4 registers of the two wave halves)
-  // passes through a 1.1 KiB buffer of the wave's own in LDS and comes back as 16 bytes per lane, 8 lanes
-  // to a 128-byte row piece: 64 stores per wave and tile, each of 8 whole 128-byte lines.
-  static constexpr int kPieceWords = 8 * 32 + 32;  // rows 4..7 sit 32 words further: the two halves hit different banks
-  static constexpr int kPieceBufs = 4;
-  static_assert(TL::NT / 64 * kPieceBufs * kPieceWords * 4 <= TL::LDS_BYTES, "piece buffers must fit the operand LDS");
-  __device__ __forceinline__ void operator()(floatx16 (&acc)[TL::MB][TL::NB], int batch, int,
+  // operands swapped: a lane owns four consecutive columns of one row of every block, so the tile leaves as 16-byte
+  // stores straight from the accumulators (a store instruction covers 16 rows x 64 bytes, the block beside it the
+  // other half of those 128-byte lines)
+  static constexpr bool kSwap = true;
+  __device__ __forceinline__ void operator()(floatx4 (&acc)[TL::MB][TL::NB], int batch, int,
                                              int, int ks, int m0, int n0) const {
     const Frag<TL> f;
     float* base = C + (int64_t)ks * split_stride + (int64_t)batch * batch_stride;
     // 16-byte stores need aligned rows and whole groups of 4 columns inside N (uniform over the launch)
     const bool vec = ((reinterpret_cast<uintptr_t>(base) | (uintptr_t)(ldc * 4)) & 15) == 0 && (N & 3) == 0;
-    if (!vec) {
 #pragma unroll
-      for (int mb = 0; mb < TL::MB; ++mb)
+    for (int mb = 0; mb < TL::MB; ++mb) {
+      const int m = m0 + f.m_row(mb);
+      if (m < M) {
+        float* row = base + (int64_t)m * ldc;
 #pragma unroll
         for (int nb = 0; nb < TL::NB; ++nb) {
-          const int n = n0 + f.n_of(nb);
+          const int n = n0 + f.n_quad(nb);
+          const floatx4 v = alpha * acc[mb][nb];
+          if (vec) {
+            if (n < N) *reinterpret_cast<floatx4*>(row + n) = v;
+          } else {
 #pragma unroll
-          for (int r = 0; r < 16; ++r) {
-            const int m = m0 + f.m_of(mb, r);
-            if (m < M && n < N) base[(int64_t)m * ldc + n] = alpha * acc[mb][nb][r];
+            for (int r = 0; r < 4; ++r)
+              if (n + r < N) row[n + r] = v[r];
           }
         }
-      return;
+      }
     }
-    extern __shared__ __align__(16) char lds_raw[];
-    __syncthreads();  // every wave has read its last operand slab: the LDS is free
-    float* buf = reinterpret_cast<float*>(lds_raw) + (threadIdx.x >> 6) * (kPieceBufs * kPieceWords);
-    const int wofs = f.half * 160 + (f.lane & 31);  // register i of this lane -> row 4 half + i, column lane % 32
-    const int rrow = f.lane >> 3, rcol = 4 * (f.lane & 7);
-    const int rofs = rrow * 32 + (rrow >> 2) * 32 + rcol;
-#pragma unroll
-    for (int mb = 0; mb < TL::MB; ++mb)
-#pragma unroll
-      for (int nb = 0; nb < TL::NB; ++nb)
-#pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          float* b = buf + (((mb * TL::NB + nb) * 4 + g) % kPieceBufs) * kPieceWords;
-#pragma unroll
-          for (int i = 0; i < 4; ++i) b[wofs + 32 * i] = alpha * acc[mb][nb][4 * g + i];
-          // the wave's LDS operations complete in order: no barrier between its own writes and reads
-          const float4 v = *reinterpret_cast<const float4*>(b + rofs);
-          const int m = m0 + f.m_block(mb) + 8 * g + rrow;
-          const int n = n0 + f.wn * TL::WTN + nb * 32 + rcol;
-          if (m < M && n < N) *reinterpret_cast<float4*>(base + (int64_t)m * ldc + n) = v;
-        }
   }
 };
 
@@ -299,6 +322,7 @@ struct EpiCayleyIter {
   int d, it, max_iters;
   float tol;
   const float* bscale = nullptr;  // acc is scaled by bscale[4 * batch + 3] when given (Cayley Adam)
+  static constexpr bool kSwap = true;  // four consecutive columns of a row per lane: 16-byte accesses
   __device__ __forceinline__ bool skip(int batch) const {
     if (it == 0) return false;
     const unsigned* dl = delta + (int64_t)batch * max_iters;
@@ -307,7 +331,7 @@ struct EpiCayleyIter {
     if (blockIdx.x == 0 && threadIdx.x == 0) delta[(int64_t)batch * max_iters + it] = 0u;
     return true;
   }
-  __device__ __forceinline__ void operator()(floatx16 (&acc)[TL::MB][TL::NB], int batch, int,
+  __device__ __forceinline__ void operator()(floatx4 (&acc)[TL::MB][TL::NB], int batch, int,
                                              int, int, int m0, int n0) const {
     const Frag<TL> f;
     const int64_t bo = (int64_t)batch * d * d;
@@ -317,27 +341,33 @@ struct EpiCayleyIter {
     for (int mb = 0; mb < TL::MB; ++mb)
 #pragma unroll
       for (int nb = 0; nb < TL::NB; ++nb) {
-        const int n = n0 + f.n_of(nb);
+        const int m = m0 + f.m_row(mb), n = n0 + f.n_quad(nb);
+        if (m < d && n < d) {  // d is a multiple of 128: all four columns are inside or none
+          const int64_t idx = bo + (int64_t)m * d + n;
+          const floatx4 rt = *reinterpret_cast<const floatx4*>(Rt + idx);
+          const floatx4 zo = *reinterpret_cast<const floatx4*>(Zt + idx);
+          floatx4 z, u;
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int m = m0 + f.m_of(mb, r);
-          if (m < d && n < d) {
-            const int64_t idx = bo + (int64_t)m * d + n;
-            const float rt = Rt[idx];
-            const float z = rt - bs * acc[mb][nb][r];
-            dmax = umax(dmax, abs_bits(z - Zt[idx]));
-            Zt[idx] = z;
-            const float u = rt + z;
-            if (Usplit) {
-              const int64_t so = 3 * bo + (int64_t)m * 3 * d + n;
-              const __bf16 hi = (__bf16)u;
-              const __bf16 lo = (__bf16)(u - (float)hi);
-              Usplit[so] = hi;
-              Usplit[so + d] = hi;
-              Usplit[so + 2 * d] = lo;
-            } else {
-              Unew[idx] = u;
+          for (int r = 0; r < 4; ++r) {
+            z[r] = rt[r] - bs * acc[mb][nb][r];
+            dmax = umax(dmax, abs_bits(z[r] - zo[r]));
+            u[r] = rt[r] + z[r];
+          }
+          *reinterpret_cast<floatx4*>(Zt + idx) = z;
+          if (Usplit) {
+            typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+            const int64_t so = 3 * bo + (int64_t)m * 3 * d + n;
+            bf16x4 hi, lo;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              hi[r] = (__bf16)u[r];
+              lo[r] = (__bf16)(u[r] - (float)hi[r]);
             }
+            *reinterpret_cast<bf16x4*>(Usplit + so) = hi;
+            *reinterpret_cast<bf16x4*>(Usplit + so + d) = hi;
+            *reinterpret_cast<bf16x4*>(Usplit + so + 2 * d) = lo;
+          } else {
+            *reinterpret_cast<floatx4*>(Unew + idx) = u;
           }
         }
       }
@@ -365,7 +395,7 @@ template <class TL>
 struct EpiOrtho : EpiBase {
   unsigned* err;  // [batch], bit pattern of a non-negative float, zeroed before launch
   int d;
-  __device__ __forceinline__ void operator()(floatx16 (&acc)[TL::MB][TL::NB], int batch, int,
+  __device__ __forceinline__ void operator()(floatx4 (&acc)[TL::MB][TL::NB], int batch, int,
                                              int, int, int m0, int n0) const {
     const Frag<TL> f;
     unsigned e = 0u;
@@ -375,7 +405,7 @@ struct EpiOrtho : EpiBase {
       for (int nb = 0; nb < TL::NB; ++nb) {
         const int n = n0 + f.n_of(nb);
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
+        for (int r = 0; r < 4; ++r) {
           const int m = m0 + f.m_of(mb, r);
           if (m < d && n < d && m != n) e = umax(e, abs_bits(acc[mb][nb][r]));
         }
@@ -391,22 +421,26 @@ template <class TL>
 struct EpiAmax : EpiBase {
   float* part;
   int n_tokens, d, P;
-  __device__ __forceinline__ void operator()(floatx16 (&acc)[TL::MB][TL::NB], int batch, int tm,
+  __device__ __forceinline__ void operator()(floatx4 (&acc)[TL::MB][TL::NB], int batch, int tm,
                                              int, int, int m0, int n0) const {
     const Frag<TL> f;
     const int p = tm * TL::WGM + f.wm;
 #pragma unroll
-    for (int nb = 0; nb < TL::NB; ++nb) {
-      float a = 0.f;
+    for (int g = 0; g < TL::NB / 4; ++g) {  // 64 tokens: lane l ends up with token l of them
+      float a[4];
 #pragma unroll
-      for (int mb = 0; mb < TL::MB; ++mb)
-        if (m0 + f.m_block(mb) < d) {
+      for (int k = 0; k < 4; ++k) {
+        a[k] = 0.f;
 #pragma unroll
-          for (int r = 0; r < 16; ++r) a = fmaxf(a, fabsf(acc[mb][nb][r]));
-        }
-      a = fmaxf(a, __shfl_xor(a, 32));
-      const int token = n0 + f.n_of(nb);
-      if (f.half == 0 && token < n_tokens) part[((int64_t)batch * P + p) * n_tokens + token] = a;
+        for (int mb = 0; mb < TL::MB; ++mb)
+          if (m0 + f.m_block(mb) < d) {
+#pragma unroll
+            for (int r = 0; r < 4; ++r) a[k] = fmaxf(a[k], fabsf(acc[mb][4 * g + k][r]));
+          }
+      }
+      const float v = quarter_reduce4<OpMax>(a[0], a[1], a[2], a[3]);
+      const int token = n0 + f.wn * TL::WTN + 64 * g + f.lane;
+      if (token < n_tokens) part[((int64_t)batch * P + p) * n_tokens + token] = v;
     }
   }
 };
@@ -414,8 +448,8 @@ struct EpiAmax : EpiBase {
 // ---- fake-quant pass B: quantise the recomputed y ----------------------------------
 // Same orientation as the moment epilogue (token on the lane, features on the registers): the
 // scale and its reciprocal are taken once per token, the error sums accumulate in registers and
-// meet only the other half-wave, and the codes leave as 16-byte stores (a lane and its partner in
-// the other half-wave exchange two packed words first).  q = clamp(rint(y * (1/s)), -7, 7) in fp32;
+// meet only the other lane quarters, and the codes leave as 16-byte stores (the four lanes of a
+// token exchange packed words over four blocks first).  q = clamp(rint(y * (1/s)), -7, 7) in fp32;
 // pe[(batch*P + p)*n_tokens + token] = {sum (y - q s)^2, sum y^2} over the wave's feature rows.
 template <class TL>
 struct EpiQuant : EpiBase {
@@ -423,53 +457,59 @@ struct EpiQuant : EpiBase {
   int8_t* codes;        // [batch][n_tokens][d] or null
   float2* err_part;     // or null
   int n_tokens, d, P;
-  __device__ __forceinline__ void operator()(floatx16 (&acc)[TL::MB][TL::NB], int batch, int tm,
+  __device__ __forceinline__ void operator()(floatx4 (&acc)[TL::MB][TL::NB], int batch, int tm,
                                              int, int, int m0, int n0) const {
     const Frag<TL> f;
     const int p = tm * TL::WGM + f.wm;
+    static_assert(TL::MB % 4 == 0, "codes leave four blocks at a time");
 #pragma unroll
-    for (int nb = 0; nb < TL::NB; ++nb) {
-      const int token = n0 + f.n_of(nb);
-      const bool tv = token < n_tokens;
-      const float s = tv ? scales[(int64_t)batch * n_tokens + token] : 0.f;
-      const bool live = s > 0.f;
-      const float rinv = live ? __fdiv_rn(1.0f, s) : 0.f;
-      int8_t* crow = codes + ((int64_t)batch * n_tokens + token) * d;
-      float e2 = 0.f, y2 = 0.f;
+    for (int g = 0; g < TL::NB / 4; ++g) {
+      float e2[4], y2[4];
 #pragma unroll
-      for (int mb = 0; mb < TL::MB; ++mb) {
-        if (m0 + f.m_block(mb) < d) {
-          unsigned pk[4];
+      for (int k = 0; k < 4; ++k) {
+        const int token = n0 + f.n_of(4 * g + k);
+        const bool tv = token < n_tokens;
+        const float s = tv ? scales[(int64_t)batch * n_tokens + token] : 0.f;
+        const bool live = s > 0.f;
+        const float rinv = live ? __fdiv_rn(1.0f, s) : 0.f;
+        int8_t* crow = codes + ((int64_t)batch * n_tokens + token) * d;
+        e2[k] = 0.f; y2[k] = 0.f;
 #pragma unroll
-          for (int g = 0; g < 4; ++g) {
-            unsigned pack = 0u;
+        for (int m4 = 0; m4 < TL::MB / 4; ++m4) {
+          if (m0 + f.m_block(4 * m4) < d) {  // d is a multiple of 128: the four blocks are inside together
+            float pk[4];
 #pragma unroll
-            for (int e = 0; e < 4; ++e) {
-              const float y = acc[mb][nb][4 * g + e];
-              float q = rintf(__fmul_rn(y, rinv));
-              q = fminf(fmaxf(q, -7.f), 7.f);
-              if (!live) q = 0.f;
-              const float diff = y - q * s;
-              e2 = fmaf(diff, diff, e2);
-              y2 = fmaf(y, y, y2);
-              pack |= ((unsigned)(int)q & 0xffu) << (8 * e);
+            for (int i = 0; i < 4; ++i) {
+              unsigned pack = 0u;
+#pragma unroll
+              for (int e = 0; e < 4; ++e) {
+                const float y = acc[4 * m4 + i][4 * g + k][e];
+                float qv = rintf(__fmul_rn(y, rinv));
+                qv = fminf(fmaxf(qv, -7.f), 7.f);
+                if (!live) qv = 0.f;
+                const float diff = y - qv * s;
+                e2[k] = fmaf(diff, diff, e2[k]);
+                y2[k] = fmaf(y, y, y2[k]);
+                pack |= ((unsigned)(int)qv & 0xffu) << (8 * e);
+              }
+              pk[i] = __uint_as_float(pack);
             }
-            pk[g] = pack;
+            // word i of quarter c = features 16 i + 4 c .. + 3 of these 64: transposed among the four lanes of the
+            // token, quarter c holds all 16 bytes of block c
+            swap_halves(pk[0], pk[2]);
+            swap_halves(pk[1], pk[3]);
+            swap_quarters(pk[0], pk[1]);
+            swap_quarters(pk[2], pk[3]);
+            const uintx4 out = {__float_as_uint(pk[0]), __float_as_uint(pk[1]), __float_as_uint(pk[2]), __float_as_uint(pk[3])};
+            if (codes && tv) *reinterpret_cast<uintx4*>(crow + m0 + f.m_block(4 * m4) + 16 * f.q) = out;
           }
-          // the lane and its partner (lane ^ 32) own alternate groups of four features: two words change
-          // hands, then the lower half-wave stores bytes 0..15 of the 32-feature block, the upper 16..31
-          const unsigned r0 = (unsigned)__shfl_xor((int)(f.half ? pk[0] : pk[2]), 32);
-          const unsigned r1 = (unsigned)__shfl_xor((int)(f.half ? pk[1] : pk[3]), 32);
-          uintx4 out;
-          if (f.half == 0) out = uintx4{pk[0], r0, pk[1], r1};
-          else out = uintx4{r0, pk[2], r1, pk[3]};
-          if (codes && tv) *reinterpret_cast<uintx4*>(crow + m0 + f.m_block(mb) + 16 * f.half) = out;
         }
       }
       if (err_part) {
-        e2 += __shfl_xor(e2, 32);
-        y2 += __shfl_xor(y2, 32);
-        if (f.half == 0 && tv) err_part[((int64_t)batch * P + p) * n_tokens + token] = make_float2(e2, y2);
+        const float2 v = make_float2(quarter_reduce4<OpAdd>(e2[0], e2[1], e2[2], e2[3]),
+                                     quarter_reduce4<OpAdd>(y2[0], y2[1], y2[2], y2[3]));
+        const int token = n0 + f.wn * TL::WTN + 64 * g + f.lane;
+        if (token < n_tokens) err_part[((int64_t)batch * P + p) * n_tokens + token] = v;
       }
     }
   }

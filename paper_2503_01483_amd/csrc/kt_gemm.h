@@ -8,16 +8,24 @@
 // forward passes and feature-major (token-minor) copies feed X^T * G.
 //
 // Tiling: 64-wide wavefronts, each wave owns WTM x WTN of the tile as a grid of
-// 32x32 MFMA blocks (v_mfma_f32_32x32x16_bf16, or 4 x v_mfma_f32_32x32x2_f32 per
+// 16x16 MFMA blocks (v_mfma_f32_16x16x32_bf16, or 4 x v_mfma_f32_16x16x4_f32 per
 // 16-byte fragment on the fp32 path).  In the accumulator layout of these
-// instructions a lane owns ONE column n (= lane & 31) and 16 rows
-// m = 8*(r/4) + 4*(lane>>5) + (r&3), r = 0..15.  Callers put the index they
-// reduce over (the hidden dimension of a token row) on m, so row statistics
-// accumulate in registers with no cross-lane traffic until one final shuffle.
+// instructions a lane owns ONE column n (= lane & 15) and 4 consecutive rows
+// m = 4*(lane>>4) + r, r = 0..3.  Callers put the index they reduce over (the hidden
+// dimension of a token row) on m, so row statistics accumulate in registers with no
+// cross-lane traffic until one final exchange between the four lane quarters; callers
+// that store C row-major take the operands in swapped order (SWAP) and own four
+// consecutive columns of one row instead.
 //
-// LDS: each stage holds BM + BN rows of 128 bytes of K; 16-byte chunks are
-// XOR-swizzled with the row pair so both the 16-byte stores and the MFMA fragment
-// reads are bank-conflict free.  Two stages, register prefetch of the next K slab.
+// Why 16x16x32 and not 32x32x16: both issue at the same 1024 flop per cycle and SIMD, but
+// the large products here run at the board's power limit, and per flop the 16x16 form reads
+// and writes half as many accumulator words.  Matrix instructions alone, random bf16
+// operands, 256 accumulator registers per lane, whole chip: 2075 TFLOP/s against 1800 (all-zero
+// operands: 2475 for both, the 2.4 GHz clock).
+//
+// LDS: stages of 128 bytes of K (a slab) per row, two of the A operand's rows and three of the B
+// operand's, filled straight from global memory (buffer_load ... lds); 16-byte chunks are
+// XOR-swizzled with the row pair so that the MFMA fragment reads are bank-conflict free.
 #pragma once
 #include <hip/hip_runtime.h>
 #include <stdint.h>
@@ -32,31 +40,47 @@ typedef float floatx4 __attribute__((ext_vector_type(4)));
 typedef int intx4 __attribute__((ext_vector_type(4)));
 typedef unsigned uintx4 __attribute__((ext_vector_type(4)));
 
-constexpr int kRowBytes = 128;  // bytes of K per LDS tile row
-constexpr int kChunks = 8;      // 16-byte chunks per row
+constexpr int kRowBytes = 128;  // bytes of K per LDS tile row: a slab, the unit in which K is counted and blocked
+constexpr int kStagesA = 2, kStagesB = 3;
 
 template <typename T>
 struct Mma;
 
+// One 16x16 block, one 16-byte fragment of each operand per lane: lane l holds row l & 15 and the
+// 16 bytes of K at chunk l >> 4 (bf16: K = 32 in one instruction; fp32: K = 16 in four, each taking
+// one of the four values; which value of K is multiplied in which instruction does not matter as
+// long as both operands agree).
+//
+// The bf16 instruction is inline assembly so that its accumulators stay in accumulation registers: the 64
+// blocks of a 128 x 128 wave tile are all 256 of them, and left to the register allocator (builtin) the
+// loop body moved ~950 accumulators between the two files and spilled 130-185 registers.  The compiler
+// does not know it is a matrix instruction: accumulators are read by anything else only behind
+// settle(), and the fragments are only ever written by LDS reads.
 template <>
 struct Mma<__bf16> {
-  static __device__ __forceinline__ void run(const intx4& a, const intx4& b, floatx16& c) {
-    c = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, a),
-                                                __builtin_bit_cast(bf16x8, b), c, 0, 0, 0);
+  static __device__ __forceinline__ void run(const intx4& a, const intx4& b, floatx4& c) {
+    asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
   }
 };
 
 template <>
 struct Mma<float> {
-  static __device__ __forceinline__ void run(const intx4& a, const intx4& b, floatx16& c) {
+  static __device__ __forceinline__ void run(const intx4& a, const intx4& b, floatx4& c) {
     const floatx4 fa = __builtin_bit_cast(floatx4, a);
     const floatx4 fb = __builtin_bit_cast(floatx4, b);
-    c = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[0], fb[0], c, 0, 0, 0);
-    c = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[1], fb[1], c, 0, 0, 0);
-    c = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[2], fb[2], c, 0, 0, 0);
-    c = __builtin_amdgcn_mfma_f32_32x32x2f32(fa[3], fb[3], c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[0], fb[0], c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[1], fb[1], c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[2], fb[2], c, 0, 0, 0);
+    c = __builtin_amdgcn_mfma_f32_16x16x4f32(fa[3], fb[3], c, 0, 0, 0);
   }
 };
+
+// Holds every use of these accumulators behind this point (after the matrix instructions: 16 wait states, more than
+// the 8-pass forms need before another instruction type reads their result).
+template <typename T>
+__device__ __forceinline__ void settle(floatx4& c0, floatx4& c1, floatx4& c2, floatx4& c3) {
+  if constexpr (sizeof(T) == 2) asm volatile("s_nop 15" : "+a"(c0), "+a"(c1), "+a"(c2), "+a"(c3));
+}
 
 // Tile shape: BM x BN per workgroup, WGM x WGN waves.
 template <typename T_, int BM_, int BN_, int WGM_, int WGN_>
@@ -65,26 +89,21 @@ struct Tile {
   static constexpr int BM = BM_, BN = BN_, WGM = WGM_, WGN = WGN_;
   static constexpr int NT = WGM * WGN * 64;
   static constexpr int WTM = BM / WGM, WTN = BN / WGN;
-  static constexpr int MB = WTM / 32, NB = WTN / 32;
+  static constexpr int MB = WTM / 16, NB = WTN / 16;
   static constexpr int BK = kRowBytes / (int)sizeof(T);  // elements of K per slab
   static constexpr int A_BYTES = BM * kRowBytes, B_BYTES = BN * kRowBytes;
-  static constexpr int STAGE_BYTES = A_BYTES + B_BYTES;
-  static constexpr int LDS_BYTES = 2 * STAGE_BYTES;
-  static constexpr int A_LD = BM * kChunks / NT;  // 16-byte loads per thread per slab
-  static constexpr int B_LD = BN * kChunks / NT;
-  static_assert(BM % (32 * WGM) == 0 && BN % (32 * WGN) == 0, "wave tile must be 32-blocked");
-  static_assert((BM * kChunks) % NT == 0 && (BN * kChunks) % NT == 0, "loads must divide evenly");
-  static_assert(NT % kChunks == 0, "thread count must be a multiple of 8");
+  static constexpr int LDS_BYTES = kStagesA * A_BYTES + kStagesB * B_BYTES;
+  static constexpr int A_LD = A_BYTES / (16 * NT);  // 16-byte loads per thread per stage
+  static constexpr int B_LD = B_BYTES / (16 * NT);
+  static_assert(BM % (64 * WGM) == 0 && BN % (64 * WGN) == 0, "the epilogues take wave tiles 64 rows or columns at a time");
+  static_assert(A_BYTES % (16 * NT) == 0 && B_BYTES % (16 * NT) == 0, "loads must divide evenly");
 };
 
 // LDS has 64 banks of 4 bytes: two 128-byte tile rows share one bank window, and a
 // 16-byte access is served 16 lanes at a time.  XOR-ing the chunk index with (row >> 1)
 // makes 16 consecutive rows at the same logical chunk hit 16 distinct 16-byte slots of
 // the 256-byte window (measured: 194 B/clk/CU, against 122 with a plain row & 7 key).
-__device__ __forceinline__ int swizzle_key(int row) { return (row >> 1) & (kChunks - 1); }
-__device__ __forceinline__ int lds_off(int row, int chunk) {
-  return row * kRowBytes + ((chunk ^ swizzle_key(row)) << 4);
-}
+__device__ __forceinline__ int swizzle_key(int row) { return (row >> 1) & 7; }
 
 // Two transposing 8-byte LDS reads (ds_read_b64_tr_b16) -> one MFMA operand: 8 values along K for
 // this lane's row, taken from a tile that is stored with K as the ROW index.  In a group of 16
@@ -104,20 +123,22 @@ __device__ __forceinline__ intx4 read_tr_operand(const char* lds, int addr_lo, i
 // Geometry of one accumulator element, shared by every epilogue.
 template <class TL>
 struct Frag {
-  int lane, half, wm, wn;
+  int lane, l16, q, wm, wn;
   __device__ __forceinline__ Frag() {
     const int wave = threadIdx.x >> 6;
     lane = threadIdx.x & 63;
-    half = lane >> 5;
+    l16 = lane & 15;
+    q = lane >> 4;
     wm = wave / TL::WGN;
     wn = wave % TL::WGN;
   }
-  // row offset inside the workgroup tile of accumulator register r in block mb
-  __device__ __forceinline__ int m_of(int mb, int r) const {
-    return wm * TL::WTM + mb * 32 + ((r >> 2) << 3) + (half << 2) + (r & 3);
-  }
-  __device__ __forceinline__ int m_block(int mb) const { return wm * TL::WTM + mb * 32; }
-  __device__ __forceinline__ int n_of(int nb) const { return wn * TL::WTN + nb * 32 + (lane & 31); }
+  // offsets inside the workgroup tile of accumulator register r of block (mb, nb): row m_of, column n_of ...
+  __device__ __forceinline__ int m_of(int mb, int r) const { return m_block(mb) + 4 * q + r; }
+  __device__ __forceinline__ int m_block(int mb) const { return wm * TL::WTM + mb * 16; }
+  __device__ __forceinline__ int n_of(int nb) const { return wn * TL::WTN + nb * 16 + l16; }
+  // ... and with the operands swapped (SWAP): row m_row, columns n_quad .. n_quad + 3 in r = 0..3
+  __device__ __forceinline__ int m_row(int mb) const { return m_block(mb) + l16; }
+  __device__ __forceinline__ int n_quad(int nb) const { return wn * TL::WTN + nb * 16 + 4 * q; }
 };
 
 template <class F, int... Is>
@@ -190,6 +211,50 @@ __device__ __forceinline__ void phase_stamp(const GemmShape& g, int word, bool w
 #define KT_STAMP_LOOP_START()
 #endif
 
+// 16 bytes per lane from global memory straight into LDS: lane l lands at LDS byte lds_base + OFF + 16 l (lds_base
+// wave-uniform).  Assembly, so that the compiler does not tie the LDS reads to these loads with a full
+// wait: the waits are placed by hand (vmcnt, in issue order).
+typedef int sgprx4 __attribute__((ext_vector_type(4)));
+template <int OFF>
+__device__ __forceinline__ void buffer_to_lds_16(uint32_t voffset, const sgprx4& rsrc, unsigned lds_base) {
+  asm volatile("s_add_u32 m0, %1, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %2, 0 offen lds"
+               :: "v"(voffset), "s"(lds_base), "s"(rsrc), "n"(OFF)
+               : "memory", "scc");
+}
+// Raw buffer over everything from `base` on (offsets are unsigned 32-bit, checked by the host).
+__device__ __forceinline__ sgprx4 raw_buffer(const char* base) {
+  const uint64_t p = reinterpret_cast<uint64_t>(base);
+  return sgprx4{(int)(uint32_t)p, (int)(uint32_t)((p >> 32) & 0xffff), -1, 0x00027000};
+}
+
+// Waits until at most N vector-memory operations of this wave are in flight (LDS operations: none), then
+// meets the other waves.
+template <int N>
+__device__ __forceinline__ void stage_barrier() {
+  static_assert(N < 64, "the counter has six bits");
+  __builtin_amdgcn_sched_barrier(0);
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | 0x70);  // vmcnt(N) expcnt(7) lgkmcnt(0)
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_sched_barrier(0);
+}
+
+// Slot of one step (0 .. MB NB - 1) behind which LDS read r of the next step's fragments is issued: the B fragments
+// first (r < NB), then A fragment i = r - NB, which must wait for the last MFMA that uses the old one.
+template <int MB, int NB>
+constexpr int fragment_read_slot(int r, int base, int spacing) {
+  if (r < NB) return base + r * spacing;
+  const int i = r - NB;
+  int slot = base + NB * spacing;
+  for (int k = 0; k <= i; ++k) {
+    const int free_at = NB * (k + 1) - 1;
+    if (slot < free_at) slot = free_at;
+    if (k < i) slot += spacing;
+  }
+  return slot < MB * NB ? slot : MB * NB - 1;
+}
+
 // Main loop.  Rows of A beyond M (and of B beyond N) are read from the last valid
 // row, so every load stays inside the operand; the epilogue masks them out.
 // K is addressed in slabs: slab g of an operand row starts at byte
@@ -201,221 +266,267 @@ __device__ __forceinline__ void phase_stamp(const GemmShape& g, int word, bool w
 // The slab range [slab0, slab0 + k_slabs) must lie inside both operands' rows, and
 // (BM-1)*lda*sizeof(T) + 128 (same for B) must fit 32 bits (the host checks this).
 //
-// Schedule.  One K slab = 4 sub-steps of MB*NB MFMA "slots".  Everything that is not
-// an MFMA is dealt out over the slots, one or two instructions behind each MFMA, and
-// pinned there with sched_barrier, so the matrix pipe never waits for a block of
-// memory instructions to issue:
-//   sub-steps 0-2: behind the first slots, read the fragments of the next sub-step;
-//                  spread over all their slots, write the NEXT slab (registers -> other
-//                  LDS stage) one 16-byte chunk at a time, and refill each freed
-//                  register with the same chunk of slab+2 from global memory
-//   sub-step 3:    barrier (LDS only), then read sub-step 0 of the next slab
-// The fragments of sub-step s+1 are therefore on their way a whole sub-step before
-// the MFMAs that use them, each global load a whole slab before its LDS store, and
-// neither the LDS nor the vector-memory path ever sees a burst (a burst of 16 stores
-// per wave made the matrix pipe wait ~1000 cycles per slab).
+// Schedule.  A slab is two steps of MB*NB MFMA "slots", each on one set of fragments (64 bytes of K)
+// that was read from LDS during the step before.  Everything that is not an MFMA is dealt out
+// over the slots, one instruction behind an MFMA, and pinned there with sched_barrier, so the
+// matrix pipe never waits for a block of memory instructions to issue.  Slab s:
+//   first step:  read the fragments of the second step
+//   second step, slot BAR (half of it): wait for this wave's loads of slab s + 1, barrier.  Behind it
+//     slab s + 1 is complete, and the stages of slab s are free: every wave has its fragments.  Read the
+//     fragments of the next step; load A of slab s + 2 into the stage A of slab s had, then B of slab
+//     s + 3 into the stage of B's; the loads are spread over the slots up to the next BAR
+// A step walks the blocks row by row (snake: neighbouring MFMAs share an operand).  The B
+// fragments are double-buffered; A fragment i is used by one row of blocks only, so the next
+// step's is read into the same registers once that row is done.  With the large tile an A load has
+// 1600 cycles or more until the barrier that waits for it, a B load 2000 to 3400; three stages of
+// both operands would not fit the LDS.
+//
+// What bounds it: the board's power limit for the large tile (the clock falls as the matrix pipe
+// fills).  Cycles of the main loop of a 256 x 256 x 4096 tile (131 072 is the matrix pipe back to back):
+//   173 000  loads through registers: an LDS store and the load behind it hold the only wave of a SIMD up by
+//            ~20 cycles each; fragment reads and barriers cost next to nothing
+//   163 000 - 170 000  straight into LDS in stages of 64 bytes of K: every 128-byte line is fetched twice
+//   151 000  this form (and the scalar address arithmetic of the next slab ahead of its barrier; behind it: 153 600)
 //
 // ATN (bf16, BM = 256): operand A is given with K as its ROW index instead, A[k][lda] with the tile's
 // 256 rows m as consecutive columns (the activations X [token][feature] for dR = X^T G: no
 // token-minor copy of X is needed).  K is walked in the order the other operand stores it
-// (token_position() of the epilogues: position 4a + b of a 128-token group is token a + 32 b).
-// A slab is then 64 tile rows of 512 bytes, padded to 576 so that the four consecutive rows a
-// transposing read touches lie 64 bytes apart in the bank window; fragments come from
-// read_tr_operand.  Rows k >= k_valid are not read (the last valid row is read instead; the other
+// (token_position() of the epilogues: position 4a + b of a 64-token group is token a + 16 b), one
+// group per slab.  A stage is then 64 tile rows of 512 bytes.  Fragments come from read_tr_operand,
+// two lane quarters at a time reading 32 bytes of rows k .. k+3 and of rows k+8 .. k+11: the 32-byte
+// pieces of a row are XOR-swizzled with 2 (row % 4) + (row / 8) % 2, which puts those eight into
+// different banks.  Rows k >= k_valid are not read (the last valid row is read instead; the other
 // operand is zero there).
-constexpr int kAtnRowBytes = 576;
-constexpr int kAtnStageBytes = 64 * kAtnRowBytes;
-
-template <class TL, bool ATN = false>
+template <class TL, bool ATN, bool SWAP>
 __device__ __forceinline__ void gemm_mainloop(const typename TL::T* __restrict__ A, int64_t lda,
                                               int M, int m0,
                                               const typename TL::T* __restrict__ B, int64_t ldb,
                                               int N, int n0, int slab0, int k_slabs,
                                               int slabs_per_block, int64_t block_bytes_a,
                                               int64_t block_bytes_b,
-                                              floatx16 (&acc)[TL::MB][TL::NB], char* lds, int k_valid = 0
+                                              floatx4 (&acc)[TL::MB][TL::NB], char* lds, int k_valid
                                               KT_STAMP_PARAM) {
   using T = typename TL::T;
   static_assert(!ATN || (sizeof(T) == 2 && TL::BM == 256 && TL::NT == 256), "ATN: bf16, 256 tile rows, 4 waves");
-  constexpr int A_STAGE = ATN ? kAtnStageBytes : TL::A_BYTES;
   constexpr int EPC = 16 / (int)sizeof(T);  // elements per 16-byte chunk
-  constexpr int MB = TL::MB, NB = TL::NB, NMMA = MB * NB, NFRAG = MB + NB;
+  constexpr int MB = TL::MB, NB = TL::NB, SLOTS = MB * NB, NFRAG = MB + NB;
   constexpr int A_LD = TL::A_LD, B_LD = TL::B_LD, NLD = A_LD + B_LD;
-  constexpr int ROWS_PER_PASS = TL::NT / kChunks;
-  // LDS layout: [A stage 0][A stage 1][B stage 0][B stage 1]; every stage offset and
-  // every per-block row offset below is a compile-time immediate of the ds_ instruction.
-  constexpr int B_BASE = 2 * A_STAGE;
-  static_assert(kChunks / 2 == 4, "the schedule is written for 4 K sub-steps per slab");
-  static_assert(ROWS_PER_PASS % 16 == 0, "swizzle key must not change between load passes");
-  static_assert(NFRAG <= NMMA && NLD <= 3 * NMMA, "not enough MFMA slots to hide the memory instructions");
+  constexpr int WAVE_LD = TL::NT * 16;  // bytes of a stage one load of every thread fills
+  constexpr int BAR = SLOTS / 2, SPACE0 = SLOTS >= 4 * NFRAG ? 3 : 1, SPACE1 = SLOTS >= 4 * NFRAG ? 2 : 1;
+  // load i is issued LOAD_AT(i) slots behind the barrier: the A loads in the first quarter of the interval
+  // (a 256 x 256 x 4096 tile takes 163 000 cycles with 1/8, 157 000 with 3/16 or 3/8, 153 600 with this)
+  constexpr int A_GAP = 2 * SLOTS / 4 / A_LD, B_GAP = 2 * SLOTS * 3 / 4 / B_LD;
+  constexpr auto load_slot = [](int i) constexpr {
+    return SLOTS + BAR + 1 + (i < A_LD ? i * A_GAP : A_LD * A_GAP + (i - A_LD) * B_GAP);
+  };
+  static_assert(A_GAP >= 1 && B_GAP >= 1 && load_slot(NLD - 1) - 2 * SLOTS < SLOTS + BAR - 3 && BAR + NFRAG * SPACE1 <= SLOTS,
+                "not enough MFMA slots to hide the memory instructions");
 
-  const int tid = threadIdx.x;
-  const int lrow = tid >> 3;  // row handled by this thread in load pass 0
-  const int lchunk = tid & 7;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
-  // global addressing: uniform 64-bit base (advanced per slab) + 32-bit byte offsets
+  // global addressing: uniform 64-bit base + 32-bit byte offsets.  Load i of a thread fills 16 bytes at
+  // WAVE_LD i + 16 tid of a stage: row (NT / 8) i + tid / 8, chunk position tid % 8
   const char* Ab = reinterpret_cast<const char*>(ATN ? A + m0 : A + (int64_t)m0 * lda);
   const char* Bb = reinterpret_cast<const char*>(B + (int64_t)n0 * ldb);
-  // byte offsets of K slab `slab` (relative to slab0) inside a row of A / of B: uniform values
-  int64_t ka = 0, kb = 0;
   uint32_t og[NLD];
-  // ATN: thread (chunk tid & 31 of the 512-byte row, row group tid >> 5) moves tile rows
-  // (tid >> 5) + 8 i of a slab; tile row pr of slab g holds position 64 (g & 1) + pr of 128-token
-  // group g >> 1, i.e. token (pr >> 2) + 16 (g & 1) + 32 (pr & 3) of the group.
-  const int atn_chunk = tid & 31, atn_rg = tid >> 5;
-  auto atn_token = [&](int i) __attribute__((always_inline)) {
-    const int pr = atn_rg + 8 * i;
-    return (pr >> 2) + 32 * (pr & 3);
-  };
-  auto locate = [&](int slab) __attribute__((always_inline)) {
-    const int g = slab0 + slab;
-    const int blk = g / slabs_per_block;
-    const int64_t in_blk = (int64_t)(g - blk * slabs_per_block) * kRowBytes;
-    kb = blk * block_bytes_b + in_blk;
-    if constexpr (ATN) {
-      const int grp0 = (g >> 1) * 128, half16 = (g & 1) * 16;  // tile row 0 of this slab is token grp0 + half16
-      ka = (int64_t)(grp0 + half16) * lda * (int64_t)sizeof(T);
-      if (grp0 + 128 > k_valid) {  // last, partial group: rows past the end read the last valid token
-        ka = (int64_t)grp0 * lda * (int64_t)sizeof(T);
-        const int last = k_valid - 1 - grp0;  // >= 0: the group starts inside the operand
-#pragma unroll
-        for (int i = 0; i < A_LD; ++i) {
-          const int t = half16 + atn_token(i);
-          og[i] = (uint32_t)(((int64_t)(t < last ? t : last) * lda + atn_chunk * EPC) * (int64_t)sizeof(T));
-        }
-      }
-    } else {
-      ka = blk * block_bytes_a + in_blk;
-    }
+  static_assert(TL::NT / 8 % 16 == 0, "swizzle key must not change between the loads of a thread");
+  const int chunk = (tid & 7) ^ swizzle_key(tid >> 3);
+  // ATN: row 8 i + 2 wave + lane / 32, 16-byte position lane % 32; tile row pr of a slab holds position pr of its
+  // 64-token group, i.e. token pr / 4 + 16 (pr % 4) of the group
+  auto atn_row = [&](int i) __attribute__((always_inline)) { return 8 * i + 2 * wave + (lane >> 5); };
+  auto atn_token = [&](int i) __attribute__((always_inline)) { return (atn_row(i) >> 2) + 16 * (atn_row(i) & 3); };
+  auto atn_offset = [&](int i, int token) __attribute__((always_inline)) {
+    const int r = atn_row(i), piece_key = 2 * (r & 3) + ((r >> 3) & 1);
+    return (uint32_t)(((int64_t)token * lda + ((lane & 31) ^ (2 * piece_key)) * EPC) * (int64_t)sizeof(T));
   };
 #pragma unroll
   for (int i = 0; i < A_LD; ++i) {
     if constexpr (ATN) {
-      og[i] = (uint32_t)(((int64_t)atn_token(i) * lda + atn_chunk * EPC) * (int64_t)sizeof(T));
+      og[i] = atn_offset(i, atn_token(i));
     } else {
-      int row = lrow + i * ROWS_PER_PASS;
+      int row = i * (TL::NT / 8) + (tid >> 3);
       row = (m0 + row < M) ? row : (M - 1 - m0);
-      og[i] = (uint32_t)(((int64_t)row * lda + lchunk * EPC) * (int64_t)sizeof(T));
+      og[i] = (uint32_t)(((int64_t)row * lda + chunk * EPC) * (int64_t)sizeof(T));
     }
   }
 #pragma unroll
   for (int i = 0; i < B_LD; ++i) {
-    int row = lrow + i * ROWS_PER_PASS;
+    int row = i * (TL::NT / 8) + (tid >> 3);
     row = (n0 + row < N) ? row : (N - 1 - n0);
-    og[A_LD + i] = (uint32_t)(((int64_t)row * ldb + lchunk * EPC) * (int64_t)sizeof(T));
+    og[A_LD + i] = (uint32_t)(((int64_t)row * ldb + chunk * EPC) * (int64_t)sizeof(T));
   }
-  const int st_off = lds_off(lrow, lchunk);  // + i*ROWS_PER_PASS*128 per pass (same key)
-  const int st_off_atn = atn_rg * kAtnRowBytes + atn_chunk * 16;  // + i * 8 rows per load
 
-  const Frag<TL> f;
-  // fragment addresses: one per K sub-step and operand; blocks and stages are immediates
-  const int key = swizzle_key(f.lane & 31);
-  int fa_s[4], fb_s[4];
+  // The slabs to request next (A, B) and where they start inside a row: uniform values, advanced slab by slab; past
+  // the last one: the last one again.
+  int req_a = slab0, req_b = slab0, in_block_a = slab0 % slabs_per_block, in_block_b = in_block_a;
+  const int last_slab = slab0 + k_slabs - 1;
+  const char* an = Ab + (ATN ? (int64_t)slab0 * 64 * lda * (int64_t)sizeof(T)
+                             : (slab0 / slabs_per_block) * block_bytes_a + (int64_t)in_block_a * kRowBytes);
+  const char* bn = Bb + (slab0 / slabs_per_block) * block_bytes_b + (int64_t)in_block_b * kRowBytes;
+  const int64_t a_wrap = block_bytes_a - (int64_t)(slabs_per_block - 1) * kRowBytes;
+  const int64_t b_wrap = block_bytes_b - (int64_t)(slabs_per_block - 1) * kRowBytes;
+  sgprx4 rsrc_a, rsrc_b;
+  // take the next slab as the one gload() loads
+  auto locate_a = [&]() __attribute__((always_inline)) {
+    const char* a0 = an;
+    if constexpr (ATN) {
+      const int grp0 = req_a * 64;
+      if (grp0 + 64 > k_valid) {  // the last, partial group (and a group of padding behind it): re-read the last valid token
+        const int base = grp0 < k_valid ? grp0 : (k_valid - 1) & ~63;
+        a0 = Ab + (int64_t)base * lda * (int64_t)sizeof(T);
+        const int last = k_valid - 1 - base;  // >= 0: the group starts inside the operand
 #pragma unroll
-  for (int s = 0; s < 4; ++s) {
-    const int coff = (((2 * s + f.half) ^ key) & (kChunks - 1)) << 4;
-    fa_s[s] = (f.wm * TL::WTM + (f.lane & 31)) * kRowBytes + coff;
-    fb_s[s] = B_BASE + (f.wn * TL::WTN + (f.lane & 31)) * kRowBytes + coff;
-  }
-  // ATN fragments: tile rows 16 s + tr_row (+4), columns (features) wm * WTM + 32 block + tr_col ..
-  const int atn_g16 = f.lane >> 4, atn_rr = f.lane & 15;
-  const int atn_tr = (8 * (atn_g16 >> 1) + (atn_rr >> 2)) * kAtnRowBytes +
-                     (f.wm * TL::WTM + 16 * (atn_g16 & 1) + 4 * (atn_rr & 3)) * 2;
-
-  intx4 rg[NLD];        // one K slab in flight from global memory
-  intx4 fr[2][NFRAG];   // MFMA fragments, double buffered: [buf][0..MB) = A, [MB..) = B
-
-  // loads chunk i of the slab last passed to locate()
-  auto gload = [&](auto i_c) __attribute__((always_inline)) {
-    constexpr int i = decltype(i_c)::value;
-    const char* base = i < A_LD ? Ab + ka : Bb + kb;
-    rg[i] = *reinterpret_cast<const intx4*>(base + og[i]);
-  };
-  auto lstore = [&](auto i_c, auto stage_c) __attribute__((always_inline)) {
-    constexpr int i = decltype(i_c)::value;
-    constexpr int stage = decltype(stage_c)::value;
-    if constexpr (ATN && i < A_LD) {
-      *reinterpret_cast<intx4*>(lds + st_off_atn + stage * A_STAGE + i * 8 * kAtnRowBytes) = rg[i];
-    } else {
-      constexpr int off = i < A_LD ? stage * A_STAGE + i * ROWS_PER_PASS * kRowBytes
-                                   : B_BASE + stage * TL::B_BYTES + (i - A_LD) * ROWS_PER_PASS * kRowBytes;
-      *reinterpret_cast<intx4*>(lds + st_off + off) = rg[i];
+        for (int i = 0; i < A_LD; ++i) {
+          const int t = atn_token(i);
+          og[i] = atn_offset(i, grp0 < k_valid && t < last ? t : last);
+        }
+      }
+    }
+    rsrc_a = raw_buffer(a0);
+    if (req_a < last_slab) {
+      ++req_a;
+      if constexpr (ATN) {
+        an += (int64_t)64 * lda * (int64_t)sizeof(T);
+      } else {
+        const bool wrap = ++in_block_a == slabs_per_block;
+        if (wrap) in_block_a = 0;
+        an += wrap ? a_wrap : (int64_t)kRowBytes;
+      }
     }
   };
-  auto fread = [&](auto buf_c, auto i_c, auto stage_c, auto s_c) __attribute__((always_inline)) {
-    constexpr int buf = decltype(buf_c)::value, i = decltype(i_c)::value;
-    constexpr int stage = decltype(stage_c)::value, s = decltype(s_c)::value;
-    if constexpr (ATN && i < MB) {
-      constexpr int off = stage * A_STAGE + s * 16 * kAtnRowBytes + i * 64;
-      fr[buf][i] = read_tr_operand(lds, atn_tr + off, atn_tr + off + 4 * kAtnRowBytes);
-    } else if constexpr (i < MB)
-      fr[buf][i] = *reinterpret_cast<const intx4*>(lds + fa_s[s] + stage * A_STAGE + i * 32 * kRowBytes);
-    else
-      fr[buf][i] = *reinterpret_cast<const intx4*>(lds + fb_s[s] + stage * TL::B_BYTES + (i - MB) * 32 * kRowBytes);
+  auto locate_b = [&]() __attribute__((always_inline)) {
+    rsrc_b = raw_buffer(bn);
+    if (req_b < last_slab) {
+      ++req_b;
+      const bool wrap = ++in_block_b == slabs_per_block;
+      if (wrap) in_block_b = 0;
+      bn += wrap ? b_wrap : (int64_t)kRowBytes;
+    }
   };
-  auto mma = [&](auto buf_c, auto j_c) __attribute__((always_inline)) {
-    constexpr int buf = decltype(buf_c)::value, j = decltype(j_c)::value;
-    Mma<T>::run(fr[buf][j / NB], fr[buf][MB + j % NB], acc[j / NB][j % NB]);
-  };
-  using C0 = std::integral_constant<int, 0>;
 
-  // One slab.  PAR: parity of the slab (LDS stage).  The body is the same for every
-  // slab, so that the compiler sees one loop and no accumulator-carrying branches: near
-  // the end of K the "slab+2" request is clamped to the last slab (a redundant, in-bounds
-  // load) and the last slab's LDS store / fragment read move data nobody uses.
-  auto one_slab = [&](auto par_c, int slab) __attribute__((always_inline)) {
-    constexpr int PAR = decltype(par_c)::value;
-    constexpr bool MORE = true, LOAD2 = true;
-    using Cur = std::integral_constant<int, PAR>;
-    using Nxt = std::integral_constant<int, PAR ^ 1>;
-    locate(slab + 2 < k_slabs ? slab + 2 : k_slabs - 1);
-    static_for<4 * NMMA>([&](auto g_c) __attribute__((always_inline)) {
-      constexpr int g = decltype(g_c)::value;  // slot index inside the slab
-      constexpr int s = g / NMMA, j = g % NMMA;
-      using Buf = std::integral_constant<int, s & 1>;
-      using NBuf = std::integral_constant<int, (s + 1) & 1>;
-      if constexpr (g == 3 * NMMA && MORE) lds_barrier();
-      mma(Buf{}, std::integral_constant<int, j>{});
-      // fragments of the next sub-step: one LDS read behind each of the first slots
-      static_for<NFRAG>([&](auto i_c) __attribute__((always_inline)) {
-        constexpr int i = decltype(i_c)::value;
-        if constexpr (i == j) {
-          if constexpr (s < 3) fread(NBuf{}, i_c, Cur{}, std::integral_constant<int, (s + 1) & 3>{});
-          else if constexpr (MORE) fread(NBuf{}, i_c, Nxt{}, C0{});
+  // LDS layout: [A stage 0, 1][B stage 0, 1, 2]
+  constexpr int B_BASE = kStagesA * TL::A_BYTES;
+  const unsigned lds_wave = (unsigned)(size_t)(__attribute__((address_space(3))) char*)lds + wave * 1024u;
+  unsigned b_write = 0;  // byte offset of the B stage to fill next
+  int b_read = 0;        // ... of the B stage whose fragments are read
+  const Frag<TL> f;
+  // fragment addresses, one per step of a slab: blocks and the A stage are instruction immediates
+  const int key = swizzle_key(f.l16);
+  int fa_s[2], fb_s[2], fb_now[2];
+#pragma unroll
+  for (int h = 0; h < 2; ++h) {
+    const int coff = ((4 * h + f.q) ^ key) << 4;
+    fa_s[h] = (f.wm * TL::WTM + f.l16) * kRowBytes + coff;
+    fb_now[h] = fb_s[h] = B_BASE + (f.wn * TL::WTN + f.l16) * kRowBytes + coff;
+  }
+  // ATN: rows 8 q + l16 / 4 (+4), 32-byte piece wm WTM / 16 + block, column 4 (l16 % 4) of it
+  int ft[ATN ? MB : 1];
+  if constexpr (ATN) {
+#pragma unroll
+    for (int i = 0; i < MB; ++i)
+      ft[i] = (8 * f.q + (f.l16 >> 2)) * 512 + (((f.wm * TL::WTM / 16 + i) ^ (2 * (f.l16 >> 2) + (f.q & 1))) << 5) + 8 * (f.l16 & 3);
+  }
+
+  intx4 fra[MB], frb[2][NB];  // MFMA fragments
+
+  // load i of the slabs the locates took: A into A stage `stage`, B into the stage at b_write
+  auto gload = [&](auto i_c, auto stage_c) __attribute__((always_inline)) {
+    constexpr int i = decltype(i_c)::value, stage = decltype(stage_c)::value;
+    if constexpr (i < A_LD)
+      buffer_to_lds_16<stage * TL::A_BYTES + i * WAVE_LD>(og[i], rsrc_a, lds_wave);
+    else
+      buffer_to_lds_16<B_BASE + (i - A_LD) * WAVE_LD>(og[i], rsrc_b, lds_wave + b_write);
+  };
+  // LDS read r of the fragments of step h of the slab in A stage `stage` (r < NB: B fragment r, else A fragment r - NB)
+  auto fread = [&](auto r_c, auto stage_c, auto h_c) __attribute__((always_inline)) {
+    constexpr int r = decltype(r_c)::value, stage = decltype(stage_c)::value, h = decltype(h_c)::value;
+    if constexpr (r < NB) {
+      frb[h][r] = *reinterpret_cast<const intx4*>(lds + fb_now[h] + r * 16 * kRowBytes);
+    } else {
+      constexpr int i = r - NB, off = stage * TL::A_BYTES;
+      if constexpr (ATN)
+        fra[i] = read_tr_operand(lds, ft[i] + off + h * 32 * 512, ft[i] + off + h * 32 * 512 + 4 * 512);
+      else
+        fra[i] = *reinterpret_cast<const intx4*>(lds + fa_s[h] + off + i * 16 * kRowBytes);
+    }
+  };
+  using S0 = std::integral_constant<int, 0>;
+  using S1 = std::integral_constant<int, 1>;
+
+  // Slab s with s % 2 = STAGE.  The body is the same for every slab, so that the compiler sees one loop and no
+  // accumulator-carrying branches: near the end of K the requests are clamped to the last slab (redundant,
+  // in-bounds loads into stages nobody reads) and the last slab reads fragments nobody uses.
+  auto one_slab = [&](auto stage_c) __attribute__((always_inline)) {
+    constexpr int STAGE = decltype(stage_c)::value;
+    using Cur = std::integral_constant<int, STAGE>;
+    using Nxt = std::integral_constant<int, STAGE ^ 1>;
+    static_for<2 * SLOTS>([&](auto g_c) __attribute__((always_inline)) {
+      constexpr int g = decltype(g_c)::value, h = g / SLOTS, j = g % SLOTS;
+      if constexpr (g == SLOTS + BAR) {
+        stage_barrier<B_LD>();  // in flight at most: B of slab s + 2
+      }
+      if constexpr (g == SLOTS + BAR - 3) locate_a();  // every load of the former requests has been issued
+      if constexpr (g == SLOTS + BAR - 2) locate_b();
+      if constexpr (g == SLOTS + BAR - 1) {
+        b_write = b_write == 2 * TL::B_BYTES ? 0 : b_write + TL::B_BYTES;
+        b_read = b_read == 2 * TL::B_BYTES ? 0 : b_read + TL::B_BYTES;
+        fb_now[0] = fb_s[0] + b_read;
+        fb_now[1] = fb_s[1] + b_read;
+      }
+      constexpr int mb = j / NB, nb = (mb & 1) ? NB - 1 - j % NB : j % NB;
+      if constexpr (SWAP) Mma<T>::run(frb[h][nb], fra[mb], acc[mb][nb]);
+      else Mma<T>::run(fra[mb], frb[h][nb], acc[mb][nb]);
+      static_for<NFRAG>([&](auto r_c) __attribute__((always_inline)) {
+        constexpr int r = decltype(r_c)::value;
+        if constexpr (h == 0) {
+          if constexpr (fragment_read_slot<MB, NB>(r, 0, SPACE0) == j) fread(r_c, Cur{}, S1{});
+        } else {
+          if constexpr (fragment_read_slot<MB, NB>(r, BAR, SPACE1) == j) fread(r_c, Nxt{}, S0{});
         }
       });
-      // next slab: registers -> other LDS stage, spread evenly over the three sub-steps
-      // before the barrier; the freed register is refilled at once with slab+2
       static_for<NLD>([&](auto i_c) __attribute__((always_inline)) {
-        constexpr int i = decltype(i_c)::value;
-        if constexpr (i * 3 * NMMA / NLD == g) {
-          if constexpr (MORE) lstore(i_c, Nxt{});
-          if constexpr (LOAD2) gload(i_c);
-        }
+        constexpr int at = load_slot(decltype(i_c)::value);
+        if constexpr (at == g) gload(i_c, Cur{});
+        else if constexpr (at - 2 * SLOTS == g) gload(i_c, Nxt{});  // the stage of the slab before this one
       });
       __builtin_amdgcn_sched_barrier(0);
     });
   };
-  using P0 = std::integral_constant<int, 0>;
-  using P1 = std::integral_constant<int, 1>;
 
-  // prologue: slab 0 -> LDS stage 0, slab 1 -> registers, first fragments -> buffer 0
-  locate(0);
-  static_for<NLD>([&](auto i_c) __attribute__((always_inline)) { gload(i_c); });
-  static_for<NLD>([&](auto i_c) __attribute__((always_inline)) { lstore(i_c, P0{}); });
-  locate(k_slabs > 1 ? 1 : 0);
-  static_for<NLD>([&](auto i_c) __attribute__((always_inline)) { gload(i_c); });
-  lds_barrier();
-  static_for<NFRAG>([&](auto i_c) __attribute__((always_inline)) { fread(P0{}, i_c, P0{}, C0{}); });
+  // Prologue, as if slabs -2 and -1 had run: A and B of slab 0, B of slab 1, and of A(1), B(2) the loads that slab -1
+  // issues behind its barrier; slab 0 issues the others.  Then the fragments of its first step.
+  constexpr auto early_loads = [load_slot](int n) constexpr {
+    int c = 0;
+    for (int i = 0; i < n; ++i) c += load_slot(i) < 2 * SLOTS;
+    return c;
+  };
+  locate_a();
+  locate_b();
+  static_for<NLD>([&](auto i_c) __attribute__((always_inline)) { gload(i_c, S0{}); });
+  locate_b();
+  b_write = TL::B_BYTES;
+  static_for<B_LD>([&](auto i_c) __attribute__((always_inline)) { gload(std::integral_constant<int, A_LD + decltype(i_c)::value>{}, S0{}); });
+  locate_a();
+  locate_b();
+  b_write = 2 * TL::B_BYTES;
+  static_for<NLD>([&](auto i_c) __attribute__((always_inline)) {
+    if constexpr (load_slot(decltype(i_c)::value) < 2 * SLOTS) gload(i_c, S1{});
+  });
+  stage_barrier<B_LD + early_loads(NLD)>();
+  static_for<NFRAG>([&](auto r_c) __attribute__((always_inline)) { fread(r_c, S0{}, S0{}); });
   __builtin_amdgcn_sched_barrier(0);
   KT_STAMP_LOOP_START();
 
   int slab = 0;
   for (; slab + 1 < k_slabs; slab += 2) {
-    one_slab(P0{}, slab);
-    one_slab(P1{}, slab + 1);
+    one_slab(S0{});
+    one_slab(S1{});
   }
-  if (slab < k_slabs) one_slab(P0{}, slab);
+  if (slab < k_slabs) one_slab(S0{});
+  // no load into LDS outlives the loop
+  __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
+  asm volatile("" ::: "memory");
 }
 
 // Workgroup -> tile.  Consecutive workgroup ids land on different XCDs (8 of them,
@@ -456,18 +567,25 @@ __global__ __launch_bounds__(TL::NT) void gemm_nt_kernel(GemmShape g, Epi epi) {
   int slabs = g.slabs_total - slab0;
   slabs = slabs < g.slabs_per_split ? slabs : g.slabs_per_split;
 
-  floatx16 acc[TL::MB][TL::NB];
+  floatx4 acc[TL::MB][TL::NB];
 #pragma unroll
   for (int mb = 0; mb < TL::MB; ++mb)
 #pragma unroll
-    for (int nb = 0; nb < TL::NB; ++nb)
+    for (int nb = 0; nb < TL::NB; nb += 4) {
 #pragma unroll
-      for (int r = 0; r < 16; ++r) acc[mb][nb][r] = 0.0f;
+      for (int k = 0; k < 4; ++k) acc[mb][nb + k] = floatx4{0.f, 0.f, 0.f, 0.f};
+      settle<T>(acc[mb][nb], acc[mb][nb + 1], acc[mb][nb + 2], acc[mb][nb + 3]);
+    }
 
   const T* A = static_cast<const T*>(g.A) + (int64_t)batch * g.batch_stride_a;
   const T* B = static_cast<const T*>(g.B) + (int64_t)batch * g.batch_stride_b;
-  gemm_mainloop<TL, ATN>(A, g.lda, g.M, m0, B, g.ldb, g.N, n0, slab0, slabs, g.slabs_per_block,
+  gemm_mainloop<TL, ATN, Epi::kSwap>(A, g.lda, g.M, m0, B, g.ldb, g.N, n0, slab0, slabs, g.slabs_per_block,
                          g.block_bytes_a, g.block_bytes_b, acc, lds, g.k_valid KT_STAMP_ARG);
+#pragma unroll
+  for (int mb = 0; mb < TL::MB; ++mb)
+#pragma unroll
+    for (int nb = 0; nb < TL::NB; nb += 4)
+      settle<T>(acc[mb][nb], acc[mb][nb + 1], acc[mb][nb + 2], acc[mb][nb + 3]);
   KT_STAMP(g, 2);
   epi(acc, batch, tm, tn, ks, m0, n0);
   KT_STAMP(g, 3);
