@@ -117,11 +117,17 @@ using TB_M128 = Tile<bf16, 128, 256, 1, 4>;  // features on m, d % 256 != 0
 using TB_N128 = Tile<bf16, 256, 128, 4, 1>;  // features on n, d % 256 != 0
 using TB_128 = Tile<bf16, 128, 128, 2, 2>;   // d x d outputs, d % 256 != 0
 using TF = Tile<float, 128, 128, 2, 2>;      // fp32 path, every contraction
+using TF_64 = Tile<float, 64, 64, 2, 2>;     // fp32 path, d x d outputs of few tiles
 
 static inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
 static inline int64_t round_up(int64_t a, int64_t b) { return ceil_div(a, b) * b; }
 
 constexpr int kNumCUs = 256;
+
+// fp32 d x d products (retraction, dR): 64 x 64 tiles while 128 x 128 ones would leave CUs idle.  A 128 x 128 tile takes
+// a CU about 4100 cycles per 32 of K, a 64 x 64 one a quarter of that, so t large tiles take one round and 4 t small
+// ones ceil(4 t / 256) quarter rounds: fewer up to t = 192.  Same bits (the order of K is the same).
+static inline bool small_f32_tiles(int64_t d, int64_t batch) { return ceil_div(d, 128) * ceil_div(d, 128) * batch <= kNumCUs * 3 / 4; }
 // Token-minor operands (X^T, G^T) are stored in blocks of this many tokens: within a block a
 // feature row is contiguous, blocks follow each other feature-row-set by feature-row-set, so
 // the 256 rows a tile streams together span 2 MiB per block instead of one page per row.
@@ -244,7 +250,8 @@ static LossGradPlan plan_loss_grad(int64_t batch, int64_t n, int64_t d, kt_dtype
   int64_t slabs;
   if (p.fp32) {
     p.P = (int)ceil_div(d, TF::BM) * TF::WGM;
-    p.tiles_dd = (int)(ceil_div(d, TF::BM) * ceil_div(d, TF::BN));
+    const int64_t bm = small_f32_tiles(d, batch) ? TF_64::BM : TF::BM;
+    p.tiles_dd = (int)(ceil_div(d, bm) * ceil_div(d, bm));
     slabs = p.ldt / TF::BK;
   } else if (d % 256 == 0) {
     p.P = (int)(d / TB_BIG::BM) * TB_BIG::WGM;
@@ -741,13 +748,17 @@ static kt_status cayley_run(const CayleyPlan& p, char* ws, float* R, const float
       if (!launch_ok()) return fail(KT_ERR_DEVICE, "Cayley update launch failed");
     }
   } else {
-  // M = dR R^T
-  {
-    EpiStore<TF> e;
-    e.C = Mm; e.ldc = d; e.batch_stride = dd; e.split_stride = 0; e.M = D; e.N = D;
-    if (!launch_gemm<TF>(G, d, dd, D, R, d, dd, D, d, 0, (int)batch, e, st))
-      return fail(KT_ERR_DEVICE, "dR R^T GEMM launch failed");
-  }
+  const bool small = small_f32_tiles(d, batch);
+  auto product = [&](const float* A, const float* B, float* C) -> bool {  // C = A B^T
+    auto go = [&](auto tile_tag) -> bool {
+      using TL = decltype(tile_tag);
+      EpiStore<TL> e;
+      e.C = C; e.ldc = d; e.batch_stride = dd; e.split_stride = 0; e.M = D; e.N = D;
+      return launch_gemm<TL>(A, d, dd, D, B, d, dd, D, d, 0, (int)batch, e, st);
+    };
+    return small ? go(TF_64{}) : go(TF{});
+  };
+  if (!product(G, R, Mm)) return fail(KT_ERR_DEVICE, "dR R^T GEMM launch failed");
   // delta[it] collects max |Zt_new - Zt_old| of iteration it through atomicMax
   hipLaunchKernelGGL(fill_u32_kernel, dim3(64), dim3(256), 0, st, delta, batch * kCayleyMaxIters, 0u);
   if (!launch_ok()) return fail(KT_ERR_DEVICE, "fill launch failed");
@@ -758,19 +769,20 @@ static kt_status cayley_run(const CayleyPlan& p, char* ws, float* R, const float
     hipLaunchKernelGGL(adam_scalars2_kernel, dim3((unsigned)batch), dim3(256), 0, st, adam->sq_part,
                  (int)((d / 32) * (d / 32)), adam->lr, adam->q, adam->eps, adam->scal, adam->scalars_out);
     if (!launch_ok()) return fail(KT_ERR_DEVICE, "Cayley Adam scalar launch failed");
-    EpiStore<TF> e;  // M <- S R = S (Rt)^T
-    e.C = adam->M; e.ldc = d; e.batch_stride = dd; e.split_stride = 0; e.M = D; e.N = D;
-    if (!launch_gemm<TF>(Bm, d, dd, D, Rt, d, dd, D, d, 0, (int)batch, e, st))
-      return fail(KT_ERR_DEVICE, "momentum projection GEMM launch failed");
+    // M <- S R = S (Rt)^T
+    if (!product(Bm, Rt, adam->M)) return fail(KT_ERR_DEVICE, "momentum projection GEMM launch failed");
   }
   // fixed point in transposed space: Zt <- Rt - U Bm^T, U <- Rt + Zt
   for (int it = 0; it < kCayleyMaxIters; ++it) {
-    EpiCayleyIter<TF> e;
-    e.Rt = Rt; e.Zt = Zt; e.Unew = U[(it + 1) & 1]; e.Usplit = nullptr; e.delta = delta;
-    e.d = D; e.it = it; e.max_iters = kCayleyMaxIters; e.tol = kCayleyTol;
-    e.bscale = adam ? adam->scal : nullptr;
-    if (!launch_gemm<TF>(U[it & 1], d, dd, D, Bm, d, dd, D, d, 0, (int)batch, e, st))
-      return fail(KT_ERR_DEVICE, "Cayley iteration launch failed");
+    auto go = [&](auto tile_tag) -> bool {
+      using TL = decltype(tile_tag);
+      EpiCayleyIter<TL> e;
+      e.Rt = Rt; e.Zt = Zt; e.Unew = U[(it + 1) & 1]; e.Usplit = nullptr; e.delta = delta;
+      e.d = D; e.it = it; e.max_iters = kCayleyMaxIters; e.tol = kCayleyTol;
+      e.bscale = adam ? adam->scal : nullptr;
+      return launch_gemm<TL>(U[it & 1], d, dd, D, Bm, d, dd, D, d, 0, (int)batch, e, st);
+    };
+    if (!(small ? go(TF_64{}) : go(TF{}))) return fail(KT_ERR_DEVICE, "Cayley iteration launch failed");
   }
   }
   hipLaunchKernelGGL(cayley_finish_kernel, dim3(D / 32, D / 32, (unsigned)batch), dim3(256), 0, st, Zt, D,
@@ -780,10 +792,13 @@ static kt_status cayley_run(const CayleyPlan& p, char* ws, float* R, const float
     hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(256), 0, st, reinterpret_cast<unsigned*>(ortho_err),
                        batch, 0u);
     if (!launch_ok()) return fail(KT_ERR_DEVICE, "fill launch failed");
-    EpiOrtho<TF> e;
-    e.err = reinterpret_cast<unsigned*>(ortho_err); e.d = D;
-    // Zt Zt^T = R^T R
-    if (!launch_gemm<TF>(Zt, d, dd, D, Zt, d, dd, D, d, 0, (int)batch, e, st))
+    auto off_diagonal = [&](auto tile_tag) -> bool {  // Zt Zt^T = R^T R
+      using TL = decltype(tile_tag);
+      EpiOrtho<TL> e;
+      e.err = reinterpret_cast<unsigned*>(ortho_err); e.d = D;
+      return launch_gemm<TL>(Zt, d, dd, D, Zt, d, dd, D, d, 0, (int)batch, e, st);
+    };
+    if (!(small_f32_tiles(d, batch) ? off_diagonal(TF_64{}) : off_diagonal(TF{})))
       return fail(KT_ERR_DEVICE, "orthogonality GEMM launch failed");
     hipLaunchKernelGGL(ortho_diag_kernel, dim3(D, (unsigned)batch), dim3(256), 0, st, Zt, D,
                        reinterpret_cast<unsigned*>(ortho_err));
@@ -967,8 +982,9 @@ kt_status kt_kurtosis_loss_grad(const void* X, int64_t ldx, const void* R, int64
     return run_loss_grad_fused(p, X, ldx, R, ldr, r_dtype, batch, n, d, kappa_target, loss, row_kurt, dR,
                                ws, st);
   if (p.fp32)
-    return run_loss_grad<float, TF, TF>(p, X, ldx, R, ldr, r_dtype, batch, n, d, kappa_target, loss,
-                                        row_kurt, dR, ws, st);
+    return small_f32_tiles(d, batch)
+               ? run_loss_grad<float, TF, TF_64>(p, X, ldx, R, ldr, r_dtype, batch, n, d, kappa_target, loss, row_kurt, dR, ws, st)
+               : run_loss_grad<float, TF, TF>(p, X, ldx, R, ldr, r_dtype, batch, n, d, kappa_target, loss, row_kurt, dR, ws, st);
   if (d % 256 == 0)
     return run_loss_grad<bf16, TB_BIG, TB_BIG>(p, X, ldx, R, ldr, r_dtype, batch, n, d, kappa_target,
                                                loss, row_kurt, dR, ws, st);
@@ -999,8 +1015,9 @@ kt_status kt_pooled_kurtosis_loss_grad(const void* X, int64_t ldx, const void* R
   PooledArgs pa;
   pa.rms_eps = rms_eps; pa.kappa_out = kappa;
   if (p.fp32)
-    return run_loss_grad<float, TF, TF>(p, X, ldx, R, ldr, r_dtype, batch, n, d, kappa_target, loss, nullptr,
-                                        dR, ws, st, &pa);
+    return small_f32_tiles(d, batch)
+               ? run_loss_grad<float, TF, TF_64>(p, X, ldx, R, ldr, r_dtype, batch, n, d, kappa_target, loss, nullptr, dR, ws, st, &pa)
+               : run_loss_grad<float, TF, TF>(p, X, ldx, R, ldr, r_dtype, batch, n, d, kappa_target, loss, nullptr, dR, ws, st, &pa);
   if (d % 256 == 0)
     return run_loss_grad<bf16, TB_BIG, TB_BIG>(p, X, ldx, R, ldr, r_dtype, batch, n, d, kappa_target, loss,
                                                nullptr, dR, ws, st, &pa);

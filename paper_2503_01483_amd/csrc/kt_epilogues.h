@@ -67,6 +67,7 @@ __device__ __forceinline__ float quarter_pick(int q, float v0, float v1, float v
 // cancellation in fp32; the partials of a row are merged in fp64 (row_central_sums in kt_aux.h).
 template <class TL>
 struct EpiMoments : EpiBase {
+  static_assert(TL::MB % 4 == 0 && TL::NB % 4 == 0, "features and tokens are taken 64 at a time");
   floatx4* part;
   int n_tokens, d, P;
   __device__ __forceinline__ void operator()(floatx4 (&acc)[TL::MB][TL::NB], int batch, int tm,
@@ -148,6 +149,7 @@ __device__ __forceinline__ float grad_value(float y, float alpha, float mu, floa
 
 template <class TL>
 struct EpiGrad : EpiBase {
+  static_assert(TL::MB % 4 == 0 && TL::NB % 4 == 0, "features and tokens are taken 64 at a time");
   using T = typename TL::T;
   const floatx4* coef;
   T* GT;
@@ -197,6 +199,7 @@ struct EpiGrad : EpiBase {
 // gradient is bit-identical) at the price of n d 4 bytes of scratch, one write and one read of them.
 template <class TL>
 struct EpiMomentsKeep : EpiBase {
+  static_assert(TL::MB % 4 == 0 && TL::NB % 4 == 0, "features and tokens are taken 64 at a time");
   EpiMoments<TL> mom;
   float* YT;
   int64_t ldt, tb, batch_stride;  // batch_stride in elements of YT
@@ -419,6 +422,7 @@ struct EpiOrtho : EpiBase {
 // same orientation as EpiMoments; part[(batch*P + p)*n_tokens + token]
 template <class TL>
 struct EpiAmax : EpiBase {
+  static_assert(TL::MB % 4 == 0 && TL::NB % 4 == 0, "features and tokens are taken 64 at a time");
   float* part;
   int n_tokens, d, P;
   __device__ __forceinline__ void operator()(floatx4 (&acc)[TL::MB][TL::NB], int batch, int tm,
@@ -453,6 +457,7 @@ struct EpiAmax : EpiBase {
 // pe[(batch*P + p)*n_tokens + token] = {sum (y - q s)^2, sum y^2} over the wave's feature rows.
 template <class TL>
 struct EpiQuant : EpiBase {
+  static_assert(TL::MB % 4 == 0 && TL::NB % 4 == 0, "features and tokens are taken 64 at a time");
   const float* scales;  // [batch][n_tokens]
   int8_t* codes;        // [batch][n_tokens][d] or null
   float2* err_part;     // or null
@@ -461,7 +466,6 @@ struct EpiQuant : EpiBase {
                                              int, int, int m0, int n0) const {
     const Frag<TL> f;
     const int p = tm * TL::WGM + f.wm;
-    static_assert(TL::MB % 4 == 0, "codes leave four blocks at a time");
 #pragma unroll
     for (int g = 0; g < TL::NB / 4; ++g) {
       float e2[4], y2[4];

@@ -75,12 +75,6 @@ struct Mma<float> {
   }
 };
 
-// Holds every use of these accumulators behind this point (after the matrix instructions: 16 wait states, more than
-// the 8-pass forms need before another instruction type reads their result).
-template <typename T>
-__device__ __forceinline__ void settle(floatx4& c0, floatx4& c1, floatx4& c2, floatx4& c3) {
-  if constexpr (sizeof(T) == 2) asm volatile("s_nop 15" : "+a"(c0), "+a"(c1), "+a"(c2), "+a"(c3));
-}
 
 // Tile shape: BM x BN per workgroup, WGM x WGN waves.
 template <typename T_, int BM_, int BN_, int WGM_, int WGN_>
@@ -95,9 +89,22 @@ struct Tile {
   static constexpr int LDS_BYTES = kStagesA * A_BYTES + kStagesB * B_BYTES;
   static constexpr int A_LD = A_BYTES / (16 * NT);  // 16-byte loads per thread per stage
   static constexpr int B_LD = B_BYTES / (16 * NT);
-  static_assert(BM % (64 * WGM) == 0 && BN % (64 * WGN) == 0, "the epilogues take wave tiles 64 rows or columns at a time");
+  static_assert(BM % (16 * WGM) == 0 && BN % (16 * WGN) == 0, "wave tile must be 16-blocked");
   static_assert(A_BYTES % (16 * NT) == 0 && B_BYTES % (16 * NT) == 0, "loads must divide evenly");
 };
+
+// Holds every use of the accumulators behind this point (after the matrix instructions: 16 wait states, more than
+// the 8-pass forms need before another instruction type reads their result).
+template <class TL>
+__device__ __forceinline__ void settle_all(floatx4 (&acc)[TL::MB][TL::NB]) {
+  if constexpr (sizeof(typename TL::T) == 2) {
+    static_assert(TL::NB % 2 == 0, "accumulators settle two blocks at a time");
+#pragma unroll
+    for (int mb = 0; mb < TL::MB; ++mb)
+#pragma unroll
+      for (int nb = 0; nb < TL::NB; nb += 2) asm volatile("s_nop 15" : "+a"(acc[mb][nb]), "+a"(acc[mb][nb + 1]));
+  }
+}
 
 // LDS has 64 banks of 4 bytes: two 128-byte tile rows share one bank window, and a
 // 16-byte access is served 16 lanes at a time.  XOR-ing the chunk index with (row >> 1)
@@ -315,11 +322,11 @@ __device__ __forceinline__ void gemm_mainloop(const typename TL::T* __restrict__
   constexpr int BAR = SLOTS / 2, SPACE0 = SLOTS >= 4 * NFRAG ? 3 : 1, SPACE1 = SLOTS >= 4 * NFRAG ? 2 : 1;
   // load i is issued LOAD_AT(i) slots behind the barrier: the A loads in the first quarter of the interval
   // (a 256 x 256 x 4096 tile takes 163 000 cycles with 1/8, 157 000 with 3/16 or 3/8, 153 600 with this)
-  constexpr int A_GAP = 2 * SLOTS / 4 / A_LD, B_GAP = 2 * SLOTS * 3 / 4 / B_LD;
+  constexpr int A_GAP = 2 * SLOTS / 4 / A_LD, B_GAP = (2 * SLOTS - 4 - A_LD * A_GAP) / B_LD;
   constexpr auto load_slot = [](int i) constexpr {
     return SLOTS + BAR + 1 + (i < A_LD ? i * A_GAP : A_LD * A_GAP + (i - A_LD) * B_GAP);
   };
-  static_assert(A_GAP >= 1 && B_GAP >= 1 && load_slot(NLD - 1) - 2 * SLOTS < SLOTS + BAR - 3 && BAR + NFRAG * SPACE1 <= SLOTS,
+  static_assert(A_GAP >= 1 && B_GAP >= 1 && load_slot(NLD - 1) - 2 * SLOTS < SLOTS + BAR - 3 && BAR + NB * SPACE1 <= SLOTS && BAR >= 2,
                 "not enough MFMA slots to hide the memory instructions");
 
   const int tid = threadIdx.x, lane = tid & 63;
@@ -571,21 +578,14 @@ __global__ __launch_bounds__(TL::NT) void gemm_nt_kernel(GemmShape g, Epi epi) {
 #pragma unroll
   for (int mb = 0; mb < TL::MB; ++mb)
 #pragma unroll
-    for (int nb = 0; nb < TL::NB; nb += 4) {
-#pragma unroll
-      for (int k = 0; k < 4; ++k) acc[mb][nb + k] = floatx4{0.f, 0.f, 0.f, 0.f};
-      settle<T>(acc[mb][nb], acc[mb][nb + 1], acc[mb][nb + 2], acc[mb][nb + 3]);
-    }
+    for (int nb = 0; nb < TL::NB; ++nb) acc[mb][nb] = floatx4{0.f, 0.f, 0.f, 0.f};
+  settle_all<TL>(acc);
 
   const T* A = static_cast<const T*>(g.A) + (int64_t)batch * g.batch_stride_a;
   const T* B = static_cast<const T*>(g.B) + (int64_t)batch * g.batch_stride_b;
   gemm_mainloop<TL, ATN, Epi::kSwap>(A, g.lda, g.M, m0, B, g.ldb, g.N, n0, slab0, slabs, g.slabs_per_block,
                          g.block_bytes_a, g.block_bytes_b, acc, lds, g.k_valid KT_STAMP_ARG);
-#pragma unroll
-  for (int mb = 0; mb < TL::MB; ++mb)
-#pragma unroll
-    for (int nb = 0; nb < TL::NB; nb += 4)
-      settle<T>(acc[mb][nb], acc[mb][nb + 1], acc[mb][nb + 2], acc[mb][nb + 3]);
+  settle_all<TL>(acc);
   KT_STAMP(g, 2);
   epi(acc, batch, tm, tn, ks, m0, n0);
   KT_STAMP(g, 3);
