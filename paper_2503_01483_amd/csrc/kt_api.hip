@@ -15,6 +15,7 @@
 #include "kt_cayley_d128.h"
 #include "kt_fused_d128.h"
 #include "kt_hadamard.h"
+#include "kt_skinny.h"
 
 namespace kt {
 
@@ -124,10 +125,14 @@ static inline int64_t round_up(int64_t a, int64_t b) { return ceil_div(a, b) * b
 
 constexpr int kNumCUs = 256;
 
-// fp32 d x d products (retraction, dR): 64 x 64 tiles while 128 x 128 ones would leave CUs idle.  A 128 x 128 tile takes
-// a CU about 4100 cycles per 32 of K, a 64 x 64 one a quarter of that, so t large tiles take one round and 4 t small
-// ones ceil(4 t / 256) quarter rounds: fewer up to t = 192.  Same bits (the order of K is the same).
-static inline bool small_f32_tiles(int64_t d, int64_t batch) { return ceil_div(d, 128) * ceil_div(d, 128) * batch <= kNumCUs * 3 / 4; }
+// fp32 products: 64 x 64 tiles when `tiles` 128 x 128 ones would leave CUs idle, in all of the launch or in its last
+// round.  A 128 x 128 tile takes a CU about 4100 cycles per 32 of K, a 64 x 64 one a little over a quarter of that, four
+// of them share a CU, and the bits are the same (the order of K is).  kt_fuse_rotation, us, large / small tiles: 48 tiles
+// 26 / 14, 256 tiles 143 / 139 (d = 2048), 704 tiles 378 / 354, 1024 tiles 976 / 989, 3584 tiles 3377 / 3448.
+static inline bool use_small_f32(int64_t tiles) {
+  return tiles <= kNumCUs || 33 * tiles < 32 * round_up(tiles, kNumCUs);
+}
+static inline bool small_f32_tiles(int64_t d, int64_t batch) { return use_small_f32(ceil_div(d, 128) * ceil_div(d, 128) * batch); }
 // Token-minor operands (X^T, G^T) are stored in blocks of this many tokens: within a block a
 // feature row is contiguous, blocks follow each other feature-row-set by feature-row-set, so
 // the 256 rows a tile streams together span 2 MiB per block instead of one page per row.
@@ -571,6 +576,58 @@ static kt_status run_loss_grad_fused(const LossGradPlan& p, const void* X, int64
   return KT_OK;
 }
 
+// ------------------------------------------------------------------ rotated rows ----
+// A few tokens (kt_skinny.h): Y = X R straight from R, partial sums of the row ranges in `scratch` (rt_bytes, the room
+// of the transposed copy of R that this path does not make).  R as the caller laid it out, so 16-byte reads of it
+// have to be possible.
+static bool skinny_ok(kt_dtype xdt, const void* R, int64_t ldr, kt_dtype rdt, int64_t n) {
+  return xdt == KT_BF16 && n <= kSkinnyMaxTokens && (reinterpret_cast<uintptr_t>(R) & 15) == 0 && ldr % (rdt == KT_F32 ? 4 : 8) == 0;
+}
+
+template <typename TR>
+static bool launch_skinny(const bf16* X, int64_t ldx, const TR* R, int64_t ldr, int64_t batch, int64_t n, int64_t d,
+                          char* scratch, size_t rt_bytes, float* Y, hipStream_t st) {
+  // about two workgroups per CU; every row range at least 256 rows (one round of the four waves); partials must fit
+  int64_t s = ceil_div(2 * kNumCUs, (d / 64) * batch);
+  const int64_t fit = (int64_t)(rt_bytes / ((size_t)batch * n * d * 4));
+  if (s > fit) s = fit;
+  if (s < 1) s = 1;
+  const int64_t k_per_wg = round_up(ceil_div(d, s), 256);
+  s = ceil_div(d, k_per_wg);
+  float* part = s > 1 ? reinterpret_cast<float*>(scratch) : Y;
+  const int64_t count = batch * n * d;
+  auto go = [&](auto tb_c) {
+    hipLaunchKernelGGL((skinny_rotate_kernel<TR, decltype(tb_c)::value>), dim3((unsigned)(d / 64), (unsigned)s, (unsigned)batch),
+                       dim3(256), 0, st, X, ldx, n * ldx, R, ldr, (int)n, (int)d, (int)k_per_wg, part, count);
+  };
+  if (n <= 16) go(std::integral_constant<int, 1>{});
+  else if (n <= 32) go(std::integral_constant<int, 2>{});
+  else go(std::integral_constant<int, 4>{});
+  if (s > 1)
+    hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)(ceil_div(count, 256) < 4096 ? ceil_div(count, 256) : 4096)),
+                       dim3(256), 0, st, part, count, (int)s, Y, count);
+  return launch_ok();
+}
+
+// Y [problems][rows][d] = X R (token-major, tokens on the rows of the GEMM) with the tile that fills the chip: the large one
+// (TL) unless it leaves CUs without a tile, then 128 x 128 (bf16) or 64 x 64 (fp32).  Fake-quant calls, us, large / small
+// tile: bf16 d = 4096, n = 128: 97 / 58, 1024: 105 / 64, 2048 (128 large tiles): 109 / 91, 2560: 112 / 116; d = 2048,
+// n = 4096 (128): 67 / 53, 6144: 72 / 73; fp32 d = 1024, n = 256: 75 / 30, 4096 (256 large tiles): 84 / 80; d = 2048,
+// n = 2048 (256): 154 / 142.
+template <typename T, class TL>
+static bool launch_rows_gemm(const T* X, int64_t ldx, int64_t x_batch_stride, const T* RT, int64_t problems, int64_t rows,
+                             int64_t d, float* Y, hipStream_t st) {
+  using Small = std::conditional_t<sizeof(T) == 4, TF_64, TB_128>;
+  auto go = [&](auto tile_tag) -> bool {
+    using G = decltype(tile_tag);
+    EpiStore<G> e;
+    e.C = Y; e.ldc = d; e.batch_stride = rows * d; e.split_stride = 0; e.M = (int)rows; e.N = (int)d;
+    return launch_gemm<G>(X, ldx, x_batch_stride, (int)rows, RT, d, d * d, (int)d, d, 0, (int)problems, e, st);
+  };
+  const int64_t tiles = ceil_div(rows, TL::BM) * ceil_div(d, TL::BN) * problems;
+  return (sizeof(T) == 4 ? use_small_f32(tiles) : tiles <= kNumCUs / 2) ? go(Small{}) : go(TL{});
+}
+
 // ------------------------------------------------------------------ fake-quant ----
 template <typename T, class TFWD, class TQ>
 static kt_status run_quant(const QuantPlan& p, const void* X, int64_t ldx, const void* R, int64_t ldr,
@@ -582,9 +639,11 @@ static kt_status run_quant(const QuantPlan& p, const void* X, int64_t ldx, const
   float* scales_ws = reinterpret_cast<float*>(ws + p.o_scales);
   float2* errpart = reinterpret_cast<float2*>(ws + p.o_errpart);
   const T* Xp = static_cast<const T*>(X);
-  if (!prep_rt<T>(R, ldr, rdt, RT, batch, d, st)) return fail(KT_ERR_DEVICE, "prep_rt launch failed");
+  const bool staged = !scales_in && (codes || err);
+  const bool skinny = staged && p.stage_problems == batch && skinny_ok(sizeof(T) == 2 ? KT_BF16 : KT_F32, R, ldr, rdt, n);
+  if (!skinny && !prep_rt<T>(R, ldr, rdt, RT, batch, d, st)) return fail(KT_ERR_DEVICE, "prep_rt launch failed");
   const float* scales = scales_in;
-  if (!scales_in && (codes || err)) {
+  if (staged) {
     // One GEMM instead of two: Y = X R is staged in fp32 (token-major: tokens on the rows of the GEMM), a
     // row kernel takes the maximum and quantises.  4 n d bytes written and read against 2 n d^2 flop saved.
     float* Ybuf = reinterpret_cast<float*>(ws + p.o_y);
@@ -592,11 +651,15 @@ static kt_status run_quant(const QuantPlan& p, const void* X, int64_t ldx, const
       const int64_t nb = batch - b0 < p.stage_problems ? batch - b0 : p.stage_problems;
       for (int64_t t0 = 0; t0 < n; t0 += p.stage_rows) {
         const int64_t nt = n - t0 < p.stage_rows ? n - t0 : p.stage_rows;
-        EpiStore<TQ> e;
-        e.C = Ybuf; e.ldc = d; e.batch_stride = nt * d; e.split_stride = 0; e.M = (int)nt; e.N = (int)d;
-        if (!launch_gemm<TQ>(Xp + (b0 * n + t0) * ldx, ldx, n * ldx, (int)nt, RT + b0 * d * d, d, d * d, (int)d, d,
-                             0, (int)nb, e, st))
-          return fail(KT_ERR_DEVICE, "rotation GEMM launch failed");
+        bool ok;
+        if (skinny) {
+          const bf16* Xb = reinterpret_cast<const bf16*>(Xp);
+          ok = rdt == KT_F32 ? launch_skinny(Xb, ldx, static_cast<const float*>(R), ldr, batch, n, d, ws + p.o_rt, p.o_amax - p.o_rt, Ybuf, st)
+                             : launch_skinny(Xb, ldx, static_cast<const bf16*>(R), ldr, batch, n, d, ws + p.o_rt, p.o_amax - p.o_rt, Ybuf, st);
+        } else {
+          ok = launch_rows_gemm<T, TQ>(Xp + (b0 * n + t0) * ldx, ldx, n * ldx, RT + b0 * d * d, nb, nt, d, Ybuf, st);
+        }
+        if (!ok) return fail(KT_ERR_DEVICE, "rotation GEMM launch failed");
         const int64_t rows = nb * nt, row0 = b0 * n + t0;
         float* so = scales_out ? scales_out + row0 : nullptr;
         int8_t* co = codes ? codes + row0 * d : nullptr;
@@ -1179,7 +1242,8 @@ kt_status kt_rotate_quant_metrics(const void* X, int64_t ldx, const void* R, int
     using TL = decltype(tile_tag);
     T* RT = reinterpret_cast<T*>(ws);
     const T* Xp = static_cast<const T*>(X);
-    if (!prep_rt<T>(R, ldr, r_dtype, RT, batch, d, st)) return fail(KT_ERR_DEVICE, "prep_rt launch failed");
+    const bool skinny = sp == batch && skinny_ok(x_dtype, R, ldr, r_dtype, n);
+    if (!skinny && !prep_rt<T>(R, ldr, r_dtype, RT, batch, d, st)) return fail(KT_ERR_DEVICE, "prep_rt launch failed");
     if (success) {
       hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(256), 0, st, reinterpret_cast<unsigned*>(success),
                          2 * batch, 0u);
@@ -1188,11 +1252,15 @@ kt_status kt_rotate_quant_metrics(const void* X, int64_t ldx, const void* R, int
       const int64_t nb = batch - b0 < sp ? batch - b0 : sp;
       for (int64_t t0 = 0; t0 < n; t0 += sr) {
         const int64_t nt = n - t0 < sr ? n - t0 : sr, row0 = b0 * n + t0;
-        EpiStore<TL> e;
-        e.C = Yb; e.ldc = d; e.batch_stride = nt * d; e.split_stride = 0; e.M = (int)nt; e.N = (int)d;
-        if (!launch_gemm<TL>(Xp + row0 * ldx, ldx, n * ldx, (int)nt, RT + b0 * d * d, d, d * d, (int)d, d, 0, (int)nb,
-                             e, st))
-          return fail(KT_ERR_DEVICE, "rotation GEMM launch failed");
+        bool ok;
+        if (skinny) {
+          const bf16* Xb = static_cast<const bf16*>(X);
+          ok = r_dtype == KT_F32 ? launch_skinny(Xb, ldx, static_cast<const float*>(R), ldr, batch, n, d, ws, rt_bytes, Yb, st)
+                                 : launch_skinny(Xb, ldx, static_cast<const bf16*>(R), ldr, batch, n, d, ws, rt_bytes, Yb, st);
+        } else {
+          ok = launch_rows_gemm<T, TL>(Xp + row0 * ldx, ldx, n * ldx, RT + b0 * d * d, nb, nt, d, Yb, st);
+        }
+        if (!ok) return fail(KT_ERR_DEVICE, "rotation GEMM launch failed");
         // the row in 4 / 8 / 16 / 32 float4 registers per lane; rows that fill them exactly skip every bounds test
         auto rows_kernel = d == 1024   ? quant_metrics_row_kernel<T, 4, true>
                            : d < 1024  ? quant_metrics_row_kernel<T, 4, false>
@@ -1262,19 +1330,25 @@ kt_status kt_fuse_rotation(const float* W, int64_t ldw, const float* R, int64_t 
   float* RT = reinterpret_cast<float*>(ws);
   if (!prep_rt<float>(R, ldr, KT_F32, RT, 1, d, st)) return fail(KT_ERR_DEVICE, "prep_rt launch failed");
   ProfScope prof(5, st);
-  EpiStore<TF> e;
-  e.C = Wout; e.ldc = ldo; e.batch_stride = 0; e.split_stride = 0;
+  // C [M][N] = A B^T, contraction over d; 64 x 64 tiles while 128 x 128 ones would leave CUs idle
+  auto product = [&](const float* A, int64_t lda, int64_t M, const float* B, int64_t ldb, int64_t N) -> bool {
+    auto go = [&](auto tile_tag) -> bool {
+      using TL = decltype(tile_tag);
+      EpiStore<TL> e;
+      e.C = Wout; e.ldc = ldo; e.batch_stride = 0; e.split_stride = 0; e.M = (int)M; e.N = (int)N;
+      return launch_gemm<TL>(A, lda, 0, (int)M, B, ldb, 0, (int)N, d, 0, 1, e, st);
+    };
+    return use_small_f32(ceil_div(M, TF::BM) * ceil_div(N, TF::BN)) ? go(TF_64{}) : go(TF{});
+  };
   if (side == 0) {  // Wout [k][d] = W R = W (R^T)^T
-    e.M = (int)k; e.N = (int)d;
-    if (!launch_gemm<TF>(W, ldw, 0, (int)k, RT, d, 0, (int)d, d, 0, 1, e, st))
+    if (!product(W, ldw, k, RT, d, d))
       return fail(KT_ERR_DEVICE, "fusion GEMM launch failed");
   } else {          // Wout [d][k] = R^T W = R^T (W^T)^T
     float* Wt = reinterpret_cast<float*>(ws + rt_bytes);
     hipLaunchKernelGGL(transpose_f32_kernel, dim3((unsigned)ceil_div(k, 32), (unsigned)ceil_div(d, 32)), dim3(256),
                        0, st, W, ldw, Wt, d, (int)d, (int)k);
     if (!launch_ok()) return fail(KT_ERR_DEVICE, "weight transpose launch failed");
-    e.M = (int)d; e.N = (int)k;
-    if (!launch_gemm<TF>(RT, d, 0, (int)d, Wt, d, 0, (int)k, d, 0, 1, e, st))
+    if (!product(RT, d, d, Wt, d, k))
       return fail(KT_ERR_DEVICE, "fusion GEMM launch failed");
   }
   return KT_OK;

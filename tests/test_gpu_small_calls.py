@@ -1,0 +1,71 @@
+"""Calls that leave most of the chip without a tile take other kernels than large ones: a handful of tokens straight from
+R, small tiles for few outputs.  Each at the edges of its range, element by element against a 64-bit product; the bound is that of
+an fp32 sum of d products in any order, d 2^-24 sum |x| |r| (the products of bf16 values are exact), doubled for the
+partial sums."""
+import numpy as np
+import pytest
+import torch
+
+import ktgen
+import paper_2503_01483_amd as kt
+
+pytestmark = pytest.mark.gpu
+
+
+def _problem(batch, n, d, xdt, rdt, ld_pad, seed):
+    X = torch.stack([ktgen.make_x(n, d, seed=seed + b, outlier_cols=3, outlier_scale=40.0, dtype=xdt) for b in range(batch)])
+    R = torch.stack([ktgen.random_orthogonal(d, seed=seed + 10 + b) for b in range(batch)])
+    if rdt == "bf16":
+        R = R.to(torch.bfloat16)
+    wide = torch.full((batch, d, d + ld_pad), 7.0, dtype=R.dtype)
+    wide[:, :, :d] = R
+    return X.cuda(), wide.cuda()[:, :, :d], R
+
+
+@pytest.mark.parametrize("batch,n,d,xdt,rdt,ld_pad", [
+    (1, 1, 256, "bf16", "f32", 0), (1, 16, 1152, "bf16", "f32", 4), (2, 17, 384, "bf16", "f32", 0),
+    (1, 32, 128, "bf16", "bf16", 8), (3, 33, 640, "bf16", "bf16", 0), (1, 64, 2048, "bf16", "f32", 0),
+    (1, 5, 512, "bf16", "f32", 1),      # rows of R not 16-byte aligned: general path
+    (1, 65, 2048, "bf16", "f32", 0), (1, 700, 896, "bf16", "f32", 0), (1, 130, 384, "f32", "f32", 0),
+])
+def test_rotated_rows(batch, n, d, xdt, rdt, ld_pad):
+    X, R, Rh = _problem(batch, n, d, xdt, rdt, ld_pad, 3 * n + d)
+    Y = torch.full((batch, n, d), float("nan"), device="cuda")
+    thr = torch.empty((batch, n), device="cuda")
+    kt.kt_rotate_quant_metrics(X, R, quantile=1.0, Y=Y, threshold=thr)
+    scales = torch.empty((batch, n), device="cuda")
+    codes = torch.empty((batch, n, d), dtype=torch.int8, device="cuda")
+    err = torch.empty((batch, n, 2), device="cuda")
+    kt.kt_rotate_fakequant_int4(X, R, scales_out=scales, codes=codes, err=err)
+    torch.cuda.synchronize()
+    for b in range(batch):
+        x = ktgen.to_f64(X[b])
+        r = ktgen.to_f64(ktgen.bf16_round(Rh[b]) if xdt == "bf16" else Rh[b])
+        ref, bound = x @ r, 2.0 * d * 2.0 ** -24 * (np.abs(x) @ np.abs(r))
+        y = Y[b].cpu().double().numpy()
+        assert np.all(np.abs(y - ref) <= bound)
+        assert np.array_equal(thr[b].cpu().numpy(), np.abs(y).max(1).astype(np.float32))
+        s = scales[b].cpu().numpy()
+        assert np.all(np.abs(s - np.abs(ref).max(1) / 7) <= (bound.max(1) + 1e-6 * np.abs(ref).max(1)) / 7)
+        # codes from the library's own scale: off by rounding only where the value sits within the bound of a boundary
+        v = ref / s[:, None].astype(np.float64)
+        q = codes[b].cpu().numpy()
+        off = np.abs(q - np.clip(v, -7, 7)) - 0.5
+        assert np.all(off <= bound / s[:, None] + 1e-5)
+        e = ((ref - q * s[:, None].astype(np.float64)) ** 2).sum(1)
+        assert np.allclose(err[b, :, 0].cpu().numpy(), e, rtol=1e-4) and np.allclose(err[b, :, 1].cpu().numpy(), (ref ** 2).sum(1), rtol=1e-4)
+
+
+@pytest.mark.parametrize("side", [0, 1])
+@pytest.mark.parametrize("k,d", [(4, 128), (132, 256), (1000, 384), (2052, 2048), (5632, 2048)])
+def test_fused_weights_small_and_large_tiles(side, k, d):
+    """The number of 128 x 128 tiles decides the tile; 704 of them (the last size) take small tiles again."""
+    g = torch.Generator().manual_seed(k + d)
+    W = torch.randn((k, d) if side == 0 else (d, k), generator=g)
+    R = ktgen.random_orthogonal(d, seed=k)
+    out = kt.kt_fuse_rotation(W.cuda(), R.cuda(), side)
+    torch.cuda.synchronize()
+    w, r = W.double().numpy(), R.double().numpy()
+    ref = w @ r if side == 0 else r.T @ w
+    size = np.abs(w) @ np.abs(r) if side == 0 else np.abs(r).T @ np.abs(w)
+    assert np.all(np.abs(out.cpu().double().numpy() - ref) <= d * 2.0 ** -23 * size)
