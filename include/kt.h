@@ -311,12 +311,14 @@ kt_status kt_quant_sensitivity(const float* Y, int64_t count, int32_t bits, cons
  * This covers the hidden and FFN sizes 2^k, 3, 5, 7, 9, 11, 15, 27 x 2^k (5120, 6144, 13824,
  * 14336, 28672, ...); 11008 = 43 x 2^8 has no such factor up to order 128 and is refused.
  *  X, Y   [n][ldx], [n][ldy] row-major, `dtype` (KT_BF16: fp32 arithmetic, rounded to nearest
- *         even at the end; for m > 1 the result of the S factor passes through Y in bf16 before the
- *         H_m factor is applied); Y may be X (in place).  Rows 16-byte aligned.
+ *         even at the end; for m > 1 and d > 32768 - and on fewer than 64 rows of d = 32768 - the
+ *         result of the S factor passes through Y in bf16 before the H_m factor is applied); Y may
+ *         be X (in place).  Rows 16-byte aligned.
  *  signs  [d] int8 +-1 (the random diagonal of a "random Hadamard" rotation), or NULL.
  *  d      as above with 128 <= 2^k <= 4096 and m <= 128.  For m = 1 without signs the transform
  *         is its own inverse.
- * No workspace.  HBM-bound: one read and one write of the rows per factor.
+ * No workspace.  HBM-bound: one read and one write of the rows (per factor for fp32 rows with m > 1
+ * and where the bf16 result passes through Y).
  */
 kt_status kt_hadamard_rows(const void* X, int64_t ldx, void* Y, int64_t ldy, const int8_t* signs,
                            int64_t n, int64_t d, kt_dtype dtype, void* stream);

@@ -1,8 +1,9 @@
 // kt_hadamard.h -- the online rotations of "Placement of the Rotations" (R3, R4, R5: random
 // Hadamard matrices applied to activations at run time):  y = (x * signs) H_d / sqrt(d) per token
 // row.  hadamard_rows_kernel: H_d the Sylvester-Hadamard matrix, d = 2^k <= 4096.
-// hadamard_cross_kernel (end of file): the second factor of H_d = H_m (x) S_{2^k} for the sizes
-// m 2^k that are not powers of two (or exceed 4096).
+// hadamard_cross_kernel: the second factor of H_d = H_m (x) S_{2^k} for the sizes m 2^k that are not
+// powers of two (or exceed 4096).  hadamard_onepass_kernel (end of file): both factors in one pass
+// over bf16 rows of up to 32768.
 //
 // HBM-bound: 2 d element reads + 2 d element writes per row against d log2 d additions.  One WAVE
 // owns a chunk of 4096 consecutive elements (4096 / d whole rows) and never meets the other waves:
@@ -414,6 +415,229 @@ __global__ __launch_bounds__(256) void hadamard_cross_mfma_kernel(__bf16* __rest
     }
     // the next tile's stores to xt come after every wave has passed the barrier above (its reads of
     // xt are done), its stores to yt after the next barrier (the copy-out above is done)
+  }
+}
+
+// ---- both factors in one pass, bf16 rows of up to 32768 elements ------------------------------------
+// Two kernels move a row through memory twice.  Here a workgroup keeps a whole row in LDS:
+//   H_m (x) S_p2 = H_M (x) S_P,  M = m 2^j <= 32 waves (4, or 8 above d = 16384), P = p2 / 2^j = 64 or 128,
+// (H_M = H_m (x) S_2^j).  The H_M factor comes FIRST, on the matrix cores: the inputs are bf16 and the entries +-1,
+// so every product is exact and nothing is rounded between the factors.  A wave takes 32 of the M outputs and all
+// P columns, so that the S_P factor is butterflies in its own registers (32 x 32 blocks, a lane owns one output and
+// 16 columns of each block: five or more index bits are register bits, the sixth is the wave half).
+// Per row: registers -> LDS (with the signs, an XOR of the sign bits that is the same for every row), request the next
+// row, matrix instructions (the row read with K = input index as the row of the LDS tile, transposing reads), butterflies,
+// bf16 results -> the same LDS, 16-byte stores.  Four barriers a row; the workgroups that share a CU overlap.
+// LDS rows are 2 P bytes; 64-byte pieces (reads) and 16-byte chunks (results) are XOR-swizzled with the row.
+// Bound: HBM, one read and one write of the rows.  512 MiB of rows, two kernels / this one: d = 14336 491 / 215 us
+// (5.0 TB/s; 16 rows, set-up and all: 17 / 11), 13824 683 / 228, 8192 547 / 219, 5120 528 / 253, 28672 483 / 344,
+// 1536 (one wave of four at work) 778 / 510.
+struct HadamardFactor {
+  unsigned long long squares[2];  // bit x: x is a quadratic residue modulo q
+  int m, kind, h, q, log2j;       // H_m as in hadamard_cross_kernel; M = m << log2j
+};
+
+// whether H_m[a][b] is -1
+__device__ __forceinline__ int hadamard_negative(const HadamardFactor& f, int a, int b) {
+  int neg = 0;
+  if (f.kind == 0) {
+    neg = __builtin_popcount(a & b) & 1;
+  } else {
+    const int alow = a < f.h, blow = b < f.h;
+    const int u = alow ? a : a - f.h, v = blow ? b : b - f.h;
+    int plus;  // conference matrix entry + identity (u == v: the identity alone)
+    if (u == v) {
+      plus = 1;
+    } else if (u == 0 || v == 0) {
+      plus = !(f.kind == 1 && v == 0);
+    } else {
+      int x = u - v;
+      if (x < 0) x += f.q;
+      plus = (int)((f.squares[x >> 6] >> (x & 63)) & 1);
+    }
+    // kind 2: [C + I, C - I; C - I, -C - I]: the diagonal changes sign off the first block, C in the last one
+    if (f.kind == 2) {
+      if (!alow && !blow) plus ^= 1;
+      else if (alow != blow && u == v) plus ^= 1;
+    }
+    neg = !plus;
+  }
+  return neg;
+}
+
+// LOGP = log2 P; 64 WAVES threads; d <= 32 WAVES P
+template <int LOGP, int WAVES>
+__global__ __launch_bounds__(64 * WAVES, 2) void hadamard_onepass_kernel(const __bf16* __restrict__ X, int64_t ldx,
+                                                                                  __bf16* __restrict__ Y, int64_t ldy,
+                                                                                  const int8_t* __restrict__ signs, int64_t n,
+                                                                                  float scale, HadamardFactor fac) {
+  constexpr int P = 1 << LOGP, NBLK = P / 32, ROWB = 2 * P, CPR = P / 8;  // CPR: 16-byte chunks per tile row
+  constexpr int NT = 64 * WAVES, KSM = 2 * WAVES, NCH = 32 * WAVES * CPR / NT;  // matrix steps, chunks per thread: at most
+  extern __shared__ __align__(16) char had_lds[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, half = lane >> 5, l32 = lane & 31;
+  const int M = fac.m << fac.log2j, KS = (M + 15) >> 4, chunks = M * CPR;
+  // 64-byte piece of a row read by a transposing read, and 16-byte chunk of a result row: see above
+  auto read_key = [](int k) __attribute__((always_inline)) { return LOGP == 6 ? (k >> 1) & 1 : k & 3; };
+  auto out_key = [](int a) __attribute__((always_inline)) { return LOGP == 6 ? (a >> 1) & 7 : a & 15; };
+
+  // the signs of H_m as 128-bit rows in LDS: bit a of row b
+  unsigned* tab = reinterpret_cast<unsigned*>(had_lds);
+  for (int i = tid; i < 4 * fac.m; i += NT) tab[i] = 0u;
+  __syncthreads();
+  for (int i = tid; i < fac.m * fac.m; i += NT) {
+    const int b = i / fac.m, a = i - b * fac.m;
+    if (hadamard_negative(fac, a, b)) atomicOr(&tab[4 * b + (a >> 5)], 1u << (a & 31));
+  }
+  __syncthreads();
+  // this wave's 32 columns of H_M as B operands: lane = output o = 32 wave + l32, 8 inputs i = 16 s + 8 half + e;
+  // H_M[i][o] = H_m[i / 2^j][o / 2^j] (-1)^(common bits of i and o below 2^j)
+  intx4 hf[KSM];
+  {
+    const int o = 32 * wave + l32, low = o & ((1 << fac.log2j) - 1);
+    unsigned row[4] = {0u, 0u, 0u, 0u};
+    if (o < M) {
+#pragma unroll
+      for (int w = 0; w < 4; ++w) row[w] = tab[4 * (o >> fac.log2j) + w];
+    }
+#pragma unroll
+    for (int s = 0; s < KSM; ++s) {
+      const int i0 = 16 * s + 8 * half, a0 = i0 >> fac.log2j;
+      const unsigned word = a0 < 64 ? (a0 < 32 ? row[0] : row[1]) : (a0 < 96 ? row[2] : row[3]);
+      const unsigned bits = word >> (a0 & 31);  // the eight inputs share a word: a0 is a multiple of 8 / 2^j
+#pragma unroll
+      for (int w = 0; w < 4; ++w) {
+        unsigned v = 0u;
+#pragma unroll
+        for (int e = 0; e < 2; ++e) {
+          const int i = i0 + 2 * w + e;
+          const unsigned neg = ((bits >> ((i >> fac.log2j) - a0)) ^ (unsigned)__builtin_popcount(i & low)) & 1u;
+          v |= ((i < M && o < M) ? 0x3f80u | neg << 15 : 0u) << (16 * e);  // bf16 1.0 is 0x3f80
+        }
+        hf[s][w] = (int)v;
+      }
+    }
+  }
+  // chunk tid + NT i of a row: the sign bits of its eight values, as the words to XOR with or (8 waves, whose matrix
+  // operands leave fewer registers) as one byte to make them from
+  constexpr bool PACKED = WAVES == 8;
+  intx4 flip[PACKED ? 1 : NCH];
+  unsigned flip8[(NCH + 3) / 4];
+  auto sign_words = [](unsigned byte) __attribute__((always_inline)) {
+    intx4 v;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = (int)((byte << (15 - 2 * e) & 0x8000u) | (byte << (30 - 2 * e) & 0x80000000u));
+    return v;
+  };
+#pragma unroll
+  for (int i = 0; i < NCH; ++i) {
+    unsigned byte = 0u;
+    const int c = tid + NT * i;
+    if (signs && c < chunks) {
+      unsigned b[2];
+      __builtin_memcpy(b, signs + 8 * c, 8);  // (any alignment)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) byte |= (b[e >> 2] >> (8 * (e & 3) + 7) & 1u) << e;
+    }
+    if constexpr (PACKED) flip8[i / 4] = (i % 4 ? flip8[i / 4] : 0u) | byte << (8 * (i % 4));
+    else flip[i] = sign_words(byte);
+  }
+  __syncthreads();  // the table has been read
+  // tile rows M .. 16 KS - 1 meet zeros of H_M: they have to be finite
+  for (int c = chunks + tid; c < 16 * KS * CPR; c += NT) reinterpret_cast<intx4*>(had_lds)[c] = intx4{0, 0, 0, 0};
+
+  const int g16 = lane >> 4, rr = lane & 15;
+  const int tr_row = 8 * (g16 >> 1) + (rr >> 2), tr_col = 16 * (g16 & 1) + 4 * (rr & 3);
+  int tr[NBLK];
+#pragma unroll
+  for (int b = 0; b < NBLK; ++b) tr[b] = tr_row * ROWB + ((b ^ read_key(tr_row)) << 6) + 2 * tr_col;
+
+  intx4 nxt[NCH];
+  auto request = [&](int64_t row) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < NCH; ++i) {
+      const int c = tid + NT * i;
+      if (row < n && c < chunks) nxt[i] = *reinterpret_cast<const intx4*>(X + row * ldx + 8 * c);
+    }
+  };
+  request(blockIdx.x);
+#pragma unroll 1
+  for (int64_t row = blockIdx.x; row < n; row += gridDim.x) {
+#pragma unroll
+    for (int i = 0; i < NCH; ++i) {
+      const int c = tid + NT * i, k = c / CPR, pos = c % CPR;
+      if (c < chunks) *reinterpret_cast<intx4*>(had_lds + k * ROWB + ((pos ^ (read_key(k) << 2)) << 4)) = nxt[i] ^ (PACKED ? sign_words(flip8[i / 4] >> (8 * (i % 4)) & 0xffu) : flip[PACKED ? 0 : i]);
+    }
+    request(row + gridDim.x);
+    lds_barrier();  // (the requested row stays in flight)
+    floatx16 acc[NBLK];
+#pragma unroll
+    for (int b = 0; b < NBLK; ++b)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[b][r] = 0.f;
+    if (32 * wave < M) {
+#pragma unroll
+      for (int s = 0; s < KSM; ++s)
+        if (s < KS) {
+#pragma unroll
+          for (int b = 0; b < NBLK; ++b) {
+            const intx4 xf = read_tr_operand(had_lds, tr[b] + s * 16 * ROWB, tr[b] + s * 16 * ROWB + 4 * ROWB);
+            acc[b] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16x8, xf), __builtin_bit_cast(bf16x8, hf[s]),
+                                                             acc[b], 0, 0, 0);
+          }
+          __builtin_amdgcn_sched_barrier(0);  // fragments of one step at a time
+        }
+    }
+    lds_barrier();  // every wave has read the row
+    // lane: output 32 wave + l32, column 32 b + 8 (r / 4) + 4 half + (r & 3): index bits 0, 1 (r & 3), 3, 4 (r / 4) and 5 .. (b)
+#pragma unroll
+    for (int st = 1; st < 16; st <<= 1)
+#pragma unroll
+      for (int b = 0; b < NBLK; ++b)
+#pragma unroll
+        for (int r = 0; r < 16; ++r)
+          if ((r & st) == 0) {
+            const float u = acc[b][r], v = acc[b][r | st];
+            acc[b][r] = u + v;
+            acc[b][r | st] = u - v;
+          }
+#pragma unroll
+    for (int st = 1; st < NBLK; st <<= 1)
+#pragma unroll
+      for (int b = 0; b < NBLK; ++b)
+        if ((b & st) == 0) {
+          const floatx16 u = acc[b], v = acc[b | st];
+          acc[b] = u + v;
+          acc[b | st] = u - v;
+        }
+    // bit 2, the wave half: exchanging registers r / 4 even and odd, the lower half ends up with the eight columns of the
+    // even group, the upper half with those of the odd one: 16 bytes of a result row per lane
+    const int a = 32 * wave + l32;
+    if (a < M) {
+#pragma unroll
+      for (int b = 0; b < NBLK; ++b)
+#pragma unroll
+        for (int gp = 0; gp < 2; ++gp) {
+          typedef __bf16 bf16x8v __attribute__((ext_vector_type(8)));
+          bf16x8v o;
+#pragma unroll
+          for (int i = 0; i < 4; ++i) {
+            float x = acc[b][8 * gp + i], y = acc[b][8 * gp + 4 + i];
+            swap_halves(x, y);
+            o[i] = (__bf16)((x + y) * scale);
+            o[4 + i] = (__bf16)((x - y) * scale);
+          }
+          const int pos = 4 * b + 2 * gp + half;
+          *reinterpret_cast<bf16x8v*>(had_lds + a * ROWB + ((pos ^ out_key(a)) << 4)) = o;
+        }
+    }
+    lds_barrier();
+#pragma unroll
+    for (int i = 0; i < NCH; ++i) {
+      const int c = tid + NT * i, k = c / CPR, pos = c % CPR;
+      if (c < chunks)
+        *reinterpret_cast<intx4*>(Y + row * ldy + 8 * c) = *reinterpret_cast<const intx4*>(had_lds + k * ROWB + ((pos ^ out_key(k)) << 4));
+    }
+    lds_barrier();  // the results have been read: the next row may come
   }
 }
 

@@ -1,0 +1,58 @@
+"""bf16 rows of m 2^k elements, m > 1, up to 32768, are transformed in one pass: the order-M factor exactly on the matrix
+cores, the rest in fp32, ONE rounding to bf16.  So the bound has no intermediate rounding in it: 1e-5 of the row norm for the
+fp32 tree plus 2^-8 of the value for the rounding."""
+import numpy as np
+import pytest
+import torch
+
+import ktgen
+import oracle
+import paper_2503_01483_amd as kt
+
+pytestmark = pytest.mark.gpu
+
+
+# Paley I and II, Sylvester; one to eight waves at work, M a multiple of 16 or not, 64 and 128 columns, more rows than workgroups
+@pytest.mark.parametrize("n,d", [(3, 1536), (70, 2560), (5, 4608), (9, 5120), (40, 5632), (600, 6144), (4, 8192), (3, 9216), (5, 13824),
+                                 (530, 14336), (2, 16384), (1, 18432), (3, 20480), (300, 24576), (2, 28672), (2, 27648), (65, 32768)])
+@pytest.mark.parametrize("use_signs", [True, False])
+def test_one_rounding(n, d, use_signs):
+    rows = min(n, 4)  # the oracle's rows: the first ones and the last
+    X = ktgen.make_x(n, d, seed=n + d, outlier_cols=3, outlier_scale=40.0, t_frac=0.02, dtype="bf16")
+    g = torch.Generator().manual_seed(d)
+    store = (torch.randint(0, 2, (d + 1,), generator=g) * 2 - 1).to(torch.int8)
+    sd = store.cuda()[1:] if use_signs else None    # any alignment
+    Y = kt.kt_hadamard_rows(X.cuda(), signs=sd)
+    torch.cuda.synchronize()
+    pick = np.unique(np.r_[np.arange(rows), n - 1])
+    ref = oracle.hadamard_rows(ktgen.to_f64(X)[pick], store[1:].numpy().astype(np.float64) if use_signs else None)
+    got = Y.float().cpu().numpy().astype(np.float64)
+    rown = np.linalg.norm(ref, axis=1, keepdims=True)
+    assert (np.abs(got[pick] - ref) <= 1e-5 * rown + np.abs(ref) * 2.0 ** -8).all()
+    assert np.allclose(np.linalg.norm(got, axis=1), np.linalg.norm(ktgen.to_f64(X), axis=1), rtol=3e-3)
+
+
+@pytest.mark.parametrize("d", [3072, 14336, 28672])
+def test_strided_rows_in_place(d):
+    n = 11
+    buf = torch.randn(n, d + 72, device="cuda").to(torch.bfloat16)
+    X, guard = buf[:, :d], buf[:, d:].clone()
+    ref = oracle.hadamard_rows(ktgen.to_f64(X.contiguous()))
+    other = torch.empty(n, d + 8, dtype=torch.bfloat16, device="cuda")
+    kt.kt_hadamard_rows(X, out=other[:, :d])
+    kt.kt_hadamard_rows(X, out=X)
+    torch.cuda.synchronize()
+    assert torch.equal(other[:, :d], X) and torch.equal(buf[:, d:], guard)
+    rown = np.linalg.norm(ref, axis=1, keepdims=True)
+    assert (np.abs(ktgen.to_f64(X.contiguous()) - ref) <= 1e-5 * rown + np.abs(ref) * 2.0 ** -8).all()
+
+
+def test_infinities_and_nan_stay_in_their_row():
+    d = 13824  # 108 x 128: the tile has padding rows
+    X = torch.ones(5, d, device="cuda", dtype=torch.bfloat16)
+    X[1, 77] = float("inf")
+    X[3, 4000] = float("nan")
+    Y = kt.kt_hadamard_rows(X)
+    torch.cuda.synchronize()
+    assert torch.isinf(Y[1]).all() and torch.isnan(Y[3]).all()
+    assert torch.isfinite(Y[[0, 2, 4]]).all() and torch.equal(Y[0], Y[2]) and torch.equal(Y[0], Y[4])
