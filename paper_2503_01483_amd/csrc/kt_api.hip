@@ -1239,9 +1239,9 @@ kt_status kt_rotate_fakequant_int4(const void* X, int64_t ldx, const void* R, in
   if (!p.fp32 && d == 128) {  // one pass over X (kt_fused_d128.h)
     bf16* RT = reinterpret_cast<bf16*>(ws + p.o_rt);
     if (!prep_rt<bf16>(R, ldr, r_dtype, RT, batch, d, st)) return fail(KT_ERR_DEVICE, "prep_rt launch failed");
-    const int64_t tiles = ceil_div(n, 32);
-    int64_t wgs = ceil_div(4 * kNumCUs, batch);  // about four workgroups per CU over all problems
-    if (wgs > ceil_div(tiles, 4)) wgs = ceil_div(tiles, 4);
+    const int64_t tiles = ceil_div(n, 16);
+    int64_t wgs = ceil_div(2 * kNumCUs, batch);  // two workgroups per CU over all problems: what the registers let it hold
+    if (wgs > ceil_div(tiles, 8)) wgs = ceil_div(tiles, 8);  // a wave loads all of R^T (32 KiB) first: 32 tokens at least
     hipLaunchKernelGGL(quant_d128_kernel, dim3((unsigned)wgs, (unsigned)batch), dim3(256), 0, st,
                        static_cast<const bf16*>(X), ldx, n * ldx, RT, (int)n, clip_ratio, scales_in, scales_out, codes,
                        reinterpret_cast<float2*>(err));

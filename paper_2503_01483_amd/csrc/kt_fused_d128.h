@@ -56,6 +56,16 @@ __device__ __forceinline__ void mfma_y(floatx16& y, const intx4& rt, const intx4
 __device__ __forceinline__ void mfma_dr(floatx16& acc, const intx4& xt, const intx4& gt) {
   asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(xt), "v"(gt));
 }
+// the 16 x 16 forms (quant_d128_kernel)
+__device__ __forceinline__ void mfma16_y_first(floatx4& y, const intx4& rt, const intx4& x) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=&v"(y) : "a"(rt), "v"(x));
+}
+__device__ __forceinline__ void mfma16_y(floatx4& y, const intx4& rt, const intx4& x) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(y) : "a"(rt), "v"(x));
+}
+__device__ __forceinline__ void mfma16_result_fence(floatx4 (&y)[8]) {
+  asm volatile("s_nop 15" : "+v"(y[0]), "+v"(y[1]), "+v"(y[2]), "+v"(y[3]), "+v"(y[4]), "+v"(y[5]), "+v"(y[6]), "+v"(y[7]));
+}
 // An 8-pass matrix instruction must be 11 issue slots old before another instruction type
 // reads its result.
 __device__ __forceinline__ void mfma_result_fence(floatx16& a, floatx16& b, floatx16& c, floatx16& d) {
@@ -384,42 +394,45 @@ __global__ __launch_bounds__(256) void fused_d128_kernel(const __bf16* __restric
 // A lane pair holds a whole rotated token row, so the row maximum, the scale, the codes and the
 // error sums all come out of ONE pass over X (the generic path parks the rotated rows in an fp32
 // staging buffer between the GEMM and a row kernel).
-// Every wave is on its own: 32-token tiles, its rows staged through 8 KiB of private LDS (loads of
+// Every wave is on its own: 16-token tiles, its rows staged through 4 KiB of private LDS (loads of
 // the next tile in flight), R^T fragments in accumulation registers, no workgroup barrier.
+// 16 x 16 blocks (one token, 32 features per lane) keep a wave under 256 registers, so that two share a SIMD: one wave's
+// loads, matrix instructions and quantiser arithmetic hide behind the other's.  256 problems x 4096 tokens: one wave per
+// SIMD (32-token tiles, 324 registers, twice the workgroups) 139 us, this form 118 us; two tiles in flight instead of one: 7 % slower.
 // Arithmetic identical to the generic path: s = (clip amax) / 7, q = clamp(rint(y (1/s)), -7, 7).
 // grid = (waves / 4, batch).
-__global__ __launch_bounds__(256) void quant_d128_kernel(const __bf16* __restrict__ X, int64_t ldx,
+__global__ __launch_bounds__(256, 2) void quant_d128_kernel(const __bf16* __restrict__ X, int64_t ldx,
                                                          int64_t x_batch_stride, const __bf16* __restrict__ RT,
                                                          int n, float clip, const float* __restrict__ scales_in,
                                                          float* __restrict__ scales_out, int8_t* __restrict__ codes,
                                                          float2* __restrict__ err) {
-  __shared__ __align__(16) char lds_all[4 * 32 * 256];
+  __shared__ __align__(16) char lds_all[4 * 16 * 256];
   constexpr int D = 128;
   const int b = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int half = lane >> 5, l32 = lane & 31;
-  char* lds = lds_all + wave * (32 * 256);
+  const int q = lane >> 4, l16 = lane & 15;
+  char* lds = lds_all + wave * (16 * 256);
   X += (int64_t)b * x_batch_stride;
   RT += (int64_t)b * D * D;
-  const int tiles = (n + 31) / 32;
+  const int tiles = (n + 15) / 16;
   const int wave_id = blockIdx.x * 4 + wave, stride = gridDim.x * 4;
 
-  intx4 rtf[8][4];
+  intx4 rtf[4][8];  // K step, block of 16 features
 #pragma unroll
-  for (int s = 0; s < 8; ++s)
+  for (int s = 0; s < 4; ++s)
 #pragma unroll
-    for (int mb = 0; mb < 4; ++mb) {
-      rtf[s][mb] = *reinterpret_cast<const intx4*>(RT + (mb * 32 + l32) * D + (2 * s + half) * 8);
+    for (int mb = 0; mb < 8; ++mb) {
+      rtf[s][mb] = *reinterpret_cast<const intx4*>(RT + (mb * 16 + l16) * D + 32 * s + 8 * q);
       asm volatile("" : "+a"(rtf[s][mb]));
     }
 
-  // chunk i of a lane: tile row (lane >> 4) + 4 i, 16-byte column lane & 15
-  intx4 nxt[8];
+  // chunk i of a lane: tile row q + 4 i, 16-byte column l16
+  intx4 nxt[4];
   auto request = [&](int tile) __attribute__((always_inline)) {
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int row = tile * 32 + (lane >> 4) + 4 * i;
+    for (int i = 0; i < 4; ++i) {
+      const int row = tile * 16 + q + 4 * i;
       intx4 v = {0, 0, 0, 0};
-      if (tile < tiles && row < n) v = *reinterpret_cast<const intx4*>(X + (int64_t)row * ldx + (lane & 15) * 8);
+      if (tile < tiles && row < n) v = *reinterpret_cast<const intx4*>(X + (int64_t)row * ldx + l16 * 8);
       nxt[i] = v;
     }
   };
@@ -427,32 +440,30 @@ __global__ __launch_bounds__(256) void quant_d128_kernel(const __bf16* __restric
   for (int tile = wave_id; tile < tiles; tile += stride) {
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the previous tile's fragment reads are done
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
-      const int row = (lane >> 4) + 4 * i;
-      *reinterpret_cast<intx4*>(lds + row * 256 + (((lane & 15) ^ f128_xkey(row)) << 4)) = nxt[i];
+    for (int i = 0; i < 4; ++i) {
+      const int row = q + 4 * i;
+      *reinterpret_cast<intx4*>(lds + row * 256 + ((l16 ^ f128_xkey(row)) << 4)) = nxt[i];
     }
     request(tile + stride);
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // LDS of one wave executes in order; keep the compiler in order too
-    floatx16 acc[4];
+    floatx4 acc[8];  // features 16 mb + 4 q + r of token l16
     {
-      const char* xrow = lds + l32 * 256;
-      intx4 xb[2];
-      xb[0] = *reinterpret_cast<const intx4*>(xrow + (((0 + half) ^ f128_xkey(l32)) << 4));
+      const char* xrow = lds + l16 * 256;
+      intx4 xb[4];
 #pragma unroll
-      for (int s = 0; s < 8; ++s) {
-        if (s + 1 < 8)
-          xb[(s + 1) & 1] = *reinterpret_cast<const intx4*>(xrow + (((2 * (s + 1) + half) ^ f128_xkey(l32)) << 4));
+      for (int s = 0; s < 4; ++s) xb[s] = *reinterpret_cast<const intx4*>(xrow + (((4 * s + q) ^ f128_xkey(l16)) << 4));
 #pragma unroll
-        for (int mb = 0; mb < 4; ++mb) {
+      for (int s = 0; s < 4; ++s)
+#pragma unroll
+        for (int mb = 0; mb < 8; ++mb) {
           if (s == 0)
-            mfma_y_first(acc[mb], rtf[0][mb], xb[0]);
+            mfma16_y_first(acc[mb], rtf[0][mb], xb[0]);
           else
-            mfma_y(acc[mb], rtf[s][mb], xb[s & 1]);
+            mfma16_y(acc[mb], rtf[s][mb], xb[s]);
         }
-      }
-      mfma_result_fence(acc[0], acc[1], acc[2], acc[3]);
+      mfma16_result_fence(acc);
     }
-    const int token = tile * 32 + l32;
+    const int token = tile * 16 + l16;
     const bool tv = token < n;
     const int64_t to = (int64_t)b * n + token;
     float s;
@@ -461,51 +472,57 @@ __global__ __launch_bounds__(256) void quant_d128_kernel(const __bf16* __restric
     } else {
       float a = 0.f;
 #pragma unroll
-      for (int mb = 0; mb < 4; ++mb)
+      for (int mb = 0; mb < 8; ++mb)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) a = fmaxf(a, fabsf(acc[mb][r]));
-      a = fmaxf(a, __shfl_xor(a, 32));
+        for (int r = 0; r < 4; ++r) a = fmaxf(a, fabsf(acc[mb][r]));
+      float o = a;
+      swap_halves(a, o);
+      a = fmaxf(a, o);
+      o = a;
+      swap_quarters(a, o);
+      a = fmaxf(a, o);
       s = __fdiv_rn(__fmul_rn(clip, a), 7.0f);
     }
-    if (scales_out && tv && half == 0) scales_out[to] = s;
+    if (scales_out && tv && q == 0) scales_out[to] = s;
     if (codes || err) {
       const bool live = s > 0.f;
       const float rinv = live ? __fdiv_rn(1.0f, s) : 0.f;
+      const float top = live ? 7.f : 0.f;  // a row with scale 0 gets codes 0
       float e2 = 0.f, y2 = 0.f;
       int8_t* crow = codes + to * D;
 #pragma unroll
-      for (int mb = 0; mb < 4; ++mb) {
-        unsigned pk[4];
+      for (int m4 = 0; m4 < 2; ++m4) {
+        float pk[4];
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          unsigned pack = 0u;
+        for (int i = 0; i < 4; ++i) {
+          unsigned t[4];
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            const float y = acc[mb][4 * g + e];
-            float q = rintf(__fmul_rn(y, rinv));
-            q = fminf(fmaxf(q, -7.f), 7.f);
-            if (!live) q = 0.f;
-            const float diff = y - q * s;
+            // clamp(rint(v)) = rint(clamp(v)) for whole bounds; 1.5 2^23 + v has rint(v) (ties to even) in its low bits
+            const float y = acc[4 * m4 + i][e];
+            const float v = __builtin_amdgcn_fmed3f(__fmul_rn(y, rinv), -top, top);
+            const float m = __fadd_rn(v, 12582912.f);
+            t[e] = __float_as_uint(m);
+            const float diff = fmaf(-__fsub_rn(m, 12582912.f), s, y);
             e2 = fmaf(diff, diff, e2);
             y2 = fmaf(y, y, y2);
-            pack |= ((unsigned)(int)q & 0xffu) << (8 * e);
           }
-          pk[g] = pack;
+          const unsigned lo = __builtin_amdgcn_perm(t[1], t[0], 0x0c0c0400u), hi = __builtin_amdgcn_perm(t[3], t[2], 0x04000c0cu);
+          pk[i] = __uint_as_float(lo | hi);
         }
-        // A lane owns features 8g + 4 half .. + 3 of the 32-feature block, its partner (lane ^ 32) the other
-        // four of each eight: swap two words so that each of the two holds 16 consecutive bytes of the
-        // token's row (lower half-wave bytes 0..15 of the block, upper 16..31) and stores them at once.
-        const unsigned r0 = (unsigned)__shfl_xor((int)(half ? pk[0] : pk[2]), 32);
-        const unsigned r1 = (unsigned)__shfl_xor((int)(half ? pk[1] : pk[3]), 32);
-        uintx4 out;
-        if (half == 0) out = uintx4{pk[0], r0, pk[1], r1};
-        else out = uintx4{r0, pk[2], r1, pk[3]};
-        if (codes && tv) *reinterpret_cast<uintx4*>(crow + mb * 32 + 16 * half) = out;
+        // word i of quarter c = features 16 i + 4 c .. + 3 of these 64: transposed among the four lanes of the token,
+        // quarter c holds all 16 bytes of block c
+        swap_halves(pk[0], pk[2]);
+        swap_halves(pk[1], pk[3]);
+        swap_quarters(pk[0], pk[1]);
+        swap_quarters(pk[2], pk[3]);
+        const uintx4 out = {__float_as_uint(pk[0]), __float_as_uint(pk[1]), __float_as_uint(pk[2]), __float_as_uint(pk[3])};
+        if (codes && tv) *reinterpret_cast<uintx4*>(crow + 64 * m4 + 16 * q) = out;
       }
       if (err) {
-        e2 += __shfl_xor(e2, 32);
-        y2 += __shfl_xor(y2, 32);
-        if (half == 0 && tv) err[to] = make_float2(e2, y2);
+        e2 = quarter_sum_all(e2);
+        y2 = quarter_sum_all(y2);
+        if (q == 0 && tv) err[to] = make_float2(e2, y2);
       }
     }
   }
