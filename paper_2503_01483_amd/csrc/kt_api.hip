@@ -950,7 +950,7 @@ static kt_status launch_hadamard_onepass(const bf16* X, int64_t ldx, bf16* Y, in
     return fail(KT_ERR_DEVICE, "the Hadamard kernel needs %zu bytes of LDS per workgroup", lds);
   const int64_t wgs = (WAVES == 4 ? 2 : 1) * kNumCUs;  // what the registers let a CU hold
   hipLaunchKernelGGL((hadamard_onepass_kernel<LOGP, WAVES>), dim3((unsigned)(n < wgs ? n : wgs)), dim3(64 * WAVES), lds, st, X, ldx, Y, ldy,
-                     signs, n, 1.0f / sqrtf((float)d), f);
+                     signs, n, 65536.0f / sqrtf((float)d), f);
   if (!launch_ok()) return fail(KT_ERR_DEVICE, "Hadamard launch failed");
   return KT_OK;
 }

@@ -422,8 +422,10 @@ __global__ __launch_bounds__(256) void hadamard_cross_mfma_kernel(__bf16* __rest
 // Two kernels move a row through memory twice.  Here a workgroup keeps a whole row in LDS:
 //   H_m (x) S_p2 = H_M (x) S_P,  M = m 2^j <= 32 waves (4, or 8 above d = 16384), P = p2 / 2^j = 64 or 128,
 // (H_M = H_m (x) S_2^j).  The H_M factor comes FIRST, on the matrix cores: the inputs are bf16 and the entries +-1,
-// so every product is exact and nothing is rounded between the factors.  A wave takes 32 of the M outputs and all
-// P columns, so that the S_P factor is butterflies in its own registers (32 x 32 blocks, a lane owns one output and
+// so every product is exact and nothing is rounded between the factors.  The entries go in as +-2^-16 and the final scale
+// makes up for it: a sum of 32768 bf16 values fits 32 bits whatever they are, and 2^-16 times the smallest one (2^-133) is
+// the smallest fp32 number, so the products stay exact.  A wave takes 32 of the M outputs and all P columns, so that the
+// S_P factor is butterflies in its own registers (32 x 32 blocks, a lane owns one output and
 // 16 columns of each block: five or more index bits are register bits, the sixth is the wave half).
 // Per row: registers -> LDS (with the signs, an XOR of the sign bits that is the same for every row), request the next
 // row, matrix instructions (the row read with K = input index as the row of the LDS tile, transposing reads), butterflies,
@@ -465,7 +467,7 @@ __device__ __forceinline__ int hadamard_negative(const HadamardFactor& f, int a,
   return neg;
 }
 
-// LOGP = log2 P; 64 WAVES threads; d <= 32 WAVES P
+// LOGP = log2 P; 64 WAVES threads; d <= 32 WAVES P; scale = 2^16 / sqrt(d)
 template <int LOGP, int WAVES>
 __global__ __launch_bounds__(64 * WAVES, 2) void hadamard_onepass_kernel(const __bf16* __restrict__ X, int64_t ldx,
                                                                                   __bf16* __restrict__ Y, int64_t ldy,
@@ -511,7 +513,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void hadamard_onepass_kernel(const _
         for (int e = 0; e < 2; ++e) {
           const int i = i0 + 2 * w + e;
           const unsigned neg = ((bits >> ((i >> fac.log2j) - a0)) ^ (unsigned)__builtin_popcount(i & low)) & 1u;
-          v |= ((i < M && o < M) ? 0x3f80u | neg << 15 : 0u) << (16 * e);  // bf16 1.0 is 0x3f80
+          v |= ((i < M && o < M) ? 0x3780u | neg << 15 : 0u) << (16 * e);  // bf16 2^-16 is 0x3780
         }
         hf[s][w] = (int)v;
       }

@@ -56,3 +56,30 @@ def test_infinities_and_nan_stay_in_their_row():
     torch.cuda.synchronize()
     assert torch.isinf(Y[1]).all() and torch.isnan(Y[3]).all()
     assert torch.isfinite(Y[[0, 2, 4]]).all() and torch.equal(Y[0], Y[2]) and torch.equal(Y[0], Y[4])
+
+
+@pytest.mark.parametrize("n,d", [(2, 1536), (3, 8192), (5, 14336), (3, 28672), (66, 32768)])
+@pytest.mark.parametrize("size", [3e37, 1e36, 1e-36, 1e-39])
+def test_whole_range_of_bf16(n, d, size):
+    """A sum of d values that only fits 32 bits after the division by sqrt(d), and values down to the smallest: bf16 numbers
+    below 2^-126 lie 2^-133 apart, so half of that is added to the bound."""
+    g = torch.Generator().manual_seed(d)
+    X = (torch.randn(n, d, generator=g) * size).to(torch.bfloat16)
+    Y = kt.kt_hadamard_rows(X.cuda())
+    torch.cuda.synchronize()
+    pick = [0, n - 1]
+    ref, got = oracle.hadamard_rows(ktgen.to_f64(X)[pick]), Y.cpu().double().numpy()[pick]
+    rown = np.linalg.norm(ref, axis=1, keepdims=True)
+    assert (np.abs(got - ref) <= 1e-5 * rown + np.abs(ref) * 2.0 ** -8 + 2.0 ** -134).all()
+
+
+@pytest.mark.parametrize("d", [1536, 14336, 28672])
+def test_results_beyond_bf16_are_infinite_and_alone(d):
+    """Rows of the largest bf16 value: only column 0 of every segment of 2^k is not zero."""
+    top = torch.finfo(torch.bfloat16).max
+    Y = kt.kt_hadamard_rows(torch.full((2, d), top, dtype=torch.bfloat16, device="cuda"))
+    torch.cuda.synchronize()
+    ref, got = oracle.hadamard_rows(np.full((2, d), top)), Y.cpu().double().numpy()
+    beyond = np.abs(ref) > 1.01 * top
+    assert beyond.any() and np.array_equal(got[beyond], np.sign(ref[beyond]) * np.inf)
+    assert (np.abs(got - ref)[~beyond] <= np.abs(ref)[~beyond] * 2.0 ** -8).all()
