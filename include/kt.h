@@ -314,7 +314,8 @@ kt_status kt_quant_sensitivity(const float* Y, int64_t count, int32_t bits, cons
  *         even at the end; for m > 1 and d > 32768 - and on fewer than 64 rows of d = 32768 - the
  *         result of the S factor passes through Y in bf16 before the H_m factor is applied); Y may
  *         be X (in place).  Rows 16-byte aligned.
- *  signs  [d] int8 +-1 (the random diagonal of a "random Hadamard" rotation), or NULL.
+ *  signs  [d] int8 +-1 (the random diagonal of a "random Hadamard" rotation), or NULL.  Any other
+ *         value multiplies as well (0 drops a channel), slowly on bf16 rows that take one pass.
  *  d      as above with 128 <= 2^k <= 4096 and m <= 128.  For m = 1 without signs the transform
  *         is its own inverse.
  * No workspace.  HBM-bound: one read and one write of the rows (per factor for fp32 rows with m > 1

@@ -427,8 +427,8 @@ __global__ __launch_bounds__(256) void hadamard_cross_mfma_kernel(__bf16* __rest
 // the smallest fp32 number, so the products stay exact.  A wave takes 32 of the M outputs and all P columns, so that the
 // S_P factor is butterflies in its own registers (32 x 32 blocks, a lane owns one output and
 // 16 columns of each block: five or more index bits are register bits, the sixth is the wave half).
-// Per row: registers -> LDS (with the signs, an XOR of the sign bits that is the same for every row), request the next
-// row, matrix instructions (the row read with K = input index as the row of the LDS tile, transposing reads), butterflies,
+// Per row: registers -> LDS (with the signs, an XOR of the sign bits that is the same for every row; `signs` that are not all
+// +-1 go to hadamard_rows_any_factor), request the next row, matrix instructions (the row read with K = input index as the row of the LDS tile, transposing reads), butterflies,
 // bf16 results -> the same LDS, 16-byte stores.  Four barriers a row; the workgroups that share a CU overlap.
 // LDS rows are 2 P bytes; 64-byte pieces (reads) and 16-byte chunks (results) are XOR-swizzled with the row.
 // Bound: HBM, one read and one write of the rows.  512 MiB of rows, two kernels / this one: d = 14336 491 / 215 us
@@ -467,6 +467,51 @@ __device__ __forceinline__ int hadamard_negative(const HadamardFactor& f, int a,
   return neg;
 }
 
+// The rows for `signs` that are not all +-1 (0 to drop a channel, say): a sum of M products per lane, its column, and wave,
+// its output, in fp32; the S_P factor across the lanes.  Correct, not fast: x times such a factor is no bf16 number.
+template <int LOGP, int WAVES>
+__device__ __forceinline__ void hadamard_rows_any_factor(const __bf16* X, int64_t ldx, __bf16* Y, int64_t ldy, const int8_t* signs,
+                                                         int64_t n, float scale, const HadamardFactor& fac, char* lds) {
+  constexpr int P = 1 << LOGP, CPR = P / 8, NT = 64 * WAVES;
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, M = fac.m << fac.log2j;
+  const __bf16* tile = reinterpret_cast<const __bf16*>(lds);
+#pragma unroll 1
+  for (int64_t row = blockIdx.x; row < n; row += gridDim.x) {
+#pragma unroll 1
+    for (int c = tid; c < M * CPR; c += NT) reinterpret_cast<intx4*>(lds)[c] = *reinterpret_cast<const intx4*>(X + row * ldx + 8 * c);
+    __syncthreads();
+#pragma unroll 1
+    for (int o = wave; o < M; o += WAVES) {
+      const int low = o & ((1 << fac.log2j) - 1);
+      float u[P / 64] = {};
+#pragma unroll 1
+      for (int i = 0; i < M; ++i) {
+        const bool neg = (hadamard_negative(fac, i >> fac.log2j, o >> fac.log2j) ^ __builtin_popcount(i & low)) & 1;
+#pragma unroll
+        for (int e = 0; e < P / 64; ++e) {
+          const float v = (float)tile[i * P + 64 * e + lane] * 0x1p-16f * (float)signs[i * P + 64 * e + lane];
+          u[e] += neg ? -v : v;
+        }
+      }
+      if constexpr (P == 128) {
+        const float a = u[0], b = u[1];
+        u[0] = a + b;
+        u[1] = a - b;
+      }
+#pragma unroll
+      for (int st = 1; st < 64; st <<= 1)
+#pragma unroll
+        for (int e = 0; e < P / 64; ++e) {
+          const float other = __shfl_xor(u[e], st);
+          u[e] = lane & st ? other - u[e] : u[e] + other;
+        }
+#pragma unroll
+      for (int e = 0; e < P / 64; ++e) Y[row * ldy + o * P + 64 * e + lane] = (__bf16)(u[e] * scale);
+    }
+    __syncthreads();
+  }
+}
+
 // LOGP = log2 P; 64 WAVES threads; d <= 32 WAVES P; scale = 2^16 / sqrt(d)
 template <int LOGP, int WAVES>
 __global__ __launch_bounds__(64 * WAVES, 2) void hadamard_onepass_kernel(const __bf16* __restrict__ X, int64_t ldx,
@@ -475,6 +520,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void hadamard_onepass_kernel(const _
                                                                                   float scale, HadamardFactor fac) {
   constexpr int P = 1 << LOGP, NBLK = P / 32, ROWB = 2 * P, CPR = P / 8;  // CPR: 16-byte chunks per tile row
   constexpr int NT = 64 * WAVES, KSM = 2 * WAVES, NCH = 32 * WAVES * CPR / NT;  // matrix steps, chunks per thread: at most
+  constexpr bool PACKED = WAVES == 8;  // the matrix operands leave few registers
   extern __shared__ __align__(16) char had_lds[];
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, half = lane >> 5, l32 = lane & 31;
   const int M = fac.m << fac.log2j, KS = (M + 15) >> 4, chunks = M * CPR;
@@ -482,15 +528,37 @@ __global__ __launch_bounds__(64 * WAVES, 2) void hadamard_onepass_kernel(const _
   auto read_key = [](int k) __attribute__((always_inline)) { return LOGP == 6 ? (k >> 1) & 1 : k & 3; };
   auto out_key = [](int a) __attribute__((always_inline)) { return LOGP == 6 ? (a >> 1) & 7 : a & 15; };
 
-  // the signs of H_m as 128-bit rows in LDS: bit a of row b
+  unsigned sg[NCH][2];  // requested first, looked at behind the set-up of the table
+#pragma unroll
+  for (int i = 0; i < NCH; ++i) {
+    const int c = tid + NT * i;
+    sg[i][0] = sg[i][1] = 0x01010101u;
+    if (signs && c < chunks) __builtin_memcpy(sg[i], signs + 8 * c, 8);  // (any alignment)
+  }
+  // the signs of H_m as 128-bit rows in LDS: bit a of row b; and a word that is not zero if `signs` holds anything but +-1
   unsigned* tab = reinterpret_cast<unsigned*>(had_lds);
-  for (int i = tid; i < 4 * fac.m; i += NT) tab[i] = 0u;
+  for (int i = tid; i < 4 * fac.m + 1; i += NT) tab[i] = 0u;
   __syncthreads();
   for (int i = tid; i < fac.m * fac.m; i += NT) {
     const int b = i / fac.m, a = i - b * fac.m;
     if (hadamard_negative(fac, a, b)) atomicOr(&tab[4 * b + (a >> 5)], 1u << (a & 31));
   }
+  unsigned other = 0u;  // not zero: this thread has seen a value that is neither 1 nor -1
+  unsigned flip8[(NCH + 3) / 4];  // the sign bits of a chunk's eight values, one byte per chunk
+#pragma unroll
+  for (int i = 0; i < NCH; ++i) {
+    unsigned byte = 0u;
+#pragma unroll
+    for (int w = 0; w < 2; ++w) {
+      const unsigned neg = sg[i][w] >> 7 & 0x01010101u;
+      other |= sg[i][w] ^ (neg * 0xfeu | 0x01010101u);
+      byte |= (neg * 0x10204080u >> 28) << (4 * w);  // bits 0, 8, 16, 24 side by side
+    }
+    flip8[i / 4] = (i % 4 ? flip8[i / 4] : 0u) | byte << (8 * (i % 4));
+  }
+  if (other) atomicOr(&tab[4 * fac.m], 1u);
   __syncthreads();
+  const unsigned any_other = tab[4 * fac.m];
   // this wave's 32 columns of H_M as B operands: lane = output o = 32 wave + l32, 8 inputs i = 16 s + 8 half + e;
   // H_M[i][o] = H_m[i / 2^j][o / 2^j] (-1)^(common bits of i and o below 2^j)
   intx4 hf[KSM];
@@ -517,13 +585,16 @@ __global__ __launch_bounds__(64 * WAVES, 2) void hadamard_onepass_kernel(const _
         }
         hf[s][w] = (int)v;
       }
+      if constexpr (PACKED || LOGP == 6) asm volatile("" : "+v"(hf[s]));  // finished here: half-made words that wait for their end at the loop were spilled
     }
   }
-  // chunk tid + NT i of a row: the sign bits of its eight values, as the words to XOR with or (8 waves, whose matrix
-  // operands leave fewer registers) as one byte to make them from
-  constexpr bool PACKED = WAVES == 8;
+  __syncthreads();  // the table has been read
+  if (__builtin_expect(any_other != 0u, 0)) {
+    hadamard_rows_any_factor<LOGP, WAVES>(X, ldx, Y, ldy, signs, n, scale, fac, had_lds);
+    return;
+  }
+  // the words to XOR a chunk with (PACKED: made from the byte every time)
   intx4 flip[PACKED ? 1 : NCH];
-  unsigned flip8[(NCH + 3) / 4];
   auto sign_words = [](unsigned byte) __attribute__((always_inline)) {
     intx4 v;
 #pragma unroll
@@ -531,19 +602,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void hadamard_onepass_kernel(const _
     return v;
   };
 #pragma unroll
-  for (int i = 0; i < NCH; ++i) {
-    unsigned byte = 0u;
-    const int c = tid + NT * i;
-    if (signs && c < chunks) {
-      unsigned b[2];
-      __builtin_memcpy(b, signs + 8 * c, 8);  // (any alignment)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) byte |= (b[e >> 2] >> (8 * (e & 3) + 7) & 1u) << e;
-    }
-    if constexpr (PACKED) flip8[i / 4] = (i % 4 ? flip8[i / 4] : 0u) | byte << (8 * (i % 4));
-    else flip[i] = sign_words(byte);
-  }
-  __syncthreads();  // the table has been read
+  for (int i = 0; i < (PACKED ? 0 : NCH); ++i) flip[i] = sign_words(flip8[i / 4] >> (8 * (i % 4)) & 0xffu);
   // tile rows M .. 16 KS - 1 meet zeros of H_M: they have to be finite
   for (int c = chunks + tid; c < 16 * KS * CPR; c += NT) reinterpret_cast<intx4*>(had_lds)[c] = intx4{0, 0, 0, 0};
 
@@ -564,6 +623,10 @@ __global__ __launch_bounds__(64 * WAVES, 2) void hadamard_onepass_kernel(const _
   request(blockIdx.x);
 #pragma unroll 1
   for (int64_t row = blockIdx.x; row < n; row += gridDim.x) {
+    if constexpr (PACKED) {  // (or the compiler makes all of the words once and spills them)
+#pragma unroll
+      for (int i = 0; i < (NCH + 3) / 4; ++i) asm volatile("" : "+v"(flip8[i]));
+    }
 #pragma unroll
     for (int i = 0; i < NCH; ++i) {
       const int c = tid + NT * i, k = c / CPR, pos = c % CPR;

@@ -83,3 +83,33 @@ def test_results_beyond_bf16_are_infinite_and_alone(d):
     beyond = np.abs(ref) > 1.01 * top
     assert beyond.any() and np.array_equal(got[beyond], np.sign(ref[beyond]) * np.inf)
     assert (np.abs(got - ref)[~beyond] <= np.abs(ref)[~beyond] * 2.0 ** -8).all()
+
+
+@pytest.mark.parametrize("n,d", [(5, 1536), (530, 5120), (3, 8192), (4, 14336), (3, 28672), (66, 32768)])
+@pytest.mark.parametrize("low,high", [(-1, 1), (-128, 127)])
+def test_factors_that_are_not_signs(n, d, low, high):
+    """`signs` multiplies, whatever int8 values it holds: 0 drops a channel."""
+    g = torch.Generator().manual_seed(d + high)
+    X = torch.randn(n, d, generator=g).to(torch.bfloat16)
+    f = torch.randint(low, high + 1, (d,), generator=g).to(torch.int8)
+    f[0], f[d - 1] = low, 0
+    Y = kt.kt_hadamard_rows(X.cuda(), signs=f.cuda())
+    ones = torch.ones(d, dtype=torch.int8)
+    ones[d - 1] = 3     # one such value anywhere
+    Z = kt.kt_hadamard_rows(X.cuda(), signs=ones.cuda())
+    torch.cuda.synchronize()
+    pick = [0, n - 1]
+    for got, factor in ((Y, f), (Z, ones)):
+        ref, y = oracle.hadamard_rows(ktgen.to_f64(X)[pick], factor.numpy().astype(np.float64)), got.cpu().double().numpy()[pick]
+        rown = np.linalg.norm(ref, axis=1, keepdims=True)
+        assert (np.abs(y - ref) <= 1e-5 * rown + np.abs(ref) * 2.0 ** -8).all()
+
+
+def test_factors_that_are_not_signs_in_place():
+    n, d = 600, 6144
+    X = torch.randn(n, d, device="cuda").to(torch.bfloat16)
+    f = torch.randint(-2, 3, (d,), device="cuda").to(torch.int8)
+    Y = kt.kt_hadamard_rows(X, signs=f)
+    kt.kt_hadamard_rows(X, signs=f, out=X)
+    torch.cuda.synchronize()
+    assert torch.equal(X, Y)
