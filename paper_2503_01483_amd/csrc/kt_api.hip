@@ -629,6 +629,24 @@ static bool launch_rows_gemm(const T* X, int64_t ldx, int64_t x_batch_stride, co
 }
 
 // ------------------------------------------------------------------ fake-quant ----
+// Workgroups per problem for quant_d128_kernel.  A wave loads all of R^T (32 KiB) before its first tile.
+//  - While one workgroup per CU holds them: one 16-token tile per wave.  us, one tile / two per wave: 1 problem of 4096 tokens
+//    12.1 / 12.9, of 16384 12.1 / 13.2; two workgroups on a CU with one tile each: 32768 tokens 15.7 against 13.5.
+//  - Beyond: two tiles or more per wave, and as many workgroups as finish first when they start in rounds of 512 (two per
+//    CU, what the registers let it hold), a round taking its longest wave's tiles and R^T, about four more.  512 / batch
+//    rounded up would leave a second round nearly empty: 100 x 16384 tokens 223 us, here 156; 200 x 16384 415 and 300; 40 x
+//    65536 343 and 238.
+static int64_t quant_d128_wgs(int64_t batch, int64_t n) {
+  const int64_t tiles = ceil_div(n, 16);
+  if (ceil_div(tiles, 4) * batch <= kNumCUs) return ceil_div(tiles, 4);
+  int64_t best = 1, least = -1;
+  for (int64_t k = 1; k <= ceil_div(tiles, 8) && k <= 4 * ceil_div(2 * kNumCUs, batch); ++k) {
+    const int64_t cost = ceil_div(k * batch, 2 * kNumCUs) * (ceil_div(tiles, 4 * k) + 4);
+    if (least < 0 || cost < least) { best = k; least = cost; }
+  }
+  return best;
+}
+
 template <typename T, class TFWD, class TQ>
 static kt_status run_quant(const QuantPlan& p, const void* X, int64_t ldx, const void* R, int64_t ldr,
                            kt_dtype rdt, int64_t batch, int64_t n, int64_t d, float clip,
@@ -1239,10 +1257,7 @@ kt_status kt_rotate_fakequant_int4(const void* X, int64_t ldx, const void* R, in
   if (!p.fp32 && d == 128) {  // one pass over X (kt_fused_d128.h)
     bf16* RT = reinterpret_cast<bf16*>(ws + p.o_rt);
     if (!prep_rt<bf16>(R, ldr, r_dtype, RT, batch, d, st)) return fail(KT_ERR_DEVICE, "prep_rt launch failed");
-    const int64_t tiles = ceil_div(n, 16);
-    int64_t wgs = ceil_div(2 * kNumCUs, batch);  // two workgroups per CU over all problems: what the registers let it hold
-    if (wgs > ceil_div(tiles, 8)) wgs = ceil_div(tiles, 8);  // a wave loads all of R^T (32 KiB) first: 32 tokens at least
-    hipLaunchKernelGGL(quant_d128_kernel, dim3((unsigned)wgs, (unsigned)batch), dim3(256), 0, st,
+    hipLaunchKernelGGL(quant_d128_kernel, dim3((unsigned)quant_d128_wgs(batch, n), (unsigned)batch), dim3(256), 0, st,
                        static_cast<const bf16*>(X), ldx, n * ldx, RT, (int)n, clip_ratio, scales_in, scales_out, codes,
                        reinterpret_cast<float2*>(err));
     if (!launch_ok()) return fail(KT_ERR_DEVICE, "d=128 fake-quant launch failed");

@@ -391,14 +391,14 @@ __global__ __launch_bounds__(256) void fused_d128_kernel(const __bf16* __restric
 }
 
 // ---- single-pass rotate + int4 fake-quant for d = 128 (bf16) -------------------------------
-// A lane pair holds a whole rotated token row, so the row maximum, the scale, the codes and the
+// The four lanes l, l + 16, l + 32, l + 48 hold a whole rotated token row, so the row maximum, the scale, the codes and the
 // error sums all come out of ONE pass over X (the generic path parks the rotated rows in an fp32
 // staging buffer between the GEMM and a row kernel).
 // Every wave is on its own: 16-token tiles, its rows staged through 4 KiB of private LDS (loads of
 // the next tile in flight), R^T fragments in accumulation registers, no workgroup barrier.
 // 16 x 16 blocks (one token, 32 features per lane) keep a wave under 256 registers, so that two share a SIMD: one wave's
 // loads, matrix instructions and quantiser arithmetic hide behind the other's.  256 problems x 4096 tokens: one wave per
-// SIMD (32-token tiles, 324 registers, twice the workgroups) 139 us, this form 118 us; two tiles in flight instead of one: 7 % slower.
+// SIMD (32-token tiles, 324 registers, twice the workgroups) 139 us, this form 106 us; two tiles in flight instead of one: 7 % slower.
 // Arithmetic identical to the generic path: s = (clip amax) / 7, q = clamp(rint(y (1/s)), -7, 7).
 // grid = (waves / 4, batch).
 __global__ __launch_bounds__(256, 2) void quant_d128_kernel(const __bf16* __restrict__ X, int64_t ldx,
@@ -420,10 +420,7 @@ __global__ __launch_bounds__(256, 2) void quant_d128_kernel(const __bf16* __rest
 #pragma unroll
   for (int s = 0; s < 4; ++s)
 #pragma unroll
-    for (int mb = 0; mb < 8; ++mb) {
-      rtf[s][mb] = *reinterpret_cast<const intx4*>(RT + (mb * 16 + l16) * D + 32 * s + 8 * q);
-      asm volatile("" : "+a"(rtf[s][mb]));
-    }
+    for (int mb = 0; mb < 8; ++mb) rtf[s][mb] = *reinterpret_cast<const intx4*>(RT + (mb * 16 + l16) * D + 32 * s + 8 * q);
 
   // chunk i of a lane: tile row q + 4 i, 16-byte column l16
   intx4 nxt[4];
@@ -437,6 +434,11 @@ __global__ __launch_bounds__(256, 2) void quant_d128_kernel(const __bf16* __rest
     }
   };
   request(wave_id);
+  // into accumulation registers, behind all of the requests (a pin behind each one waits for it: 32 times the latency of the L2)
+#pragma unroll
+  for (int s = 0; s < 4; ++s)
+#pragma unroll
+    for (int mb = 0; mb < 8; ++mb) asm volatile("" : "+a"(rtf[s][mb]));
   for (int tile = wave_id; tile < tiles; tile += stride) {
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the previous tile's fragment reads are done
 #pragma unroll

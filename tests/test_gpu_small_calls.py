@@ -69,3 +69,35 @@ def test_fused_weights_small_and_large_tiles(side, k, d):
     ref = w @ r if side == 0 else r.T @ w
     size = np.abs(w) @ np.abs(r) if side == 0 else np.abs(r).T @ np.abs(w)
     assert np.all(np.abs(out.cpu().double().numpy() - ref) <= d * 2.0 ** -23 * size)
+
+
+@pytest.mark.parametrize("batch,n", [
+    (1, 1), (1, 15), (3, 64), (256, 64), (255, 17), (1, 16384),      # one tile per wave
+    (256, 65), (128, 256), (129, 100), (1, 16385), (129, 129),       # two
+    (257, 64), (600, 33), (40, 1000), (513, 300),                    # two workgroups per CU, several tiles per wave, rounds
+])
+def test_heads_of_128_in_every_launch_shape(batch, n):
+    """The d = 128 fake-quant, all tokens of all problems, with its own scales and with given ones (its own again: the same
+    arithmetic, so the same codes)."""
+    d = 128
+    X, R, Rh = _problem(1, batch * n, d, "bf16", "f32", 0, batch + n)
+    X = X.view(batch, n, d)
+    Rd = torch.stack([torch.roll(R[0], b, 1) for b in range(batch)])   # a rotation of its own for every problem
+    scales, codes, err = (torch.full((batch, n), -1.0, device="cuda"), torch.full((batch + 1, n, d), 99, dtype=torch.int8, device="cuda"),
+                          torch.full((batch, n, 2), -1.0, device="cuda"))
+    kt.kt_rotate_fakequant_int4(X, Rd, scales_out=scales, codes=codes[:batch], err=err)
+    again = torch.full_like(codes, 99)
+    kt.kt_rotate_fakequant_int4(X, Rd, scales_in=scales, codes=again[:batch])
+    torch.cuda.synchronize()
+    assert torch.equal(codes, again) and bool((codes[batch] == 99).all())
+    r = ktgen.to_f64(ktgen.bf16_round(Rh[0]))
+    x = ktgen.to_f64(X.reshape(batch * n, d))
+    shift = (np.arange(d)[None, :] - np.repeat(np.arange(batch), n)[:, None]) % d
+    ref = np.take_along_axis(x @ r, shift, 1)
+    bound = np.take_along_axis(2.0 * d * 2.0 ** -24 * (np.abs(x) @ np.abs(r)), shift, 1)
+    s = scales.cpu().double().numpy().reshape(-1)
+    assert np.all(np.abs(s - np.abs(ref).max(1) / 7) <= (bound.max(1) + 1e-6 * np.abs(ref).max(1)) / 7)
+    q = codes[:batch].cpu().numpy().reshape(-1, d)
+    assert np.all(np.abs(q - np.clip(ref / s[:, None], -7, 7)) - 0.5 <= bound / s[:, None] + 1e-5)
+    e = err.cpu().numpy().reshape(-1, 2)
+    assert np.allclose(e[:, 0], ((ref - q * s[:, None]) ** 2).sum(1), rtol=1e-4) and np.allclose(e[:, 1], (ref ** 2).sum(1), rtol=1e-4)
