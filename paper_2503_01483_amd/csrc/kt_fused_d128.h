@@ -80,7 +80,7 @@ __device__ __forceinline__ void mfma_result_fence_acc(floatx16& a, floatx16& b, 
 // reads to these loads with a full wait; the waits are placed by hand (vmcnt).
 __device__ __forceinline__ void load_to_lds_16(const void* src, unsigned lds_addr) {
   asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(lds_addr)
-               : "memory");
+               : "memory", "m0");
 }
 
 // grid = (S, batch): S workgroups share the token tiles of one problem.

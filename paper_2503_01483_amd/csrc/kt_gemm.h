@@ -226,13 +226,18 @@ template <int OFF>
 __device__ __forceinline__ void buffer_to_lds_16(uint32_t voffset, const sgprx4& rsrc, unsigned lds_base) {
   asm volatile("s_add_u32 m0, %1, %3\n\ts_nop 0\n\tbuffer_load_dwordx4 %0, %2, 0 offen lds"
                :: "v"(voffset), "s"(lds_base), "s"(rsrc), "n"(OFF)
-               : "memory", "scc");
+               : "memory", "scc", "m0");
 }
-// Raw buffer over everything from `base` on (offsets are unsigned 32-bit, checked by the host).
+// Raw buffer over everything from `base` on (offsets are unsigned 32-bit, checked by the host).  The loads are hidden from the
+// compiler, and a vector instruction that writes a scalar register (v_readfirstlane) has to be five issue slots old before
+// a buffer instruction reads it: the descriptor is in scalar registers from here on, and the caller sees to the slots.
 __device__ __forceinline__ sgprx4 raw_buffer(const char* base) {
   const uint64_t p = reinterpret_cast<uint64_t>(base);
-  return sgprx4{(int)(uint32_t)p, (int)(uint32_t)((p >> 32) & 0xffff), -1, 0x00027000};
+  sgprx4 r = {(int)(uint32_t)p, (int)(uint32_t)((p >> 32) & 0xffff), -1, 0x00027000};
+  asm volatile("" : "+s"(r));
+  return r;
 }
+__device__ __forceinline__ void raw_buffer_wait() { asm volatile("s_nop 4" ::: "memory"); }
 
 // Waits until at most N vector-memory operations of this wave are in flight (LDS operations: none), then
 // meets the other waves.
@@ -473,7 +478,8 @@ __device__ __forceinline__ void gemm_mainloop(const typename TL::T* __restrict__
       if constexpr (g == SLOTS + BAR) {
         stage_barrier<B_LD>();  // in flight at most: B of slab s + 2
       }
-      if constexpr (g == SLOTS + BAR - 3) locate_a();  // every load of the former requests has been issued
+      // every load of the former requests has been issued; the next one comes after four MFMAs and a barrier (raw_buffer)
+      if constexpr (g == SLOTS + BAR - 3) locate_a();
       if constexpr (g == SLOTS + BAR - 2) locate_b();
       if constexpr (g == SLOTS + BAR - 1) {
         b_write = b_write == 2 * TL::B_BYTES ? 0 : b_write + TL::B_BYTES;
@@ -510,12 +516,15 @@ __device__ __forceinline__ void gemm_mainloop(const typename TL::T* __restrict__
   };
   locate_a();
   locate_b();
+  raw_buffer_wait();
   static_for<NLD>([&](auto i_c) __attribute__((always_inline)) { gload(i_c, S0{}); });
   locate_b();
+  raw_buffer_wait();
   b_write = TL::B_BYTES;
   static_for<B_LD>([&](auto i_c) __attribute__((always_inline)) { gload(std::integral_constant<int, A_LD + decltype(i_c)::value>{}, S0{}); });
   locate_a();
   locate_b();
+  raw_buffer_wait();
   b_write = 2 * TL::B_BYTES;
   static_for<NLD>([&](auto i_c) __attribute__((always_inline)) {
     if constexpr (load_slot(decltype(i_c)::value) < 2 * SLOTS) gload(i_c, S1{});
