@@ -614,6 +614,9 @@ static bool launch_skinny(const bf16* X, int64_t ldx, const TR* R, int64_t ldr, 
 // tile: bf16 d = 4096, n = 128: 97 / 58, 1024: 105 / 64, 2048 (128 large tiles): 109 / 91, 2560: 112 / 116; d = 2048,
 // n = 4096 (128): 67 / 53, 6144: 72 / 73; fp32 d = 1024, n = 256: 75 / 30, 4096 (256 large tiles): 84 / 80; d = 2048,
 // n = 2048 (256): 154 / 142.
+// The 256 x 128 tile of d % 256 != 0 wins in one round over the CUs or two nearly full ones, two 128 x 128 on a CU in any
+// other number: 144 tiles 35.5 / 37.1, 240: 50.7 / 53.1, 288: 68.6 / 59.0, 320: 50.7 / 43.9, 384: 50.6 / 46.0,
+// 432: 72.3 / 73.6, 480: 88.2 / 91.0, 576: 92.2 / 88.1, 1152: 176 / 164.
 template <typename T, class TL>
 static bool launch_rows_gemm(const T* X, int64_t ldx, int64_t x_batch_stride, const T* RT, int64_t problems, int64_t rows,
                              int64_t d, float* Y, hipStream_t st) {
@@ -625,7 +628,11 @@ static bool launch_rows_gemm(const T* X, int64_t ldx, int64_t x_batch_stride, co
     return launch_gemm<G>(X, ldx, x_batch_stride, (int)rows, RT, d, d * d, (int)d, d, 0, (int)problems, e, st);
   };
   const int64_t tiles = ceil_div(rows, TL::BM) * ceil_div(d, TL::BN) * problems;
-  return (sizeof(T) == 4 ? use_small_f32(tiles) : tiles <= kNumCUs / 2) ? go(Small{}) : go(TL{});
+  bool small;
+  if (sizeof(T) == 4) small = use_small_f32(tiles);
+  else if (TL::BN == 128) small = tiles <= kNumCUs / 2 || (tiles > kNumCUs && (tiles > 2 * kNumCUs || 6 * tiles < 5 * 2 * kNumCUs));
+  else small = tiles <= kNumCUs / 2;
+  return small ? go(Small{}) : go(TL{});
 }
 
 // ------------------------------------------------------------------ fake-quant ----

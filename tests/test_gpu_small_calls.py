@@ -27,6 +27,8 @@ def _problem(batch, n, d, xdt, rdt, ld_pad, seed):
     (1, 32, 128, "bf16", "bf16", 8), (3, 33, 640, "bf16", "bf16", 0), (1, 64, 2048, "bf16", "f32", 0),
     (1, 5, 512, "bf16", "f32", 1),      # rows of R not 16-byte aligned: general path
     (1, 65, 2048, "bf16", "f32", 0), (1, 700, 896, "bf16", "f32", 0), (1, 130, 384, "f32", "f32", 0),
+    # 256 x 128 tiles, ragged rows: 132 and 432 (one round, two nearly full ones); 128 x 128 for 258 and 513
+    (44, 200, 384, "bf16", "f32", 0), (36, 1000, 384, "bf16", "f32", 0), (86, 130, 384, "bf16", "f32", 0), (57, 600, 384, "bf16", "f32", 0),
 ])
 def test_rotated_rows(batch, n, d, xdt, rdt, ld_pad):
     X, R, Rh = _problem(batch, n, d, xdt, rdt, ld_pad, 3 * n + d)
