@@ -244,6 +244,9 @@ kt_status kt_cayley_adam_step(float* R, const float* dR, float* M, float* v, int
  *  and a row kernel takes the maximum and quantises the staged values (one GEMM pass instead of a
  *  second one that recomputes y).  With scales_in the codes come straight out of the GEMM's registers.
  *  d = 128 in bf16 is a single fused pass with no staging.
+ *  Up to 64 bf16 tokens (d > 128, rows of R 16-byte aligned) y is summed in another order when the scales are computed
+ *  here: the fp32 rounding of a token's y then depends on n, on batch and on R's alignment, and codes from scales_in, or of
+ *  the same token in a larger call, can differ by one where y / s lies within that rounding of a boundary.
  */
 kt_status kt_rotate_fakequant_int4(const void* X, int64_t ldx, const void* R, int64_t ldr,
                                    int64_t batch, int64_t n, int64_t d,
@@ -269,7 +272,7 @@ kt_status kt_rotate_fakequant_int4(const void* X, int64_t ldx, const void* R, in
  *             the workspace).  Every output pointer may be NULL.
  * Y is materialised (this is an evaluation tool, not the training step): one GEMM pass, then one
  * wave per token with the row in registers (radix select on the bit patterns for the quantile).
- * d <= 8192.
+ * d <= 8192.  The order in which y is summed depends on the call's size as in kt_rotate_fakequant_int4.
  * Workspace: kt_workspace_bytes(KT_OP_QUANT_METRICS, ...) (sized for Y == NULL: the rotated rows then
  * pass through an fp32 staging slice of at most 1 GiB, a few problems or token rows at a time).
  */

@@ -127,8 +127,9 @@ constexpr int kNumCUs = 256;
 
 // fp32 products: 64 x 64 tiles when `tiles` 128 x 128 ones would leave CUs idle, in all of the launch or in its last
 // round.  A 128 x 128 tile takes a CU about 4100 cycles per 32 of K, a 64 x 64 one a little over a quarter of that, four
-// of them share a CU, and the bits are the same (the order of K is).  kt_fuse_rotation, us, large / small tiles: 48 tiles
-// 26 / 14, 256 tiles 143 / 139 (d = 2048), 704 tiles 378 / 354, 1024 tiles 976 / 989, 3584 tiles 3377 / 3448.
+// of them share a CU, and the bits are the same (so is the order of K; X^T G, where K is split, gets other splits).
+// kt_fuse_rotation, us, large / small tiles: 48 tiles 26 / 14, 256 tiles 143 / 139 (d = 2048), 704 tiles 378 / 354, 1024
+// tiles 976 / 989, 3584 tiles 3377 / 3448.
 static inline bool use_small_f32(int64_t tiles) {
   return tiles <= kNumCUs || 33 * tiles < 32 * round_up(tiles, kNumCUs);
 }
@@ -811,9 +812,10 @@ static kt_status cayley_run(const CayleyPlan& p, char* ws, float* R, const float
       if (!product(Bs, Us[0], 0, adam->M, 0.5f)) return fail(KT_ERR_DEVICE, "momentum projection GEMM launch failed");
     }
     const unsigned ub = (unsigned)(ceil_div(dd / 4, 256) < 512 ? ceil_div(dd / 4, 256) : 512);
-    // The first iterations run as product + elementwise update (the faster pair when they do real
-    // work); the later ones, which almost always only find the convergence flag set, as ONE launch
-    // each with the update in the GEMM epilogue: half as many launches to skip through.
+    // The first iterations run as product + elementwise update; the later ones, which almost always only find the
+    // convergence flag set, as ONE launch each with the update in the GEMM epilogue: half as many launches to skip through.
+    // With the epilogue's present 16-byte accesses the single launch is no slower where it does real work either: steps of two
+    // iterations, us, pairs up to the sixth / single launches throughout: d = 1024 194 / 187, 2048 315 / 312, 4096 1276 / 1268.
     auto fused_iteration = [&](int it) -> bool {
       auto go = [&](auto tile_tag) -> bool {
         using TL = decltype(tile_tag);
@@ -954,7 +956,8 @@ static bool hadamard_split(int64_t d, int* m, int* p2, int* kind) {
 
 // One pass over bf16 rows (hadamard_onepass_kernel) for H_m (x) S_p2 with m > 1 where a row fits the LDS of a workgroup.
 // Returns false when the sizes do not fit its layout.  One exception: 32768 = S_8 (x) S_4096 on few rows, where the set-up
-// of eight waves costs more than the second kernel (16 rows: 17.0 us in one pass, 13.7 in two; 256 rows: 22 against 28).
+// of eight waves costs more than the second kernel (16 rows: 13.6 us in one pass, 12.4 in two; 64: 14.3 and 13.4, 88: 14.5
+// and 14.8, 256: 16.7 and 26.6; from 64 rows on the result is rounded once only).
 static bool hadamard_onepass_plan(int64_t n, int64_t d, int m, int p2, int kind, int* log2j, int* logp) {
   if (d > 32768 || (kind == 0 && d > 16384 && n < 64)) return false;
   const int limit = d > 16384 ? 256 : 128;  // 32 outputs per wave, 8 or 4 waves

@@ -2,10 +2,11 @@
 fp32: the transform adds d values with fp32 rounding in a tree of depth log2 d: 1e-5 of the row
 norm per output.  bf16: the same fp32 result rounded to nearest even: at most one bf16 ulp
 (2^-8 relative) from the oracle value rounded the same way, plus the fp32 term.  Sizes m 2^k with
-m > 1 run as two factors with the intermediate z (the Sylvester transform of each of the m segments
-of a row) stored in the output buffer: in bf16 that intermediate is rounded too, by at most 2^-8 |z|
-each (the unit roundoff of an 8-bit significand), and an output is +-1/sqrt(m) times the sum of the m
-intermediates of its column: the bound adds 2^-8 sum_j |z_j| / sqrt(m), with z from the oracle."""
+m > 1 are two factors.  fp32 rows, and bf16 rows longer than 32768 (32768 itself on fewer than 64 rows), run them as two
+kernels with the intermediate z (the Sylvester transform of each of the m segments of a row) stored in the output buffer:
+in bf16 that intermediate is rounded too, by at most 2^-8 |z| each (the unit roundoff of an 8-bit significand), and an output
+is +-1/sqrt(m) times the sum of the m intermediates of its column: the bound adds 2^-8 sum_j |z_j| / sqrt(m), with z from the
+oracle.  Shorter bf16 rows take one kernel and are rounded once; test_gpu_hadamard_onepass.py holds them to that."""
 import numpy as np
 import pytest
 import torch
@@ -102,3 +103,30 @@ def test_bad_shapes_are_refused():
         kt.kt_hadamard_rows(torch.zeros(4, 11008, device="cuda"))      # 43 * 2^8: no Paley order
     with pytest.raises(Exception):
         kt.kt_hadamard_rows(torch.zeros(4, 768, device="cuda"))        # 12 * 64: the power-of-two part is too short
+
+
+# two kernels in bf16: the vector form of the second factor (m = 8) and the matrix-core one (m = 16, 28, 36)
+@pytest.mark.parametrize("n,d", [(3, 32768), (63, 32768), (5, 36864), (3, 57344), (4, 65536)])
+@pytest.mark.parametrize("use_signs", [True, False])
+@pytest.mark.parametrize("strided", [False, True])
+def test_bf16_rows_of_two_kernels(n, d, use_signs, strided):
+    m, p2, kind = oracle.hadamard_factor(d)
+    pick = [0, n // 2, n - 1]
+    X = ktgen.make_x(n, d, seed=n + d, outlier_cols=3, outlier_scale=40.0, t_frac=0.02, dtype="bf16")
+    g = torch.Generator().manual_seed(d)
+    signs = (torch.randint(0, 2, (d,), generator=g) * 2 - 1).to(torch.int8) if use_signs else None
+    sd = None if signs is None else signs.cuda()
+    if strided:  # in place, one launch per segment
+        buf = torch.full((n, d + 40), 3.0, dtype=torch.bfloat16, device="cuda")
+        Y = buf[:, :d]
+        Y.copy_(X)
+        kt.kt_hadamard_rows(Y, signs=sd, out=Y)
+        assert bool((buf[:, d:] == 3.0).all())
+    else:
+        Y = kt.kt_hadamard_rows(X.cuda(), signs=sd)
+    torch.cuda.synchronize()
+    Xs = ktgen.to_f64(X)[pick] * (1.0 if signs is None else signs.numpy().astype(np.float64)[None, :])
+    ref, got = oracle.hadamard_rows(Xs), Y.float().cpu().numpy().astype(np.float64)[pick]
+    rown = np.linalg.norm(ref, axis=1, keepdims=True)
+    tol = 1e-5 * rown + np.abs(ref) * 2.0 ** -8 + _intermediate_rounding_bound(Xs, m, p2)
+    assert (np.abs(got - ref) <= tol).all(), float((np.abs(got - ref) / tol).max())

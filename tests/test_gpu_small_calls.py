@@ -61,7 +61,8 @@ def test_rotated_rows(batch, n, d, xdt, rdt, ld_pad):
 @pytest.mark.parametrize("side", [0, 1])
 @pytest.mark.parametrize("k,d", [(4, 128), (132, 256), (1000, 384), (2052, 2048), (5632, 2048)])
 def test_fused_weights_small_and_large_tiles(side, k, d):
-    """The number of 128 x 128 tiles decides the tile; 704 of them (the last size) take small tiles again."""
+    """The number of 128 x 128 tiles decides the tile: 1 to 24 and, a little over one round of CUs, 272 and 704, all small
+    (sizes for the large one: test_gpu_large_fp32_tiles.py)."""
     g = torch.Generator().manual_seed(k + d)
     W = torch.randn((k, d) if side == 0 else (d, k), generator=g)
     R = ktgen.random_orthogonal(d, seed=k)
@@ -103,3 +104,23 @@ def test_heads_of_128_in_every_launch_shape(batch, n):
     assert np.all(np.abs(q - np.clip(ref / s[:, None], -7, 7)) - 0.5 <= bound / s[:, None] + 1e-5)
     e = err.cpu().numpy().reshape(-1, 2)
     assert np.allclose(e[:, 0], ((ref - q * s[:, None]) ** 2).sum(1), rtol=1e-4) and np.allclose(e[:, 1], (ref ** 2).sum(1), rtol=1e-4)
+
+
+@pytest.mark.parametrize("batch,n,d,rdt", [(1, 1, 4096, "f32"), (1, 16, 4096, "f32"), (2, 33, 1152, "bf16"), (1, 64, 2048, "f32"), (1, 65, 2048, "f32")])
+def test_own_scales_handed_back(batch, n, d, rdt):
+    """With given scales y comes from the GEMM, without them and up to 64 tokens from the few-token kernel, whose sums have
+    another order: a code may differ where y / s lies that close to a rounding boundary, and by one only."""
+    X, R, Rh = _problem(batch, n, d, "bf16", rdt, 0, n + d)
+    scales, codes, again = (torch.empty((batch, n), device="cuda"), torch.empty((batch, n, d), dtype=torch.int8, device="cuda"),
+                            torch.empty((batch, n, d), dtype=torch.int8, device="cuda"))
+    kt.kt_rotate_fakequant_int4(X, R, scales_out=scales, codes=codes)
+    kt.kt_rotate_fakequant_int4(X, R, scales_in=scales, codes=again)
+    torch.cuda.synchronize()
+    if n > 64:
+        assert torch.equal(codes, again)
+    for b in range(batch):
+        x, r, s = ktgen.to_f64(X[b]), ktgen.to_f64(ktgen.bf16_round(Rh[b])), scales[b].cpu().double().numpy()[:, None]
+        v, slack = x @ r / s, 2.0 * d * 2.0 ** -24 * (np.abs(x) @ np.abs(r)) / s + 1e-5
+        diff = codes[b].cpu().numpy().astype(int) - again[b].cpu().numpy()
+        assert np.abs(diff).max() <= 1
+        assert np.all(np.abs(np.abs(v - np.floor(v)) - 0.5)[diff != 0] <= slack[diff != 0])
