@@ -431,9 +431,9 @@ __global__ __launch_bounds__(256) void hadamard_cross_mfma_kernel(__bf16* __rest
 // +-1 go to hadamard_rows_any_factor), request the next row, matrix instructions (the row read with K = input index as the row of the LDS tile, transposing reads), butterflies,
 // bf16 results -> the same LDS, 16-byte stores.  Four barriers a row; the workgroups that share a CU overlap.
 // LDS rows are 2 P bytes; 64-byte pieces (reads) and 16-byte chunks (results) are XOR-swizzled with the row.
-// Bound: HBM, one read and one write of the rows.  512 MiB of rows, two kernels / this one: d = 14336 491 / 215 us
-// (5.0 TB/s; 16 rows, set-up and all: 17 / 11), 13824 683 / 228, 8192 547 / 219, 5120 528 / 253, 28672 483 / 344,
-// 1536 (one wave of four at work) 778 / 510.
+// Bound: HBM, one read and one write of the rows.  512 MiB of rows, two kernels / this one: d = 14336 491 / 221 us
+// (4.9 TB/s; 16 rows, set-up and all: 15.9 / 8.6), 13824 683 / 223, 8192 547 / 215, 5120 528 / 243, 28672 483 / 288 (eight
+// waves of 256 registers, one workgroup per CU: its barriers overlap with nothing), 1536 (one wave of four at work) 778 / 513.
 struct HadamardFactor {
   unsigned long long squares[2];  // bit x: x is a quadratic residue modulo q
   int m, kind, h, q, log2j;       // H_m as in hadamard_cross_kernel; M = m << log2j
