@@ -127,7 +127,7 @@ constexpr int kNumCUs = 256;
 
 // fp32 products: 64 x 64 tiles when `tiles` 128 x 128 ones would leave CUs idle, in all of the launch or in its last
 // round.  A 128 x 128 tile takes a CU about 4100 cycles per 32 of K, a 64 x 64 one a little over a quarter of that, four
-// of them share a CU, and the bits are the same (so is the order of K; X^T G, where K is split, gets other splits).
+// of them share a CU, and the bits are the same (so are the order of K and its splits).
 // kt_fuse_rotation, us, large / small tiles: 48 tiles 26 / 14, 256 tiles 143 / 139 (d = 2048), 704 tiles 378 / 354, 1024
 // tiles 976 / 989, 3584 tiles 3377 / 3448.
 static inline bool use_small_f32(int64_t tiles) {
@@ -256,8 +256,9 @@ static LossGradPlan plan_loss_grad(int64_t batch, int64_t n, int64_t d, kt_dtype
   int64_t slabs;
   if (p.fp32) {
     p.P = (int)ceil_div(d, TF::BM) * TF::WGM;
-    const int64_t bm = small_f32_tiles(d, batch) ? TF_64::BM : TF::BM;
-    p.tiles_dd = (int)(ceil_div(d, bm) * ceil_div(d, bm));
+    // (also where X^T G takes 64 x 64 tiles: a quarter of the splits would be sums four times as long, in fp32; d = 1024,
+    // 16384 tokens: dR off by 8.8e-7 of its norm instead of 6.9e-7)
+    p.tiles_dd = (int)(ceil_div(d, TF::BM) * ceil_div(d, TF::BN));
     slabs = p.ldt / TF::BK;
   } else if (d % 256 == 0) {
     p.P = (int)(d / TB_BIG::BM) * TB_BIG::WGM;
