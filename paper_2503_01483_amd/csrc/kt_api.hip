@@ -227,8 +227,23 @@ struct LossGradPlan {
 // room to keep it (4 n d bytes per problem); beyond, for the recompute form.
 constexpr int64_t kKeepYMaxBytes = (int64_t)64 << 30;
 
+// Workgroups per problem of fused_d128_kernel (a CU holds one at a time): the number that finishes first when they start
+// in rounds of 256, a round taking its longest workgroup's tiles and about three more (R^T, the first tile, dR), and every
+// partial dR beyond one per problem about a hundredth of a tile (written and read again).
+static int fused_d128_wgs(int64_t batch, int64_t n) {
+  const int64_t tiles = ceil_div(n, kF128Tile);
+  int64_t best = 1;
+  double least = -1.0;
+  for (int64_t k = 1; k <= tiles && k <= 4 * ceil_div(kNumCUs, batch); ++k) {
+    const double cost = (double)(ceil_div(k * batch, kNumCUs) * (ceil_div(tiles, k) + 3)) + (k > 1 ? 0.01 * (double)(k * batch) : 0.0);
+    if (least < 0.0 || cost < least) { best = k; least = cost; }
+  }
+  return (int)best;
+}
+
+// max_fused_wgs: no more workgroups per problem than this on the d = 128 path (a caller's smaller workspace)
 static LossGradPlan plan_loss_grad(int64_t batch, int64_t n, int64_t d, kt_dtype xdt, bool pooled = false,
-                                   bool keep_y = false) {
+                                   bool keep_y = false, int64_t max_fused_wgs = INT32_MAX) {
   LossGradPlan p;
   p.keep_y = false;
   p.o_yt = 0;
@@ -237,15 +252,14 @@ static LossGradPlan plan_loss_grad(int64_t batch, int64_t n, int64_t d, kt_dtype
   p.fused = !p.fp32 && d == 128 && !pooled;  // the pooled loss needs its global statistics before the gradient
   p.fused_wgs = 0;
   if (p.fused) {
-    const int64_t tiles = ceil_div(n, kF128Tile);
-    int64_t wgs = ceil_div(kNumCUs, batch);  // about one workgroup per CU over all problems
-    p.fused_wgs = (int)(wgs < tiles ? wgs : tiles);
+    p.fused_wgs = fused_d128_wgs(batch, n);
+    if (p.fused_wgs > max_fused_wgs) p.fused_wgs = (int)max_fused_wgs;
     p.ldt = p.tb = p.nblk = 0;
     p.P = p.tiles_dd = p.slabs_per_split = p.split_k = p.loss_blocks = 0;
     Carver c;
-    p.o_rt = c.take((size_t)batch * d * d * p.esz);
+    p.o_rt = 0;
     p.o_losspart = c.take((size_t)batch * p.fused_wgs * 8);
-    p.o_splitk = c.take((size_t)p.fused_wgs * batch * d * d * 4);
+    p.o_splitk = c.take(p.fused_wgs > 1 ? (size_t)p.fused_wgs * batch * d * d * 4 : 0);  // one: straight into dR
     p.o_part = p.o_coef = p.o_xt = p.o_gt = p.o_gstat = 0;
     p.total = c.off;
     return p;
@@ -555,21 +569,19 @@ static kt_status run_loss_grad_fused(const LossGradPlan& p, const void* X, int64
                                      char* ws, hipStream_t st) {
   if (!ensure_dynamic_lds(reinterpret_cast<const void*>(fused_d128_kernel), kF128LdsBytes))
     return fail(KT_ERR_DEVICE, "the fused d=128 kernel needs %d bytes of LDS per workgroup", kF128LdsBytes);
-  bf16* RT = reinterpret_cast<bf16*>(ws + p.o_rt);
   double* loss_part = reinterpret_cast<double*>(ws + p.o_losspart);
-  float* dR_part = reinterpret_cast<float*>(ws + p.o_splitk);
-  if (!prep_rt<bf16>(R, ldr, rdt, RT, batch, d, st)) return fail(KT_ERR_DEVICE, "prep_rt launch failed");
+  float* dR_part = p.fused_wgs > 1 ? reinterpret_cast<float*>(ws + p.o_splitk) : dR;
   {
     ProfScope prof(0, st);
-    hipLaunchKernelGGL(fused_d128_kernel, dim3(p.fused_wgs, (unsigned)batch), dim3(256), kF128LdsBytes, st,
-                       static_cast<const bf16*>(X), ldx, n * ldx, RT, (int)n, kappa_target, row_kurt,
+    hipLaunchKernelGGL(fused_d128_kernel, dim3(p.fused_wgs, (unsigned)batch), dim3(512), kF128LdsBytes, st,
+                       static_cast<const bf16*>(X), ldx, n * ldx, R, ldr, rdt == KT_BF16 ? 1 : 0, (int)n, kappa_target, row_kurt,
                        loss_part, dR_part, dR ? 1 : 0);
     if (!launch_ok()) return fail(KT_ERR_DEVICE, "fused kernel launch failed");
   }
   hipLaunchKernelGGL(finalize_loss_kernel, dim3((unsigned)batch), dim3(256), 0, st, loss_part, p.fused_wgs,
                      (int)n, loss);
   if (!launch_ok()) return fail(KT_ERR_DEVICE, "finalize_loss launch failed");
-  if (dR) {
+  if (dR && p.fused_wgs > 1) {
     const int64_t count = batch * d * d;
     hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)(ceil_div(count, 256) < 4096 ? ceil_div(count, 256) : 4096)),
                        dim3(256), 0, st, dR_part, count, p.fused_wgs, dR, count);
@@ -1107,6 +1119,8 @@ kt_status kt_kurtosis_loss_grad(const void* X, int64_t ldx, const void* R, int64
   if (!loss) return fail(KT_ERR_INVALID_ARG, "loss must not be null");
   if (!(kappa_target >= 0.f)) return fail(KT_ERR_INVALID_ARG, "kappa_target must be >= 0");
   LossGradPlan p = plan_loss_grad(batch, n, d, x_dtype);
+  // a workspace of less than kt_workspace_bytes() still serves while one workgroup's partials per problem fit
+  for (int k = p.fused_wgs - 1; p.fused && k >= 1 && workspace_bytes < p.total; --k) p = plan_loss_grad(batch, n, d, x_dtype, false, false, k);
   s = check_ws(workspace, workspace_bytes, p.total);
   if (s != KT_OK) return s;
   if (!p.fused && dR) {  // room for Y: keep it instead of recomputing it (same result)

@@ -17,15 +17,12 @@
 // Partial dR and loss sums of the workgroups of a problem are added by fixed-order
 // reduction kernels afterwards.
 //
-// LDS (160 KiB): three X tiles and two G tiles of 32 KiB, rows of 256 bytes (X(i+2) arrives
-// while E reads X(i) and B reads X(i+1); stage E of one tile overlaps stages C-D of the next);
-// R^T lives in registers.
-//  X: 16-byte chunks XOR-swizzled with xkey(row) = 4*(row%4) + (row/4)%4: distinct over 16
-//  consecutive rows (conflict-free 16-byte fragment reads of 16 rows at one column), and the
-//  4 consecutive tokens a half wave reads transposed fall into 4 different 64-byte bank groups.
-//  G: 8-byte units XOR-swizzled with gkey(t) = 8*(t%4) + (t/4)%8: distinct over 32 tokens
-//  (conflict-free 8-byte stores from 32 token lanes), same property for the transposed reads.
-//  stores from 32 token lanes and conflict-free transposing reads.
+// LDS (160 KiB): three X tiles and two G tiles of 32 KiB, rows of 256 bytes; R^T lives in registers.
+//  X: 16-byte chunks XOR-swizzled with xkey(row) = 4*(row%4) + (row/4)%4: distinct over 16 consecutive rows (conflict-free
+//  16-byte fragment reads of 16 rows at one column), and the rows k..k+3, k+8..k+11 that two lane quarters read transposed,
+//  32 bytes each, fall into eight different 32-byte bank groups.
+//  G: 8-byte units XOR-swizzled with gkey(t) = 2*p(t), p a permutation of 0..15: two neighbouring units of 16 tokens are
+//  distinct (conflict-free 8-byte stores of two lane quarters), and p/2 is distinct over the eight rows of a transposed read.
 #pragma once
 #include "kt_aux.h"
 #include "kt_gemm.h"
@@ -38,7 +35,7 @@ constexpr int kF128GOff = 3 * kF128BufBytes;     // LDS: X[3] | G[2]
 constexpr int kF128LdsBytes = 5 * kF128BufBytes;  // 160 KiB
 
 __device__ __forceinline__ int f128_xkey(int row) { return ((row & 3) << 2) | ((row >> 2) & 3); }
-__device__ __forceinline__ int f128_gkey(int t) { return ((t & 3) << 3) | ((t >> 2) & 7); }
+__device__ __forceinline__ int f128_gkey(int t) { return ((t & 3) << 3) | ((t & 8) >> 1) | ((t & 4) >> 1); }
 
 // The matrix-core instructions of this kernel are written as inline assembly so that the
 // register file of every operand is fixed: R^T fragments and the dR accumulators live in
@@ -47,16 +44,6 @@ __device__ __forceinline__ int f128_gkey(int t) { return ((t & 3) << 3) | ((t >>
 // registers of R^T and accumulators get shuffled between the two files every tile.
 // The compiler does not know these are matrix instructions: results are read by other
 // instruction types only behind mfma_result_fence().
-__device__ __forceinline__ void mfma_y_first(floatx16& y, const intx4& rt, const intx4& x) {
-  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, 0" : "=&v"(y) : "a"(rt), "v"(x));
-}
-__device__ __forceinline__ void mfma_y(floatx16& y, const intx4& rt, const intx4& x) {
-  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+v"(y) : "a"(rt), "v"(x));
-}
-__device__ __forceinline__ void mfma_dr(floatx16& acc, const intx4& xt, const intx4& gt) {
-  asm volatile("v_mfma_f32_32x32x16_bf16 %0, %1, %2, %0" : "+a"(acc) : "v"(xt), "v"(gt));
-}
-// the 16 x 16 forms (quant_d128_kernel)
 __device__ __forceinline__ void mfma16_y_first(floatx4& y, const intx4& rt, const intx4& x) {
   asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=&v"(y) : "a"(rt), "v"(x));
 }
@@ -66,36 +53,84 @@ __device__ __forceinline__ void mfma16_y(floatx4& y, const intx4& rt, const intx
 __device__ __forceinline__ void mfma16_result_fence(floatx4 (&y)[8]) {
   asm volatile("s_nop 15" : "+v"(y[0]), "+v"(y[1]), "+v"(y[2]), "+v"(y[3]), "+v"(y[4]), "+v"(y[5]), "+v"(y[6]), "+v"(y[7]));
 }
-// An 8-pass matrix instruction must be 11 issue slots old before another instruction type
-// reads its result.
-__device__ __forceinline__ void mfma_result_fence(floatx16& a, floatx16& b, floatx16& c, floatx16& d) {
-  asm volatile("s_nop 15" : "+v"(a), "+v"(b), "+v"(c), "+v"(d));
+__device__ __forceinline__ void mfma16_dr(floatx4& acc, const intx4& xt, const intx4& gt) {
+  asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, %0" : "+v"(acc) : "v"(xt), "v"(gt));
 }
-__device__ __forceinline__ void mfma_result_fence_acc(floatx16& a, floatx16& b, floatx16& c, floatx16& d) {
-  asm volatile("s_nop 15" : "+a"(a), "+a"(b), "+a"(c), "+a"(d));
+__device__ __forceinline__ void mfma16_result_fence(floatx4 (&a)[2][4]) {
+  asm volatile("s_nop 15" : "+v"(a[0][0]), "+v"(a[0][1]), "+v"(a[0][2]), "+v"(a[0][3]), "+v"(a[1][0]), "+v"(a[1][1]), "+v"(a[1][2]), "+v"(a[1][3]));
 }
 
 // 16 bytes per lane from global memory straight into LDS: lane l lands at lds_addr + 16 l
 // (lds_addr is wave-uniform).  Written as assembly so that the compiler does not tie later LDS
 // reads to these loads with a full wait; the waits are placed by hand (vmcnt).
-__device__ __forceinline__ void load_to_lds_16(const void* src, unsigned lds_addr) {
-  asm volatile("s_mov_b32 m0, %1\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, off" ::"v"(src), "s"(lds_addr)
+// Source: a wave-uniform base (from scalar instructions) and 32 bits of byte offset per lane.
+__device__ __forceinline__ void load_to_lds_16(uint32_t voffset, const char* base, unsigned lds_addr) {
+  asm volatile("s_mov_b32 m0, %2\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %0, %1" ::"v"(voffset), "s"(base), "s"(lds_addr)
                : "memory", "m0");
+}
+
+// One problem's R (row-major, fp32 or bf16, any alignment) rounded to bf16 into a swizzled 128 x 256-byte LDS tile, K as the
+// row: what fragments of R^T are read from (transposing reads), so that no launch has to write R^T first.  8 bytes a step.
+template <int NT>
+__device__ __forceinline__ void stage_rotation(const void* __restrict__ R, int64_t ldr, int r_bf16, char* tile) {
+  typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+  const bool vec = ((reinterpret_cast<uintptr_t>(R) | (uintptr_t)(ldr * (r_bf16 ? 2 : 4))) & (r_bf16 ? 7 : 15)) == 0;  // uniform
+  auto place = [&](int u, bf16x4 v) __attribute__((always_inline)) {
+    const int row = u >> 5, c = u & 31;
+    *reinterpret_cast<bf16x4*>(tile + row * 256 + (((c >> 1) ^ f128_xkey(row)) << 4) + ((c & 1) << 3)) = v;
+  };
+  constexpr int N = 128 * 32 / NT;
+  if (r_bf16) {
+    const __bf16* src = static_cast<const __bf16*>(R);
+    bf16x4 v[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const int u = (int)threadIdx.x + NT * i;
+      const __bf16* p = src + (int64_t)(u >> 5) * ldr + 4 * (u & 31);
+      if (vec) {
+        v[i] = *reinterpret_cast<const bf16x4*>(p);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[i][e] = p[e];
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < N; ++i) place((int)threadIdx.x + NT * i, v[i]);
+  } else {
+    const float* src = static_cast<const float*>(R);
+    floatx4 v[N];
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+      const int u = (int)threadIdx.x + NT * i;
+      const float* p = src + (int64_t)(u >> 5) * ldr + 4 * (u & 31);
+      if (vec) {
+        v[i] = *reinterpret_cast<const floatx4*>(p);
+      } else {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[i][e] = p[e];
+      }
+    }
+#pragma unroll
+    for (int i = 0; i < N; ++i) place((int)threadIdx.x + NT * i, bf16x4{(__bf16)v[i][0], (__bf16)v[i][1], (__bf16)v[i][2], (__bf16)v[i][3]});
+  }
 }
 
 // grid = (S, batch): S workgroups share the token tiles of one problem.
 // dR_part[(wg * batch + b) * 128*128 + k*128 + j], loss_part[b * S + wg].
 //
-// Software pipeline over the tiles i = 0, 1, ... of a workgroup (one barrier per tile).
-// X(i) lives in X buffer i % 3, G(i) in G buffer i & 1.  Iteration i:
-//   request X(i+2) (global -> LDS, buffer last read by E(i-1)); wait for X(i+1)
-//   B(i+1): Y = X R on the wave's own 32 rows (it moved those rows itself: no barrier)
-//   E(i) and C/D(i+1) as ONE instruction stream: one matrix instruction of
-//     dR += X(i)^T G(i) every ~20 vector instructions of the statistics / dL/dY arithmetic
-//   barrier (G(i+1) complete for every wave; buffers of tile i free)
-__global__ __launch_bounds__(256) void fused_d128_kernel(const __bf16* __restrict__ X, int64_t ldx,
+// Eight waves, two per SIMD, 16 tokens of the tile each (16 x 16 matrix blocks: R^T 128 registers, Y 32, a 32 x 64 share of
+// dR 32).  Phase i of a workgroup (one barrier each): B - D of its tile i, E of its tile i - 1, the loads of tile i + 1.
+// X(i) lives in X buffer i % 3, G(i) in G buffer i & 1.  Waves 0 - 3 run E behind D, waves 4 - 7 ahead of B: of the two waves of a
+// SIMD one is at its matrix instructions while the other is at its vector instructions.
+//
+// What bounds it: the board's power limit (1.4 kW, 1.8 - 1.9 GHz of 2.4; with X out of the caches instead of HBM the same cycles
+// run at 2.2 GHz).  256 problems x 131072 tokens (8 GiB, 2.2e12 flop), launches in a row, ms: four waves of 32 tokens with E
+// dealt between the vector instructions of C and D 2.95 (5950 cycles a tile, one wave's issue), eight waves in two roles (B -
+// D; E and loads) 2.87 (5280), this form 2.73 (4950; 2.83 with E behind D in every wave).  Fewer cycles did not help further:
+// E in 32 x 32 blocks, the loads dealt between matrix instructions and independent vector instructions side by side 2.8 - 2.95.
+__global__ __launch_bounds__(512) void fused_d128_kernel(const __bf16* __restrict__ X, int64_t ldx,
                                                          int64_t x_batch_stride,
-                                                         const __bf16* __restrict__ RT, int n,
+                                                         const void* __restrict__ R, int64_t ldr, int r_bf16, int n,
                                                          float kappa_target,
                                                          float* __restrict__ row_kurt,
                                                          double* __restrict__ loss_part,
@@ -106,288 +141,203 @@ __global__ __launch_bounds__(256) void fused_d128_kernel(const __bf16* __restric
   const int b = blockIdx.y, S = gridDim.x, wg = blockIdx.x, batch = gridDim.y;
   const int tid = threadIdx.x, lane = tid & 63;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int half = lane >> 5, l32 = lane & 31;
-  const int wm2 = wave >> 1, wn2 = wave & 1;  // dR quadrant of this wave in stage E
+  const int q = lane >> 4, l16 = lane & 15;
   X += (int64_t)b * x_batch_stride;
-  RT += (int64_t)b * D * D;
+  R = static_cast<const char*>(R) + (int64_t)b * D * ldr * (r_bf16 ? 2 : 4);
   const int tiles = (n + T - 1) / T;
   const int my_tiles = wg < tiles ? (tiles - wg + S - 1) / S : 0;  // tiles wg, wg+S, ...
-  const unsigned lds_base = (unsigned)(size_t)(__attribute__((address_space(3))) char*)lds;
 
-  // R^T fragments for all 8 K sub-steps and 4 feature blocks: 128 registers, loaded once
-  intx4 rtf[8][4];
-#pragma unroll
-  for (int s = 0; s < 8; ++s)
-#pragma unroll
-    for (int mb = 0; mb < 4; ++mb) {
-      rtf[s][mb] = *reinterpret_cast<const intx4*>(RT + (mb * 32 + l32) * D + (2 * s + half) * 8);
-      asm volatile("" : "+a"(rtf[s][mb]));
-    }
-
-  // X tile movement: a wave owns rows 32*wave .. +31 of the tile and moves them with 8
-  // instructions of 4 rows (1 KiB) each.  The 16-byte swizzle is applied on the source side:
-  // LDS chunk position (l & 15) of row r receives global chunk (l & 15) ^ xkey(r).
-  const int xrow0 = wave * 32 + (lane >> 4);  // tile row of instruction 0; instruction i: + 4 i
-  const __bf16* xlane[4];                     // source of instruction i at tile 0: xlane[i & 3] + 4 i ldx
-#pragma unroll
-  for (int i = 0; i < 4; ++i)
-    xlane[i] = X + (int64_t)xrow0 * ldx + (((lane & 15) ^ f128_xkey(4 * i + (lane >> 4))) << 3);
+  // X tile movement: a wave owns rows 16 wave .. + 15 of the tile and moves them with 4 instructions of 4 rows (1 KiB)
+  // each.  The 16-byte swizzle is applied on the source side: LDS chunk position l16 of row r receives global chunk
+  // l16 ^ xkey(r).
+  const unsigned lds_wave = (unsigned)(size_t)(__attribute__((address_space(3))) char*)lds + wave * (16 * 256);
+  const uint32_t xrow_off = (uint32_t)((wave * 16 + q) * ldx * 2);  // bytes from the tile's first row (ldx <= 2^22)
   auto load_tile = [&](int tile, int buf) __attribute__((always_inline)) {
-    const unsigned dst = lds_base + buf * BUF + wave * (32 * 256);
-    const int64_t tile_off = (int64_t)tile * T * ldx;
+    const char* src = reinterpret_cast<const char*>(X) + (int64_t)tile * T * ldx * 2;
+    auto one = [&](int i) __attribute__((always_inline)) {
+      load_to_lds_16(xrow_off + ((l16 ^ f128_xkey(4 * i + q)) << 4), src + (int64_t)(4 * i) * ldx * 2, lds_wave + buf * BUF + i * 1024);
+    };
     if (tile * T + T <= n) {
 #pragma unroll
-      for (int i = 0; i < 8; ++i)
-        load_to_lds_16(xlane[i & 3] + tile_off + (int64_t)(4 * i) * ldx, dst + i * 1024);
+      for (int i = 0; i < 4; ++i) one(i);
     } else {  // last, partial tile: rows past the end are zero-filled
 #pragma unroll
-      for (int i = 0; i < 8; ++i) {
-        if (tile * T + xrow0 + 4 * i < n)
-          load_to_lds_16(xlane[i & 3] + tile_off + (int64_t)(4 * i) * ldx, dst + i * 1024);
+      for (int i = 0; i < 4; ++i) {
+        if (tile * T + wave * 16 + 4 * i + q < n)
+          one(i);
         else
-          *reinterpret_cast<intx4*>(lds + buf * BUF + wave * (32 * 256) + i * 1024 + lane * 16) =
-              intx4{0, 0, 0, 0};
+          *reinterpret_cast<intx4*>(lds + buf * BUF + wave * (16 * 256) + i * 1024 + lane * 16) = intx4{0, 0, 0, 0};
       }
     }
   };
+  if (my_tiles > 0) load_tile(wg, 0);
 
-  floatx16 acc2[2][2];
+  // dR: 32 features of X (rows) x 64 of G (columns) per wave
+  const int wm4 = wave >> 1, wn2 = wave & 1;
+  floatx4 acc2[2][4];
 #pragma unroll
   for (int i = 0; i < 2; ++i)
 #pragma unroll
-    for (int j = 0; j < 2; ++j) {
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc2[i][j][r] = 0.f;
-      asm volatile("" : "+a"(acc2[i][j]));
+    for (int j = 0; j < 4; ++j) {
+      acc2[i][j] = floatx4{0.f, 0.f, 0.f, 0.f};
     }
   double loss_acc = 0.0;
   const float inv_d = 1.0f / (float)D;
   const float grad_scale = 4.0f / ((float)n * (float)D);
 
-  // lane constants of the transposing reads (stage E): token row 16 s + tr_tok (+4) of the tile
-  const int g16 = lane >> 4, rr = lane & 15;
-  const int tr_feat = 16 * (g16 & 1) + 4 * (rr & 3);
-  const int tr_tok = 8 * (g16 >> 1) + (rr >> 2);
-  int xa_lo[2], xa_hi[2], gb_lo[2][2], gb_hi[2][2];  // G: [parity of s][block]
+  // lane constants of the transposing reads (stage E): token row 32 s + 8 q + l16 / 4 (+4), 4 features 4 (l16 % 4) of a block of 16
+  // (row + 4 and the next block of 16 features: other bits of the address)
+  const int tr_row = 8 * q + (l16 >> 2), ux = wm4 * 8 + (l16 & 3), ug = wn2 * 16 + (l16 & 3);  // 8-byte unit of block 0
+  int xa = tr_row * 256 + (((ux >> 1) ^ f128_xkey(tr_row)) << 4) + ((ux & 1) << 3);
+  int ga = kF128GOff + tr_row * 256 + ((ug ^ f128_gkey(tr_row)) << 3);
+  constexpr int kRow4 = 4 * 256 + 16, kBlock = 32;
+
+  // R^T fragments for all 4 K steps and 8 feature blocks: 128 registers, read once from G buffer 1 (first written in
+  // phase 1).  From global memory every wave would take 32 KiB through the L1: 2 us of a call of few tiles.
+  stage_rotation<512>(R, ldr, r_bf16, lds + kF128GOff + BUF);
+  lds_barrier();
+  intx4 rtf[4][8];
+  const int ra = kF128GOff + BUF + tr_row * 256 + ((((l16 & 3) >> 1) ^ f128_xkey(tr_row)) << 4) + ((l16 & 1) << 3);
 #pragma unroll
-  for (int ib = 0; ib < 2; ++ib) {
-    const int u = (wm2 * 64 + ib * 32 + tr_feat) >> 2;  // 8-byte unit inside the X row
-    const int sel = (u & 1) << 3, ch = u >> 1, t_hi = tr_tok + 4;
-    xa_lo[ib] = tr_tok * 256 + (((ch ^ f128_xkey(tr_tok)) << 4) | sel);
-    xa_hi[ib] = t_hi * 256 + (((ch ^ f128_xkey(t_hi)) << 4) | sel);
-  }
+  for (int s = 0; s < 4; ++s)
 #pragma unroll
-  for (int par = 0; par < 2; ++par)
-#pragma unroll
-    for (int jb = 0; jb < 2; ++jb) {
-      const int u = (wn2 * 64 + jb * 32 + tr_feat) >> 2;
-      const int t_lo = 16 * par + tr_tok, t_hi = t_lo + 4;
-      const int z_lo = f128_gkey(t_lo), z_hi = f128_gkey(t_hi);
-      gb_lo[par][jb] = tr_tok * 256 + ((u ^ z_lo) << 3);
-      gb_hi[par][jb] = (tr_tok + 4) * 256 + ((u ^ z_hi) << 3);
+    for (int mb = 0; mb < 8; ++mb) {
+      const int at = ra ^ (mb * kBlock);
+      rtf[s][mb] = read_tr_operand(lds, at + s * 32 * 256, (at ^ kRow4) + s * 32 * 256);
     }
+#pragma unroll
+  for (int s = 0; s < 4; ++s)
+#pragma unroll
+    for (int mb = 0; mb < 8; ++mb) asm volatile("" : "+a"(rtf[s][mb]));
 
-  floatx16 acc[4];  // Y^T of the tile in flight: 64 of the 128 features of this lane's token
-
-  // B: Y^T (128 features x this wave's 32 tokens) = R^T X^T from X buffer `buf`
-  auto stage_b = [&](int buf) __attribute__((always_inline)) {
-    const char* xrow = lds + buf * BUF + (wave * 32 + l32) * 256;
-    intx4 xb[2];
-    xb[0] = *reinterpret_cast<const intx4*>(xrow + (((0 + half) ^ f128_xkey(l32)) << 4));
+  // B, C, D of tile `tile` (X buffer xbuf, G buffer gbuf)
+  auto stage_bcd = [&](int tile, int xbuf, int gbuf) __attribute__((always_inline)) {
+    floatx4 acc[8];  // Y of token 16 wave + l16 of the tile: features 16 mb + 4 q + r
+    {
+      const char* xrow = lds + xbuf * BUF + (wave * 16 + l16) * 256;
+      intx4 xb[4];
 #pragma unroll
-    for (int s = 0; s < 8; ++s) {
-      if (s + 1 < 8)
-        xb[(s + 1) & 1] = *reinterpret_cast<const intx4*>(xrow + (((2 * (s + 1) + half) ^ f128_xkey(l32)) << 4));
+      for (int s = 0; s < 4; ++s) xb[s] = *reinterpret_cast<const intx4*>(xrow + (((4 * s + q) ^ f128_xkey(l16)) << 4));
 #pragma unroll
-      for (int mb = 0; mb < 4; ++mb) {
-        if (s == 0)
-          mfma_y_first(acc[mb], rtf[0][mb], xb[0]);
-        else
-          mfma_y(acc[mb], rtf[s][mb], xb[s & 1]);
-      }
-    }
-    mfma_result_fence(acc[0], acc[1], acc[2], acc[3]);
-  };
-
-  // C, D of tile `tile` (statistics of this lane's token, dL/dY -> G buffer gbuf_w) with the 32
-  // matrix instructions of E (X buffer xbuf_r, G buffer gbuf_r) dealt between the arithmetic.
-  // WITH_CD / WITH_E switch the two halves off for the first and last tile of a workgroup.
-  auto stage_cde = [&](auto with_cd_c, auto with_e_c, int tile, int gbuf_w, int xbuf_r,
-                       int gbuf_r) __attribute__((always_inline)) {
-    constexpr bool WITH_CD = decltype(with_cd_c)::value, WITH_E = decltype(with_e_c)::value;
-    const char* xbase = lds + xbuf_r * BUF;
-    const char* gbase = lds + kF128GOff + gbuf_r * BUF;
-    intx4 fa[2][2], fb[2][2];
-    // one operand of K sub-step s (two transposing reads): 0 X block 0, 1 G block 0, 2 G block 1, 3 X block 1
-    auto fread_one = [&](auto s_c, auto which_c) __attribute__((always_inline)) {
-      constexpr int s = decltype(s_c)::value, which = decltype(which_c)::value;
-      if constexpr (which == 0 || which == 3) {
-        constexpr int ib = which == 0 ? 0 : 1;
-        fa[s & 1][ib] = read_tr_operand(xbase, xa_lo[ib] + s * 16 * 256, xa_hi[ib] + s * 16 * 256);
-      } else {
-        constexpr int jb = which - 1;
-        fb[s & 1][jb] = read_tr_operand(gbase, gb_lo[s & 1][jb] + s * 16 * 256, gb_hi[s & 1][jb] + s * 16 * 256);
-      }
-    };
-    auto fread = [&](auto s_c) __attribute__((always_inline)) {
-      static_for<4>([&](auto w_c) __attribute__((always_inline)) { fread_one(s_c, w_c); });
-    };
-    // matrix instruction k of E: K sub-step k / 4, dR block (k / 2) & 1, k & 1.  The four operands of the next
-    // sub-step are read one per instruction slot, BEHIND the slot's matrix instruction and in the order the next
-    // sub-step uses them: never more than eight LDS reads are in flight, so the wait in front of a matrix
-    // instruction can name exactly the reads it needs (the counter has four bits: with all sixteen reads of a
-    // sub-step issued at once, every fourth matrix instruction also waited for reads it did not need).
-    auto tick = [&](auto k_c) __attribute__((always_inline)) {
-      if constexpr (WITH_E) {
-        constexpr int k = decltype(k_c)::value, s = k >> 2, ib = (k >> 1) & 1, jb = k & 1;
-        __builtin_amdgcn_sched_barrier(0);
-        mfma_dr(acc2[ib][jb], fa[s & 1][ib], fb[s & 1][jb]);
-        if constexpr (s + 1 < 8) fread_one(integral_constant<int, s + 1>{}, integral_constant<int, k & 3>{});
-        __builtin_amdgcn_sched_barrier(0);
-      }
-    };
-    if constexpr (WITH_E) fread(integral_constant<int, 0>{});
-    if constexpr (!WITH_CD) {
-      static_for<32>(tick);
-    } else {
-      const int tok_local = wave * 32 + l32;
-      const int token = tile * T + tok_local;
-      const bool valid = token < n;
-      float s1 = 0.f;
-      static_for<4>([&](auto mb_c) __attribute__((always_inline)) {
-        constexpr int mb = decltype(mb_c)::value;
+      for (int s = 0; s < 4; ++s)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) s1 += acc[mb][r];
-        tick(integral_constant<int, mb>{});
-      });
-      s1 += __shfl_xor(s1, 32);
-      const float mu = s1 * inv_d;
-      float s2 = 0.f, s3 = 0.f, s4 = 0.f;
-      static_for<16>([&](auto g_c) __attribute__((always_inline)) {
-        constexpr int g = decltype(g_c)::value, mb = g >> 2, q = g & 3;
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          const float c = acc[mb][4 * q + e] - mu;
-          acc[mb][4 * q + e] = c;
-          const float c2 = c * c;
-          s2 += c2;
-          s3 = fmaf(c2, c, s3);
-          s4 = fmaf(c2, c2, s4);
+        for (int mb = 0; mb < 8; ++mb) {
+          if (s == 0)
+            mfma16_y_first(acc[mb], rtf[0][mb], xb[0]);
+          else
+            mfma16_y(acc[mb], rtf[s][mb], xb[s]);
         }
-        tick(integral_constant<int, 4 + g>{});
-      });
-      s2 += __shfl_xor(s2, 32);
-      s3 += __shfl_xor(s3, 32);
-      s4 += __shfl_xor(s4, 32);
-      tick(integral_constant<int, 20>{});
-      const float m2 = s2 * inv_d, m3 = s3 * inv_d, m4 = s4 * inv_d;
-      const bool ok = valid && m2 > 1e-10f * (m2 + mu * mu);  // same rule as finalize_rows_kernel
-      // branch-free: a degenerate or out-of-range token gets kappa = 0 and no gradient
-      const float m2s = ok ? m2 : 1.f;
-      const float inv_m2sq = 1.0f / (m2s * m2s);
-      const float kappa = ok ? m4 * inv_m2sq : 0.f;
-      float sgn = 1.f, term = kappa;
-      if (kappa_target != 0.f) {  // uniform
-        const float dk = kappa - kappa_target;
-        sgn = (float)((dk > 0.f) - (dk < 0.f));
-        term = fabsf(dk);
-      }
-      const float alpha = ok ? sgn * grad_scale * inv_m2sq : 0.f;
-      const float beta = kappa * m2;
-      loss_acc += (half == 0 && valid) ? (double)term : 0.0;
-      tick(integral_constant<int, 21>{});
-      if (want_grad) {
-        const int swz = f128_gkey(tok_local);
-        char* grow = lds + kF128GOff + gbuf_w * BUF + tok_local * 256;
-        static_for<16>([&](auto g_c) __attribute__((always_inline)) {
-          constexpr int g = decltype(g_c)::value, mb = g >> 2, q = g & 3;
-          typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-          bf16x4 v;
+      mfma16_result_fence(acc);
+    }
+    const int token = tile * T + wave * 16 + l16;
+    const bool valid = token < n;
+    float s1 = 0.f;
 #pragma unroll
-          for (int e = 0; e < 4; ++e) {
-            const float c = acc[mb][4 * q + e];
-            v[e] = (__bf16)(alpha * fmaf(c, fmaf(c, c, -beta), -m3));
-          }
-          const int u = mb * 8 + 2 * q + half;  // 8-byte unit: features 4u .. 4u+3
-          *reinterpret_cast<bf16x4*>(grow + ((u ^ swz) << 3)) = v;
-          constexpr int k0 = 22 + (g * 10) / 16, k1 = 22 + ((g + 1) * 10) / 16;
-          if constexpr (k1 > k0) tick(integral_constant<int, k0>{});
-        });
-      } else {
-        static_for<10>([&](auto j_c) __attribute__((always_inline)) {
-          tick(integral_constant<int, 22 + decltype(j_c)::value>{});
-        });
+    for (int mb = 0; mb < 8; ++mb)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) s1 += acc[mb][r];
+    const float mu = quarter_sum_all(s1) * inv_d;
+    float s2 = 0.f, s3 = 0.f, s4 = 0.f;
+#pragma unroll
+    for (int mb = 0; mb < 8; ++mb)
+#pragma unroll
+      for (int r = 0; r < 4; ++r) {
+        const float c = acc[mb][r] - mu;
+        acc[mb][r] = c;
+        const float c2 = c * c;
+        s2 += c2;
+        s3 = fmaf(c2, c, s3);
+        s4 = fmaf(c2, c2, s4);
       }
-      if (row_kurt && half == 0 && valid) row_kurt[(int64_t)b * n + token] = kappa;
+    const float m2 = quarter_sum_all(s2) * inv_d, m3 = quarter_sum_all(s3) * inv_d, m4 = quarter_sum_all(s4) * inv_d;
+    const bool ok = valid && m2 > 1e-10f * (m2 + mu * mu);  // same rule as finalize_rows_kernel
+    // branch-free: a degenerate or out-of-range token gets kappa = 0 and no gradient
+    const float m2s = ok ? m2 : 1.f;
+    const float inv_m2sq = 1.0f / (m2s * m2s);
+    const float kappa = ok ? m4 * inv_m2sq : 0.f;
+    float sgn = 1.f, term = kappa;
+    if (kappa_target != 0.f) {  // uniform
+      const float dk = kappa - kappa_target;
+      sgn = (float)((dk > 0.f) - (dk < 0.f));
+      term = fabsf(dk);
     }
-  };
-  using Yes = std::true_type;
-  using No = std::false_type;
-
-  if (my_tiles > 0) {
-    load_tile(wg, 0);
-    if (my_tiles > 1) load_tile(wg + S, 1);
-    // vmcnt(8) leaves the 8 newest loads in flight; a partial tile issues fewer than 8
-    if (my_tiles > 1 && (wg + S) * T + T <= n)
-      __builtin_amdgcn_s_waitcnt(0x0F78);
-    else
-      __builtin_amdgcn_s_waitcnt(0x0F70);  // vmcnt(0)
-    asm volatile("" ::: "memory");
-    stage_b(0);
-    stage_cde(Yes{}, No{}, wg, 0, 0, 0);
-    lds_barrier();
-    int xcur = 0;
-    // advance to tile i+1: request X(i+2), wait for X(i+1), B(i+1); returns the X buffer of i+1
-    auto advance = [&](int i) __attribute__((always_inline)) {
-      const int xnxt = xcur == 2 ? 0 : xcur + 1, xnn = xnxt == 2 ? 0 : xnxt + 1;
-      const int t2 = wg + (i + 2) * S;
-      const bool more2 = i + 2 < my_tiles;
-      if (more2) load_tile(t2, xnn);  // buffer last read by E(i-1)
-      if (more2 && t2 * T + T <= n)
-        __builtin_amdgcn_s_waitcnt(0x0F78);  // X(i+1) landed, X(i+2) in flight
-      else
-        __builtin_amdgcn_s_waitcnt(0x0F70);
-      asm volatile("" ::: "memory");
-      stage_b(xnxt);
-      return xnxt;
-    };
+    const float alpha = ok ? sgn * grad_scale * inv_m2sq : 0.f;
+    const float beta = kappa * m2;
+    loss_acc += (q == 0 && valid) ? (double)term : 0.0;
     if (want_grad) {
-      for (int i = 0; i + 1 < my_tiles; ++i) {
-        const int xnxt = advance(i);
-        stage_cde(Yes{}, Yes{}, wg + (i + 1) * S, (i + 1) & 1, xcur, i & 1);
-        lds_barrier();
-        xcur = xnxt;
-      }
-      stage_cde(No{}, Yes{}, 0, 0, xcur, (my_tiles - 1) & 1);
-    } else {
-      for (int i = 0; i + 1 < my_tiles; ++i) {
-        const int xnxt = advance(i);
-        stage_cde(Yes{}, No{}, wg + (i + 1) * S, (i + 1) & 1, xcur, i & 1);
-        lds_barrier();
-        xcur = xnxt;
+      char* grow = lds + kF128GOff + gbuf * BUF + (wave * 16 + l16) * 256;
+#pragma unroll
+      for (int mb = 0; mb < 8; ++mb) {
+        typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+        bf16x4 v;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const float c = acc[mb][r];
+          v[r] = (__bf16)(alpha * fmaf(c, fmaf(c, c, -beta), -m3));
+        }
+        *reinterpret_cast<bf16x4*>(grow + (((4 * mb + q) ^ f128_gkey(l16)) << 3)) = v;  // 8-byte unit: features 4 u .. 4 u + 3
       }
     }
+    if (row_kurt && q == 0 && valid) row_kurt[(int64_t)b * n + token] = kappa;
+  };
+
+  // E: dR += X^T G of a tile
+  auto stage_e = [&](int xbuf, int gbuf) __attribute__((always_inline)) {
+    asm volatile("" : "+v"(xa), "+v"(ga));  // (the addresses of the blocks are made here and not kept across the phases)
+    const int x0 = xa + xbuf * BUF, g0 = ga + gbuf * BUF;
+    intx4 fx[2][2], fg[2][4];
+    // operand k of K step s (two transposing reads): the G blocks 0 .. 3, the X blocks 4, 5
+    auto fread = [&](auto s_c, auto k_c) __attribute__((always_inline)) {
+      constexpr int s = decltype(s_c)::value, k = decltype(k_c)::value;
+      const int at = (k < 4 ? g0 : x0) ^ ((k & 3) * kBlock);
+      (k < 4 ? fg[s & 1][k & 3] : fx[s & 1][k & 1]) = read_tr_operand(lds, at + s * 32 * 256, (at ^ kRow4) + s * 32 * 256);
+    };
+    static_for<6>([&](auto k_c) __attribute__((always_inline)) { fread(integral_constant<int, 0>{}, k_c); });
+    static_for<32>([&](auto g_c) __attribute__((always_inline)) {
+      constexpr int g = decltype(g_c)::value, s = g >> 3, k = g & 7, ib = k >> 2, jb = k & 3;
+      __builtin_amdgcn_sched_barrier(0);
+      mfma16_dr(acc2[ib][jb], fx[s & 1][ib], fg[s & 1][jb]);
+      if constexpr (s + 1 < 4 && k < 6) fread(integral_constant<int, s + 1>{}, integral_constant<int, k>{});
+      __builtin_amdgcn_sched_barrier(0);
+    });
+    mfma16_result_fence(acc2);
+  };
+
+  // phase i
+  const bool e_first = wave >= 4;
+  int xbuf = 0;  // i % 3
+  for (int i = 0; i <= my_tiles; ++i) {
+    const int xnext = xbuf == 2 ? 0 : xbuf + 1, xprev = xbuf == 0 ? 2 : xbuf - 1;
+    const bool with_e = want_grad && i > 0;
+    // this wave's rows of X(i) have landed (and with the barrier at the end of this phase everybody's)
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)" ::: "memory");
+    if (i + 1 < my_tiles) load_tile(wg + (i + 1) * S, xnext);  // buffer last read by E(i-2)
+    if (e_first && with_e) stage_e(xprev, (i - 1) & 1);
+    if (i < my_tiles) stage_bcd(wg + i * S, xbuf, i & 1);
+    if (!e_first && with_e) stage_e(xprev, (i - 1) & 1);
+    lds_barrier();  // G(i) is complete, X(i) has landed, the buffers of tile i - 1 are free
+    xbuf = xnext;
   }
 
   // ---- wrap-up: partial dR and partial loss of this workgroup ----------------------------
   if (want_grad) {
-    mfma_result_fence_acc(acc2[0][0], acc2[0][1], acc2[1][0], acc2[1][1]);
     float* out = dR_part + ((int64_t)wg * batch + b) * (D * D);
 #pragma unroll
     for (int ib = 0; ib < 2; ++ib)
 #pragma unroll
-      for (int jb = 0; jb < 2; ++jb)
+      for (int jb = 0; jb < 4; ++jb)
 #pragma unroll
-        for (int r = 0; r < 16; ++r) {
-          const int k = wm2 * 64 + ib * 32 + ((r >> 2) << 3) + (half << 2) + (r & 3);
-          const int j = wn2 * 64 + jb * 32 + l32;
-          out[k * D + j] = acc2[ib][jb][r];
-        }
+        for (int r = 0; r < 4; ++r) out[(wm4 * 32 + ib * 16 + 4 * q + r) * D + wn2 * 64 + jb * 16 + l16] = acc2[ib][jb][r];
   }
-  __syncthreads();
   double* sh = reinterpret_cast<double*>(lds);
-  const double total = block_sum_256(loss_acc, sh);
-  if (tid == 0) loss_part[(int64_t)b * S + wg] = total;
+  sh[tid] = loss_acc;
+  __syncthreads();
+#pragma unroll
+  for (int s = 256; s >= 1; s >>= 1) {
+    if (tid < s) sh[tid] += sh[tid + s];
+    __syncthreads();
+  }
+  if (tid == 0) loss_part[(int64_t)b * S + wg] = sh[0];
 }
 
 // ---- single-pass rotate + int4 fake-quant for d = 128 (bf16) -------------------------------
