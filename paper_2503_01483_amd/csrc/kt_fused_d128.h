@@ -6,14 +6,14 @@
 // reads X three times and writes and re-reads two token-minor copies.  Here a workgroup
 // walks token tiles of 128 rows of one problem and, per tile,
 //   B. Y = X_tile R            (MFMA; token on the lane, all 128 features of a token in the
-//                               registers of one lane pair)
+//                               registers of four lanes)
 //   C. per-token mean, centred moments (two-pass, fp32), kurtosis, loss term,
 //      coefficients           (Eq. 3 and its chain rule; Y is still in registers: no recompute)
 //   D. G = dL/dY -> bf16 -> LDS, token-major like the X tile
 //   E. dR += X_tile^T G_tile   (MFMA; both operands are read token-minor straight out of the
 //                               token-major LDS tiles with ds_read_b64_tr_b16, the gfx950
 //                               transposing LDS read)
-// and keeps its 128 x 128 share of dR in accumulator registers until its last tile.
+// and keeps its 128 x 128 share of dR in registers until its last tile.
 // Partial dR and loss sums of the workgroups of a problem are added by fixed-order
 // reduction kernels afterwards.
 //
@@ -38,12 +38,11 @@ __device__ __forceinline__ int f128_xkey(int row) { return ((row & 3) << 2) | ((
 __device__ __forceinline__ int f128_gkey(int t) { return ((t & 3) << 3) | ((t & 8) >> 1) | ((t & 4) >> 1); }
 
 // The matrix-core instructions of this kernel are written as inline assembly so that the
-// register file of every operand is fixed: R^T fragments and the dR accumulators live in
-// accumulation registers (only the matrix core touches them), Y and the LDS fragments in
-// vector registers (the vector ALU consumes Y).  Left to the register allocator the 256
-// registers of R^T and accumulators get shuffled between the two files every tile.
+// register file of every operand is fixed: R^T fragments live in accumulation registers (only
+// the matrix core touches them), everything else in vector registers.  Left to the register
+// allocator the registers of R^T get shuffled between the two files every tile.
 // The compiler does not know these are matrix instructions: results are read by other
-// instruction types only behind mfma_result_fence().
+// instruction types only behind mfma16_result_fence().
 __device__ __forceinline__ void mfma16_y_first(floatx4& y, const intx4& rt, const intx4& x) {
   asm volatile("v_mfma_f32_16x16x32_bf16 %0, %1, %2, 0" : "=&v"(y) : "a"(rt), "v"(x));
 }
