@@ -142,7 +142,6 @@ constexpr int kHadMfmaFrom = 12;  // bf16 Hadamard factors of at least this orde
 constexpr int kSensBlocks = 1024;  // workgroups of the sensitivity sweeps
 constexpr int kCayleyMaxIters = 32;
 constexpr float kCayleyTol = 3e-7f;
-constexpr int kCayleyFusedFrom = 6;  // three-term path: iterations from here on are single launches
 
 #ifdef KT_PHASE_STAMPS
 static int g_stamp_next = -1;  // developer build: slot the next GEMM launch records its phase stamps in (-1: none)
@@ -183,6 +182,32 @@ static bool launch_gemm(const void* A, int64_t lda, int64_t bsa, int M, const vo
   g.stamp_slot = g_stamp_next >= 0 && g_stamp_next < kStampSlots ? g_stamp_next++ : -1;
 #endif
   hipLaunchKernelGGL(kern, dim3(g.grid_padded, batch), dim3(TL::NT), lds_bytes, stream, g, epi);
+  return launch_ok();
+}
+
+// The fixed point of `batch` retractions (cayley_iterate_kernel): U and B are [d][K] in the GEMM dtype.  As many workgroups per
+// problem as the chip holds, at most one per tile.
+template <class TL>
+static int64_t cayley_control_words(int64_t d) {
+  return kCayleyControlWords + ceil_div(d, TL::BM) * ceil_div(d, TL::BN);
+}
+template <class TL>
+static bool launch_cayley_iterations(const typename TL::T* U0, const typename TL::T* U1, const typename TL::T* B, int64_t K, int64_t d,
+                                     int64_t batch, const EpiCayleyIter<TL>& epi, unsigned* control, hipStream_t stream) {
+  auto kern = cayley_iterate_kernel<TL>;
+  if ((TL::BM - 1) * K * (int64_t)sizeof(typename TL::T) + 512 > (int64_t)UINT32_MAX) return false;
+  if (!ensure_dynamic_lds(reinterpret_cast<const void*>(kern), TL::LDS_BYTES)) return false;
+  GemmShape g = {};
+  g.B = B; g.lda = g.ldb = K; g.batch_stride_a = g.batch_stride_b = d * K;
+  g.M = g.N = (int)d;
+  g.tiles_m = (int)ceil_div(d, TL::BM);
+  g.tiles_n = (int)ceil_div(d, TL::BN);
+  g.tiles_total = g.tiles_m * g.tiles_n;
+  g.slabs_total = g.slabs_per_block = (int)(K / TL::BK);
+  const int64_t fit = kNumCUs * (160 * 1024 / TL::LDS_BYTES);
+  const unsigned wgs = (unsigned)(g.tiles_total < fit ? g.tiles_total : fit);
+  hipLaunchKernelGGL(kern, dim3(wgs, (unsigned)batch), dim3(TL::NT), TL::LDS_BYTES, stream, g, epi, U0, U1, control,
+                     cayley_control_words<TL>(d));
   return launch_ok();
 }
 
@@ -335,7 +360,7 @@ static CayleyPlan plan_cayley(int64_t batch, int64_t d) {
   p.o_delta = c.take((size_t)batch * kCayleyMaxIters * 4);
   // Cayley Adam scalars: partial sums (fp64) and {r, alpha, ||W||, alpha/(2r)} per problem
   p.g2_blocks = (int)(ceil_div(d * d / 4, 256) < 1024 ? ceil_div(d * d / 4, 256) : 1024);
-  p.o_g2 = c.take((size_t)batch * p.g2_blocks * 8);
+  p.o_g2 = c.take((size_t)batch * p.g2_blocks * 8);  // (then the control words of the iterations, which are fewer)
   p.o_sq = c.take((size_t)batch * (d / 32) * (d / 32) * 8);
   p.o_scal = c.take((size_t)batch * 4 * 4);
   p.total = c.off;
@@ -787,6 +812,24 @@ static kt_status cayley_run(const CayleyPlan& p, char* ws, float* R, const float
   unsigned* delta = reinterpret_cast<unsigned*>(ws + p.o_delta);
   const int D = (int)d;
   const int64_t dd = d * d;
+  // below d = 4096 a 256 x 256 tiling leaves most CUs without a tile: 128 x 128 there; fp32: the tile that fills the chip
+  const bool big = (d / 256) * (d / 256) * batch >= kNumCUs, small = small_f32_tiles(d, batch);
+  // The control words of the iterations lie where Cayley Adam had its block sums of ||G||^2, cleared by the set-up kernel; a
+  // tile grid too large for that room takes that of the sums of ||S||^2, behind the kernel that reads them.
+  const int64_t control_words = p.split ? (big ? cayley_control_words<TB_BIG>(d) : cayley_control_words<TB_128>(d))
+                                        : (small ? cayley_control_words<TF_64>(d) : cayley_control_words<TF>(d));
+  const bool late_control = control_words * 4 > (int64_t)p.g2_blocks * 8;
+  unsigned* control = reinterpret_cast<unsigned*>(ws + (late_control ? p.o_sq : p.o_g2));
+  const int ncontrol = late_control ? 0 : (int)control_words;
+  auto iterations = [&](auto tile_tag, const auto* U0, const auto* U1, const auto* B, int64_t K) -> bool {
+    using TL = decltype(tile_tag);
+    EpiCayleyIter<TL> e;
+    e.Rt = Rt; e.Zt = Zt; e.Unew = nullptr; e.Usplit = nullptr; e.delta = delta;
+    e.d = D; e.it = 0; e.max_iters = kCayleyMaxIters; e.tol = kCayleyTol;
+    e.bscale = adam ? adam->scal : nullptr;
+    if (late_control) hipLaunchKernelGGL(fill_u32_kernel, dim3(64), dim3(256), 0, st, control, batch * control_words, 0u);
+    return launch_cayley_iterations<TL>(U0, U1, B, K, d, batch, e, control, st);
+  };
 
   if (p.split) {
     // three-term bf16 path: operands live as [d][3d] bf16
@@ -798,23 +841,20 @@ static kt_status cayley_run(const CayleyPlan& p, char* ws, float* R, const float
     hipLaunchKernelGGL(split3_kernel, dim3(sb, 1, (unsigned)batch), dim3(256), 0, st, G, D, D, Us[0], 0);
     hipLaunchKernelGGL(split3_kernel, dim3(sb, 1, (unsigned)batch), dim3(256), 0, st, R, D, D, Us[1], 1);
     if (!launch_ok()) return fail(KT_ERR_DEVICE, "split launch failed");
-    // below d = 4096 a 256 x 256 tiling leaves most CUs without a tile: use 128 x 128 there
-    const bool big = (d / 256) * (d / 256) * batch >= kNumCUs;
-    auto product = [&](const __bf16* A3, const __bf16* B3, int it, float* Cdst = nullptr, float alpha = 1.f) -> bool {
+    auto product = [&](const __bf16* A3, const __bf16* B3, float* C, float alpha) -> bool {
       auto go = [&](auto tile_tag) -> bool {
         using TL = decltype(tile_tag);
-        EpiCayleyProduct<TL> e;
-        e.C = Cdst ? Cdst : Mm; e.alpha = alpha;
+        EpiStore<TL> e;
+        e.C = C; e.alpha = alpha;
         e.ldc = d; e.batch_stride = dd; e.split_stride = 0; e.M = D; e.N = D;
-        e.delta = delta; e.it = it; e.max_iters = kCayleyMaxIters; e.tol = kCayleyTol;
         return launch_gemm<TL>(A3, 3 * d, sd, D, B3, 3 * d, sd, D, 3 * d, 0, (int)batch, e, st);
       };
       return big ? go(TB_BIG{}) : go(TB_128{});
     };
-    if (!product(Us[0], Us[1], 0)) return fail(KT_ERR_DEVICE, "dR R^T GEMM launch failed");
-    hipLaunchKernelGGL(fill_u32_kernel, dim3(64), dim3(256), 0, st, delta, batch * kCayleyMaxIters, 0u);
+    if (!product(Us[0], Us[1], Mm, 1.f)) return fail(KT_ERR_DEVICE, "dR R^T GEMM launch failed");
     hipLaunchKernelGGL(cayley_setup_kernel, dim3(D / 32, D / 32, (unsigned)batch), dim3(256), 0, st, Mm, R,
-                       D, half_coef, (float*)nullptr, Rt, Zt, (float*)nullptr, Bs, Us[0], adam ? adam->sq_part : nullptr);
+                       D, half_coef, (float*)nullptr, Rt, Zt, (float*)nullptr, Bs, Us[0], adam ? adam->sq_part : nullptr, delta, kCayleyMaxIters,
+                       control, ncontrol);
     if (!launch_ok()) return fail(KT_ERR_DEVICE, "Cayley set-up launch failed");
     if (adam) {
       hipLaunchKernelGGL(adam_scalars2_kernel, dim3((unsigned)batch), dim3(256), 0, st, adam->sq_part,
@@ -822,36 +862,11 @@ static kt_status cayley_run(const CayleyPlan& p, char* ws, float* R, const float
       if (!launch_ok()) return fail(KT_ERR_DEVICE, "Cayley Adam scalar launch failed");
       // M <- S R = (1/2) S (2 Rt)^T: S sits in Bs as [hi|lo|hi], 2 Rt in Us[0] as [hi|hi|lo]; the same three
       // cross terms come out whichever operand carries which layout
-      if (!product(Bs, Us[0], 0, adam->M, 0.5f)) return fail(KT_ERR_DEVICE, "momentum projection GEMM launch failed");
+      if (!product(Bs, Us[0], adam->M, 0.5f)) return fail(KT_ERR_DEVICE, "momentum projection GEMM launch failed");
     }
-    const unsigned ub = (unsigned)(ceil_div(dd / 4, 256) < 512 ? ceil_div(dd / 4, 256) : 512);
-    // The first iterations run as product + elementwise update; the later ones, which almost always only find the
-    // convergence flag set, as ONE launch each with the update in the GEMM epilogue: half as many launches to skip through.
-    // With the epilogue's present 16-byte accesses the single launch is no slower where it does real work either: steps of two
-    // iterations, us, pairs up to the sixth / single launches throughout: d = 1024 194 / 187, 2048 315 / 312, 4096 1276 / 1268.
-    auto fused_iteration = [&](int it) -> bool {
-      auto go = [&](auto tile_tag) -> bool {
-        using TL = decltype(tile_tag);
-        EpiCayleyIter<TL> e;
-        e.Rt = Rt; e.Zt = Zt; e.Unew = nullptr; e.Usplit = Us[(it + 1) & 1]; e.delta = delta;
-        e.d = D; e.it = it; e.max_iters = kCayleyMaxIters; e.tol = kCayleyTol;
-        e.bscale = adam ? adam->scal : nullptr;
-        return launch_gemm<TL>(Us[it & 1], 3 * d, sd, D, Bs, 3 * d, sd, D, 3 * d, 0, (int)batch, e, st);
-      };
-      return big ? go(TB_BIG{}) : go(TB_128{});
-    };
-    for (int it = 0; it < kCayleyMaxIters; ++it) {
-      if (it >= kCayleyFusedFrom) {
-        if (!fused_iteration(it)) return fail(KT_ERR_DEVICE, "Cayley iteration launch failed");
-        continue;
-      }
-      if (!product(Us[it & 1], Bs, it)) return fail(KT_ERR_DEVICE, "Cayley iteration launch failed");
-      hipLaunchKernelGGL(cayley_update_kernel, dim3(ub, (unsigned)batch), dim3(256), 0, st, Mm, Rt, Zt,
-                         Us[(it + 1) & 1], D, delta, it, kCayleyMaxIters, kCayleyTol, adam ? adam->scal : nullptr);
-      if (!launch_ok()) return fail(KT_ERR_DEVICE, "Cayley update launch failed");
-    }
+    const bool launched = big ? iterations(TB_BIG{}, Us[0], Us[1], Bs, 3 * d) : iterations(TB_128{}, Us[0], Us[1], Bs, 3 * d);
+    if (!launched) return fail(KT_ERR_DEVICE, "Cayley iteration launch failed");
   } else {
-  const bool small = small_f32_tiles(d, batch);
   auto product = [&](const float* A, const float* B, float* C) -> bool {  // C = A B^T
     auto go = [&](auto tile_tag) -> bool {
       using TL = decltype(tile_tag);
@@ -862,11 +877,9 @@ static kt_status cayley_run(const CayleyPlan& p, char* ws, float* R, const float
     return small ? go(TF_64{}) : go(TF{});
   };
   if (!product(G, R, Mm)) return fail(KT_ERR_DEVICE, "dR R^T GEMM launch failed");
-  // delta[it] collects max |Zt_new - Zt_old| of iteration it through atomicMax
-  hipLaunchKernelGGL(fill_u32_kernel, dim3(64), dim3(256), 0, st, delta, batch * kCayleyMaxIters, 0u);
-  if (!launch_ok()) return fail(KT_ERR_DEVICE, "fill launch failed");
   hipLaunchKernelGGL(cayley_setup_kernel, dim3(D / 32, D / 32, (unsigned)batch), dim3(256), 0, st, Mm, R,
-                     D, half_coef, Bm, Rt, Zt, U[0], (__bf16*)nullptr, (__bf16*)nullptr, adam ? adam->sq_part : nullptr);
+                     D, half_coef, Bm, Rt, Zt, U[0], (__bf16*)nullptr, (__bf16*)nullptr, adam ? adam->sq_part : nullptr,
+                     delta, kCayleyMaxIters, control, ncontrol);
   if (!launch_ok()) return fail(KT_ERR_DEVICE, "Cayley set-up launch failed");
   if (adam) {
     hipLaunchKernelGGL(adam_scalars2_kernel, dim3((unsigned)batch), dim3(256), 0, st, adam->sq_part,
@@ -875,18 +888,9 @@ static kt_status cayley_run(const CayleyPlan& p, char* ws, float* R, const float
     // M <- S R = S (Rt)^T
     if (!product(Bm, Rt, adam->M)) return fail(KT_ERR_DEVICE, "momentum projection GEMM launch failed");
   }
-  // fixed point in transposed space: Zt <- Rt - U Bm^T, U <- Rt + Zt
-  for (int it = 0; it < kCayleyMaxIters; ++it) {
-    auto go = [&](auto tile_tag) -> bool {
-      using TL = decltype(tile_tag);
-      EpiCayleyIter<TL> e;
-      e.Rt = Rt; e.Zt = Zt; e.Unew = U[(it + 1) & 1]; e.Usplit = nullptr; e.delta = delta;
-      e.d = D; e.it = it; e.max_iters = kCayleyMaxIters; e.tol = kCayleyTol;
-      e.bscale = adam ? adam->scal : nullptr;
-      return launch_gemm<TL>(U[it & 1], d, dd, D, Bm, d, dd, D, d, 0, (int)batch, e, st);
-    };
-    if (!(small ? go(TF_64{}) : go(TF{}))) return fail(KT_ERR_DEVICE, "Cayley iteration launch failed");
-  }
+  // fixed point in transposed space: Zt <- Rt - U Bm^T, U <- Rt + Zt; delta[it] collects max |Zt_new - Zt_old|
+  const bool launched = small ? iterations(TF_64{}, U[0], U[1], Bm, d) : iterations(TF{}, U[0], U[1], Bm, d);
+  if (!launched) return fail(KT_ERR_DEVICE, "Cayley iteration launch failed");
   }
   hipLaunchKernelGGL(cayley_finish_kernel, dim3(D / 32, D / 32, (unsigned)batch), dim3(256), 0, st, Zt, D,
                      R, static_cast<__bf16*>(R_lowp), delta, kCayleyMaxIters, kCayleyTol, info);
@@ -901,7 +905,7 @@ static kt_status cayley_run(const CayleyPlan& p, char* ws, float* R, const float
       e.err = reinterpret_cast<unsigned*>(ortho_err); e.d = D;
       return launch_gemm<TL>(Zt, d, dd, D, Zt, d, dd, D, d, 0, (int)batch, e, st);
     };
-    if (!(small_f32_tiles(d, batch) ? off_diagonal(TF_64{}) : off_diagonal(TF{})))
+    if (!(small ? off_diagonal(TF_64{}) : off_diagonal(TF{})))
       return fail(KT_ERR_DEVICE, "orthogonality GEMM launch failed");
     hipLaunchKernelGGL(ortho_diag_kernel, dim3(D, (unsigned)batch), dim3(256), 0, st, Zt, D,
                        reinterpret_cast<unsigned*>(ortho_err));

@@ -396,7 +396,8 @@ __global__ __launch_bounds__(256) void split3_kernel(const float* __restrict__ i
 }
 
 // Cayley set-up: from M = dR R^T build  Bm = (lr/2)(M - M^T)  (exactly skew),
-// Rt = R^T, Zt0 = Rt, U0 = 2 Rt (Bm and U0 either as fp32 or as split bf16 operands).  32 x 32 tiles; grid = (d/32, d/32, batch).
+// Rt = R^T, Zt0 = Rt, U0 = 2 Rt (Bm and U0 either as fp32 or as split bf16 operands); clears the changes and control words.
+// 32 x 32 tiles; grid = (d/32, d/32, batch).
 __global__ __launch_bounds__(256) void cayley_setup_kernel(const float* __restrict__ Mm,
                                                            const float* __restrict__ R, int d,
                                                            float half_lr, float* __restrict__ Bm,
@@ -405,7 +406,9 @@ __global__ __launch_bounds__(256) void cayley_setup_kernel(const float* __restri
                                                            float* __restrict__ U0,
                                                            __bf16* __restrict__ Bs,
                                                            __bf16* __restrict__ Us,
-                                                           double* __restrict__ sq_part) {
+                                                           double* __restrict__ sq_part,
+                                                           unsigned* __restrict__ delta, int ndelta,
+                                                           unsigned* __restrict__ control, int ncontrol) {
   __shared__ float tm[32][33];
   __shared__ float tr[32][33];
   __shared__ double shsum[256];
@@ -413,6 +416,10 @@ __global__ __launch_bounds__(256) void cayley_setup_kernel(const float* __restri
   const int64_t bo = (int64_t)blockIdx.z * d * d;
   const int i0 = blockIdx.x * 32, j0 = blockIdx.y * 32;
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
+  if (blockIdx.x == 0 && blockIdx.y == 0) {  // this problem's words of cayley_iterate_kernel
+    for (int i = threadIdx.x; i < ndelta; i += 256) delta[(int64_t)blockIdx.z * ndelta + i] = 0u;
+    for (int i = threadIdx.x; i < ncontrol; i += 256) control[(int64_t)blockIdx.z * ncontrol + i] = 0u;
+  }
   // load the mirrored tile (rows j0.., cols i0..) of M and of R
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
@@ -514,54 +521,6 @@ __global__ __launch_bounds__(256) void adam_scalars2_kernel(const double* __rest
       scalars_out[3 * blockIdx.x + 2] = wn;
     }
   }
-}
-
-// One fixed-point update from the GEMM product C = U B^T (three-term bf16 path):
-//   Zt_new = Rt - C;  delta[it] = max |Zt_new - Zt|;  U_next = Rt + Zt_new as [hi|hi|lo].
-// Four consecutive elements per thread (16-byte loads); grid-stride; grid.y = batch.
-// Returns at once (handing the delta on) when an earlier iteration has converged.
-__global__ __launch_bounds__(256) void cayley_update_kernel(const float* __restrict__ C,
-                                                            const float* __restrict__ Rt,
-                                                            float* __restrict__ Zt,
-                                                            __bf16* __restrict__ Us, int d,
-                                                            unsigned* __restrict__ delta, int it,
-                                                            int max_iters, float tol,
-                                                            const float* __restrict__ bscale) {
-  __shared__ unsigned sh[4];
-  unsigned* dl = delta + (int64_t)blockIdx.y * max_iters;
-  if (it > 0 && cayley_converged(dl, it - 1, tol)) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) dl[it] = 0u;  // a zero change: later launches return too
-    return;
-  }
-  const int64_t dd = (int64_t)d * d, bo = (int64_t)blockIdx.y * dd;
-  const float bs = bscale ? bscale[4 * blockIdx.y + 3] : 1.f;  // Cayley Adam: factor of S
-  unsigned dmax = 0u;
-  for (int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x; q < dd / 4; q += (int64_t)gridDim.x * 256) {
-    const int64_t i = q * 4;
-    const int64_t m = i / d, n = i - m * d;
-    const floatx4 c = *reinterpret_cast<const floatx4*>(C + bo + i);
-    const floatx4 rt = *reinterpret_cast<const floatx4*>(Rt + bo + i);
-    const floatx4 zo = *reinterpret_cast<const floatx4*>(Zt + bo + i);
-    floatx4 z;
-    __bf16 hi[4], lo[4];
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      z[e] = rt[e] - bs * c[e];
-      dmax = umax(dmax, abs_bits(z[e] - zo[e]));
-      split_bf16(rt[e] + z[e], hi[e], lo[e]);
-    }
-    *reinterpret_cast<floatx4*>(Zt + bo + i) = z;
-    __bf16* o = Us + 3 * bo + m * 3 * d + n;
-    typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
-    const bf16x4 vh = {hi[0], hi[1], hi[2], hi[3]}, vl = {lo[0], lo[1], lo[2], lo[3]};
-    *reinterpret_cast<bf16x4*>(o) = vh;
-    *reinterpret_cast<bf16x4*>(o + d) = vh;
-    *reinterpret_cast<bf16x4*>(o + 2 * (int64_t)d) = vl;
-  }
-  dmax = wave_umax(dmax);
-  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = dmax;
-  __syncthreads();
-  if (threadIdx.x == 0) atomicMax(&dl[it], umax(umax(sh[0], sh[1]), umax(sh[2], sh[3])));
 }
 
 // Cayley wrap-up: R = Zt^T (and its bf16 copy), info = iterations used or -1.  An iteration that did

@@ -282,8 +282,7 @@ __device__ __forceinline__ unsigned wave_umax(unsigned v) {
 // ---- Cayley fixed point, in transposed space ---------------------------------------
 // acc = U_k * B^T.  Zt_new = Rt - acc;  U_{k+1} = Rt + Zt_new;
 // delta[it] = max |Zt_new - Zt_old| (bit pattern of a non-negative float, max is
-// order independent so the result is deterministic).  The launch for iteration `it`
-// returns at once when iteration it-1 already met the tolerance.
+// order independent so the result is deterministic).
 // When an iteration counts as converged.  The map is linear, Z_k+1 - Z_k = -B (Z_k - Z_k-1), so the
 // changes shrink geometrically with the spectral radius rho of B = (lr/2) A and the iterate just written
 // is within d_k rho / (1 - rho) of the fixed point (d_k = max |Z_k - Z_k-1|).  rho is estimated from the
@@ -308,13 +307,18 @@ __device__ __forceinline__ bool cayley_converged_hist(float d1, float d0, float 
   if (nprev < 2 || !(d1 <= 64.f * tol)) return false;
   return d1 >= 0.9f * d0 && d1 >= 0.8f * d00;
 }
+// (the changes are read past the caches of this XCD: inside cayley_iterate_kernel others have just written them)
+__device__ __forceinline__ bool cayley_converged_now(const unsigned* dl, int k, float tol) {
+  auto at = [&](int i) { return __uint_as_float(__hip_atomic_load(dl + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)); };
+  return cayley_converged_hist(at(k), k > 0 ? at(k - 1) : 0.f, k > 1 ? at(k - 2) : 0.f, k > 1 ? 2 : k, tol);
+}
 __device__ __forceinline__ bool cayley_converged(const unsigned* dl, int k, float tol) {
   return cayley_converged_hist(__uint_as_float(dl[k]), k > 0 ? __uint_as_float(dl[k - 1]) : 0.f,
                                k > 1 ? __uint_as_float(dl[k - 2]) : 0.f, k > 1 ? 2 : k, tol);
 }
 
 // Unew is written as fp32, or (Usplit != null) as the [hi | hi | lo] bf16 operand of the
-// three-term bf16 GEMM that runs the next iteration.
+// three-term bf16 GEMM that runs the next iteration.  (cayley_iterate_kernel sets `it` and the two targets.)
 template <class TL>
 struct EpiCayleyIter {
   const float* Rt;
@@ -326,14 +330,6 @@ struct EpiCayleyIter {
   float tol;
   const float* bscale = nullptr;  // acc is scaled by bscale[4 * batch + 3] when given (Cayley Adam)
   static constexpr bool kSwap = true;  // four consecutive columns of a row per lane: 16-byte accesses
-  __device__ __forceinline__ bool skip(int batch) const {
-    if (it == 0) return false;
-    const unsigned* dl = delta + (int64_t)batch * max_iters;
-    if (!cayley_converged(dl, it - 1, tol)) return false;
-    // converged earlier: record a zero change so that every later launch returns too
-    if (blockIdx.x == 0 && threadIdx.x == 0) delta[(int64_t)batch * max_iters + it] = 0u;
-    return true;
-  }
   __device__ __forceinline__ void operator()(floatx4 (&acc)[TL::MB][TL::NB], int batch, int,
                                              int, int, int m0, int n0) const {
     const Frag<TL> f;
@@ -379,17 +375,129 @@ struct EpiCayleyIter {
   }
 };
 
-// Plain fp32 store of one Cayley iteration's product (the update runs as a separate
-// elementwise kernel); returns at once when an earlier iteration has converged.
+// ---- the whole fixed point in one launch ---------------------------------------------------
+// Control words of one problem, all zero at the start: done[k] = tiles of iteration k that are complete, claim[t] = how many
+// iterations of tile t have been taken.
+constexpr int kCayleyControlWords = 64;  // done[0 .. 31], stop at 32; claim[] behind them
+
+// Iterations k = 0, 1, ... of  Zt <- Rt - U_k B^T, U_k+1 = Rt + Zt  until they converge, with the dependency of each on all
+// tiles of the one before inside the launch.  grid = (workgroups, problems); a workgroup owns the tiles w, w + gridDim.x, ...
+//
+// No workgroup relies on another one being resident: a tile of an iteration is taken by raising claim[t]; a workgroup takes
+// its own ones as the iteration opens, and while it waits for the others it takes whatever nobody has taken.  So every tile
+// that is waited for is in the hands of a running workgroup, whatever else runs on the chip.  (The wait ends after
+// kCayleyWaitTicks all the same; the step then counts as not converged.)
+//
+// The results of a tile become visible with a release at device scope by one thread behind the workgroup's stores, and are
+// acquired at that scope behind the wait; done[], claim[] and the changes are atomics.
+//
+// Why one launch: the host cannot know when the iteration has converged, so a launch per iteration means all 32 of them, and one
+// that only finds the convergence flag set costs 2 to 5 us.
+constexpr long long kCayleyWaitTicks = 20ll * 100000000;  // 20 s of the 100 MHz counter
+
 template <class TL>
-struct EpiCayleyProduct : EpiStore<TL> {
-  const unsigned* delta;  // [batch][max_iters]
-  int it, max_iters;
-  float tol;
-  __device__ __forceinline__ bool skip(int batch) const {
-    return it > 0 && cayley_converged(delta + (int64_t)batch * max_iters, it - 1, tol);
+__global__ __launch_bounds__(TL::NT) void cayley_iterate_kernel(GemmShape g, EpiCayleyIter<TL> epi, const typename TL::T* U0,
+                                                                const typename TL::T* U1, unsigned* control, int64_t control_stride) {
+  extern __shared__ __align__(16) char lds[];
+  using T = typename TL::T;
+  const int batch = blockIdx.y, tiles = g.tiles_total;
+  unsigned* done = control + (int64_t)batch * control_stride;
+  unsigned* stop = done + 32;
+  unsigned* claim = done + kCayleyControlWords;
+  unsigned* delta = epi.delta + (int64_t)batch * epi.max_iters;
+  const T* B = static_cast<const T*>(g.B) + (int64_t)batch * g.batch_stride_b;
+  int* said = reinterpret_cast<int*>(lds);  // {tile or -1, iteration}, from wave 0 (the LDS is free between two tiles)
+  auto load = [](const unsigned* p) __attribute__((always_inline)) {
+    return (unsigned)__builtin_amdgcn_readfirstlane((int)__hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+  };
+
+  int it = 0, own = blockIdx.x;  // wave 0: the open iteration, the next of this workgroup's tiles in it
+  bool looked = false;           // ... has just found a tile of somebody else's: look for the next one at once
+  // tile t of iteration `it`, if nobody has it (wave 0)
+  auto take = [&](int t) __attribute__((always_inline)) {
+    int got = 0;
+    if (threadIdx.x == 0) got = atomicCAS(claim + t, (unsigned)it, (unsigned)it + 1) == (unsigned)it;
+    return __builtin_amdgcn_readfirstlane(got) != 0;
+  };
+  // the next tile for this workgroup, -1 when there is none left (wave 0)
+  auto next_tile = [&]() __attribute__((always_inline)) {
+    for (;;) {
+      while (own < tiles) {
+        const int t = own;
+        own += gridDim.x;
+        if (take(t)) return t;
+      }
+      const long long t0 = __builtin_amdgcn_s_memrealtime();
+      for (int polls = looked ? 15 : 0; load(done + it) < (unsigned)tiles; ++polls) {
+        if ((polls & 15) == 15) {
+          if (load(stop) != 0u) return -1;
+          if ((long long)__builtin_amdgcn_s_memrealtime() - t0 > kCayleyWaitTicks) {
+            if (threadIdx.x == 0) {
+              __hip_atomic_store(stop, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+              for (int k = it; k < epi.max_iters; ++k) atomicMax(delta + k, 0x7fc00000u);
+            }
+            return -1;
+          }
+          int mine = -1;
+          for (int t = threadIdx.x; t < tiles; t += 64)
+            if (mine < 0 && __hip_atomic_load(claim + t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)it) mine = t;
+          const unsigned long long found = __ballot(mine >= 0);
+          if (found) {
+            const int t = __builtin_amdgcn_readlane(mine, __builtin_ctzll(found));
+            looked = true;
+            if (take(t)) return t;
+          }
+        }
+        __builtin_amdgcn_s_sleep(2);
+      }
+      looked = false;
+      __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+      if (it + 1 == epi.max_iters || cayley_converged_now(delta, it, epi.tol)) return -1;
+      ++it;
+      own = blockIdx.x;
+    }
+  };
+
+#pragma unroll 1
+  for (;;) {
+    __syncthreads();
+    if (threadIdx.x < 64) {
+      const int t = next_tile();
+      if (threadIdx.x == 0) {
+        said[0] = t;
+        said[1] = it;
+      }
+    }
+    __syncthreads();
+    const int t = __builtin_amdgcn_readfirstlane(said[0]), k = __builtin_amdgcn_readfirstlane(said[1]);
+    __syncthreads();
+    if (t < 0) return;
+    int tm, tn;
+    tile_in_bands(g, (tiles & 7) ? t : (t & 7) * (tiles >> 3) + (t >> 3), tm, tn);  // (neighbours on one XCD, as in tile_of_block)
+    const int m0 = tm * TL::BM, n0 = tn * TL::BN;
+    floatx4 acc[TL::MB][TL::NB];
+#pragma unroll
+    for (int mb = 0; mb < TL::MB; ++mb)
+#pragma unroll
+      for (int nb = 0; nb < TL::NB; ++nb) acc[mb][nb] = floatx4{0.f, 0.f, 0.f, 0.f};
+    settle_all<TL>(acc);
+    gemm_mainloop<TL, false, true>((k & 1 ? U1 : U0) + (int64_t)batch * g.batch_stride_a, g.lda, g.M, m0, B, g.ldb, g.N, n0, 0, g.slabs_total,
+                                   g.slabs_per_block, 0, 0, acc, lds, 0);
+    settle_all<TL>(acc);
+    EpiCayleyIter<TL> e = epi;
+    e.it = k;
+    T* next = const_cast<T*>(k & 1 ? U0 : U1);
+    if constexpr (sizeof(T) == 2) e.Usplit = next;
+    else e.Unew = next;
+    e(acc, batch, tm, tn, 0, m0, n0);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's stores (and its change) have reached the L2
+    __syncthreads();
+    if (threadIdx.x == 0) {
+      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+      __hip_atomic_fetch_add(done + k, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    }
   }
-};
+}
 
 // ---- orthogonality check: max |acc_mn| over m != n -----------------------------------
 // The diagonal (sums of squares close to 1, where fp32 accumulation loses ~1e-7 per

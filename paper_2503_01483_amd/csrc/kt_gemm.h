@@ -546,6 +546,18 @@ __device__ __forceinline__ void gemm_mainloop(const typename TL::T* __restrict__
   asm volatile("" ::: "memory");
 }
 
+// Tile L of the walk in bands of 4 tile-rows.
+__device__ __forceinline__ void tile_in_bands(const GemmShape& g, int L, int& tm, int& tn) {
+  constexpr int BAND = 4;
+  const int band_tiles = BAND * g.tiles_n;
+  const int band = L / band_tiles;
+  const int first_m = band * BAND;
+  const int rows = (g.tiles_m - first_m) < BAND ? (g.tiles_m - first_m) : BAND;
+  const int in_band = L - band * band_tiles;
+  tm = first_m + in_band % rows;
+  tn = in_band / rows;
+}
+
 // Workgroup -> tile.  Consecutive workgroup ids land on different XCDs (8 of them,
 // each with its own L2), so ids are first regrouped so that each XCD walks a
 // contiguous range of tiles, then the range is walked in bands of 4 tile-rows so
@@ -558,14 +570,7 @@ __device__ __forceinline__ bool tile_of_block(const GemmShape& g, int& tm, int& 
   const int per_split = g.tiles_m * g.tiles_n;
   ks = L / per_split;
   L -= ks * per_split;
-  constexpr int BAND = 4;
-  const int band_tiles = BAND * g.tiles_n;
-  const int band = L / band_tiles;
-  const int first_m = band * BAND;
-  const int rows = (g.tiles_m - first_m) < BAND ? (g.tiles_m - first_m) : BAND;
-  const int in_band = L - band * band_tiles;
-  tm = first_m + in_band % rows;
-  tn = in_band / rows;
+  tile_in_bands(g, L, tm, tn);
   return true;
 }
 
