@@ -147,19 +147,20 @@ constexpr float kCayleyTol = 3e-7f;
 static int g_stamp_next = -1;  // developer build: slot the next GEMM launch records its phase stamps in (-1: none)
 #endif
 
-template <class TL, class Epi, bool ATN = false>
+template <class TL, class Epi, bool ATN = false, bool BTN = false>
 static bool launch_gemm(const void* A, int64_t lda, int64_t bsa, int M, const void* B, int64_t ldb,
                         int64_t bsb, int N, int64_t K, int slabs_per_split, int batch,
                         const Epi& epi, hipStream_t stream, int64_t k_block = 0,
                         int64_t block_stride_a = 0, int64_t block_stride_b = 0, int k_valid = 0) {
-  // ATN: A is [K][lda] with the M index along its rows (see gemm_mainloop); K blocking applies to B only
-  auto kern = gemm_nt_kernel<TL, Epi, ATN>;
+  // ATN: A is [K][lda] with the M index along its rows (see gemm_mainloop); K blocking applies to B only.  BTN: B [K][ldb].
+  auto kern = gemm_nt_kernel<TL, Epi, ATN, BTN>;
   constexpr int lds_bytes = TL::LDS_BYTES;
   // the kernel addresses the rows of a tile with 32-bit byte offsets from the tile's first row
   const int64_t esz = (int64_t)sizeof(typename TL::T);
-  if ((ATN ? 127 : TL::BM - 1) * lda * esz + 512 > (int64_t)UINT32_MAX || (TL::BN - 1) * ldb * esz + 128 > (int64_t)UINT32_MAX)
+  if ((ATN ? 127 : TL::BM - 1) * lda * esz + 512 > (int64_t)UINT32_MAX || (BTN ? 127 : TL::BN - 1) * ldb * esz + 512 > (int64_t)UINT32_MAX)
     return false;
   if (ATN && (k_valid < 1 || k_valid > K)) return false;
+  if (esz == 4 && ((ATN && M % 4 != 0) || (BTN && N % 4 != 0))) return false;
   if (!ensure_dynamic_lds(reinterpret_cast<const void*>(kern), lds_bytes)) return false;
   GemmShape g;
   g.A = A; g.B = B; g.lda = lda; g.ldb = ldb;
@@ -183,6 +184,25 @@ static bool launch_gemm(const void* A, int64_t lda, int64_t bsa, int M, const vo
 #endif
   hipLaunchKernelGGL(kern, dim3(g.grid_padded, batch), dim3(TL::NT), lds_bytes, stream, g, epi);
   return launch_ok();
+}
+
+// Whether a row-major fp32 operand can be read in place, K as its row index (16-byte loads).  Otherwise a launch copies it first.
+static bool f32_in_place(const void* p, int64_t ld) { return ((reinterpret_cast<uintptr_t>(p) | (uintptr_t)(ld * 4)) & 15) == 0; }
+
+static bool overlap(const void* a, size_t a_bytes, const void* b, size_t b_bytes) {
+  const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
+  return x < y + b_bytes && y < x + a_bytes;
+}
+
+// C = R^T X^T with the features on the rows of the GEMM: R is either R^T in the GEMM dtype (in_place false, rows of d) or, fp32,
+// the rotation as the caller laid it out.
+template <class TL, class Epi>
+static bool launch_features_gemm(const typename TL::T* R, int64_t ldr, bool in_place, const typename TL::T* X, int64_t ldx, int64_t batch,
+                                 int64_t n, int64_t d, const Epi& e, hipStream_t st) {
+  if constexpr (sizeof(typename TL::T) == 4) {
+    if (in_place) return launch_gemm<TL, Epi, true>(R, ldr, d * ldr, (int)d, X, ldx, n * ldx, (int)n, d, 0, (int)batch, e, st, 0, 0, 0, (int)d);
+  }
+  return launch_gemm<TL>(R, d, d * d, (int)d, X, ldx, n * ldx, (int)n, d, 0, (int)batch, e, st);
 }
 
 // The fixed point of `batch` retractions (cayley_iterate_kernel): U and B are [d][K] in the GEMM dtype.  As many workgroups per
@@ -648,7 +668,7 @@ static bool launch_skinny(const bf16* X, int64_t ldx, const TR* R, int64_t ldr, 
   return launch_ok();
 }
 
-// Y [problems][rows][d] = X R (token-major, tokens on the rows of the GEMM) with the tile that fills the chip: the large one
+// Y [problems][rows][d] = X R (token-major, tokens on the rows of the GEMM; R as in launch_features_gemm) with the tile that fills the chip: the large one
 // (TL) unless it leaves CUs without a tile, then 128 x 128 (bf16) or 64 x 64 (fp32).  Fake-quant calls, us, large / small
 // tile: bf16 d = 4096, n = 128: 97 / 58, 1024: 105 / 64, 2048 (128 large tiles): 109 / 91, 2560: 112 / 116; d = 2048,
 // n = 4096 (128): 67 / 53, 6144: 72 / 73; fp32 d = 1024, n = 256: 75 / 30, 4096 (256 large tiles): 84 / 80; d = 2048,
@@ -657,14 +677,18 @@ static bool launch_skinny(const bf16* X, int64_t ldx, const TR* R, int64_t ldr, 
 // other number: 144 tiles 35.5 / 37.1, 240: 50.7 / 53.1, 288: 68.6 / 59.0, 320: 50.7 / 43.9, 384: 50.6 / 46.0,
 // 432: 72.3 / 73.6, 480: 88.2 / 91.0, 576: 92.2 / 88.1, 1152: 176 / 164.
 template <typename T, class TL>
-static bool launch_rows_gemm(const T* X, int64_t ldx, int64_t x_batch_stride, const T* RT, int64_t problems, int64_t rows,
-                             int64_t d, float* Y, hipStream_t st) {
+static bool launch_rows_gemm(const T* X, int64_t ldx, int64_t x_batch_stride, const T* R, int64_t ldr, bool in_place, int64_t problems,
+                             int64_t rows, int64_t d, float* Y, hipStream_t st) {
   using Small = std::conditional_t<sizeof(T) == 4, TF_64, TB_128>;
   auto go = [&](auto tile_tag) -> bool {
     using G = decltype(tile_tag);
     EpiStore<G> e;
     e.C = Y; e.ldc = d; e.batch_stride = rows * d; e.split_stride = 0; e.M = (int)rows; e.N = (int)d;
-    return launch_gemm<G>(X, ldx, x_batch_stride, (int)rows, RT, d, d * d, (int)d, d, 0, (int)problems, e, st);
+    if constexpr (sizeof(T) == 4) {
+      if (in_place)
+        return launch_gemm<G, EpiStore<G>, false, true>(X, ldx, x_batch_stride, (int)rows, R, ldr, d * ldr, (int)d, d, 0, (int)problems, e, st);
+    }
+    return launch_gemm<G>(X, ldx, x_batch_stride, (int)rows, R, d, d * d, (int)d, d, 0, (int)problems, e, st);
   };
   const int64_t tiles = ceil_div(rows, TL::BM) * ceil_div(d, TL::BN) * problems;
   bool small;
@@ -705,7 +729,10 @@ static kt_status run_quant(const QuantPlan& p, const void* X, int64_t ldx, const
   const T* Xp = static_cast<const T*>(X);
   const bool staged = !scales_in && (codes || err);
   const bool skinny = staged && p.stage_problems == batch && skinny_ok(sizeof(T) == 2 ? KT_BF16 : KT_F32, R, ldr, rdt, n);
-  if (!skinny && !prep_rt<T>(R, ldr, rdt, RT, batch, d, st)) return fail(KT_ERR_DEVICE, "prep_rt launch failed");
+  const bool in_place = sizeof(T) == 4 && f32_in_place(R, ldr);
+  if (!skinny && !in_place && !prep_rt<T>(R, ldr, rdt, RT, batch, d, st)) return fail(KT_ERR_DEVICE, "prep_rt launch failed");
+  const T* Rg = in_place ? static_cast<const T*>(R) : RT;
+  const int64_t r_stride = in_place ? d * ldr : d * d;
   const float* scales = scales_in;
   if (staged) {
     // One GEMM instead of two: Y = X R is staged in fp32 (token-major: tokens on the rows of the GEMM), a
@@ -721,7 +748,7 @@ static kt_status run_quant(const QuantPlan& p, const void* X, int64_t ldx, const
           ok = rdt == KT_F32 ? launch_skinny(Xb, ldx, static_cast<const float*>(R), ldr, batch, n, d, ws + p.o_rt, p.o_amax - p.o_rt, Ybuf, st)
                              : launch_skinny(Xb, ldx, static_cast<const bf16*>(R), ldr, batch, n, d, ws + p.o_rt, p.o_amax - p.o_rt, Ybuf, st);
         } else {
-          ok = launch_rows_gemm<T, TQ>(Xp + (b0 * n + t0) * ldx, ldx, n * ldx, RT + b0 * d * d, nb, nt, d, Ybuf, st);
+          ok = launch_rows_gemm<T, TQ>(Xp + (b0 * n + t0) * ldx, ldx, n * ldx, Rg + b0 * r_stride, ldr, in_place, nb, nt, d, Ybuf, st);
         }
         if (!ok) return fail(KT_ERR_DEVICE, "rotation GEMM launch failed");
         const int64_t rows = nb * nt, row0 = b0 * n + t0;
@@ -745,7 +772,7 @@ static kt_status run_quant(const QuantPlan& p, const void* X, int64_t ldx, const
   if (!scales_in) {
     EpiAmax<TFWD> e;
     e.part = amax; e.n_tokens = (int)n; e.d = (int)d; e.P = p.P;
-    if (!launch_gemm<TFWD>(RT, d, d * d, (int)d, Xp, ldx, n * ldx, (int)n, d, 0, (int)batch, e, st))
+    if (!launch_features_gemm<TFWD>(Rg, ldr, in_place, Xp, ldx, batch, n, d, e, st))
       return fail(KT_ERR_DEVICE, "amax GEMM launch failed");
     hipLaunchKernelGGL(quant_scale_kernel, dim3((unsigned)ceil_div(n, 256), (unsigned)batch), dim3(256),
                        0, st, amax, p.P, n, clip, scales_ws, scales_out);
@@ -760,7 +787,7 @@ static kt_status run_quant(const QuantPlan& p, const void* X, int64_t ldx, const
     EpiQuant<TFWD> e;
     e.scales = scales; e.codes = codes; e.err_part = err ? errpart : nullptr;
     e.n_tokens = (int)n; e.d = (int)d; e.P = p.P;
-    if (!launch_gemm<TFWD>(RT, d, d * d, (int)d, Xp, ldx, n * ldx, (int)n, d, 0, (int)batch, e, st))
+    if (!launch_features_gemm<TFWD>(Rg, ldr, in_place, Xp, ldx, batch, n, d, e, st))
       return fail(KT_ERR_DEVICE, "quantise GEMM launch failed");
   }
   if (err) {
@@ -1332,7 +1359,9 @@ kt_status kt_rotate_quant_metrics(const void* X, int64_t ldx, const void* R, int
     T* RT = reinterpret_cast<T*>(ws);
     const T* Xp = static_cast<const T*>(X);
     const bool skinny = sp == batch && skinny_ok(x_dtype, R, ldr, r_dtype, n);
-    if (!skinny && !prep_rt<T>(R, ldr, r_dtype, RT, batch, d, st)) return fail(KT_ERR_DEVICE, "prep_rt launch failed");
+    const bool in_place = sizeof(T) == 4 && f32_in_place(R, ldr) && !(Y && overlap(Y, batch * n * d * 4, R, ((batch * d - 1) * ldr + d) * 4));
+    if (!skinny && !in_place && !prep_rt<T>(R, ldr, r_dtype, RT, batch, d, st)) return fail(KT_ERR_DEVICE, "prep_rt launch failed");
+    const T* Rg = in_place ? static_cast<const T*>(R) : RT;
     if (success) {
       hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(256), 0, st, reinterpret_cast<unsigned*>(success),
                          2 * batch, 0u);
@@ -1347,7 +1376,7 @@ kt_status kt_rotate_quant_metrics(const void* X, int64_t ldx, const void* R, int
           ok = r_dtype == KT_F32 ? launch_skinny(Xb, ldx, static_cast<const float*>(R), ldr, batch, n, d, ws, rt_bytes, Yb, st)
                                  : launch_skinny(Xb, ldx, static_cast<const bf16*>(R), ldr, batch, n, d, ws, rt_bytes, Yb, st);
         } else {
-          ok = launch_rows_gemm<T, TL>(Xp + row0 * ldx, ldx, n * ldx, RT + b0 * d * d, nb, nt, d, Yb, st);
+          ok = launch_rows_gemm<T, TL>(Xp + row0 * ldx, ldx, n * ldx, Rg + b0 * (in_place ? d * ldr : d * d), ldr, in_place, nb, nt, d, Yb, st);
         }
         if (!ok) return fail(KT_ERR_DEVICE, "rotation GEMM launch failed");
         // the row in 4 / 8 / 16 / 32 float4 registers per lane; rows that fill them exactly skip every bounds test
@@ -1416,28 +1445,40 @@ kt_status kt_fuse_rotation(const float* W, int64_t ldw, const float* R, int64_t 
   if (s != KT_OK) return s;
   char* ws = static_cast<char*>(workspace);
   hipStream_t st = static_cast<hipStream_t>(stream);
-  float* RT = reinterpret_cast<float*>(ws);
-  if (!prep_rt<float>(R, ldr, KT_F32, RT, 1, d, st)) return fail(KT_ERR_DEVICE, "prep_rt launch failed");
+  // C [M][N] = A B^T, contraction over d; 64 x 64 tiles while 128 x 128 ones would leave CUs idle.  R and (side 1) W are read as
+  // they lie where their rows are 16-byte aligned and the result does not go over them, transposed into the workspace first where not.
   ProfScope prof(5, st);
-  // C [M][N] = A B^T, contraction over d; 64 x 64 tiles while 128 x 128 ones would leave CUs idle
-  auto product = [&](const float* A, int64_t lda, int64_t M, const float* B, int64_t ldb, int64_t N) -> bool {
+  const size_t out_bytes = ((side == 0 ? k : d) - 1) * ldo * 4 + wcols * 4;
+  const bool r_here = f32_in_place(R, ldr) && !overlap(Wout, out_bytes, R, ((d - 1) * ldr + d) * 4);
+  const bool w_here = f32_in_place(W, ldw) && !overlap(Wout, out_bytes, W, ((d - 1) * ldw + wcols) * 4);
+  float* RT = reinterpret_cast<float*>(ws);
+  if (!r_here && !prep_rt<float>(R, ldr, KT_F32, RT, 1, d, st)) return fail(KT_ERR_DEVICE, "prep_rt launch failed");
+  auto product = [&](auto atn_c, auto btn_c, const float* A, int64_t lda, int64_t M, const float* B, int64_t ldb, int64_t N) -> bool {
     auto go = [&](auto tile_tag) -> bool {
       using TL = decltype(tile_tag);
       EpiStore<TL> e;
       e.C = Wout; e.ldc = ldo; e.batch_stride = 0; e.split_stride = 0; e.M = (int)M; e.N = (int)N;
-      return launch_gemm<TL>(A, lda, 0, (int)M, B, ldb, 0, (int)N, d, 0, 1, e, st);
+      return launch_gemm<TL, EpiStore<TL>, decltype(atn_c)::value, decltype(btn_c)::value>(A, lda, 0, (int)M, B, ldb, 0, (int)N, d, 0, 1, e, st,
+                                                                                          0, 0, 0, (int)d);
     };
     return use_small_f32(ceil_div(M, TF::BM) * ceil_div(N, TF::BN)) ? go(TF_64{}) : go(TF{});
   };
-  if (side == 0) {  // Wout [k][d] = W R = W (R^T)^T
-    if (!product(W, ldw, k, RT, d, d))
+  const std::true_type yes;
+  const std::false_type no;
+  if (side == 0) {  // Wout [k][d] = W R
+    if (!(r_here ? product(no, yes, W, ldw, k, R, ldr, d) : product(no, no, W, ldw, k, RT, d, d)))
       return fail(KT_ERR_DEVICE, "fusion GEMM launch failed");
-  } else {          // Wout [d][k] = R^T W = R^T (W^T)^T
+  } else {          // Wout [d][k] = R^T W
     float* Wt = reinterpret_cast<float*>(ws + rt_bytes);
-    hipLaunchKernelGGL(transpose_f32_kernel, dim3((unsigned)ceil_div(k, 32), (unsigned)ceil_div(d, 32)), dim3(256),
-                       0, st, W, ldw, Wt, d, (int)d, (int)k);
-    if (!launch_ok()) return fail(KT_ERR_DEVICE, "weight transpose launch failed");
-    if (!product(RT, d, d, Wt, d, k))
+    if (!w_here) {
+      hipLaunchKernelGGL(transpose_f32_kernel, dim3((unsigned)ceil_div(k, 32), (unsigned)ceil_div(d, 32)), dim3(256),
+                         0, st, W, ldw, Wt, d, (int)d, (int)k);
+      if (!launch_ok()) return fail(KT_ERR_DEVICE, "weight transpose launch failed");
+    }
+    if (!(r_here && w_here ? product(yes, yes, R, ldr, d, W, ldw, k)
+          : r_here         ? product(yes, no, R, ldr, d, Wt, d, k)
+          : w_here         ? product(no, yes, RT, d, d, W, ldw, k)
+                           : product(no, no, RT, d, d, Wt, d, k)))
       return fail(KT_ERR_DEVICE, "fusion GEMM launch failed");
   }
   return KT_OK;

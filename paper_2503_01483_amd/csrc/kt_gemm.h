@@ -310,7 +310,15 @@ constexpr int fragment_read_slot(int r, int base, int spacing) {
 // pieces of a row are XOR-swizzled with 2 (row % 4) + (row / 8) % 2, which puts those eight into
 // different banks.  Rows k >= k_valid are not read (the last valid row is read instead; the other
 // operand is zero there).
-template <class TL, bool ATN, bool SWAP>
+//
+// ATN / BTN in fp32: A (B) is given with K as its row index, in the order of the rows: R, W and X are read as they lie in
+// memory and no launch writes a transposed copy of them first.  A stage is 32 tile rows of BM (BN) values; a fragment is four
+// 4-byte LDS reads at rows 4 q .. 4 q + 3 (the fp32 matrix instruction is slow enough to hide them), the 64-byte pieces of a
+// row XOR-swizzled with (row / 4) % 4, which puts the four lane quarters into different banks.  Columns beyond M (N) are read
+// from the last four valid ones, so M (N) is a multiple of 4; rows of A beyond k_valid as above, B has all of its rows.
+// With copies / in place, us: kt_fuse_rotation, side 1, d = 256, k = 4000: 19.4 / 11.5, d = 1024, k = 1000: 40.5 / 25.7,
+// d = 3072, k = 9000: 1312 / 1240; fp32 fake-quant, d = 1024, 16 tokens: 30.2 / 25.6.
+template <class TL, bool ATN, bool BTN, bool SWAP>
 __device__ __forceinline__ void gemm_mainloop(const typename TL::T* __restrict__ A, int64_t lda,
                                               int M, int m0,
                                               const typename TL::T* __restrict__ B, int64_t ldb,
@@ -320,7 +328,9 @@ __device__ __forceinline__ void gemm_mainloop(const typename TL::T* __restrict__
                                               floatx4 (&acc)[TL::MB][TL::NB], char* lds, int k_valid
                                               KT_STAMP_PARAM) {
   using T = typename TL::T;
-  static_assert(!ATN || (sizeof(T) == 2 && TL::BM == 256 && TL::NT == 256), "ATN: bf16, 256 tile rows, 4 waves");
+  constexpr bool F32 = sizeof(T) == 4;
+  static_assert(!ATN || F32 || (TL::BM == 256 && TL::NT == 256), "ATN in bf16: 256 tile rows, 4 waves");
+  static_assert(!BTN || F32, "BTN: fp32");
   constexpr int EPC = 16 / (int)sizeof(T);  // elements per 16-byte chunk
   constexpr int MB = TL::MB, NB = TL::NB, SLOTS = MB * NB, NFRAG = MB + NB;
   constexpr int A_LD = TL::A_LD, B_LD = TL::B_LD, NLD = A_LD + B_LD;
@@ -341,16 +351,23 @@ __device__ __forceinline__ void gemm_mainloop(const typename TL::T* __restrict__
   // global addressing: uniform 64-bit base + 32-bit byte offsets.  Load i of a thread fills 16 bytes at
   // WAVE_LD i + 16 tid of a stage: row (NT / 8) i + tid / 8, chunk position tid % 8
   const char* Ab = reinterpret_cast<const char*>(ATN ? A + m0 : A + (int64_t)m0 * lda);
-  const char* Bb = reinterpret_cast<const char*>(B + (int64_t)n0 * ldb);
+  const char* Bb = reinterpret_cast<const char*>(BTN ? B + n0 : B + (int64_t)n0 * ldb);
   uint32_t og[NLD];
   static_assert(TL::NT / 8 % 16 == 0, "swizzle key must not change between the loads of a thread");
   const int chunk = (tid & 7) ^ swizzle_key(tid >> 3);
   // ATN: row 8 i + 2 wave + lane / 32, 16-byte position lane % 32; tile row pr of a slab holds position pr of its
   // 64-token group, i.e. token pr / 4 + 16 (pr % 4) of the group
-  auto atn_row = [&](int i) __attribute__((always_inline)) { return 8 * i + 2 * wave + (lane >> 5); };
-  auto atn_token = [&](int i) __attribute__((always_inline)) { return (atn_row(i) >> 2) + 16 * (atn_row(i) & 3); };
+  // (fp32: row of the stage, columns as swizzled, at most the last four of the operand)
+  auto atn_row = [&](int i) __attribute__((always_inline)) { return F32 ? (WAVE_LD * i + 16 * tid) / (TL::BM * 4) : 8 * i + 2 * wave + (lane >> 5); };
+  auto atn_token = [&](int i) __attribute__((always_inline)) { return F32 ? atn_row(i) : (atn_row(i) >> 2) + 16 * (atn_row(i) & 3); };
+  auto f32_column = [&](int row, int pos, int left) __attribute__((always_inline)) {
+    const int c = 4 * (pos ^ (((row >> 2) & 3) << 2));
+    return c < left ? c : left - 4;
+  };
   auto atn_offset = [&](int i, int token) __attribute__((always_inline)) {
-    const int r = atn_row(i), piece_key = 2 * (r & 3) + ((r >> 3) & 1);
+    const int r = atn_row(i);
+    if constexpr (F32) return (uint32_t)(((int64_t)token * lda + f32_column(r, tid % (TL::BM / 4), M - m0)) * 4);
+    const int piece_key = 2 * (r & 3) + ((r >> 3) & 1);
     return (uint32_t)(((int64_t)token * lda + ((lane & 31) ^ (2 * piece_key)) * EPC) * (int64_t)sizeof(T));
   };
 #pragma unroll
@@ -365,18 +382,24 @@ __device__ __forceinline__ void gemm_mainloop(const typename TL::T* __restrict__
   }
 #pragma unroll
   for (int i = 0; i < B_LD; ++i) {
-    int row = i * (TL::NT / 8) + (tid >> 3);
-    row = (n0 + row < N) ? row : (N - 1 - n0);
-    og[A_LD + i] = (uint32_t)(((int64_t)row * ldb + chunk * EPC) * (int64_t)sizeof(T));
+    if constexpr (BTN) {
+      const int row = (WAVE_LD * i + 16 * tid) / (TL::BN * 4);
+      og[A_LD + i] = (uint32_t)(((int64_t)row * ldb + f32_column(row, tid % (TL::BN / 4), N - n0)) * 4);
+    } else {
+      int row = i * (TL::NT / 8) + (tid >> 3);
+      row = (n0 + row < N) ? row : (N - 1 - n0);
+      og[A_LD + i] = (uint32_t)(((int64_t)row * ldb + chunk * EPC) * (int64_t)sizeof(T));
+    }
   }
 
   // The slabs to request next (A, B) and where they start inside a row: uniform values, advanced slab by slab; past
   // the last one: the last one again.
   int req_a = slab0, req_b = slab0, in_block_a = slab0 % slabs_per_block, in_block_b = in_block_a;
   const int last_slab = slab0 + k_slabs - 1;
-  const char* an = Ab + (ATN ? (int64_t)slab0 * 64 * lda * (int64_t)sizeof(T)
+  const char* an = Ab + (ATN ? (int64_t)slab0 * TL::BK * lda * (int64_t)sizeof(T)
                              : (slab0 / slabs_per_block) * block_bytes_a + (int64_t)in_block_a * kRowBytes);
-  const char* bn = Bb + (slab0 / slabs_per_block) * block_bytes_b + (int64_t)in_block_b * kRowBytes;
+  const char* bn = Bb + (BTN ? (int64_t)slab0 * TL::BK * ldb * (int64_t)sizeof(T)
+                             : (slab0 / slabs_per_block) * block_bytes_b + (int64_t)in_block_b * kRowBytes);
   const int64_t a_wrap = block_bytes_a - (int64_t)(slabs_per_block - 1) * kRowBytes;
   const int64_t b_wrap = block_bytes_b - (int64_t)(slabs_per_block - 1) * kRowBytes;
   sgprx4 rsrc_a, rsrc_b;
@@ -384,9 +407,9 @@ __device__ __forceinline__ void gemm_mainloop(const typename TL::T* __restrict__
   auto locate_a = [&]() __attribute__((always_inline)) {
     const char* a0 = an;
     if constexpr (ATN) {
-      const int grp0 = req_a * 64;
-      if (grp0 + 64 > k_valid) {  // the last, partial group (and a group of padding behind it): re-read the last valid token
-        const int base = grp0 < k_valid ? grp0 : (k_valid - 1) & ~63;
+      const int grp0 = req_a * TL::BK;
+      if (grp0 + TL::BK > k_valid) {  // the last, partial group (and groups of padding behind it): re-read the last valid token
+        const int base = grp0 < k_valid ? grp0 : (k_valid - 1) & ~(TL::BK - 1);
         a0 = Ab + (int64_t)base * lda * (int64_t)sizeof(T);
         const int last = k_valid - 1 - base;  // >= 0: the group starts inside the operand
 #pragma unroll
@@ -400,7 +423,7 @@ __device__ __forceinline__ void gemm_mainloop(const typename TL::T* __restrict__
     if (req_a < last_slab) {
       ++req_a;
       if constexpr (ATN) {
-        an += (int64_t)64 * lda * (int64_t)sizeof(T);
+        an += (int64_t)TL::BK * lda * (int64_t)sizeof(T);
       } else {
         const bool wrap = ++in_block_a == slabs_per_block;
         if (wrap) in_block_a = 0;
@@ -412,9 +435,13 @@ __device__ __forceinline__ void gemm_mainloop(const typename TL::T* __restrict__
     rsrc_b = raw_buffer(bn);
     if (req_b < last_slab) {
       ++req_b;
-      const bool wrap = ++in_block_b == slabs_per_block;
-      if (wrap) in_block_b = 0;
-      bn += wrap ? b_wrap : (int64_t)kRowBytes;
+      if constexpr (BTN) {
+        bn += (int64_t)TL::BK * ldb * (int64_t)sizeof(T);
+      } else {
+        const bool wrap = ++in_block_b == slabs_per_block;
+        if (wrap) in_block_b = 0;
+        bn += wrap ? b_wrap : (int64_t)kRowBytes;
+      }
     }
   };
 
@@ -433,13 +460,25 @@ __device__ __forceinline__ void gemm_mainloop(const typename TL::T* __restrict__
     fa_s[h] = (f.wm * TL::WTM + f.l16) * kRowBytes + coff;
     fb_now[h] = fb_s[h] = B_BASE + (f.wn * TL::WTN + f.l16) * kRowBytes + coff;
   }
-  // ATN: rows 8 q + l16 / 4 (+4), 32-byte piece wm WTM / 16 + block, column 4 (l16 % 4) of it
-  int ft[ATN ? MB : 1];
+  // ATN: rows 8 q + l16 / 4 (+4), 32-byte piece wm WTM / 16 + block, column 4 (l16 % 4) of it; fp32: rows 4 q .. + 3 (and 16 h),
+  // 64-byte piece wm WTM / 16 + block, column l16 of it
+  int ft[ATN ? MB : 1], fbt[BTN ? NB : 1];
   if constexpr (ATN) {
 #pragma unroll
     for (int i = 0; i < MB; ++i)
-      ft[i] = (8 * f.q + (f.l16 >> 2)) * 512 + (((f.wm * TL::WTM / 16 + i) ^ (2 * (f.l16 >> 2) + (f.q & 1))) << 5) + 8 * (f.l16 & 3);
+      ft[i] = F32 ? 4 * f.q * (TL::BM * 4) + (((f.wm * TL::WTM / 16 + i) ^ f.q) << 6) + 4 * f.l16
+                  : (8 * f.q + (f.l16 >> 2)) * 512 + (((f.wm * TL::WTM / 16 + i) ^ (2 * (f.l16 >> 2) + (f.q & 1))) << 5) + 8 * (f.l16 & 3);
   }
+  if constexpr (BTN) {
+#pragma unroll
+    for (int i = 0; i < NB; ++i) fbt[i] = B_BASE + 4 * f.q * (TL::BN * 4) + (((f.wn * TL::WTN / 16 + i) ^ f.q) << 6) + 4 * f.l16;
+  }
+  auto read_rows = [&](int addr, auto pitch_c) __attribute__((always_inline)) {
+    constexpr int pitch = decltype(pitch_c)::value;
+    const floatx4 v = {*reinterpret_cast<const float*>(lds + addr), *reinterpret_cast<const float*>(lds + addr + pitch),
+                       *reinterpret_cast<const float*>(lds + addr + 2 * pitch), *reinterpret_cast<const float*>(lds + addr + 3 * pitch)};
+    return __builtin_bit_cast(intx4, v);
+  };
 
   intx4 fra[MB], frb[2][NB];  // MFMA fragments
 
@@ -455,10 +494,13 @@ __device__ __forceinline__ void gemm_mainloop(const typename TL::T* __restrict__
   auto fread = [&](auto r_c, auto stage_c, auto h_c) __attribute__((always_inline)) {
     constexpr int r = decltype(r_c)::value, stage = decltype(stage_c)::value, h = decltype(h_c)::value;
     if constexpr (r < NB) {
-      frb[h][r] = *reinterpret_cast<const intx4*>(lds + fb_now[h] + r * 16 * kRowBytes);
+      if constexpr (BTN) frb[h][r] = read_rows(fbt[r] + b_read + h * 16 * TL::BN * 4, std::integral_constant<int, TL::BN * 4>{});
+      else frb[h][r] = *reinterpret_cast<const intx4*>(lds + fb_now[h] + r * 16 * kRowBytes);
     } else {
       constexpr int i = r - NB, off = stage * TL::A_BYTES;
-      if constexpr (ATN)
+      if constexpr (ATN && F32)
+        fra[i] = read_rows(ft[i] + off + h * 16 * TL::BM * 4, std::integral_constant<int, TL::BM * 4>{});
+      else if constexpr (ATN)
         fra[i] = read_tr_operand(lds, ft[i] + off + h * 32 * 512, ft[i] + off + h * 32 * 512 + 4 * 512);
       else
         fra[i] = *reinterpret_cast<const intx4*>(lds + fa_s[h] + off + i * 16 * kRowBytes);
@@ -574,7 +616,7 @@ __device__ __forceinline__ bool tile_of_block(const GemmShape& g, int& tm, int& 
   return true;
 }
 
-template <class TL, class Epi, bool ATN = false>
+template <class TL, class Epi, bool ATN = false, bool BTN = false>
 __global__ __launch_bounds__(TL::NT) void gemm_nt_kernel(GemmShape g, Epi epi) {
   extern __shared__ __align__(16) char lds[];
   using T = typename TL::T;
@@ -598,7 +640,7 @@ __global__ __launch_bounds__(TL::NT) void gemm_nt_kernel(GemmShape g, Epi epi) {
 
   const T* A = static_cast<const T*>(g.A) + (int64_t)batch * g.batch_stride_a;
   const T* B = static_cast<const T*>(g.B) + (int64_t)batch * g.batch_stride_b;
-  gemm_mainloop<TL, ATN, Epi::kSwap>(A, g.lda, g.M, m0, B, g.ldb, g.N, n0, slab0, slabs, g.slabs_per_block,
+  gemm_mainloop<TL, ATN, BTN, Epi::kSwap>(A, g.lda, g.M, m0, B, g.ldb, g.N, n0, slab0, slabs, g.slabs_per_block,
                          g.block_bytes_a, g.block_bytes_b, acc, lds, g.k_valid KT_STAMP_ARG);
   settle_all<TL>(acc);
   KT_STAMP(g, 2);

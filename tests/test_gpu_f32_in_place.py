@@ -1,0 +1,67 @@
+"""fp32 products that read R and W as they lie (K as the row index of the tile) against a 64-bit product: edges of the 64 and
+128 tiles on both sides, wide leading dimensions, and the copies that unaligned rows and a result over an operand still take."""
+import pytest
+import torch
+
+import paper_2503_01483_amd as kt
+
+pytestmark = pytest.mark.gpu
+
+
+def _matrix(rows, cols, ld, seed, offset=0):
+    g = torch.Generator().manual_seed(seed)
+    full = torch.randn(rows * ld + offset, generator=g, dtype=torch.float32).cuda()
+    return full[offset:].as_strided((rows, cols), (ld, 1))
+
+
+def _bound(a, b):
+    # each sum of K products errs by at most K 2^-24 |a| |b| (and one rounding); in practice by sqrt(K)
+    return (a.shape[1] * 2.0 ** -24) * (a.abs() @ b.abs()) + 1e-30
+
+
+@pytest.mark.parametrize("side", [0, 1])
+@pytest.mark.parametrize("k,d,pad,offset", [(4, 128, 0, 0), (60, 128, 4, 0), (68, 256, 0, 0), (132, 384, 8, 0), (1000, 1024, 0, 0),
+                                            (2052, 2048, 4, 0), (132, 256, 4, 1), (4, 128, 0, 3)])
+def test_fuse_reads_the_operands_in_place(side, k, d, pad, offset):
+    shape = (k, d) if side == 0 else (d, k)
+    W = _matrix(*shape, shape[1] + pad, 1, offset if side == 1 else 0)
+    R = _matrix(d, d, d + pad, 2, offset)
+    out = torch.full(shape, float("nan"), device="cuda")
+    kt.kt_fuse_rotation(W, R, side, out=out)
+    A, B = (W.double(), R.double()) if side == 0 else (R.double().T.contiguous(), W.double())
+    assert ((out.double() - A @ B).abs() <= _bound(A, B)).all()
+
+
+@pytest.mark.parametrize("side", [0, 1])
+def test_fuse_over_its_own_operand(side):
+    d = 256
+    W, R = _matrix(d, d, d, 3), _matrix(d, d, d, 4)
+    want = kt.kt_fuse_rotation(W, R, side)
+    over = R.clone()
+    kt.kt_fuse_rotation(W, over, side, out=over)
+    assert torch.equal(over, want)
+    if side == 1:
+        over = W.clone()
+        kt.kt_fuse_rotation(over, R, side, out=over)
+        assert torch.equal(over, want)
+
+
+@pytest.mark.parametrize("batch,n,d", [(1, 1, 128), (2, 65, 256), (1, 130, 384), (1, 4100, 1024)])
+def test_rotated_rows_fp32(batch, n, d):
+    X = torch.stack([_matrix(n, d, d, 10 + b) for b in range(batch)])
+    R = torch.stack([_matrix(d, d, d, 20 + b) for b in range(batch)]) / d ** 0.5
+    Y = torch.empty((batch, n, d), device="cuda")
+    kt.kt_rotate_quant_metrics(X, R, Y=Y)
+    for b in range(batch):
+        A, B = X[b].double(), R[b].double()
+        assert ((Y[b].double() - A @ B).abs() <= _bound(A, B)).all()
+    scales, codes = torch.empty((batch, n), device="cuda"), torch.empty((batch, n, d), dtype=torch.int8, device="cuda")
+    kt.kt_rotate_fakequant_int4(X, R, scales_out=scales, codes=codes)
+    given = torch.empty_like(codes)
+    kt.kt_rotate_fakequant_int4(X, R, scales_in=scales, codes=given)
+    amax = torch.empty_like(scales)
+    kt.kt_rotate_fakequant_int4(X, R, scales_out=amax)
+    # one tile's sums are in another order than the other's: a value on a rounding boundary may go either way
+    assert (codes != given).float().mean() <= 1e-4
+    torch.testing.assert_close(amax, scales, rtol=1e-5, atol=0)
+    torch.testing.assert_close(scales, Y.abs().amax(2) / 7, rtol=1e-5, atol=0)
