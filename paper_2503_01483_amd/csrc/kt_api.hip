@@ -133,6 +133,11 @@ constexpr int kNumCUs = 256;
 static inline bool use_small_f32(int64_t tiles) {
   return tiles <= kNumCUs || 33 * tiles < 32 * round_up(tiles, kNumCUs);
 }
+// go(tile) with the tile of an M x N product
+template <class Go>
+static auto with_f32_tile(int64_t M, int64_t N, int64_t batch, Go go) {
+  return use_small_f32(ceil_div(M, TF::BM) * ceil_div(N, TF::BN) * batch) ? go(TF_64{}) : go(TF{});
+}
 static inline bool small_f32_tiles(int64_t d, int64_t batch) { return use_small_f32(ceil_div(d, 128) * ceil_div(d, 128) * batch); }
 // Token-minor operands (X^T, G^T) are stored in blocks of this many tokens: within a block a
 // feature row is contiguous, blocks follow each other feature-row-set by feature-row-set, so
@@ -141,6 +146,9 @@ constexpr int64_t kTokenBlock = 4096;
 constexpr int kHadMfmaFrom = 12;  // bf16 Hadamard factors of at least this order run on the matrix cores (measured: the vector kernel wins for 4 and 8)
 constexpr int kSensBlocks = 1024;  // workgroups of the sensitivity sweeps
 constexpr int kCayleyMaxIters = 32;
+// Iterations that are a launch each; a step of usual size converges within them.  Steps, us, all iterations in one launch / the
+// first three by themselves: d = 640 168 / 165, 1152 405 / 364, 1408 663 / 563, 2432 1230 / 926, 3712 3312 / 2964, 3072 with Adam 1399 / 1259.
+constexpr int kCayleyOwnLaunches = 3;
 constexpr float kCayleyTol = 3e-7f;
 
 #ifdef KT_PHASE_STAMPS
@@ -205,7 +213,7 @@ static bool launch_features_gemm(const typename TL::T* R, int64_t ldr, bool in_p
   return launch_gemm<TL>(R, d, d * d, (int)d, X, ldx, n * ldx, (int)n, d, 0, (int)batch, e, st);
 }
 
-// The fixed point of `batch` retractions (cayley_iterate_kernel): U and B are [d][K] in the GEMM dtype.  As many workgroups per
+// Iterations kCayleyOwnLaunches, ... of `batch` retractions (cayley_iterate_kernel): U and B are [d][K] in the GEMM dtype.  As many workgroups per
 // problem as the chip holds, at most one per tile.
 template <class TL>
 static int64_t cayley_control_words(int64_t d) {
@@ -227,7 +235,7 @@ static bool launch_cayley_iterations(const typename TL::T* U0, const typename TL
   const int64_t fit = kNumCUs * (160 * 1024 / TL::LDS_BYTES);
   const unsigned wgs = (unsigned)(g.tiles_total < fit ? g.tiles_total : fit);
   hipLaunchKernelGGL(kern, dim3(wgs, (unsigned)batch), dim3(TL::NT), TL::LDS_BYTES, stream, g, epi, U0, U1, control,
-                     cayley_control_words<TL>(d));
+                     cayley_control_words<TL>(d), kCayleyOwnLaunches);
   return launch_ok();
 }
 
@@ -679,7 +687,6 @@ static bool launch_skinny(const bf16* X, int64_t ldx, const TR* R, int64_t ldr, 
 template <typename T, class TL>
 static bool launch_rows_gemm(const T* X, int64_t ldx, int64_t x_batch_stride, const T* R, int64_t ldr, bool in_place, int64_t problems,
                              int64_t rows, int64_t d, float* Y, hipStream_t st) {
-  using Small = std::conditional_t<sizeof(T) == 4, TF_64, TB_128>;
   auto go = [&](auto tile_tag) -> bool {
     using G = decltype(tile_tag);
     EpiStore<G> e;
@@ -690,12 +697,15 @@ static bool launch_rows_gemm(const T* X, int64_t ldx, int64_t x_batch_stride, co
     }
     return launch_gemm<G>(X, ldx, x_batch_stride, (int)rows, R, d, d * d, (int)d, d, 0, (int)problems, e, st);
   };
-  const int64_t tiles = ceil_div(rows, TL::BM) * ceil_div(d, TL::BN) * problems;
-  bool small;
-  if (sizeof(T) == 4) small = use_small_f32(tiles);
-  else if (TL::BN == 128) small = tiles <= kNumCUs / 2 || (tiles > kNumCUs && (tiles > 2 * kNumCUs || 6 * tiles < 5 * 2 * kNumCUs));
-  else small = tiles <= kNumCUs / 2;
-  return small ? go(Small{}) : go(TL{});
+  if constexpr (sizeof(T) == 4) {
+    return with_f32_tile(rows, d, problems, go);
+  } else {
+    const int64_t tiles = ceil_div(rows, TL::BM) * ceil_div(d, TL::BN) * problems;
+    bool small;
+    if (TL::BN == 128) small = tiles <= kNumCUs / 2 || (tiles > kNumCUs && (tiles > 2 * kNumCUs || 6 * tiles < 5 * 2 * kNumCUs));
+    else small = tiles <= kNumCUs / 2;
+    return small ? go(TB_128{}) : go(TL{});
+  }
 }
 
 // ------------------------------------------------------------------ fake-quant ----
@@ -848,14 +858,26 @@ static kt_status cayley_run(const CayleyPlan& p, char* ws, float* R, const float
   const bool late_control = control_words * 4 > (int64_t)p.g2_blocks * 8;
   unsigned* control = reinterpret_cast<unsigned*>(ws + (late_control ? p.o_sq : p.o_g2));
   const int ncontrol = late_control ? 0 : (int)control_words;
-  auto iterations = [&](auto tile_tag, const auto* U0, const auto* U1, const auto* B, int64_t K) -> bool {
+  auto iterations = [&](auto first_tag, auto tile_tag, auto* U0, auto* U1, const auto* B, int64_t K) -> bool {
+    auto epilogue = [&](auto tag) {
+      using TL = decltype(tag);
+      EpiCayleyIter<TL> e;
+      e.Rt = Rt; e.Zt = Zt; e.Unew = nullptr; e.Usplit = nullptr; e.delta = delta;
+      e.d = D; e.it = 0; e.max_iters = kCayleyMaxIters; e.tol = kCayleyTol;
+      e.bscale = adam ? adam->scal : nullptr;
+      return e;
+    };
+    for (int it = 0; it < kCayleyOwnLaunches; ++it) {
+      auto e = epilogue(first_tag);
+      auto *from = it & 1 ? U1 : U0, *to = it & 1 ? U0 : U1;
+      e.it = it;
+      if constexpr (sizeof(*B) == 2) e.Usplit = to;
+      else e.Unew = to;
+      if (!launch_gemm<decltype(first_tag)>(from, K, d * K, D, B, K, d * K, D, K, 0, (int)batch, e, st)) return false;
+    }
     using TL = decltype(tile_tag);
-    EpiCayleyIter<TL> e;
-    e.Rt = Rt; e.Zt = Zt; e.Unew = nullptr; e.Usplit = nullptr; e.delta = delta;
-    e.d = D; e.it = 0; e.max_iters = kCayleyMaxIters; e.tol = kCayleyTol;
-    e.bscale = adam ? adam->scal : nullptr;
     if (late_control) hipLaunchKernelGGL(fill_u32_kernel, dim3(64), dim3(256), 0, st, control, batch * control_words, 0u);
-    return launch_cayley_iterations<TL>(U0, U1, B, K, d, batch, e, control, st);
+    return launch_cayley_iterations<TL>(U0, U1, B, K, d, batch, epilogue(tile_tag), control, st);
   };
 
   if (p.split) {
@@ -891,7 +913,7 @@ static kt_status cayley_run(const CayleyPlan& p, char* ws, float* R, const float
       // cross terms come out whichever operand carries which layout
       if (!product(Bs, Us[0], adam->M, 0.5f)) return fail(KT_ERR_DEVICE, "momentum projection GEMM launch failed");
     }
-    const bool launched = big ? iterations(TB_BIG{}, Us[0], Us[1], Bs, 3 * d) : iterations(TB_128{}, Us[0], Us[1], Bs, 3 * d);
+    const bool launched = big ? iterations(TB_BIG{}, TB_BIG{}, Us[0], Us[1], Bs, 3 * d) : iterations(TB_128{}, TB_128{}, Us[0], Us[1], Bs, 3 * d);
     if (!launched) return fail(KT_ERR_DEVICE, "Cayley iteration launch failed");
   } else {
   auto product = [&](const float* A, const float* B, float* C) -> bool {  // C = A B^T
@@ -901,7 +923,7 @@ static kt_status cayley_run(const CayleyPlan& p, char* ws, float* R, const float
       e.C = C; e.ldc = d; e.batch_stride = dd; e.split_stride = 0; e.M = D; e.N = D;
       return launch_gemm<TL>(A, d, dd, D, B, d, dd, D, d, 0, (int)batch, e, st);
     };
-    return small ? go(TF_64{}) : go(TF{});
+    return with_f32_tile(d, d, batch, go);
   };
   if (!product(G, R, Mm)) return fail(KT_ERR_DEVICE, "dR R^T GEMM launch failed");
   hipLaunchKernelGGL(cayley_setup_kernel, dim3(D / 32, D / 32, (unsigned)batch), dim3(256), 0, st, Mm, R,
@@ -915,8 +937,9 @@ static kt_status cayley_run(const CayleyPlan& p, char* ws, float* R, const float
     // M <- S R = S (Rt)^T
     if (!product(Bm, Rt, adam->M)) return fail(KT_ERR_DEVICE, "momentum projection GEMM launch failed");
   }
-  // fixed point in transposed space: Zt <- Rt - U Bm^T, U <- Rt + Zt; delta[it] collects max |Zt_new - Zt_old|
-  const bool launched = small ? iterations(TF_64{}, U[0], U[1], Bm, d) : iterations(TF{}, U[0], U[1], Bm, d);
+  const bool launched = with_f32_tile(d, d, batch, [&](auto first) {
+    return small ? iterations(first, TF_64{}, U[0], U[1], Bm, d) : iterations(first, TF{}, U[0], U[1], Bm, d);
+  });
   if (!launched) return fail(KT_ERR_DEVICE, "Cayley iteration launch failed");
   }
   hipLaunchKernelGGL(cayley_finish_kernel, dim3(D / 32, D / 32, (unsigned)batch), dim3(256), 0, st, Zt, D,
@@ -932,7 +955,7 @@ static kt_status cayley_run(const CayleyPlan& p, char* ws, float* R, const float
       e.err = reinterpret_cast<unsigned*>(ortho_err); e.d = D;
       return launch_gemm<TL>(Zt, d, dd, D, Zt, d, dd, D, d, 0, (int)batch, e, st);
     };
-    if (!(small ? off_diagonal(TF_64{}) : off_diagonal(TF{})))
+    if (!with_f32_tile(d, d, batch, off_diagonal))
       return fail(KT_ERR_DEVICE, "orthogonality GEMM launch failed");
     hipLaunchKernelGGL(ortho_diag_kernel, dim3(D, (unsigned)batch), dim3(256), 0, st, Zt, D,
                        reinterpret_cast<unsigned*>(ortho_err));
@@ -1461,7 +1484,7 @@ kt_status kt_fuse_rotation(const float* W, int64_t ldw, const float* R, int64_t 
       return launch_gemm<TL, EpiStore<TL>, decltype(atn_c)::value, decltype(btn_c)::value>(A, lda, 0, (int)M, B, ldb, 0, (int)N, d, 0, 1, e, st,
                                                                                           0, 0, 0, (int)d);
     };
-    return use_small_f32(ceil_div(M, TF::BM) * ceil_div(N, TF::BN)) ? go(TF_64{}) : go(TF{});
+    return with_f32_tile(M, N, 1, go);
   };
   const std::true_type yes;
   const std::false_type no;

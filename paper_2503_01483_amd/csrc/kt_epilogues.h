@@ -279,6 +279,22 @@ __device__ __forceinline__ unsigned wave_umax(unsigned v) {
   return v;
 }
 
+// *word = max(*word, v over the four waves of the workgroup); the LDS of the main loop is free behind the first barrier.  One atomic a
+// workgroup, and none where the word is already as large: all of them go to one address and take it about 10 ns each (256
+// workgroups of a 512 x 512 product, one atomic a wave: 11 of 20 us).
+__device__ __forceinline__ void workgroup_umax(unsigned v, unsigned* word) {
+  extern __shared__ __align__(16) char lds[];
+  unsigned* sh = reinterpret_cast<unsigned*>(lds);
+  v = wave_umax(v);
+  __syncthreads();
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    v = umax(umax(sh[0], sh[1]), umax(sh[2], sh[3]));
+    if (v > __hip_atomic_load(word, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)) atomicMax(word, v);
+  }
+}
+
 // ---- Cayley fixed point, in transposed space ---------------------------------------
 // acc = U_k * B^T.  Zt_new = Rt - acc;  U_{k+1} = Rt + Zt_new;
 // delta[it] = max |Zt_new - Zt_old| (bit pattern of a non-negative float, max is
@@ -318,7 +334,8 @@ __device__ __forceinline__ bool cayley_converged(const unsigned* dl, int k, floa
 }
 
 // Unew is written as fp32, or (Usplit != null) as the [hi | hi | lo] bf16 operand of the
-// three-term bf16 GEMM that runs the next iteration.  (cayley_iterate_kernel sets `it` and the two targets.)
+// three-term bf16 GEMM that runs the next iteration.  As the epilogue of a launch of its own it returns at once when iteration
+// it - 1 or an earlier one has converged.  (cayley_iterate_kernel sets `it` and the two targets.)
 template <class TL>
 struct EpiCayleyIter {
   const float* Rt;
@@ -330,6 +347,12 @@ struct EpiCayleyIter {
   float tol;
   const float* bscale = nullptr;  // acc is scaled by bscale[4 * batch + 3] when given (Cayley Adam)
   static constexpr bool kSwap = true;  // four consecutive columns of a row per lane: 16-byte accesses
+  __device__ __forceinline__ bool skip(int batch) const {
+    if (it == 0 || !cayley_converged(delta + (int64_t)batch * max_iters, it - 1, tol)) return false;
+    // a zero change counts as converged: later launches return too
+    if (blockIdx.x == 0 && threadIdx.x == 0) delta[(int64_t)batch * max_iters + it] = 0u;
+    return true;
+  }
   __device__ __forceinline__ void operator()(floatx4 (&acc)[TL::MB][TL::NB], int batch, int,
                                              int, int, int m0, int n0) const {
     const Frag<TL> f;
@@ -370,18 +393,17 @@ struct EpiCayleyIter {
           }
         }
       }
-    dmax = wave_umax(dmax);
-    if (f.lane == 0) atomicMax(&delta[(int64_t)batch * max_iters + it], dmax);
+    workgroup_umax(dmax, &delta[(int64_t)batch * max_iters + it]);
   }
 };
 
-// ---- the whole fixed point in one launch ---------------------------------------------------
+// ---- the later iterations in one launch ------------------------------------------------------
 // Control words of one problem, all zero at the start: done[k] = tiles of iteration k that are complete, claim[t] = how many
 // iterations of tile t have been taken.
 constexpr int kCayleyControlWords = 64;  // done[0 .. 31], stop at 32; claim[] behind them
 
-// Iterations k = 0, 1, ... of  Zt <- Rt - U_k B^T, U_k+1 = Rt + Zt  until they converge, with the dependency of each on all
-// tiles of the one before inside the launch.  grid = (workgroups, problems); a workgroup owns the tiles w, w + gridDim.x, ...
+// Iterations k = it0, it0 + 1, ... of  Zt <- Rt - U_k B^T, U_k+1 = Rt + Zt  until they converge, with the dependency of each on
+// all tiles of the one before inside the launch.  grid = (workgroups, problems); a workgroup owns the tiles w, w + gridDim.x, ...
 //
 // No workgroup relies on another one being resident: a tile of an iteration is taken by raising claim[t]; a workgroup takes
 // its own ones as the iteration opens, and while it waits for the others it takes whatever nobody has taken.  So every tile
@@ -392,12 +414,14 @@ constexpr int kCayleyControlWords = 64;  // done[0 .. 31], stop at 32; claim[] b
 // acquired at that scope behind the wait; done[], claim[] and the changes are atomics.
 //
 // Why one launch: the host cannot know when the iteration has converged, so a launch per iteration means all 32 of them, and one
-// that only finds the convergence flag set costs 2 to 5 us.
+// that only finds the convergence flag set costs 2 to 5 us.  Why not for the first ones: a release and an acquire per tile write
+// back and drop an XCD's L2 while other workgroups work from it.  Retractions of three iterations, us, all in this launch / the
+// first three by themselves: see kCayleyOwnLaunches.
 constexpr long long kCayleyWaitTicks = 20ll * 100000000;  // 20 s of the 100 MHz counter
 
 template <class TL>
 __global__ __launch_bounds__(TL::NT) void cayley_iterate_kernel(GemmShape g, EpiCayleyIter<TL> epi, const typename TL::T* U0,
-                                                                const typename TL::T* U1, unsigned* control, int64_t control_stride) {
+                                                                const typename TL::T* U1, unsigned* control, int64_t control_stride, int it0) {
   extern __shared__ __align__(16) char lds[];
   using T = typename TL::T;
   const int batch = blockIdx.y, tiles = g.tiles_total;
@@ -411,12 +435,13 @@ __global__ __launch_bounds__(TL::NT) void cayley_iterate_kernel(GemmShape g, Epi
     return (unsigned)__builtin_amdgcn_readfirstlane((int)__hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
   };
 
-  int it = 0, own = blockIdx.x;  // wave 0: the open iteration, the next of this workgroup's tiles in it
+  if (cayley_converged_now(delta, it0 - 1, epi.tol)) return;
+  int it = it0, own = blockIdx.x;  // wave 0: the open iteration, the next of this workgroup's tiles in it
   bool looked = false;           // ... has just found a tile of somebody else's: look for the next one at once
   // tile t of iteration `it`, if nobody has it (wave 0)
   auto take = [&](int t) __attribute__((always_inline)) {
     int got = 0;
-    if (threadIdx.x == 0) got = atomicCAS(claim + t, (unsigned)it, (unsigned)it + 1) == (unsigned)it;
+    if (threadIdx.x == 0) got = atomicCAS(claim + t, (unsigned)(it - it0), (unsigned)(it - it0) + 1) == (unsigned)(it - it0);
     return __builtin_amdgcn_readfirstlane(got) != 0;
   };
   // the next tile for this workgroup, -1 when there is none left (wave 0)
@@ -440,7 +465,7 @@ __global__ __launch_bounds__(TL::NT) void cayley_iterate_kernel(GemmShape g, Epi
           }
           int mine = -1;
           for (int t = threadIdx.x; t < tiles; t += 64)
-            if (mine < 0 && __hip_atomic_load(claim + t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)it) mine = t;
+            if (mine < 0 && __hip_atomic_load(claim + t, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == (unsigned)(it - it0)) mine = t;
           const unsigned long long found = __ballot(mine >= 0);
           if (found) {
             const int t = __builtin_amdgcn_readlane(mine, __builtin_ctzll(found));
@@ -481,8 +506,8 @@ __global__ __launch_bounds__(TL::NT) void cayley_iterate_kernel(GemmShape g, Epi
 #pragma unroll
       for (int nb = 0; nb < TL::NB; ++nb) acc[mb][nb] = floatx4{0.f, 0.f, 0.f, 0.f};
     settle_all<TL>(acc);
-    gemm_mainloop<TL, false, false, true>((k & 1 ? U1 : U0) + (int64_t)batch * g.batch_stride_a, g.lda, g.M, m0, B, g.ldb, g.N, n0, 0, g.slabs_total,
-                                   g.slabs_per_block, 0, 0, acc, lds, 0);
+    gemm_mainloop<TL, false, false, true>((k & 1 ? U1 : U0) + (int64_t)batch * g.batch_stride_a, g.lda, g.M, m0, B, g.ldb, g.N, n0, 0,
+                                          g.slabs_total, g.slabs_per_block, 0, 0, acc, lds, 0);
     settle_all<TL>(acc);
     EpiCayleyIter<TL> e = epi;
     e.it = k;
@@ -521,8 +546,7 @@ struct EpiOrtho : EpiBase {
           if (m < d && n < d && m != n) e = umax(e, abs_bits(acc[mb][nb][r]));
         }
       }
-    e = wave_umax(e);
-    if (f.lane == 0) atomicMax(&err[batch], e);
+    workgroup_umax(e, &err[batch]);
   }
 };
 
