@@ -133,9 +133,12 @@ constexpr int kNumCUs = 256;
 static inline bool use_small_f32(int64_t tiles) {
   return tiles <= kNumCUs || 33 * tiles < 32 * round_up(tiles, kNumCUs);
 }
-// go(tile) with the tile of an M x N product
+// go(tile) with the tile of an M x N product.  32 x 32 ones (kt_gemm32.h) up to two a CU.  us, 64 x 64 / 32 x 32 tiles: fp32
+// fake-quant, d = 1024: 16 tokens 25.4 / 14.7, 200 tokens (224 tiles of 32) 26.1 / 15.1; metrics, 600 tokens (608) 40.7 / 49.1; fp32
+// steps, d = 256 (64) 99.3 / 93.0, 512 (256) 188.7 / 172.3, 640 (400) 161.7 / 155.5, bf16 step, d = 768 (576) 215 / 229.
 template <class Go>
 static auto with_f32_tile(int64_t M, int64_t N, int64_t batch, Go go) {
+  if (ceil_div(M, 32) * ceil_div(N, 32) * batch <= 2 * kNumCUs) return go(TF_32{});
   return use_small_f32(ceil_div(M, TF::BM) * ceil_div(N, TF::BN) * batch) ? go(TF_64{}) : go(TF{});
 }
 static inline bool small_f32_tiles(int64_t d, int64_t batch) { return use_small_f32(ceil_div(d, 128) * ceil_div(d, 128) * batch); }
@@ -161,7 +164,10 @@ static bool launch_gemm(const void* A, int64_t lda, int64_t bsa, int M, const vo
                         const Epi& epi, hipStream_t stream, int64_t k_block = 0,
                         int64_t block_stride_a = 0, int64_t block_stride_b = 0, int k_valid = 0) {
   // ATN: A is [K][lda] with the M index along its rows (see gemm_mainloop); K blocking applies to B only.  BTN: B [K][ldb].
-  auto kern = gemm_nt_kernel<TL, Epi, ATN, BTN>;
+  constexpr auto kern = [] {
+    if constexpr (std::is_same_v<TL, TF_32>) return &gemm32_kernel<Epi, ATN, BTN>;
+    else return &gemm_nt_kernel<TL, Epi, ATN, BTN>;
+  }();
   constexpr int lds_bytes = TL::LDS_BYTES;
   // the kernel addresses the rows of a tile with 32-bit byte offsets from the tile's first row
   const int64_t esz = (int64_t)sizeof(typename TL::T);

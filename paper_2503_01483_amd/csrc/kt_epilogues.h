@@ -5,6 +5,7 @@
 // fixed-point iteration once it has converged).
 #pragma once
 #include "kt_gemm.h"
+#include "kt_gemm32.h"
 
 namespace kt {
 

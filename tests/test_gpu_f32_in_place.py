@@ -65,3 +65,14 @@ def test_rotated_rows_fp32(batch, n, d):
     assert (codes != given).float().mean() <= 1e-4
     torch.testing.assert_close(amax, scales, rtol=1e-5, atol=0)
     torch.testing.assert_close(scales, Y.abs().amax(2) / 7, rtol=1e-5, atol=0)
+
+
+@pytest.mark.parametrize("side", [0, 1])
+@pytest.mark.parametrize("k,d", [(4, 256), (36, 384), (132, 512), (260, 128), (508, 1024), (516, 1024), (128, 4096)])
+def test_few_tiles(side, k, d):
+    """32 x 32 tiles with K shared by four waves: one to 32 steps a wave, ragged edges, either side of two tiles a CU."""
+    W = _matrix(*((k, d) if side == 0 else (d, k)), d if side == 0 else k, 7)
+    R = _matrix(d, d, d, 8)
+    out = kt.kt_fuse_rotation(W, R, side)
+    A, B = (W.double(), R.double()) if side == 0 else (R.double().T.contiguous(), W.double())
+    assert ((out.double() - A @ B).abs() <= _bound(A, B)).all()
