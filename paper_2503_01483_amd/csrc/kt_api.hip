@@ -113,10 +113,10 @@ struct ProfScope {
 
 // ------------------------------------------------------------------ tiles ---------
 using bf16 = __bf16;
-using TB_BIG = Tile<bf16, 256, 256, 2, 2>;   // d % 256 == 0
+using TB_BIG = Tile<bf16, 256, 256, 2, 2>;
 using TB_M128 = Tile<bf16, 128, 256, 1, 4>;  // features on m, d % 256 != 0
 using TB_N128 = Tile<bf16, 256, 128, 4, 1>;  // features on n, d % 256 != 0
-using TB_128 = Tile<bf16, 128, 128, 2, 2>;   // d x d outputs, d % 256 != 0
+using TB_128 = Tile<bf16, 128, 128, 2, 2>;   // few tiles
 using TF = Tile<float, 128, 128, 2, 2>;      // fp32 path, every contraction
 using TF_64 = Tile<float, 64, 64, 2, 2>;     // fp32 path, d x d outputs of few tiles
 
@@ -275,7 +275,7 @@ struct LossGradPlan {
   int64_t tb;      // tokens per block of the token-minor copies (row length inside a block)
   int64_t nblk;    // blocks per feature row
   int P;           // moment partials per token
-  int tiles_dd;    // tiles of the d x d output GEMM
+  bool small_fwd, small_dr;  // bf16: 128 x 128 tiles in the forward product, in dR
   int slabs_per_split, split_k;
   size_t o_rt, o_part, o_coef, o_losspart, o_xt, o_gt, o_splitk, o_gstat, o_yt, total;
   int loss_blocks;
@@ -300,12 +300,47 @@ static int fused_d128_wgs(int64_t batch, int64_t n) {
   return (int)best;
 }
 
+// ---- tiles of the bf16 loss + gradient pass: 256 x 256, alone on a CU, or 128 x 128, two to a CU.
+// Time in units of one slab of K of a 256 x 256 tile (about 1 us).  Such a tile has a prologue and an epilogue of 10 slabs' time
+// with nothing beside them (8 without row moments); two 128 x 128 tiles cover each other's, but take 0.7 (dR: 0.8) of the unit for
+// half the work, one alone on its CU 0.55.  Loss + gradient, us, 256 / 128: forward d = 512, n = 6000 56.4 / 46.0; 1152, 40000 324 / 301;
+// 1408, 20000 219 / 213; 2048, 2000 95 / 73; 2048, 8000 168 / 173; 2688, 20000 567 / 598; 3712, 8000 411 / 437; dR 512, 30000 98 / 86; 1024, 16384
+// 124 / 116; 1152, 10007 111 / 102; 1152, 40000 309 / 320; 2432, 5000 164 / 159; 2688, 20000 570 / 624; 3712, 8000 410 / 457.
+static double bf16_tile_time(bool small, int64_t tiles, int64_t slabs, double ends, double pair) {
+  if (!small) return (double)ceil_div(tiles, kNumCUs) * ((double)slabs + ends);
+  const int64_t rest = tiles % (2 * kNumCUs);
+  return (pair * (double)(tiles / (2 * kNumCUs)) + (rest == 0 ? 0.0 : rest <= kNumCUs ? 0.55 : pair)) * (double)(slabs + 4);
+}
+static bool small_forward_tiles(int64_t batch, int64_t n, int64_t d) {
+  const int64_t slabs = d / TB_BIG::BK;
+  return bf16_tile_time(true, d / 128 * ceil_div(n, 128) * batch, slabs, 0, 0.7) <
+         bf16_tile_time(false, ceil_div(d, 256) * ceil_div(n, 256) * batch, slabs, 10, 0);
+}
+// dR = X^T G over `slabs` slabs of 64 tokens: tile and slabs per range of tokens, at least eight.  Every range beyond the first
+// writes and reads another d x d partial.
+static bool small_dr_tiles(int64_t batch, int64_t slabs, int64_t d, int* slabs_per_split) {
+  double least = -1.0;
+  bool best = false;
+  for (const bool small : {false, true}) {
+    const int64_t edge = small ? 128 : 256, tiles = ceil_div(d, edge) * ceil_div(d, edge) * batch;
+    const int64_t most = ceil_div(small ? 4 * kNumCUs : kNumCUs, tiles);
+    for (int64_t s = 1; s <= most && (s == 1 || slabs / s >= 8); ++s) {
+      const int64_t per = ceil_div(slabs, s);
+      if (ceil_div(slabs, per) != s) continue;
+      const double cost = bf16_tile_time(small, tiles * s, per, 8, 0.8) + (s > 1 ? 3.0 + 1.0e-6 * (double)((s + 1) * d * d * batch) : 0.0);
+      if (least < 0.0 || cost < least) { least = cost; best = small; *slabs_per_split = (int)per; }
+    }
+  }
+  return best;
+}
+
 // max_fused_wgs: no more workgroups per problem than this on the d = 128 path (a caller's smaller workspace)
 static LossGradPlan plan_loss_grad(int64_t batch, int64_t n, int64_t d, kt_dtype xdt, bool pooled = false,
                                    bool keep_y = false, int64_t max_fused_wgs = INT32_MAX) {
   LossGradPlan p;
   p.keep_y = false;
   p.o_yt = 0;
+  p.small_fwd = p.small_dr = false;
   p.fp32 = (xdt == KT_F32);
   p.esz = p.fp32 ? 4 : 2;
   p.fused = !p.fp32 && d == 128 && !pooled;  // the pooled loss needs its global statistics before the gradient
@@ -314,7 +349,7 @@ static LossGradPlan plan_loss_grad(int64_t batch, int64_t n, int64_t d, kt_dtype
     p.fused_wgs = fused_d128_wgs(batch, n);
     if (p.fused_wgs > max_fused_wgs) p.fused_wgs = (int)max_fused_wgs;
     p.ldt = p.tb = p.nblk = 0;
-    p.P = p.tiles_dd = p.slabs_per_split = p.split_k = p.loss_blocks = 0;
+    p.P = p.slabs_per_split = p.split_k = p.loss_blocks = 0;
     Carver c;
     p.o_rt = 0;
     p.o_losspart = c.take((size_t)batch * p.fused_wgs * 8);
@@ -326,26 +361,18 @@ static LossGradPlan plan_loss_grad(int64_t batch, int64_t n, int64_t d, kt_dtype
   p.ldt = round_up(n, 128);
   p.tb = p.ldt < kTokenBlock ? p.ldt : kTokenBlock;
   p.nblk = ceil_div(p.ldt, p.tb);
-  int64_t slabs;
   if (p.fp32) {
     p.P = (int)ceil_div(d, TF::BM) * TF::WGM;
     // (also where X^T G takes 64 x 64 tiles: a quarter of the splits would be sums four times as long, in fp32; d = 1024,
     // 16384 tokens: dR off by 8.8e-7 of its norm instead of 6.9e-7)
-    p.tiles_dd = (int)(ceil_div(d, TF::BM) * ceil_div(d, TF::BN));
-    slabs = p.ldt / TF::BK;
-  } else if (d % 256 == 0) {
-    p.P = (int)(d / TB_BIG::BM) * TB_BIG::WGM;
-    p.tiles_dd = (int)((d / 256) * (d / 256));
-    slabs = p.ldt / TB_BIG::BK;
+    p.slabs_per_split = choose_slabs_per_split(ceil_div(d, TF::BM) * ceil_div(d, TF::BN) * batch, p.ldt / TF::BK, 4 * kNumCUs);
+    p.split_k = (int)ceil_div(p.ldt / TF::BK, p.slabs_per_split);
   } else {
-    p.P = (int)ceil_div(d, TB_M128::BM) * TB_M128::WGM;
-    p.tiles_dd = (int)(ceil_div(d, 128) * ceil_div(d, 128));
-    slabs = p.ldt / TB_128::BK;
+    p.P = (int)(d / 128);
+    p.small_fwd = small_forward_tiles(batch, n, d);
+    p.small_dr = small_dr_tiles(batch, p.ldt / TB_BIG::BK, d, &p.slabs_per_split);
+    p.split_k = (int)ceil_div(p.ldt / TB_BIG::BK, p.slabs_per_split);
   }
-  const bool big_tiles = !p.fp32 && d % 256 == 0;
-  p.slabs_per_split = choose_slabs_per_split((int64_t)p.tiles_dd * batch, slabs,
-                                             big_tiles ? kNumCUs : 4 * kNumCUs);
-  p.split_k = (int)ceil_div(slabs, p.slabs_per_split);
   p.loss_blocks = (int)ceil_div(n, 256);
   Carver c;
   p.o_rt = c.take((size_t)batch * d * d * p.esz);
@@ -353,7 +380,7 @@ static LossGradPlan plan_loss_grad(int64_t batch, int64_t n, int64_t d, kt_dtype
   p.o_coef = c.take((size_t)batch * n * 16);
   p.o_losspart = c.take((size_t)batch * p.loss_blocks * 8 * (pooled ? 4 : 1));
   p.o_gstat = c.take(pooled ? (size_t)batch * 4 * 8 : 0);
-  p.o_xt = c.take(big_tiles ? 0 : (size_t)batch * d * p.nblk * p.tb * p.esz);  // big tiles read X as it is
+  p.o_xt = c.take(p.fp32 ? (size_t)batch * d * p.nblk * p.tb * p.esz : 0);  // bf16: X as it is
   p.o_gt = c.take((size_t)batch * d * p.nblk * p.tb * p.esz);
   p.o_splitk = c.take(p.split_k > 1 ? (size_t)p.split_k * batch * d * d * 4 : 0);
   p.keep_y = keep_y;
@@ -503,7 +530,7 @@ struct PooledArgs {  // paper-literal pooled loss (kurtosis over all entries aft
   float* kappa_out;  // [batch] or null
 };
 
-template <typename T, class TFWD, class TDD>
+template <typename T>
 static kt_status run_loss_grad(const LossGradPlan& p, const void* X, int64_t ldx, const void* R,
                                int64_t ldr, kt_dtype rdt, int64_t batch, int64_t n, int64_t d,
                                float kappa_target, float* loss, float* row_kurt, float* dR,
@@ -520,21 +547,26 @@ static kt_status run_loss_grad(const LossGradPlan& p, const void* X, int64_t ldx
   // a0: R -> R^T in the GEMM dtype
   if (!prep_rt<T>(R, ldr, rdt, RT, batch, d, st)) return fail(KT_ERR_DEVICE, "prep_rt launch failed");
 
-  // a1: forward GEMM (features on m, tokens on n) with the moment epilogue; with keep_y it also writes Y
+  // go(tile) with the tile of the forward product (features on m, tokens on n)
+  auto with_forward_tile = [&](auto go) -> bool {
+    if constexpr (sizeof(T) == 4) return go(TF{});
+    else return p.small_fwd ? go(TB_128{}) : go(TB_BIG{});
+  };
+
+  // a1: forward GEMM with the moment epilogue; with keep_y it also writes Y
   const bool keep = p.keep_y && dR;
   float* YT = reinterpret_cast<float*>(ws + p.o_yt);
   {
     ProfScope prof(0, st);
-    EpiMoments<TFWD> e;
-    e.part = part; e.n_tokens = (int)n; e.d = (int)d; e.P = p.P;
-    bool ok;
-    if (keep) {
-      EpiMomentsKeep<TFWD> ek;
+    const bool ok = with_forward_tile([&](auto tile_tag) -> bool {
+      using TL = decltype(tile_tag);
+      EpiMoments<TL> e;
+      e.part = part; e.n_tokens = (int)n; e.d = (int)d; e.P = p.P;
+      if (!keep) return launch_gemm<TL>(RT, d, d * d, (int)d, Xp, ldx, n * ldx, (int)n, d, 0, (int)batch, e, st);
+      EpiMomentsKeep<TL> ek;
       ek.mom = e; ek.YT = YT; ek.ldt = p.ldt; ek.tb = p.tb; ek.batch_stride = d * p.nblk * p.tb;
-      ok = launch_gemm<TFWD>(RT, d, d * d, (int)d, Xp, ldx, n * ldx, (int)n, d, 0, (int)batch, ek, st);
-    } else {
-      ok = launch_gemm<TFWD>(RT, d, d * d, (int)d, Xp, ldx, n * ldx, (int)n, d, 0, (int)batch, e, st);
-    }
+      return launch_gemm<TL>(RT, d, d * d, (int)d, Xp, ldx, n * ldx, (int)n, d, 0, (int)batch, ek, st);
+    });
     if (!ok) return fail(KT_ERR_DEVICE, "forward GEMM launch failed");
   }
   if (pooled) {
@@ -560,21 +592,12 @@ static kt_status run_loss_grad(const LossGradPlan& p, const void* X, int64_t ldx
   if (!dR) return KT_OK;
   }
 
-  // bf16, d % 256 == 0: the last GEMM reads X as it is (transposing LDS reads); otherwise it needs a
-  // token-minor copy of X (zero padded to ldt tokens)
-  constexpr bool kXDirect = std::is_same<TDD, TB_BIG>::value;
-  if (!kXDirect) {
+  // fp32: the last GEMM needs a token-minor copy of X (zero padded to ldt tokens); bf16 reads X as it is (transposing LDS reads)
+  if constexpr (sizeof(T) == 4) {
     ProfScope prof(3, st);
-    if (sizeof(T) == 2) {
-      dim3 grid((unsigned)ceil_div(p.ldt, 128), (unsigned)(d / 64), (unsigned)batch);
-      hipLaunchKernelGGL(transpose16_kernel, grid, dim3(256), 0, st, reinterpret_cast<const uint16_t*>(Xp),
-                         ldx, n * ldx, reinterpret_cast<uint16_t*>(XT), p.tb, d * p.nblk * p.tb, (int)n,
-                         (int)p.ldt, (int)d);
-    } else {
-      dim3 grid((unsigned)(p.ldt / 64), (unsigned)ceil_div(d, 64), (unsigned)batch);
-      hipLaunchKernelGGL((transpose_kernel<T, T>), grid, dim3(256), 0, st, Xp, ldx, n * ldx, XT, p.tb,
-                         d * p.nblk * p.tb, (int)n, (int)p.ldt, (int)d, 1);
-    }
+    dim3 grid((unsigned)(p.ldt / 64), (unsigned)ceil_div(d, 64), (unsigned)batch);
+    hipLaunchKernelGGL((transpose_kernel<T, T>), grid, dim3(256), 0, st, Xp, ldx, n * ldx, XT, p.tb,
+                       d * p.nblk * p.tb, (int)n, (int)p.ldt, (int)d, 1);
     if (!launch_ok()) return fail(KT_ERR_DEVICE, "X transpose launch failed");
   }
   // a3: dL/dY token-minor, from the kept Y entry by entry or from a recomputed Y in the GEMM epilogue
@@ -587,29 +610,35 @@ static kt_status run_loss_grad(const LossGradPlan& p, const void* X, int64_t ldx
     if (!launch_ok()) return fail(KT_ERR_DEVICE, "gradient kernel launch failed");
   } else {
     ProfScope prof(1, st);
-    EpiGrad<TFWD> e;
-    e.coef = coef; e.GT = GT; e.ldt = p.ldt; e.tb = p.tb; e.batch_stride = d * p.nblk * p.tb;
-    e.n_tokens = (int)n; e.d = (int)d;
-    if (!launch_gemm<TFWD>(RT, d, d * d, (int)d, Xp, ldx, n * ldx, (int)n, d, 0, (int)batch, e, st))
+    const bool ok = with_forward_tile([&](auto tile_tag) -> bool {
+      using TL = decltype(tile_tag);
+      EpiGrad<TL> e;
+      e.coef = coef; e.GT = GT; e.ldt = p.ldt; e.tb = p.tb; e.batch_stride = d * p.nblk * p.tb;
+      e.n_tokens = (int)n; e.d = (int)d;
+      return launch_gemm<TL>(RT, d, d * d, (int)d, Xp, ldx, n * ldx, (int)n, d, 0, (int)batch, e, st);
+    });
+    if (!ok)
       return fail(KT_ERR_DEVICE, "backward recompute GEMM launch failed");
   }
   // a4: dR = X^T G, split over tokens
   {
     ProfScope prof(2, st);
-    EpiStore<TDD> e;
-    e.ldc = d; e.M = (int)d; e.N = (int)d;
-    if (p.split_k > 1) {
-      e.C = splitk; e.batch_stride = d * d; e.split_stride = batch * d * d;
-    } else {
-      e.C = dR; e.batch_stride = d * d; e.split_stride = 0;
-    }
+    auto go = [&](auto tile_tag) -> bool {
+      using TL = decltype(tile_tag);
+      EpiStore<TL> e;
+      e.C = p.split_k > 1 ? splitk : dR;
+      e.batch_stride = d * d; e.split_stride = p.split_k > 1 ? batch * d * d : 0;
+      e.ldc = d; e.M = (int)d; e.N = (int)d;
+      if constexpr (sizeof(T) == 2)
+        return launch_gemm<TL, EpiStore<TL>, true>(Xp, ldx, n * ldx, (int)d, GT, p.tb, d * p.nblk * p.tb, (int)d, p.ldt,
+                                                   p.slabs_per_split, (int)batch, e, st, p.tb, 0, d * p.tb, (int)n);
+      else
+        return launch_gemm<TL>(XT, p.tb, d * p.nblk * p.tb, (int)d, GT, p.tb, d * p.nblk * p.tb, (int)d, p.ldt,
+                               p.slabs_per_split, (int)batch, e, st, p.tb, d * p.tb, d * p.tb);
+    };
     bool ok;
-    if constexpr (kXDirect)
-      ok = launch_gemm<TDD, EpiStore<TDD>, true>(Xp, ldx, n * ldx, (int)d, GT, p.tb, d * p.nblk * p.tb, (int)d, p.ldt,
-                                                 p.slabs_per_split, (int)batch, e, st, p.tb, 0, d * p.tb, (int)n);
-    else
-      ok = launch_gemm<TDD>(XT, p.tb, d * p.nblk * p.tb, (int)d, GT, p.tb, d * p.nblk * p.tb, (int)d, p.ldt,
-                            p.slabs_per_split, (int)batch, e, st, p.tb, d * p.tb, d * p.tb);
+    if constexpr (sizeof(T) == 2) ok = p.small_dr ? go(TB_128{}) : go(TB_BIG{});
+    else ok = small_f32_tiles(d, batch) ? go(TF_64{}) : go(TF{});
     if (!ok) return fail(KT_ERR_DEVICE, "gradient GEMM launch failed");
     if (p.split_k > 1) {
       const int64_t count = batch * d * d;
@@ -1192,15 +1221,8 @@ kt_status kt_kurtosis_loss_grad(const void* X, int64_t ldx, const void* R, int64
   if (p.fused)
     return run_loss_grad_fused(p, X, ldx, R, ldr, r_dtype, batch, n, d, kappa_target, loss, row_kurt, dR,
                                ws, st);
-  if (p.fp32)
-    return small_f32_tiles(d, batch)
-               ? run_loss_grad<float, TF, TF_64>(p, X, ldx, R, ldr, r_dtype, batch, n, d, kappa_target, loss, row_kurt, dR, ws, st)
-               : run_loss_grad<float, TF, TF>(p, X, ldx, R, ldr, r_dtype, batch, n, d, kappa_target, loss, row_kurt, dR, ws, st);
-  if (d % 256 == 0)
-    return run_loss_grad<bf16, TB_BIG, TB_BIG>(p, X, ldx, R, ldr, r_dtype, batch, n, d, kappa_target,
-                                               loss, row_kurt, dR, ws, st);
-  return run_loss_grad<bf16, TB_M128, TB_128>(p, X, ldx, R, ldr, r_dtype, batch, n, d, kappa_target,
-                                              loss, row_kurt, dR, ws, st);
+  return p.fp32 ? run_loss_grad<float>(p, X, ldx, R, ldr, r_dtype, batch, n, d, kappa_target, loss, row_kurt, dR, ws, st)
+                : run_loss_grad<bf16>(p, X, ldx, R, ldr, r_dtype, batch, n, d, kappa_target, loss, row_kurt, dR, ws, st);
 }
 
 kt_status kt_pooled_kurtosis_loss_grad(const void* X, int64_t ldx, const void* R, int64_t ldr,
@@ -1225,15 +1247,8 @@ kt_status kt_pooled_kurtosis_loss_grad(const void* X, int64_t ldx, const void* R
   hipStream_t st = static_cast<hipStream_t>(stream);
   PooledArgs pa;
   pa.rms_eps = rms_eps; pa.kappa_out = kappa;
-  if (p.fp32)
-    return small_f32_tiles(d, batch)
-               ? run_loss_grad<float, TF, TF_64>(p, X, ldx, R, ldr, r_dtype, batch, n, d, kappa_target, loss, nullptr, dR, ws, st, &pa)
-               : run_loss_grad<float, TF, TF>(p, X, ldx, R, ldr, r_dtype, batch, n, d, kappa_target, loss, nullptr, dR, ws, st, &pa);
-  if (d % 256 == 0)
-    return run_loss_grad<bf16, TB_BIG, TB_BIG>(p, X, ldx, R, ldr, r_dtype, batch, n, d, kappa_target, loss,
-                                               nullptr, dR, ws, st, &pa);
-  return run_loss_grad<bf16, TB_M128, TB_128>(p, X, ldx, R, ldr, r_dtype, batch, n, d, kappa_target, loss,
-                                              nullptr, dR, ws, st, &pa);
+  return p.fp32 ? run_loss_grad<float>(p, X, ldx, R, ldr, r_dtype, batch, n, d, kappa_target, loss, nullptr, dR, ws, st, &pa)
+                : run_loss_grad<bf16>(p, X, ldx, R, ldr, r_dtype, batch, n, d, kappa_target, loss, nullptr, dR, ws, st, &pa);
 }
 
 kt_status kt_cayley_step(float* R, const float* dR, void* R_lowp, int64_t batch, int64_t d, float lr,

@@ -47,55 +47,6 @@ __global__ __launch_bounds__(256) void transpose_kernel(const Tin* __restrict__ 
   }
 }
 
-// The token-minor, token-permuted, token-blocked copy of X for 2-byte elements, with
-// 16-byte global accesses on both sides (layout as described at EpiGrad; ldo = tokens per
-// block, a multiple of 128).
-// tile = 128 rows (two token groups) x 64 cols; each thread moves four 16-byte chunks in
-// and four out.  Needs cols % 64 == 0, rows_pad % 128 == 0, ldi % 8 == 0, ldo % 8 == 0.
-// grid = (ceil(rows_pad/128), cols/64, batch)
-__global__ __launch_bounds__(256) void transpose16_kernel(const uint16_t* __restrict__ in, int64_t ldi,
-                                                          int64_t in_batch_stride,
-                                                          uint16_t* __restrict__ out, int64_t ldo,
-                                                          int64_t out_batch_stride, int rows,
-                                                          int rows_pad, int cols) {
-  constexpr int PITCH = 33;  // dwords per tile row (64 elements + 1 dword of skew)
-  __shared__ uint32_t tile[128 * PITCH];
-  const int r0 = blockIdx.x * 128, c0 = blockIdx.y * 64;
-  in += (int64_t)blockIdx.z * in_batch_stride;
-  // ldo = tokens per block; the 128-token group r0 lies in block r0 / ldo
-  out += (int64_t)blockIdx.z * out_batch_stride + (int64_t)(r0 / ldo) * cols * ldo + (r0 % ldo);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int c = threadIdx.x + i * 256;
-    const int row = c >> 3, col8 = c & 7;
-    intx4 v = {0, 0, 0, 0};
-    if (r0 + row < rows) v = *reinterpret_cast<const intx4*>(in + (int64_t)(r0 + row) * ldi + c0 + col8 * 8);
-    uint32_t* t = tile + row * PITCH + col8 * 4;
-    t[0] = (uint32_t)v[0]; t[1] = (uint32_t)v[1]; t[2] = (uint32_t)v[2]; t[3] = (uint32_t)v[3];
-  }
-  __syncthreads();
-  const uint16_t* t16 = reinterpret_cast<const uint16_t*>(tile);
-#pragma unroll
-  for (int i = 0; i < 4; ++i) {
-    const int c = threadIdx.x + i * 256;
-    const int f = c >> 4, t8 = c & 15;
-    if (r0 + t8 * 8 < rows_pad) {
-      uint32_t w[4];
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        // output position p of a 64-token group holds token (p & 3) * 16 + (p & 63) / 4 of it; p is even
-        const int p = t8 * 8 + 2 * e;
-        const uint16_t* src = t16 + ((p & 64) + ((p & 3) << 4) + ((p & 63) >> 2)) * (2 * PITCH) + f;
-        const uint32_t lo = src[0];
-        const uint32_t hi = src[16 * (2 * PITCH)];
-        w[e] = lo | (hi << 16);
-      }
-      intx4 v = {(int)w[0], (int)w[1], (int)w[2], (int)w[3]};
-      *reinterpret_cast<intx4*>(out + (int64_t)(c0 + f) * ldo + t8 * 8) = v;
-    }
-  }
-}
-
 // Row-major copy with dtype conversion: out[r*ldo + c] = in[r*ldi + c].
 template <typename Tin, typename Tout>
 __global__ __launch_bounds__(256) void convert_kernel(const Tin* __restrict__ in, int64_t ldi,

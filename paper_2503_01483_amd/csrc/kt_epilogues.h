@@ -66,8 +66,10 @@ __device__ __forceinline__ float quarter_pick(int q, float v0, float v1, float v
 // the WTM features wave-row p = tm*WGM + wm owns: the mean first, then sums about it (two passes
 // over the registers), so that a row whose mean is large against its spread loses nothing to
 // cancellation in fp32; the partials of a row are merged in fp64 (row_central_sums in kt_aux.h).
+// bf16, 64 features a wave: the two waves of a token merge theirs, so that a partial is 128 features with every tile.
 template <class TL>
 struct EpiMoments : EpiBase {
+  static constexpr bool kMerge = sizeof(typename TL::T) == 2 && TL::WTM == 64;
   static_assert(TL::MB % 4 == 0 && TL::NB % 4 == 0, "features and tokens are taken 64 at a time");
   floatx4* part;
   int n_tokens, d, P;
@@ -112,12 +114,37 @@ struct EpiMoments : EpiBase {
         }
       }
       const int token = n0 + f.wn * TL::WTN + 64 * g + f.lane;
-      const floatx4 v = {quarter_pick(f.q, mean[0], mean[1], mean[2], mean[3]),
-                         quarter_reduce4<OpAdd>(s2[0], s2[1], s2[2], s2[3]),
-                         quarter_reduce4<OpAdd>(s3[0], s3[1], s3[2], s3[3]),
-                         quarter_reduce4<OpAdd>(s4[0], s4[1], s4[2], s4[3])};
-      if (token < n_tokens) part[((int64_t)batch * P + p) * n_tokens + token] = v;
+      floatx4 v = {quarter_pick(f.q, mean[0], mean[1], mean[2], mean[3]),
+                   quarter_reduce4<OpAdd>(s2[0], s2[1], s2[2], s2[3]),
+                   quarter_reduce4<OpAdd>(s3[0], s3[1], s3[2], s3[3]),
+                   quarter_reduce4<OpAdd>(s4[0], s4[1], s4[2], s4[3])};
+      if constexpr (kMerge) {
+        static_assert(!kMerge || (TL::BM == 128 && TL::NB == 4), "two waves hold the 128 features of 64 tokens");
+        extern __shared__ __align__(16) char lds[];
+        floatx4* other = reinterpret_cast<floatx4*>(lds) + 64 * f.wn + f.lane;
+        __syncthreads();  // (the last fragments have been read)
+        if (f.wm == 1) *other = v;
+        __syncthreads();
+        if (f.wm == 1) return;
+        v = merged(v, *other, 64.0);
+      }
+      const int pp = kMerge ? tm : p;
+      if (token < n_tokens && pp < P) part[((int64_t)batch * P + pp) * n_tokens + token] = v;
     }
+  }
+  // two partials of cnt values each as one (the shift formulas of row_central_sums)
+  static __device__ __forceinline__ floatx4 merged(const floatx4& a, const floatx4& b, double cnt) {
+    const double mu = 0.5 * ((double)a[0] + (double)b[0]);
+    double m2 = 0.0, m3 = 0.0, m4 = 0.0;
+    auto add = [&](const floatx4& v) __attribute__((always_inline)) {
+      const double e = (double)v[0] - mu, e2 = e * e;
+      m2 += (double)v[1] + cnt * e2;
+      m3 += (double)v[2] + 3.0 * e * (double)v[1] + cnt * e2 * e;
+      m4 += (double)v[3] + 4.0 * e * (double)v[2] + 6.0 * e2 * (double)v[1] + cnt * e2 * e2;
+    };
+    add(a);
+    add(b);
+    return floatx4{(float)mu, (float)m2, (float)m3, (float)m4};
   }
 };
 

@@ -301,11 +301,11 @@ constexpr int fragment_read_slot(int r, int base, int spacing) {
 //   163 000 - 170 000  straight into LDS in stages of 64 bytes of K: every 128-byte line is fetched twice
 //   151 000  this form (and the scalar address arithmetic of the next slab ahead of its barrier; behind it: 153 600)
 //
-// ATN (bf16, BM = 256): operand A is given with K as its ROW index instead, A[k][lda] with the tile's
-// 256 rows m as consecutive columns (the activations X [token][feature] for dR = X^T G: no
+// ATN (bf16): operand A is given with K as its ROW index instead, A[k][lda] with the tile's
+// rows m as consecutive columns (the activations X [token][feature] for dR = X^T G: no
 // token-minor copy of X is needed).  K is walked in the order the other operand stores it
 // (token_position() of the epilogues: position 4a + b of a 64-token group is token a + 16 b), one
-// group per slab.  A stage is then 64 tile rows of 512 bytes.  Fragments come from read_tr_operand,
+// group per slab.  A stage is then 64 tile rows of BM values, columns beyond M read from the last valid ones.  Fragments come from read_tr_operand,
 // two lane quarters at a time reading 32 bytes of rows k .. k+3 and of rows k+8 .. k+11: the 32-byte
 // pieces of a row are XOR-swizzled with 2 (row % 4) + (row / 8) % 2, which puts those eight into
 // different banks.  Rows k >= k_valid are not read (the last valid row is read instead; the other
@@ -329,12 +329,13 @@ __device__ __forceinline__ void gemm_mainloop(const typename TL::T* __restrict__
                                               KT_STAMP_PARAM) {
   using T = typename TL::T;
   constexpr bool F32 = sizeof(T) == 4;
-  static_assert(!ATN || F32 || (TL::BM == 256 && TL::NT == 256), "ATN in bf16: 256 tile rows, 4 waves");
   static_assert(!BTN || F32, "BTN: fp32");
   constexpr int EPC = 16 / (int)sizeof(T);  // elements per 16-byte chunk
   constexpr int MB = TL::MB, NB = TL::NB, SLOTS = MB * NB, NFRAG = MB + NB;
   constexpr int A_LD = TL::A_LD, B_LD = TL::B_LD, NLD = A_LD + B_LD;
   constexpr int WAVE_LD = TL::NT * 16;  // bytes of a stage one load of every thread fills
+  constexpr int A_PITCH = TL::BM * (int)sizeof(T);  // ATN: bytes of a stage row
+  static_assert(!ATN || (A_PITCH >= 256 && WAVE_LD % A_PITCH == 0), "ATN: whole bank windows a row, whole rows a load");
   constexpr int BAR = SLOTS / 2, SPACE0 = SLOTS >= 4 * NFRAG ? 3 : 1, SPACE1 = SLOTS >= 4 * NFRAG ? 2 : 1;
   // load i is issued LOAD_AT(i) slots behind the barrier: the A loads in the first quarter of the interval
   // (a 256 x 256 x 4096 tile takes 163 000 cycles with 1/8, 157 000 with 3/16 or 3/8, 153 600 with this)
@@ -355,10 +356,9 @@ __device__ __forceinline__ void gemm_mainloop(const typename TL::T* __restrict__
   uint32_t og[NLD];
   static_assert(TL::NT / 8 % 16 == 0, "swizzle key must not change between the loads of a thread");
   const int chunk = (tid & 7) ^ swizzle_key(tid >> 3);
-  // ATN: row 8 i + 2 wave + lane / 32, 16-byte position lane % 32; tile row pr of a slab holds position pr of its
-  // 64-token group, i.e. token pr / 4 + 16 (pr % 4) of the group
-  // (fp32: row of the stage, columns as swizzled, at most the last four of the operand)
-  auto atn_row = [&](int i) __attribute__((always_inline)) { return F32 ? (WAVE_LD * i + 16 * tid) / (TL::BM * 4) : 8 * i + 2 * wave + (lane >> 5); };
+  // ATN: stage row and 16-byte position of load i; tile row pr of a slab holds position pr of its 64-token group, i.e. token
+  // pr / 4 + 16 (pr % 4) of the group (fp32: token pr of 32).  Columns as swizzled, at most the last ones of the operand.
+  auto atn_row = [&](int i) __attribute__((always_inline)) { return (WAVE_LD * i + 16 * tid) / A_PITCH; };
   auto atn_token = [&](int i) __attribute__((always_inline)) { return F32 ? atn_row(i) : (atn_row(i) >> 2) + 16 * (atn_row(i) & 3); };
   auto f32_column = [&](int row, int pos, int left) __attribute__((always_inline)) {
     const int c = 4 * (pos ^ (((row >> 2) & 3) << 2));
@@ -367,8 +367,8 @@ __device__ __forceinline__ void gemm_mainloop(const typename TL::T* __restrict__
   auto atn_offset = [&](int i, int token) __attribute__((always_inline)) {
     const int r = atn_row(i);
     if constexpr (F32) return (uint32_t)(((int64_t)token * lda + f32_column(r, tid % (TL::BM / 4), M - m0)) * 4);
-    const int piece_key = 2 * (r & 3) + ((r >> 3) & 1);
-    return (uint32_t)(((int64_t)token * lda + ((lane & 31) ^ (2 * piece_key)) * EPC) * (int64_t)sizeof(T));
+    const int c = (tid % (A_PITCH / 16) ^ (2 * (2 * (r & 3) + ((r >> 3) & 1)))) * EPC, left = M - m0;
+    return (uint32_t)(((int64_t)token * lda + (c < left ? c : left - EPC)) * (int64_t)sizeof(T));
   };
 #pragma unroll
   for (int i = 0; i < A_LD; ++i) {
@@ -467,7 +467,7 @@ __device__ __forceinline__ void gemm_mainloop(const typename TL::T* __restrict__
 #pragma unroll
     for (int i = 0; i < MB; ++i)
       ft[i] = F32 ? 4 * f.q * (TL::BM * 4) + (((f.wm * TL::WTM / 16 + i) ^ f.q) << 6) + 4 * f.l16
-                  : (8 * f.q + (f.l16 >> 2)) * 512 + (((f.wm * TL::WTM / 16 + i) ^ (2 * (f.l16 >> 2) + (f.q & 1))) << 5) + 8 * (f.l16 & 3);
+                  : (8 * f.q + (f.l16 >> 2)) * A_PITCH + (((f.wm * TL::WTM / 16 + i) ^ (2 * (f.l16 >> 2) + (f.q & 1))) << 5) + 8 * (f.l16 & 3);
   }
   if constexpr (BTN) {
 #pragma unroll
@@ -501,7 +501,7 @@ __device__ __forceinline__ void gemm_mainloop(const typename TL::T* __restrict__
       if constexpr (ATN && F32)
         fra[i] = read_rows(ft[i] + off + h * 16 * TL::BM * 4, std::integral_constant<int, TL::BM * 4>{});
       else if constexpr (ATN)
-        fra[i] = read_tr_operand(lds, ft[i] + off + h * 32 * 512, ft[i] + off + h * 32 * 512 + 4 * 512);
+        fra[i] = read_tr_operand(lds, ft[i] + off + h * 32 * A_PITCH, ft[i] + off + h * 32 * A_PITCH + 4 * A_PITCH);
       else
         fra[i] = *reinterpret_cast<const intx4*>(lds + fa_s[h] + off + i * 16 * kRowBytes);
     }
