@@ -15,6 +15,7 @@
 #include "kt_cayley_d128.h"
 #include "kt_fused_d128.h"
 #include "kt_hadamard.h"
+#include "kt_rows.h"
 #include "kt_skinny.h"
 
 namespace kt {
@@ -277,7 +278,7 @@ struct LossGradPlan {
   int P;           // moment partials per token
   bool small_fwd, small_dr;  // bf16: 128 x 128 tiles in the forward product, in dR
   int slabs_per_split, split_k;
-  size_t o_rt, o_part, o_coef, o_losspart, o_xt, o_gt, o_splitk, o_gstat, o_yt, total;
+  size_t o_rt, o_part, o_coef, o_losspart, o_gt, o_splitk, o_gstat, o_yt, total;
   int loss_blocks;
   bool keep_y;     // the forward pass writes Y (fp32, token-minor) and the backward pass reads it instead of recomputing it
 };
@@ -354,33 +355,41 @@ static LossGradPlan plan_loss_grad(int64_t batch, int64_t n, int64_t d, kt_dtype
     p.o_rt = 0;
     p.o_losspart = c.take((size_t)batch * p.fused_wgs * 8);
     p.o_splitk = c.take(p.fused_wgs > 1 ? (size_t)p.fused_wgs * batch * d * d * 4 : 0);  // one: straight into dR
-    p.o_part = p.o_coef = p.o_xt = p.o_gt = p.o_gstat = 0;
+    p.o_part = p.o_coef = p.o_gt = p.o_gstat = 0;
     p.total = c.off;
     return p;
   }
   p.ldt = round_up(n, 128);
   p.tb = p.ldt < kTokenBlock ? p.ldt : kTokenBlock;
   p.nblk = ceil_div(p.ldt, p.tb);
-  if (p.fp32) {
-    p.P = (int)ceil_div(d, TF::BM) * TF::WGM;
-    // (also where X^T G takes 64 x 64 tiles: a quarter of the splits would be sums four times as long, in fp32; d = 1024,
-    // 16384 tokens: dR off by 8.8e-7 of its norm instead of 6.9e-7)
-    p.slabs_per_split = choose_slabs_per_split(ceil_div(d, TF::BM) * ceil_div(d, TF::BN) * batch, p.ldt / TF::BK, 4 * kNumCUs);
-    p.split_k = (int)ceil_div(p.ldt / TF::BK, p.slabs_per_split);
-  } else {
-    p.P = (int)(d / 128);
-    p.small_fwd = small_forward_tiles(batch, n, d);
-    p.small_dr = small_dr_tiles(batch, p.ldt / TB_BIG::BK, d, &p.slabs_per_split);
-    p.split_k = (int)ceil_div(p.ldt / TB_BIG::BK, p.slabs_per_split);
-  }
-  p.loss_blocks = (int)ceil_div(n, 256);
   Carver c;
+  if (p.fp32) {
+    // token ranges as for 128 x 128 tiles (also with smaller ones: a quarter of the ranges would be sums four times as long, in
+    // fp32; d = 1024, 16384 tokens: dR off by 8.8e-7 of its norm instead of 6.9e-7), whole blocks of 128 tokens
+    p.slabs_per_split = (int)round_up(choose_slabs_per_split(ceil_div(d, TF::BM) * ceil_div(d, TF::BN) * batch, p.ldt / TF::BK, 4 * kNumCUs), 4);
+    p.split_k = (int)ceil_div(p.ldt / TF::BK, p.slabs_per_split);
+    p.P = 1;
+    p.loss_blocks = (int)(p.ldt / 4 < 2048 ? p.ldt / 4 : 2048);  // workgroups of loss_rows_kernel per problem
+    p.o_rt = c.take((size_t)batch * d * d * 4);
+    p.o_part = c.take(pooled ? (size_t)batch * n * 16 : 0);
+    p.o_losspart = c.take((size_t)batch * p.loss_blocks * 8 * (pooled ? 4 : 1));
+    p.o_gstat = c.take(pooled ? (size_t)batch * 4 * 8 : 0);
+    p.o_gt = c.take((size_t)batch * p.ldt * d * 4);  // Y, then dL/dY
+    p.o_splitk = c.take(p.split_k > 1 ? (size_t)p.split_k * batch * d * d * 4 : 0);
+    p.o_coef = 0;
+    p.total = c.off;
+    return p;
+  }
+  p.P = (int)(d / 128);
+  p.small_fwd = small_forward_tiles(batch, n, d);
+  p.small_dr = small_dr_tiles(batch, p.ldt / TB_BIG::BK, d, &p.slabs_per_split);
+  p.split_k = (int)ceil_div(p.ldt / TB_BIG::BK, p.slabs_per_split);
+  p.loss_blocks = (int)ceil_div(n, 256);
   p.o_rt = c.take((size_t)batch * d * d * p.esz);
   p.o_part = c.take((size_t)batch * p.P * n * 16);
   p.o_coef = c.take((size_t)batch * n * 16);
   p.o_losspart = c.take((size_t)batch * p.loss_blocks * 8 * (pooled ? 4 : 1));
   p.o_gstat = c.take(pooled ? (size_t)batch * 4 * 8 : 0);
-  p.o_xt = c.take(p.fp32 ? (size_t)batch * d * p.nblk * p.tb * p.esz : 0);  // bf16: X as it is
   p.o_gt = c.take((size_t)batch * d * p.nblk * p.tb * p.esz);
   p.o_splitk = c.take(p.split_k > 1 ? (size_t)p.split_k * batch * d * d * 4 : 0);
   p.keep_y = keep_y;
@@ -514,13 +523,22 @@ static kt_status check_ws(void* ws, size_t have, size_t need) {
 template <typename Tout>
 static bool prep_rt(const void* R, int64_t ldr, kt_dtype rdt, Tout* RT, int64_t batch, int64_t d,
                     hipStream_t st) {
-  dim3 grid((unsigned)ceil_div(d, 64), (unsigned)ceil_div(d, 64), (unsigned)batch);
+  const dim3 grid((unsigned)(d / 64), (unsigned)(d / 64), (unsigned)batch);
   if (rdt == KT_F32)
-    hipLaunchKernelGGL((transpose_kernel<float, Tout>), grid, dim3(256), 0, st,
-                       static_cast<const float*>(R), ldr, d * ldr, RT, d, d * d, (int)d, (int)d, (int)d, 0);
+    hipLaunchKernelGGL((transpose_kernel<float, Tout>), grid, dim3(256), 0, st, static_cast<const float*>(R), ldr, RT, (int)d);
   else
-    hipLaunchKernelGGL((transpose_kernel<bf16, Tout>), grid, dim3(256), 0, st,
-                       static_cast<const bf16*>(R), ldr, d * ldr, RT, d, d * d, (int)d, (int)d, (int)d, 0);
+    hipLaunchKernelGGL((transpose_kernel<bf16, Tout>), grid, dim3(256), 0, st, static_cast<const bf16*>(R), ldr, RT, (int)d);
+  return launch_ok();
+}
+
+// out = sum of the `splits` partials; with `loss` (batch > 0) also the loss sums.
+static bool launch_splitk_reduce(const float* part, int64_t count, int splits, float* out, const LossSum& loss, hipStream_t st) {
+  const int64_t wgs = ceil_div(count, 1024) < 2048 ? ceil_div(count, 1024) : 2048;
+  hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)(wgs + loss.problems)), dim3(256), 0, st, part, count, splits, out, count, loss);
+  return launch_ok();
+}
+static bool launch_loss_sum(const LossSum& loss, hipStream_t st) {
+  hipLaunchKernelGGL(finalize_loss_kernel, dim3((unsigned)loss.problems), dim3(256), 0, st, loss);
   return launch_ok();
 }
 
@@ -530,27 +548,27 @@ struct PooledArgs {  // paper-literal pooled loss (kurtosis over all entries aft
   float* kappa_out;  // [batch] or null
 };
 
-template <typename T>
-static kt_status run_loss_grad(const LossGradPlan& p, const void* X, int64_t ldx, const void* R,
+// bf16, d > 128 or pooled.
+static kt_status run_loss_grad_bf16(const LossGradPlan& p, const void* X, int64_t ldx, const void* R,
                                int64_t ldr, kt_dtype rdt, int64_t batch, int64_t n, int64_t d,
                                float kappa_target, float* loss, float* row_kurt, float* dR,
                                char* ws, hipStream_t st, const PooledArgs* pooled = nullptr) {
+  using T = bf16;
   T* RT = reinterpret_cast<T*>(ws + p.o_rt);
   floatx4* part = reinterpret_cast<floatx4*>(ws + p.o_part);
   floatx4* coef = reinterpret_cast<floatx4*>(ws + p.o_coef);
   double* loss_part = reinterpret_cast<double*>(ws + p.o_losspart);
-  T* XT = reinterpret_cast<T*>(ws + p.o_xt);
   T* GT = reinterpret_cast<T*>(ws + p.o_gt);
   float* splitk = reinterpret_cast<float*>(ws + p.o_splitk);
   const T* Xp = static_cast<const T*>(X);
+  const LossSum loss_sum = {loss_part, p.loss_blocks, (int)n, (int)batch, loss};
 
   // a0: R -> R^T in the GEMM dtype
   if (!prep_rt<T>(R, ldr, rdt, RT, batch, d, st)) return fail(KT_ERR_DEVICE, "prep_rt launch failed");
 
   // go(tile) with the tile of the forward product (features on m, tokens on n)
   auto with_forward_tile = [&](auto go) -> bool {
-    if constexpr (sizeof(T) == 4) return go(TF{});
-    else return p.small_fwd ? go(TB_128{}) : go(TB_BIG{});
+    return p.small_fwd ? go(TB_128{}) : go(TB_BIG{});
   };
 
   // a1: forward GEMM with the moment epilogue; with keep_y it also writes Y
@@ -586,20 +604,10 @@ static kt_status run_loss_grad(const LossGradPlan& p, const void* X, int64_t ldx
   hipLaunchKernelGGL(finalize_rows_kernel, dim3(p.loss_blocks, (unsigned)batch), dim3(256), 0, st, part,
                      p.P, (int)n, (int)d, kappa_target, coef, row_kurt, loss_part);
   if (!launch_ok()) return fail(KT_ERR_DEVICE, "finalize_rows launch failed");
-  hipLaunchKernelGGL(finalize_loss_kernel, dim3((unsigned)batch), dim3(256), 0, st, loss_part,
-                     p.loss_blocks, (int)n, loss);
-  if (!launch_ok()) return fail(KT_ERR_DEVICE, "finalize_loss launch failed");
+  if ((!dR || p.split_k == 1) && !launch_loss_sum(loss_sum, st)) return fail(KT_ERR_DEVICE, "loss sum launch failed");
   if (!dR) return KT_OK;
   }
 
-  // fp32: the last GEMM needs a token-minor copy of X (zero padded to ldt tokens); bf16 reads X as it is (transposing LDS reads)
-  if constexpr (sizeof(T) == 4) {
-    ProfScope prof(3, st);
-    dim3 grid((unsigned)(p.ldt / 64), (unsigned)ceil_div(d, 64), (unsigned)batch);
-    hipLaunchKernelGGL((transpose_kernel<T, T>), grid, dim3(256), 0, st, Xp, ldx, n * ldx, XT, p.tb,
-                       d * p.nblk * p.tb, (int)n, (int)p.ldt, (int)d, 1);
-    if (!launch_ok()) return fail(KT_ERR_DEVICE, "X transpose launch failed");
-  }
   // a3: dL/dY token-minor, from the kept Y entry by entry or from a recomputed Y in the GEMM epilogue
   if (keep) {
     ProfScope prof(1, st);
@@ -629,23 +637,12 @@ static kt_status run_loss_grad(const LossGradPlan& p, const void* X, int64_t ldx
       e.C = p.split_k > 1 ? splitk : dR;
       e.batch_stride = d * d; e.split_stride = p.split_k > 1 ? batch * d * d : 0;
       e.ldc = d; e.M = (int)d; e.N = (int)d;
-      if constexpr (sizeof(T) == 2)
-        return launch_gemm<TL, EpiStore<TL>, true>(Xp, ldx, n * ldx, (int)d, GT, p.tb, d * p.nblk * p.tb, (int)d, p.ldt,
-                                                   p.slabs_per_split, (int)batch, e, st, p.tb, 0, d * p.tb, (int)n);
-      else
-        return launch_gemm<TL>(XT, p.tb, d * p.nblk * p.tb, (int)d, GT, p.tb, d * p.nblk * p.tb, (int)d, p.ldt,
-                               p.slabs_per_split, (int)batch, e, st, p.tb, d * p.tb, d * p.tb);
+      return launch_gemm<TL, EpiStore<TL>, true>(Xp, ldx, n * ldx, (int)d, GT, p.tb, d * p.nblk * p.tb, (int)d, p.ldt,
+                                                 p.slabs_per_split, (int)batch, e, st, p.tb, 0, d * p.tb, (int)n);
     };
-    bool ok;
-    if constexpr (sizeof(T) == 2) ok = p.small_dr ? go(TB_128{}) : go(TB_BIG{});
-    else ok = small_f32_tiles(d, batch) ? go(TF_64{}) : go(TF{});
-    if (!ok) return fail(KT_ERR_DEVICE, "gradient GEMM launch failed");
-    if (p.split_k > 1) {
-      const int64_t count = batch * d * d;
-      hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)(ceil_div(count, 256) < 4096 ? ceil_div(count, 256) : 4096)),
-                         dim3(256), 0, st, splitk, count, p.split_k, dR, count);
-      if (!launch_ok()) return fail(KT_ERR_DEVICE, "split-K reduce launch failed");
-    }
+    if (!(p.small_dr ? go(TB_128{}) : go(TB_BIG{}))) return fail(KT_ERR_DEVICE, "gradient GEMM launch failed");
+    if (p.split_k > 1 && !launch_splitk_reduce(splitk, batch * d * d, p.split_k, dR, pooled ? LossSum{} : loss_sum, st))
+      return fail(KT_ERR_DEVICE, "split-K reduce launch failed");
   }
   return KT_OK;
 }
@@ -666,14 +663,11 @@ static kt_status run_loss_grad_fused(const LossGradPlan& p, const void* X, int64
                        loss_part, dR_part, dR ? 1 : 0);
     if (!launch_ok()) return fail(KT_ERR_DEVICE, "fused kernel launch failed");
   }
-  hipLaunchKernelGGL(finalize_loss_kernel, dim3((unsigned)batch), dim3(256), 0, st, loss_part, p.fused_wgs,
-                     (int)n, loss);
-  if (!launch_ok()) return fail(KT_ERR_DEVICE, "finalize_loss launch failed");
+  const LossSum loss_sum = {loss_part, p.fused_wgs, (int)n, (int)batch, loss};
   if (dR && p.fused_wgs > 1) {
-    const int64_t count = batch * d * d;
-    hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)(ceil_div(count, 256) < 4096 ? ceil_div(count, 256) : 4096)),
-                       dim3(256), 0, st, dR_part, count, p.fused_wgs, dR, count);
-    if (!launch_ok()) return fail(KT_ERR_DEVICE, "partial dR reduce launch failed");
+    if (!launch_splitk_reduce(dR_part, batch * d * d, p.fused_wgs, dR, loss_sum, st)) return fail(KT_ERR_DEVICE, "partial dR reduce launch failed");
+  } else if (!launch_loss_sum(loss_sum, st)) {
+    return fail(KT_ERR_DEVICE, "loss sum launch failed");
   }
   return KT_OK;
 }
@@ -705,10 +699,8 @@ static bool launch_skinny(const bf16* X, int64_t ldx, const TR* R, int64_t ldr, 
   if (n <= 16) go(std::integral_constant<int, 1>{});
   else if (n <= 32) go(std::integral_constant<int, 2>{});
   else go(std::integral_constant<int, 4>{});
-  if (s > 1)
-    hipLaunchKernelGGL(splitk_reduce_kernel, dim3((unsigned)(ceil_div(count, 256) < 4096 ? ceil_div(count, 256) : 4096)),
-                       dim3(256), 0, st, part, count, (int)s, Y, count);
-  return launch_ok();
+  if (!launch_ok()) return false;
+  return s == 1 || launch_splitk_reduce(part, count, (int)s, Y, LossSum{}, st);
 }
 
 // Y [problems][rows][d] = X R (token-major, tokens on the rows of the GEMM; R as in launch_features_gemm) with the tile that fills the chip: the large one
@@ -721,11 +713,11 @@ static bool launch_skinny(const bf16* X, int64_t ldx, const TR* R, int64_t ldr, 
 // 432: 72.3 / 73.6, 480: 88.2 / 91.0, 576: 92.2 / 88.1, 1152: 176 / 164.
 template <typename T, class TL>
 static bool launch_rows_gemm(const T* X, int64_t ldx, int64_t x_batch_stride, const T* R, int64_t ldr, bool in_place, int64_t problems,
-                             int64_t rows, int64_t d, float* Y, hipStream_t st) {
+                             int64_t rows, int64_t d, float* Y, int64_t y_batch_stride, hipStream_t st) {
   auto go = [&](auto tile_tag) -> bool {
     using G = decltype(tile_tag);
     EpiStore<G> e;
-    e.C = Y; e.ldc = d; e.batch_stride = rows * d; e.split_stride = 0; e.M = (int)rows; e.N = (int)d;
+    e.C = Y; e.ldc = d; e.batch_stride = y_batch_stride; e.split_stride = 0; e.M = (int)rows; e.N = (int)d;
     if constexpr (sizeof(T) == 4) {
       if (in_place)
         return launch_gemm<G, EpiStore<G>, false, true>(X, ldx, x_batch_stride, (int)rows, R, ldr, d * ldr, (int)d, d, 0, (int)problems, e, st);
@@ -741,6 +733,61 @@ static bool launch_rows_gemm(const T* X, int64_t ldx, int64_t x_batch_stride, co
     else small = tiles <= kNumCUs / 2;
     return small ? go(TB_128{}) : go(TL{});
   }
+}
+
+// fp32: token-major throughout (kt_rows.h).  Y = X R in the workspace, dL/dY over it, dR = X^T (dL/dY) with K as the row index
+// of both operands.
+static kt_status run_loss_grad_f32(const LossGradPlan& p, const float* X, int64_t ldx, const float* R, int64_t ldr, int64_t batch,
+                                   int64_t n, int64_t d, float kappa_target, float* loss, float* row_kurt, float* dR, char* ws,
+                                   hipStream_t st, const PooledArgs* pooled = nullptr) {
+  float* RT = reinterpret_cast<float*>(ws + p.o_rt);
+  float* Y = reinterpret_cast<float*>(ws + p.o_gt);
+  floatx4* part = pooled ? reinterpret_cast<floatx4*>(ws + p.o_part) : nullptr;
+  double* sums = reinterpret_cast<double*>(ws + p.o_losspart);
+  double* gstat = reinterpret_cast<double*>(ws + p.o_gstat);
+  float* splitk = reinterpret_cast<float*>(ws + p.o_splitk);
+  const bool in_place = f32_in_place(R, ldr);
+  if (!in_place && !prep_rt<float>(R, ldr, KT_F32, RT, batch, d, st)) return fail(KT_ERR_DEVICE, "prep_rt launch failed");
+  {
+    ProfScope prof(0, st);
+    if (!launch_rows_gemm<float, TF>(X, ldx, n * ldx, in_place ? R : RT, ldr, in_place, batch, n, d, Y, p.ldt * d, st))
+      return fail(KT_ERR_DEVICE, "forward GEMM launch failed");
+  }
+  const int wgs = p.loss_blocks;
+  {
+    ProfScope prof(1, st);
+    auto rows_kernel = d <= 1024 ? loss_rows_kernel<4> : d <= 4096 ? loss_rows_kernel<16> : d <= 8192 ? loss_rows_kernel<32> : loss_rows_kernel<0>;
+    hipLaunchKernelGGL(rows_kernel, dim3(wgs, (unsigned)batch), dim3(256), 0, st, Y, (int)p.ldt, (int)n, (int)d, kappa_target, row_kurt,
+                       sums, dR ? 1 : 0, pooled ? pooled->rms_eps : 0.f, part);
+    if (!launch_ok()) return fail(KT_ERR_DEVICE, "row statistics launch failed");
+    if (pooled) {
+      hipLaunchKernelGGL(pooled_stage2_kernel, dim3((unsigned)batch), dim3(256), 0, st, sums, wgs, (int)n, (int)d, kappa_target, gstat,
+                         loss, pooled->kappa_out);
+      if (dR)
+        hipLaunchKernelGGL(pooled_grad_rows_kernel, dim3((unsigned)ceil_div(n, 4), (unsigned)batch), dim3(256), 0, st, Y, (int)p.ldt, (int)n,
+                           (int)d, pooled->rms_eps, part, gstat);
+      if (!launch_ok()) return fail(KT_ERR_DEVICE, "pooled statistics launch failed");
+    }
+  }
+  const LossSum loss_sum = pooled ? LossSum{} : LossSum{sums, wgs, (int)n, (int)batch, loss};
+  if (!dR || p.split_k == 1) {
+    if (!pooled && !launch_loss_sum(loss_sum, st)) return fail(KT_ERR_DEVICE, "loss sum launch failed");
+    if (!dR) return KT_OK;
+  }
+  ProfScope prof(2, st);
+  auto go = [&](auto tile_tag) -> bool {
+    using TL = decltype(tile_tag);
+    EpiStore<TL> e;
+    e.C = p.split_k > 1 ? splitk : dR;
+    e.batch_stride = d * d; e.split_stride = p.split_k > 1 ? batch * d * d : 0;
+    e.ldc = d; e.M = (int)d; e.N = (int)d;
+    return launch_gemm<TL, EpiStore<TL>, true, true>(X, ldx, n * ldx, (int)d, Y, d, p.ldt * d, (int)d, p.ldt, p.slabs_per_split, (int)batch, e,
+                                                     st, 0, 0, 0, (int)n);
+  };
+  if (!with_f32_tile(d, d, batch * p.split_k, go)) return fail(KT_ERR_DEVICE, "gradient GEMM launch failed");
+  if (p.split_k > 1 && !launch_splitk_reduce(splitk, batch * d * d, p.split_k, dR, loss_sum, st))
+    return fail(KT_ERR_DEVICE, "split-K reduce launch failed");
+  return KT_OK;
 }
 
 // ------------------------------------------------------------------ fake-quant ----
@@ -793,7 +840,7 @@ static kt_status run_quant(const QuantPlan& p, const void* X, int64_t ldx, const
           ok = rdt == KT_F32 ? launch_skinny(Xb, ldx, static_cast<const float*>(R), ldr, batch, n, d, ws + p.o_rt, p.o_amax - p.o_rt, Ybuf, st)
                              : launch_skinny(Xb, ldx, static_cast<const bf16*>(R), ldr, batch, n, d, ws + p.o_rt, p.o_amax - p.o_rt, Ybuf, st);
         } else {
-          ok = launch_rows_gemm<T, TQ>(Xp + (b0 * n + t0) * ldx, ldx, n * ldx, Rg + b0 * r_stride, ldr, in_place, nb, nt, d, Ybuf, st);
+          ok = launch_rows_gemm<T, TQ>(Xp + (b0 * n + t0) * ldx, ldx, n * ldx, Rg + b0 * r_stride, ldr, in_place, nb, nt, d, Ybuf, nt * d, st);
         }
         if (!ok) return fail(KT_ERR_DEVICE, "rotation GEMM launch failed");
         const int64_t rows = nb * nt, row0 = b0 * n + t0;
@@ -1221,8 +1268,8 @@ kt_status kt_kurtosis_loss_grad(const void* X, int64_t ldx, const void* R, int64
   if (p.fused)
     return run_loss_grad_fused(p, X, ldx, R, ldr, r_dtype, batch, n, d, kappa_target, loss, row_kurt, dR,
                                ws, st);
-  return p.fp32 ? run_loss_grad<float>(p, X, ldx, R, ldr, r_dtype, batch, n, d, kappa_target, loss, row_kurt, dR, ws, st)
-                : run_loss_grad<bf16>(p, X, ldx, R, ldr, r_dtype, batch, n, d, kappa_target, loss, row_kurt, dR, ws, st);
+  return p.fp32 ? run_loss_grad_f32(p, static_cast<const float*>(X), ldx, static_cast<const float*>(R), ldr, batch, n, d, kappa_target, loss, row_kurt, dR, ws, st)
+                : run_loss_grad_bf16(p, X, ldx, R, ldr, r_dtype, batch, n, d, kappa_target, loss, row_kurt, dR, ws, st);
 }
 
 kt_status kt_pooled_kurtosis_loss_grad(const void* X, int64_t ldx, const void* R, int64_t ldr,
@@ -1247,8 +1294,8 @@ kt_status kt_pooled_kurtosis_loss_grad(const void* X, int64_t ldx, const void* R
   hipStream_t st = static_cast<hipStream_t>(stream);
   PooledArgs pa;
   pa.rms_eps = rms_eps; pa.kappa_out = kappa;
-  return p.fp32 ? run_loss_grad<float>(p, X, ldx, R, ldr, r_dtype, batch, n, d, kappa_target, loss, nullptr, dR, ws, st, &pa)
-                : run_loss_grad<bf16>(p, X, ldx, R, ldr, r_dtype, batch, n, d, kappa_target, loss, nullptr, dR, ws, st, &pa);
+  return p.fp32 ? run_loss_grad_f32(p, static_cast<const float*>(X), ldx, static_cast<const float*>(R), ldr, batch, n, d, kappa_target, loss, nullptr, dR, ws, st, &pa)
+                : run_loss_grad_bf16(p, X, ldx, R, ldr, r_dtype, batch, n, d, kappa_target, loss, nullptr, dR, ws, st, &pa);
 }
 
 kt_status kt_cayley_step(float* R, const float* dR, void* R_lowp, int64_t batch, int64_t d, float lr,
@@ -1420,7 +1467,7 @@ kt_status kt_rotate_quant_metrics(const void* X, int64_t ldx, const void* R, int
           ok = r_dtype == KT_F32 ? launch_skinny(Xb, ldx, static_cast<const float*>(R), ldr, batch, n, d, ws, rt_bytes, Yb, st)
                                  : launch_skinny(Xb, ldx, static_cast<const bf16*>(R), ldr, batch, n, d, ws, rt_bytes, Yb, st);
         } else {
-          ok = launch_rows_gemm<T, TL>(Xp + row0 * ldx, ldx, n * ldx, Rg + b0 * (in_place ? d * ldr : d * d), ldr, in_place, nb, nt, d, Yb, st);
+          ok = launch_rows_gemm<T, TL>(Xp + row0 * ldx, ldx, n * ldx, Rg + b0 * (in_place ? d * ldr : d * d), ldr, in_place, nb, nt, d, Yb, nt * d, st);
         }
         if (!ok) return fail(KT_ERR_DEVICE, "rotation GEMM launch failed");
         // the row in 4 / 8 / 16 / 32 float4 registers per lane; rows that fill them exactly skip every bounds test

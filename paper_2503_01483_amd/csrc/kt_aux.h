@@ -8,57 +8,43 @@ namespace kt {
 template <typename Tin>
 __device__ __forceinline__ float to_float(Tin v) { return (float)v; }
 
-// out[c*ldo + r'] = in[r*ldi + c] for r < rows, c < cols; columns r in [rows, rows_pad)
-// of `out` are zero-filled.  r' = r, or, when `permute` is set, the place of token r in the
-// permuted, blocked token order of the X^T G operands (ldo = tokens per block, block b of
-// all `cols` feature rows starts at b*cols*ldo; rows_pad must then be a multiple of 128).
-// 64 x 64 tiles through LDS, 256 threads.
-// grid = (ceil(rows_pad/64), ceil(cols/64), batch)
+// R^T in the GEMM dtype: out[c * d + r] = in[r * ldi + c], d a multiple of 128, `out` 16-byte aligned.  64 x 64 tiles through LDS, 16
+// bytes per access on both sides (`in` in single values where its rows are not that aligned).  grid = (d / 64, d / 64, batch)
 template <typename Tin, typename Tout>
-__global__ __launch_bounds__(256) void transpose_kernel(const Tin* __restrict__ in, int64_t ldi,
-                                                        int64_t in_batch_stride,
-                                                        Tout* __restrict__ out, int64_t ldo,
-                                                        int64_t out_batch_stride, int rows,
-                                                        int rows_pad, int cols, int permute) {
+__global__ __launch_bounds__(256) void transpose_kernel(const Tin* __restrict__ in, int64_t ldi, Tout* __restrict__ out, int d) {
   __shared__ float tile[64][65];
-  const int r0 = blockIdx.x * 64, c0 = blockIdx.y * 64;
-  const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-  in += (int64_t)blockIdx.z * in_batch_stride;
-  out += (int64_t)blockIdx.z * out_batch_stride;
+  constexpr int VI = 16 / (int)sizeof(Tin), VO = 16 / (int)sizeof(Tout);
+  typedef Tin vec_in __attribute__((ext_vector_type(VI)));
+  typedef Tout vec_out __attribute__((ext_vector_type(VO)));
+  in += (int64_t)blockIdx.z * d * ldi + (int64_t)blockIdx.x * 64 * ldi + blockIdx.y * 64;
+  out += (int64_t)blockIdx.z * d * d + (int64_t)blockIdx.y * 64 * d + blockIdx.x * 64;
+  const bool vec = ((reinterpret_cast<uintptr_t>(in) | (uintptr_t)(ldi * sizeof(Tin))) & 15) == 0;
+  constexpr int NI = 16 / VI, NO = 16 / VO;
+  vec_in v[NI];
 #pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const int r = r0 + ty + 4 * i, c = c0 + tx;
-    float v = 0.f;
-    if (r < rows && c < cols) v = to_float(in[(int64_t)r * ldi + c]);
-    tile[ty + 4 * i][tx] = v;
+  for (int i = 0; i < NI; ++i) {
+    const int u = threadIdx.x + 256 * i, r = u / (64 / VI), c = u % (64 / VI) * VI;
+    if (vec) {
+      v[i] = *reinterpret_cast<const vec_in*>(in + (int64_t)r * ldi + c);
+    } else {
+#pragma unroll
+      for (int e = 0; e < VI; ++e) v[i][e] = in[(int64_t)r * ldi + c + e];
+    }
+  }
+#pragma unroll
+  for (int i = 0; i < NI; ++i) {
+    const int u = threadIdx.x + 256 * i, r = u / (64 / VI), c = u % (64 / VI) * VI;
+#pragma unroll
+    for (int e = 0; e < VI; ++e) tile[r][c + e] = to_float(v[i][e]);
   }
   __syncthreads();
 #pragma unroll
-  for (int i = 0; i < 16; ++i) {
-    const int c = c0 + ty + 4 * i, r = r0 + tx;
-    if (c < cols && r < rows_pad) {
-      int64_t o = (int64_t)c * ldo + r;
-      if (permute) {  // token order and token blocks of the X^T G operands; ldo = block length
-        const int64_t p = token_position(r), blk = p / ldo;
-        o = blk * cols * ldo + (int64_t)c * ldo + (p - blk * ldo);
-      }
-      out[o] = from_float<Tout>(tile[tx][ty + 4 * i]);
-    }
-  }
-}
-
-// Row-major copy with dtype conversion: out[r*ldo + c] = in[r*ldi + c].
-template <typename Tin, typename Tout>
-__global__ __launch_bounds__(256) void convert_kernel(const Tin* __restrict__ in, int64_t ldi,
-                                                      int64_t in_batch_stride,
-                                                      Tout* __restrict__ out, int64_t ldo,
-                                                      int64_t out_batch_stride, int rows, int cols) {
-  in += (int64_t)blockIdx.z * in_batch_stride;
-  out += (int64_t)blockIdx.z * out_batch_stride;
-  const int64_t total = (int64_t)rows * cols;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)gridDim.x * 256) {
-    const int r = (int)(i / cols), c = (int)(i % cols);
-    out[(int64_t)r * ldo + c] = from_float<Tout>(to_float(in[(int64_t)r * ldi + c]));
+  for (int i = 0; i < NO; ++i) {
+    const int u = threadIdx.x + 256 * i, c = u / (64 / VO), r = u % (64 / VO) * VO;
+    vec_out w;
+#pragma unroll
+    for (int e = 0; e < VO; ++e) w[e] = from_float<Tout>(tile[r + e][c]);
+    *reinterpret_cast<vec_out*>(out + (int64_t)c * d + r) = w;
   }
 }
 
@@ -100,6 +86,38 @@ __device__ __forceinline__ void row_central_sums(const floatx4* __restrict__ par
   M[0] = M2; M[1] = M3; M[2] = M4;
 }
 
+// Central moments of a row (mean and sums of c^2, c^3, c^4) -> {alpha, mu, beta, m3} of its gradient and kappa; its loss
+// term is added to `loss`.
+__device__ __forceinline__ floatx4 row_coefficients(double mu, const double (&M)[3], int n, int d, float kappa_target, double& kappa,
+                                                    double& loss) {
+  const double inv_d = 1.0 / (double)d;
+  const double m2 = M[0] * inv_d, m3 = M[1] * inv_d, m4 = M[2] * inv_d;
+  const double r2 = m2 + mu * mu;
+  // A row counts as having no spread when its variance is below 1e-10 of its mean square (sigma below 1e-5 of the
+  // mean): fp32 accumulation leaves about 1e-13 there on a row that is constant in exact arithmetic, and a row
+  // with a real spread that small cannot be resolved from fp32 products anyway.  Above the threshold kappa is
+  // returned with an error that grows like 1e-6 |mean| / sigma instead of being silently dropped.
+  const bool ok = m2 > 1e-10 * r2;  // same rule as the d = 128 kernel
+  double alpha = 0.0, beta = 0.0;
+  kappa = 0.0;
+  if (ok) {
+    kappa = m4 / (m2 * m2);
+    double sgn = 1.0;
+    if (kappa_target != 0.f) {
+      const double dk = kappa - (double)kappa_target;
+      sgn = (dk > 0.0) - (dk < 0.0);
+      loss += fabs(dk);
+    } else {
+      loss += kappa;
+    }
+    alpha = sgn * 4.0 / ((double)n * (double)d * m2 * m2);
+    beta = kappa * m2;
+  } else if (kappa_target != 0.f) {
+    loss += fabs((double)kappa_target);
+  }
+  return floatx4{(float)alpha, (float)mu, (float)beta, (float)m3};
+}
+
 // Per token: merge the P partials in fixed order (fp64) into the central moments of
 // Eq. 3, then kappa, the loss term and the coefficients the backward epilogue needs.  One thread per token; grid = (ceil(n/256), batch).
 __global__ __launch_bounds__(256) void finalize_rows_kernel(const floatx4* __restrict__ part, int P,
@@ -112,34 +130,9 @@ __global__ __launch_bounds__(256) void finalize_rows_kernel(const floatx4* __res
   const int token = blockIdx.x * 256 + threadIdx.x;
   double term = 0.0;
   if (token < n) {
-    double mu, M[3];
+    double mu, M[3], kappa;
     row_central_sums(part, P, n, batch, token, d, mu, M);
-    const double inv_d = 1.0 / (double)d;
-    const double m2 = M[0] * inv_d, m3 = M[1] * inv_d, m4 = M[2] * inv_d;
-    const double r2 = m2 + mu * mu;
-    // A row counts as having no spread when its variance is below 1e-10 of its mean square (sigma below 1e-5 of the
-    // mean): fp32 accumulation leaves about 1e-13 there on a row that is constant in exact arithmetic, and a row
-    // with a real spread that small cannot be resolved from fp32 products anyway.  Above the threshold kappa is
-    // returned with an error that grows like 1e-6 |mean| / sigma instead of being silently dropped.
-    const bool ok = m2 > 1e-10 * r2;  // same rule as the d = 128 kernel
-    double kappa = 0.0, alpha = 0.0, beta = 0.0;
-    if (ok) {
-      kappa = m4 / (m2 * m2);
-      double sgn = 1.0;
-      if (kappa_target != 0.f) {
-        const double dk = kappa - (double)kappa_target;
-        sgn = (dk > 0.0) - (dk < 0.0);
-        term = fabs(dk);
-      } else {
-        term = kappa;
-      }
-      alpha = sgn * 4.0 / ((double)n * (double)d * m2 * m2);
-      beta = kappa * m2;
-    } else if (kappa_target != 0.f) {
-      term = fabs((double)kappa_target);
-    }
-    floatx4 c = {(float)alpha, (float)mu, (float)beta, (float)m3};
-    coef[(int64_t)batch * n + token] = c;
+    coef[(int64_t)batch * n + token] = row_coefficients(mu, M, n, d, kappa_target, kappa, term);
     if (row_kurt) row_kurt[(int64_t)batch * n + token] = (float)kappa;
   }
   const double s = block_sum_256(term, sh);
@@ -196,11 +189,7 @@ __global__ __launch_bounds__(256) void grad_from_y_kernel(const float* __restric
 // Row sums of z^k = (y / rho)^k follow from the row's sums of y^k, so the forward GEMM with the
 // moment epilogue is used unchanged.  Stage 1: per token rho and the block partials of the four
 // pooled raw sums.  grid = (ceil(n/256), batch).
-__device__ __forceinline__ void pooled_row_sums(const floatx4* __restrict__ part, int P, int n, int64_t batch,
-                                                int token, int d, double rms_eps, double& inv_rho,
-                                                double (&Z)[4]) {
-  double mu, M[3];
-  row_central_sums(part, P, n, batch, token, d, mu, M);
+__device__ __forceinline__ void pooled_row_sums(double mu, const double (&M)[3], int d, double rms_eps, double& inv_rho, double (&Z)[4]) {
   // raw sums of y^k over the row, from the central ones (fp64: nothing is lost going back)
   const double dd = (double)d, mu2 = mu * mu;
   const double S1 = dd * mu, S2 = M[0] + dd * mu2, S3 = M[1] + 3.0 * mu * M[0] + dd * mu2 * mu,
@@ -216,7 +205,11 @@ __global__ __launch_bounds__(256) void pooled_stage1_kernel(const floatx4* __res
   __shared__ double sh[256];
   const int batch = blockIdx.y, token = blockIdx.x * 256 + threadIdx.x;
   double Z[4] = {0, 0, 0, 0}, inv_rho;
-  if (token < n) pooled_row_sums(part, P, n, batch, token, d, (double)rms_eps, inv_rho, Z);
+  if (token < n) {
+    double mu, M[3];
+    row_central_sums(part, P, n, batch, token, d, mu, M);
+    pooled_row_sums(mu, M, d, (double)rms_eps, inv_rho, Z);
+  }
   for (int k = 0; k < 4; ++k) {
     const double t = block_sum_256(Z[k], sh);
     if (threadIdx.x == 0) pool_part[(((int64_t)batch * gridDim.x + blockIdx.x) << 2) + k] = t;
@@ -271,14 +264,10 @@ __global__ __launch_bounds__(256) void pooled_stage2_kernel(const double* __rest
 //   alpha' [ c'^3 - m3' - beta' c' ],  alpha' = A / rho^4,  beta' = (beta + tau) rho^2,
 //   m3' = (m3 + tau mu) rho^3,  tau = (1/d) sum_j z [c^3 - m3 - beta c]  (from the row's sums of z^k),
 // so the recompute GEMM and its epilogue are the per-row ones.  grid = (ceil(n/256), batch).
-__global__ __launch_bounds__(256) void pooled_stage3_kernel(const floatx4* __restrict__ part, int P, int n, int d,
-                                                            float rms_eps, const double* __restrict__ gstat,
-                                                            floatx4* __restrict__ coef) {
-  const int batch = blockIdx.y, token = blockIdx.x * 256 + threadIdx.x;
-  if (token >= n) return;
+__device__ __forceinline__ floatx4 pooled_coefficients(double row_mu, const double (&M)[3], int d, float rms_eps, const double* gstat) {
   double Z[4], inv_rho;
-  pooled_row_sums(part, P, n, batch, token, d, (double)rms_eps, inv_rho, Z);
-  const double mu = gstat[4 * batch], m3 = gstat[4 * batch + 1], beta = gstat[4 * batch + 2], A = gstat[4 * batch + 3];
+  pooled_row_sums(row_mu, M, d, (double)rms_eps, inv_rho, Z);
+  const double mu = gstat[0], m3 = gstat[1], beta = gstat[2], A = gstat[3];
   floatx4 c = {0.f, 0.f, 0.f, 0.f};
   if (inv_rho > 0.0 && A != 0.0) {
     const double dd = (double)d, mu2 = mu * mu;
@@ -293,29 +282,55 @@ __global__ __launch_bounds__(256) void pooled_stage3_kernel(const floatx4* __res
     c[2] = (float)((beta + tau) * rho * rho);
     c[3] = (float)((m3 + tau * mu) * rho * rho * rho);
   }
-  coef[(int64_t)batch * n + token] = c;
+  return c;
+}
+__global__ __launch_bounds__(256) void pooled_stage3_kernel(const floatx4* __restrict__ part, int P, int n, int d,
+                                                            float rms_eps, const double* __restrict__ gstat,
+                                                            floatx4* __restrict__ coef) {
+  const int batch = blockIdx.y, token = blockIdx.x * 256 + threadIdx.x;
+  if (token >= n) return;
+  double mu, M[3];
+  row_central_sums(part, P, n, batch, token, d, mu, M);
+  coef[(int64_t)batch * n + token] = pooled_coefficients(mu, M, d, rms_eps, gstat + 4 * batch);
 }
 
-// loss[batch] = (sum of the block partials, fixed order) / n.  grid = batch blocks.
-__global__ __launch_bounds__(256) void finalize_loss_kernel(const double* __restrict__ loss_part,
-                                                            int nblocks, int n,
-                                                            float* __restrict__ loss) {
-  __shared__ double sh[256];
-  const int batch = blockIdx.x;
-  double v = 0.0;
-  for (int i = threadIdx.x; i < nblocks; i += 256) v += loss_part[(int64_t)batch * nblocks + i];
-  const double s = block_sum_256(v, sh);
-  if (threadIdx.x == 0) loss[batch] = (float)(s / (double)n);
-}
+// loss[b] = (sum of the nblocks partials of problem b, fixed order) / n: one workgroup.
+struct LossSum {
+  const double* part = nullptr;
+  int nblocks = 0, n = 0, problems = 0;
+  float* loss = nullptr;
+  __device__ __forceinline__ void run(int b) const {
+    __shared__ double sh[256];
+    double v = 0.0;
+    for (int i = threadIdx.x; i < nblocks; i += 256) v += part[(int64_t)b * nblocks + i];
+    const double s = block_sum_256(v, sh);
+    if (threadIdx.x == 0) loss[b] = (float)(s / (double)n);
+  }
+};
+__global__ __launch_bounds__(256) void finalize_loss_kernel(LossSum sum) { sum.run(blockIdx.x); }
 
-// out[i] = sum_s part[s*stride + i], s ascending.
+// out[i] = sum_s part[s*stride + i], s ascending.  `loss.problems` workgroups more than that take the loss sums, which then are no
+// launch of their own (4 to 5 us behind a full chip).
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restrict__ part,
                                                             int64_t stride, int splits,
-                                                            float* __restrict__ out, int64_t count) {
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < count; i += (int64_t)gridDim.x * 256) {
-    float v = part[i];
-    for (int s = 1; s < splits; ++s) v += part[(int64_t)s * stride + i];
-    out[i] = v;
+                                                            float* __restrict__ out, int64_t count, LossSum loss) {
+  const int workers = (int)gridDim.x - loss.problems;
+  if ((int)blockIdx.x >= workers) {
+    loss.run((int)blockIdx.x - workers);
+    return;
+  }
+  // (count and stride are multiples of 4, the partials 16-byte aligned)
+  const bool vec = (reinterpret_cast<uintptr_t>(out) & 15) == 0;
+  for (int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4; i < count; i += (int64_t)workers * 1024) {
+    floatx4 v = *reinterpret_cast<const floatx4*>(part + i);
+#pragma unroll 4
+    for (int s = 1; s < splits; ++s) v += *reinterpret_cast<const floatx4*>(part + (int64_t)s * stride + i);
+    if (vec) {
+      *reinterpret_cast<floatx4*>(out + i) = v;
+    } else {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) out[i + e] = v[e];
+    }
   }
 }
 

@@ -76,3 +76,30 @@ def test_few_tiles(side, k, d):
     out = kt.kt_fuse_rotation(W, R, side)
     A, B = (W.double(), R.double()) if side == 0 else (R.double().T.contiguous(), W.double())
     assert ((out.double() - A @ B).abs() <= _bound(A, B)).all()
+
+
+@pytest.mark.parametrize("batch,n,d,pad", [(1, 1, 128, 0), (2, 127, 256, 4), (1, 129, 640, 0), (1, 5000, 384, 8), (2, 300, 1152, 0),
+                                           (1, 260, 4224, 0), (1, 70, 8320, 0)])
+@pytest.mark.parametrize("unaligned", [False, True])
+def test_row_loss_and_gradient_fp32(batch, n, d, pad, unaligned):
+    """Rows of every register form (up to 1024, 4096, 8192 values and beyond), padding of the gradient product, wide rows of X, and R
+    that has to be copied."""
+    g = torch.Generator(device="cuda").manual_seed(n + d)
+    X = (torch.randn((batch, n, d + pad), generator=g, device="cuda") + 0.3)[:, :, :d]
+    ldr = d + 1 if unaligned and batch == 1 else d
+    R = torch.randn((batch, d, ldr), generator=g, device="cuda")[:, :, :d] * d ** -0.5
+    dR, kurt = torch.full((batch, d, d), float("nan"), device="cuda"), torch.empty((batch, n), device="cuda")
+    loss = kt.kt_kurtosis_loss_grad(X, R, row_kurt=kurt, dR=dR)
+    only = kt.kt_kurtosis_loss_grad(X, R)
+    assert torch.equal(loss, only)
+    for b in range(batch):
+        x = X[b].double()
+        y = x @ R[b].double()
+        c = y - y.mean(1, keepdim=True)
+        m2, m3, m4 = ((c ** k).mean(1, keepdim=True) for k in (2, 3, 4))
+        kappa = m4 / m2 ** 2
+        G = x.T.contiguous() @ (4.0 / y.numel() / m2 ** 2 * (c ** 3 - m3 - kappa * m2 * c))
+        # y errs by about sqrt(d) 2^-24 of its size, a kurtosis by four times that, dR by sums of n terms on top
+        assert ((kurt[b].double() - kappa[:, 0]).abs() <= 1e-5 * kappa[:, 0]).all()
+        assert abs(loss[b].double() - kappa.mean()) <= 1e-5 * kappa.mean()
+        assert (dR[b].double() - G).norm() <= 1e-5 * G.norm()
