@@ -119,6 +119,9 @@ using TB_M128 = Tile<bf16, 128, 256, 1, 4>;  // features on m, d % 256 != 0
 using TB_N128 = Tile<bf16, 256, 128, 4, 1>;  // features on n, d % 256 != 0
 using TB_128 = Tile<bf16, 128, 128, 2, 2>;   // few tiles
 using TF = Tile<float, 128, 128, 2, 2>;      // fp32 path, every contraction
+using TH_BIG = Tile<_Float16, 256, 256, 2, 2>;  // retraction, d >= 1024 (split3_kernel)
+using TH_128 = Tile<_Float16, 128, 128, 2, 2>;
+using TH_64 = Tile<_Float16, 64, 64, 2, 2>;
 using TF_64 = Tile<float, 64, 64, 2, 2>;     // fp32 path, d x d outputs of few tiles
 
 static inline int64_t ceil_div(int64_t a, int64_t b) { return (a + b - 1) / b; }
@@ -405,20 +408,32 @@ static bool keep_y_recommended(int64_t batch, int64_t n, int64_t d, kt_dtype xdt
 }
 
 struct CayleyPlan {
-  bool split;  // three-term bf16 GEMMs on the bf16 matrix cores instead of fp32 MFMA
+  bool split;  // three-term fp16 products instead of fp32 ones
   size_t o_m, o_b, o_rt, o_zt, o_u0, o_u1, o_delta, o_g2, o_sq, o_scal, total;
   int g2_blocks;  // Cayley Adam: block partials of ||G||^2 per problem
 };
 
-// Large problems run their d^3 GEMMs as three-term bf16 products (about 2^-17 relative
-// per term, 3x the flops at ~16x the rate of the fp32 matrix pipe); small ones, where the
-// step costs microseconds anyway, stay in fp32.
-static bool cayley_use_split(int64_t d) { return d >= 1024 && d % 256 == 0; }
+// From d = 1024 on the d^3 products run as three-term fp16 ones (22 bits of every value, 3x the flops at 16x the rate of the fp32
+// matrix pipe); below, the two launches more and the tripled operands cost more than that gives (steps, us, fp32 / split: d = 640 86 /
+// 100, 896 109 / 120).  Steps of 256 tokens, us, d % 256 != 0 fp32 before / this: d = 1152 274 / 159, 2432 885 / 485, 3712 2706 / 1174.
+// Errors against 64 bits over d = 1024 .. 2432, (lr / 2) ||A|| = 0.003 .. 0.4, full and rank-two gradients, R Haar and near the identity: new R
+// never further off than with fp32 or three-term bf16 products, Cayley Adam's momentum 6.5e-7 .. 1.0e-6 (fp32 8.6e-7 .. 1.25e-6, bf16 5e-6).
+// The fp32 form also serves d % 256 != 0 with a workspace that has no room for the split operands.
+static bool cayley_use_split(int64_t d) { return d >= 1024; }
+// go(tile): 64 x 64 while 128 x 128 ones leave half the CUs without, else the faster of the two large ones (bf16_tile_time).  Same
+// steps, us, 64 / 128 / 256: d = 1024 141 / 164 / 319, 1408 239 / 256 / 491, 1664 249 / 239 / 441, 2048 384 / 303 / 510, 2432 584 / 484 / 600, 3072
+// 1079 / 888 / 828, 3712 1964 / 1419 / 1178.
+template <class Go>
+static auto with_f16_tile(int64_t d, int64_t batch, Go go) {
+  const int64_t t128 = d / 128 * (d / 128) * batch, t256 = ceil_div(d, 256) * ceil_div(d, 256) * batch, slabs = 3 * d / TH_BIG::BK;
+  if (t128 <= kNumCUs / 2) return go(TH_64{});
+  return bf16_tile_time(true, t128, slabs, 0, 0.75) < bf16_tile_time(false, t256, slabs, 10, 0) ? go(TH_128{}) : go(TH_BIG{});
+}
 
-static CayleyPlan plan_cayley(int64_t batch, int64_t d) {
+static CayleyPlan plan_cayley(int64_t batch, int64_t d, bool split) {
   CayleyPlan p;
   Carver c;
-  p.split = cayley_use_split(d);
+  p.split = split;
   const size_t mat = (size_t)batch * d * d * 4;
   const size_t smat = (size_t)batch * d * d * 6;  // [d][3d] bf16
   p.o_m = c.take(mat);  // M = dR R^T; in the fp32 path later reused as the second U buffer
@@ -435,6 +450,12 @@ static CayleyPlan plan_cayley(int64_t batch, int64_t d) {
   p.o_scal = c.take((size_t)batch * 4 * 4);
   p.total = c.off;
   return p;
+}
+
+// The plan for a workspace of `bytes`.
+static CayleyPlan plan_cayley_in(int64_t batch, int64_t d, size_t bytes) {
+  const CayleyPlan p = plan_cayley(batch, d, cayley_use_split(d));
+  return p.split && d % 256 != 0 && bytes < p.total ? plan_cayley(batch, d, false) : p;
 }
 
 struct QuantPlan {
@@ -931,13 +952,14 @@ static kt_status cayley_run(const CayleyPlan& p, char* ws, float* R, const float
   unsigned* delta = reinterpret_cast<unsigned*>(ws + p.o_delta);
   const int D = (int)d;
   const int64_t dd = d * d;
-  // below d = 4096 a 256 x 256 tiling leaves most CUs without a tile: 128 x 128 there; fp32: the tile that fills the chip
-  const bool big = (d / 256) * (d / 256) * batch >= kNumCUs, small = small_f32_tiles(d, batch);
+  const bool small = small_f32_tiles(d, batch);
   // The control words of the iterations lie where Cayley Adam had its block sums of ||G||^2, cleared by the set-up kernel; a
   // tile grid too large for that room takes that of the sums of ||S||^2, behind the kernel that reads them.
-  const int64_t control_words = p.split ? (big ? cayley_control_words<TB_BIG>(d) : cayley_control_words<TB_128>(d))
+  const int64_t control_words = p.split ? with_f16_tile(d, batch, [&](auto t) { return cayley_control_words<decltype(t)>(d); })
                                         : (small ? cayley_control_words<TF_64>(d) : cayley_control_words<TF>(d));
-  const bool late_control = control_words * 4 > (int64_t)p.g2_blocks * 8;
+  const int64_t room = (int64_t)p.g2_blocks * 8 - (p.split ? (int64_t)sizeof(SplitScales) : 0);
+  const bool late_control = control_words * 4 > room;
+  SplitScales* scales = reinterpret_cast<SplitScales*>(ws + p.o_g2 + (late_control ? 0 : batch * room));
   unsigned* control = reinterpret_cast<unsigned*>(ws + (late_control ? p.o_sq : p.o_g2));
   const int ncontrol = late_control ? 0 : (int)control_words;
   auto iterations = [&](auto first_tag, auto tile_tag, auto* U0, auto* U1, const auto* B, int64_t K) -> bool {
@@ -947,6 +969,7 @@ static kt_status cayley_run(const CayleyPlan& p, char* ws, float* R, const float
       e.Rt = Rt; e.Zt = Zt; e.Unew = nullptr; e.Usplit = nullptr; e.delta = delta;
       e.d = D; e.it = 0; e.max_iters = kCayleyMaxIters; e.tol = kCayleyTol;
       e.bscale = adam ? adam->scal : nullptr;
+      e.scales = scales;
       return e;
     };
     for (int it = 0; it < kCayleyOwnLaunches; ++it) {
@@ -963,29 +986,28 @@ static kt_status cayley_run(const CayleyPlan& p, char* ws, float* R, const float
   };
 
   if (p.split) {
-    // three-term bf16 path: operands live as [d][3d] bf16
-    __bf16* Bs = reinterpret_cast<__bf16*>(ws + p.o_b);
-    __bf16* Us[2] = {reinterpret_cast<__bf16*>(ws + p.o_u0), reinterpret_cast<__bf16*>(ws + p.o_u1)};
+    // three-term path: operands live as [d][3d] fp16
+    _Float16* Bs = reinterpret_cast<_Float16*>(ws + p.o_b);
+    _Float16* Us[2] = {reinterpret_cast<_Float16*>(ws + p.o_u0), reinterpret_cast<_Float16*>(ws + p.o_u1)};
     const int64_t sd = 3 * d * d;
-    const unsigned sb = (unsigned)(ceil_div(dd, 256) < 8192 ? ceil_div(dd, 256) : 8192);
-    // M = dR R^T with dR as [hi|hi|lo] (in Us[0]) and R as [hi|lo|hi] (in Us[1])
-    hipLaunchKernelGGL(split3_kernel, dim3(sb, 1, (unsigned)batch), dim3(256), 0, st, G, D, D, Us[0], 0);
-    hipLaunchKernelGGL(split3_kernel, dim3(sb, 1, (unsigned)batch), dim3(256), 0, st, R, D, D, Us[1], 1);
+    const unsigned sb = (unsigned)(ceil_div(dd, 1024) < 2048 ? ceil_div(dd, 1024) : 2048);
+    // M = dR R^T with dR as [hi|hi|lo] (in Us[0]) and R as [hi|lo|hi] (in Us[1]); the partial maxima in the room of M
+    unsigned* maxima = reinterpret_cast<unsigned*>(Mm);
+    hipLaunchKernelGGL(split_max_kernel, dim3(256, 2, (unsigned)batch), dim3(256), 0, st, G, R, dd, maxima);
+    hipLaunchKernelGGL(split3_kernel, dim3(sb, 2, (unsigned)batch), dim3(256), 0, st, G, R, D, maxima, Us[0], Us[1], scales);
     if (!launch_ok()) return fail(KT_ERR_DEVICE, "split launch failed");
-    auto product = [&](const __bf16* A3, const __bf16* B3, float* C, float alpha) -> bool {
-      auto go = [&](auto tile_tag) -> bool {
+    auto product = [&](const _Float16* A3, const _Float16* B3, const float* inv_a, const float* inv_b, float* C, unsigned* max_word, float alpha) -> bool {
+      return with_f16_tile(d, batch, [&](auto tile_tag) -> bool {
         using TL = decltype(tile_tag);
-        EpiStore<TL> e;
-        e.C = C; e.alpha = alpha;
-        e.ldc = d; e.batch_stride = dd; e.split_stride = 0; e.M = D; e.N = D;
+        EpiStoreScaled<TL> e;
+        e.C = C; e.inv_a = inv_a; e.inv_b = inv_b; e.max_word = max_word; e.d = D; e.alpha = alpha;
         return launch_gemm<TL>(A3, 3 * d, sd, D, B3, 3 * d, sd, D, 3 * d, 0, (int)batch, e, st);
-      };
-      return big ? go(TB_BIG{}) : go(TB_128{});
+      });
     };
-    if (!product(Us[0], Us[1], Mm, 1.f)) return fail(KT_ERR_DEVICE, "dR R^T GEMM launch failed");
+    if (!product(Us[0], Us[1], &scales->inv_g, &scales->inv_r, Mm, &scales->max_m, 1.f)) return fail(KT_ERR_DEVICE, "dR R^T GEMM launch failed");
     hipLaunchKernelGGL(cayley_setup_kernel, dim3(D / 32, D / 32, (unsigned)batch), dim3(256), 0, st, Mm, R,
-                       D, half_coef, (float*)nullptr, Rt, Zt, (float*)nullptr, Bs, Us[0], adam ? adam->sq_part : nullptr, delta, kCayleyMaxIters,
-                       control, ncontrol);
+                       D, half_coef, (float*)nullptr, Rt, Zt, (float*)nullptr, Bs, Us[0], scales, adam ? adam->sq_part : nullptr, delta,
+                       kCayleyMaxIters, control, ncontrol);
     if (!launch_ok()) return fail(KT_ERR_DEVICE, "Cayley set-up launch failed");
     if (adam) {
       hipLaunchKernelGGL(adam_scalars2_kernel, dim3((unsigned)batch), dim3(256), 0, st, adam->sq_part,
@@ -993,9 +1015,9 @@ static kt_status cayley_run(const CayleyPlan& p, char* ws, float* R, const float
       if (!launch_ok()) return fail(KT_ERR_DEVICE, "Cayley Adam scalar launch failed");
       // M <- S R = (1/2) S (2 Rt)^T: S sits in Bs as [hi|lo|hi], 2 Rt in Us[0] as [hi|hi|lo]; the same three
       // cross terms come out whichever operand carries which layout
-      if (!product(Bs, Us[0], adam->M, 0.5f)) return fail(KT_ERR_DEVICE, "momentum projection GEMM launch failed");
+      if (!product(Bs, Us[0], &scales->inv_b, &scales->inv_u, adam->M, nullptr, 0.5f)) return fail(KT_ERR_DEVICE, "momentum projection GEMM launch failed");
     }
-    const bool launched = big ? iterations(TB_BIG{}, TB_BIG{}, Us[0], Us[1], Bs, 3 * d) : iterations(TB_128{}, TB_128{}, Us[0], Us[1], Bs, 3 * d);
+    const bool launched = with_f16_tile(d, batch, [&](auto t) { return iterations(t, t, Us[0], Us[1], Bs, 3 * d); });
     if (!launched) return fail(KT_ERR_DEVICE, "Cayley iteration launch failed");
   } else {
   auto product = [&](const float* A, const float* B, float* C) -> bool {  // C = A B^T
@@ -1009,7 +1031,7 @@ static kt_status cayley_run(const CayleyPlan& p, char* ws, float* R, const float
   };
   if (!product(G, R, Mm)) return fail(KT_ERR_DEVICE, "dR R^T GEMM launch failed");
   hipLaunchKernelGGL(cayley_setup_kernel, dim3(D / 32, D / 32, (unsigned)batch), dim3(256), 0, st, Mm, R,
-                     D, half_coef, Bm, Rt, Zt, U[0], (__bf16*)nullptr, (__bf16*)nullptr, adam ? adam->sq_part : nullptr,
+                     D, half_coef, Bm, Rt, Zt, U[0], (_Float16*)nullptr, (_Float16*)nullptr, (SplitScales*)nullptr, adam ? adam->sq_part : nullptr,
                      delta, kCayleyMaxIters, control, ncontrol);
   if (!launch_ok()) return fail(KT_ERR_DEVICE, "Cayley set-up launch failed");
   if (adam) {
@@ -1236,7 +1258,7 @@ size_t kt_workspace_bytes(kt_op op, int64_t batch, int64_t n, int64_t d, kt_dtyp
     case KT_OP_SENSITIVITY:
       return (size_t)kSensBlocks * kSensSteps * 8 + 1024;
     case KT_OP_CAYLEY:
-      return plan_cayley(batch, d).total;
+      return plan_cayley(batch, d, cayley_use_split(d)).total;
     case KT_OP_FAKEQUANT:
       if (n < 1) return 0;
       return plan_quant(batch, n, d, x_dtype).total;
@@ -1309,7 +1331,7 @@ kt_status kt_cayley_step(float* R, const float* dR, void* R_lowp, int64_t batch,
   if (d % 128 != 0) return fail(KT_ERR_BAD_SHAPE, "d = %lld is not a multiple of 128", (long long)d);
   if (d > 16384 || batch > 65535) return fail(KT_ERR_BAD_SHAPE, "size out of range (d <= 16384, batch <= 65535)");
   if (!(lr == lr) || lr - lr != 0.f) return fail(KT_ERR_INVALID_ARG, "lr must be finite");
-  const CayleyPlan p = plan_cayley(batch, d);
+  const CayleyPlan p = plan_cayley_in(batch, d, workspace_bytes);
   kt_status s = check_ws(workspace, workspace_bytes, p.total);
   if (s != KT_OK) return s;
   char* ws = static_cast<char*>(workspace);
@@ -1328,7 +1350,7 @@ kt_status kt_cayley_step_static(float* R, const float* dR, void* R_lowp, int64_t
   if (d % 128 != 0) return fail(KT_ERR_BAD_SHAPE, "d = %lld is not a multiple of 128", (long long)d);
   if (d > 16384 || batch > 65535) return fail(KT_ERR_BAD_SHAPE, "size out of range (d <= 16384, batch <= 65535)");
   if (!(lr == lr) || lr - lr != 0.f) return fail(KT_ERR_INVALID_ARG, "lr must be finite");
-  const size_t need = plan_cayley(batch, d).total;
+  const size_t need = plan_cayley_in(batch, d, kStaticScratchBytes).total;
   if (need > kStaticScratchBytes)
     return fail(KT_ERR_NOT_SUPPORTED,
                 "batch = %lld, d = %lld needs %zu bytes of scratch; the library's static scratch holds %zu "
@@ -1356,7 +1378,7 @@ kt_status kt_cayley_adam_step(float* R, const float* dR, float* M, float* v, int
   if (!(beta1 >= 0.f && beta1 < 1.f) || !(beta2 >= 0.f && beta2 < 1.f))
     return fail(KT_ERR_INVALID_ARG, "beta1 and beta2 must lie in [0, 1)");
   if (!(eps >= 0.f) || !(q > 0.f)) return fail(KT_ERR_INVALID_ARG, "eps must be >= 0 and q > 0");
-  const CayleyPlan p = plan_cayley(batch, d);
+  const CayleyPlan p = plan_cayley_in(batch, d, workspace_bytes);
   kt_status s = check_ws(workspace, workspace_bytes, p.total);
   if (s != KT_OK) return s;
   char* ws = static_cast<char*>(workspace);

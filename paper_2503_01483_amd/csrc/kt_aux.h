@@ -334,35 +334,76 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
   }
 }
 
-// fp32 value -> bf16 head and bf16 tail (x ~ hi + lo to about 2^-17 relative).
-__device__ __forceinline__ void split_bf16(float x, __bf16& hi, __bf16& lo) {
-  hi = (__bf16)x;
-  lo = (__bf16)(x - (float)hi);
+// ---- fp32 products on the 16-bit matrix cores: A B^T ~ A_hi B_hi^T + A_hi B_lo^T + A_lo B_hi^T
+// in fp16 heads and tails, 22 bits of a value, written as ONE GEMM with K tripled: the left operand is stored as [hi | hi | lo]
+// (3 d wide), the right one as [hi | lo | hi].  Why fp16 and not bf16 (16 bits of a value, no scales): the retraction of a rotation
+// near the identity left max |R^T R - I| at 1e-6 with bf16, from the heads' and tails' own rounding.  fp16 has the range of a
+// matrix's entries only around their largest, so each operand is multiplied by a power of two first (exact).
+
+// Largest magnitudes of G (blockIdx.y = 0) and R (1): 256 partial ones each.  grid = (256, 2, problems)
+__global__ __launch_bounds__(256) void split_max_kernel(const float* __restrict__ G, const float* __restrict__ R, int64_t dd,
+                                                        unsigned* __restrict__ part) {
+  const float* in = (blockIdx.y ? R : G) + (int64_t)blockIdx.z * dd;
+  unsigned m = 0u;
+  for (int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4; i < dd; i += 256 * 1024) {
+    const floatx4 v = *reinterpret_cast<const floatx4*>(in + i);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) m = umax(m, abs_bits(v[e]));
+  }
+  __shared__ unsigned sh[4];
+  m = wave_umax(m);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = m;
+  __syncthreads();
+  if (threadIdx.x == 0) part[((int64_t)blockIdx.z * 2 + blockIdx.y) * 256 + blockIdx.x] = umax(umax(sh[0], sh[1]), umax(sh[2], sh[3]));
 }
 
-// Three-term bf16 emulation of an fp32 NT GEMM on the bf16 matrix cores:
-//   A B^T ~ A_hi B_hi^T + A_hi B_lo^T + A_lo B_hi^T
-// written as ONE bf16 GEMM with K tripled: the left operand is stored as [hi | hi | lo]
-// (3*cols wide), the right operand as [hi | lo | hi].  `right` selects the layout.
-// grid-stride over rows*cols elements; grid.z = batch.
-__global__ __launch_bounds__(256) void split3_kernel(const float* __restrict__ in, int rows, int cols,
-                                                     __bf16* __restrict__ out, int right) {
-  const int64_t total = (int64_t)rows * cols;
-  in += (int64_t)blockIdx.z * total;
-  out += (int64_t)blockIdx.z * total * 3;
-  for (int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x; i < total; i += (int64_t)gridDim.x * 256) {
-    const int64_t r = i / cols, c = i - r * cols;
-    __bf16 hi, lo;
-    split_bf16(in[i], hi, lo);
-    __bf16* o = out + r * 3 * cols + c;
-    o[0] = hi;
-    o[cols] = right ? lo : hi;
-    o[2 * (int64_t)cols] = right ? hi : lo;
+// G as the left operand (blockIdx.y = 0), R as the right one (1); the problem's scales.  U = R^T + Z^T: the entries of a
+// row are at most its norm, sqrt(d) max |R| <= 2^7 max |R|, and transients of a contracting iteration at most three times that, so
+// 2^7 above max |R| leaves it below 2^16.  grid = (any, 2, problems)
+__global__ __launch_bounds__(256) void split3_kernel(const float* __restrict__ G, const float* __restrict__ R, int d,
+                                                     const unsigned* __restrict__ part, _Float16* __restrict__ left,
+                                                     _Float16* __restrict__ right, SplitScales* __restrict__ scales) {
+  typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
+  __shared__ unsigned sh[4];
+  const int64_t dd = (int64_t)d * d, bo = (int64_t)blockIdx.z * dd;
+  const bool is_r = blockIdx.y != 0;
+  unsigned most = wave_umax(part[((int64_t)blockIdx.z * 2 + blockIdx.y) * 256 + threadIdx.x]);
+  if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = most;
+  __syncthreads();
+  most = umax(umax(sh[0], sh[1]), umax(sh[2], sh[3]));
+  const float s = split_scale(most, 15);
+  if (blockIdx.x == 0 && threadIdx.x == 0) {
+    SplitScales& o = scales[blockIdx.z];
+    if (is_r) {
+      o.inv_r = 1.f / s;
+      o.u = split_scale(most, 7);
+      o.inv_u = 1.f / o.u;
+    } else {
+      o.inv_g = 1.f / s;
+      o.max_m = 0u;
+    }
+  }
+  const float* in = (is_r ? R : G) + bo;
+  _Float16* out = (is_r ? right : left) + 3 * bo;
+  for (int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4; i < dd; i += (int64_t)gridDim.x * 1024) {
+    const int64_t r = i / d, c = i - r * d;
+    const floatx4 v = *reinterpret_cast<const floatx4*>(in + i);
+    f16x4 hi, lo;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float x = v[e] * s;
+      hi[e] = (_Float16)x;
+      lo[e] = (_Float16)(x - (float)hi[e]);
+    }
+    _Float16* o = out + r * 3 * d + c;
+    *reinterpret_cast<f16x4*>(o) = hi;
+    *reinterpret_cast<f16x4*>(o + d) = is_r ? lo : hi;
+    *reinterpret_cast<f16x4*>(o + 2 * d) = is_r ? hi : lo;
   }
 }
 
 // Cayley set-up: from M = dR R^T build  Bm = (lr/2)(M - M^T)  (exactly skew),
-// Rt = R^T, Zt0 = Rt, U0 = 2 Rt (Bm and U0 either as fp32 or as split bf16 operands); clears the changes and control words.
+// Rt = R^T, Zt0 = Rt, U0 = 2 Rt (Bm and U0 either as fp32 or as split fp16 operands); clears the changes and control words.
 // 32 x 32 tiles; grid = (d/32, d/32, batch).
 __global__ __launch_bounds__(256) void cayley_setup_kernel(const float* __restrict__ Mm,
                                                            const float* __restrict__ R, int d,
@@ -370,8 +411,9 @@ __global__ __launch_bounds__(256) void cayley_setup_kernel(const float* __restri
                                                            float* __restrict__ Rt,
                                                            float* __restrict__ Zt,
                                                            float* __restrict__ U0,
-                                                           __bf16* __restrict__ Bs,
-                                                           __bf16* __restrict__ Us,
+                                                           _Float16* __restrict__ Bs,
+                                                           _Float16* __restrict__ Us,
+                                                           SplitScales* __restrict__ scales,
                                                            double* __restrict__ sq_part,
                                                            unsigned* __restrict__ delta, int ndelta,
                                                            unsigned* __restrict__ control, int ncontrol) {
@@ -385,6 +427,16 @@ __global__ __launch_bounds__(256) void cayley_setup_kernel(const float* __restri
   if (blockIdx.x == 0 && blockIdx.y == 0) {  // this problem's words of cayley_iterate_kernel
     for (int i = threadIdx.x; i < ndelta; i += 256) delta[(int64_t)blockIdx.z * ndelta + i] = 0u;
     for (int i = threadIdx.x; i < ncontrol; i += 256) control[(int64_t)blockIdx.z * ncontrol + i] = 0u;
+  }
+  float b_scale = 1.f, u_scale = 1.f;
+  if (Bs) {  // |B| <= 2 |half_lr| max |M|
+    SplitScales& sc = scales[blockIdx.z];
+    b_scale = split_scale(abs_bits(2.f * half_lr * __uint_as_float(sc.max_m)), 15);
+    u_scale = sc.u;
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
+      sc.b = b_scale;
+      sc.inv_b = 1.f / b_scale;
+    }
   }
   // load the mirrored tile (rows j0.., cols i0..) of M and of R
 #pragma unroll
@@ -405,12 +457,13 @@ __global__ __launch_bounds__(256) void cayley_setup_kernel(const float* __restri
     const float rt = tr[tx][rr];  // R[j0+tx][i0+rr] = Rt[i0+rr][j0+tx]
     Rt[idx] = rt;
     Zt[idx] = rt;
-    if (Bs) {  // split operands of the three-term bf16 GEMM: B as [hi|lo|hi], U as [hi|hi|lo]
+    if (Bs) {  // split operands of the three-term GEMM: B as [hi|lo|hi], U as [hi|hi|lo]
       const int64_t so = 3 * bo + (int64_t)(i0 + rr) * 3 * d + j0 + tx;
-      __bf16 hi, lo;
-      split_bf16(b, hi, lo);
+      const float x = b * b_scale, y = 2.f * rt * u_scale;
+      _Float16 hi = (_Float16)x, lo = (_Float16)(x - (float)hi);
       Bs[so] = hi; Bs[so + d] = lo; Bs[so + 2 * d] = hi;
-      split_bf16(2.f * rt, hi, lo);
+      hi = (_Float16)y;
+      lo = (_Float16)(y - (float)hi);
       Us[so] = hi; Us[so + d] = hi; Us[so + 2 * d] = lo;
     } else {
       Bm[idx] = b;

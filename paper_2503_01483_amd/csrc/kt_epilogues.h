@@ -323,6 +323,59 @@ __device__ __forceinline__ void workgroup_umax(unsigned v, unsigned* word) {
   }
 }
 
+// ---- fp32 products of the retraction from fp16 heads and tails (split3_kernel) --------------------
+// Words of one problem: the operands' scales are powers of two, chosen on the device from their largest magnitudes.
+struct SplitScales {
+  float inv_g, inv_r;  // 1 / scale of the two operands of G R^T
+  unsigned max_m;      // bit pattern of max |G R^T|
+  float u, inv_u;      // scale of U
+  float b, inv_b;      // scale of B
+  float unused;
+};
+// The power of two that takes magnitudes up to that of `bits` (a non-negative float's bit pattern) below 2^exponent; 1 for zero, infinities
+// and NaN, which come out as they are.
+__device__ __forceinline__ float split_scale(unsigned bits, int exponent) {
+  const int e = (int)(bits >> 23);
+  if (bits == 0u || e >= 255) return 1.f;
+  int k = exponent - (e - 126);
+  k = k > 100 ? 100 : k;
+  return __uint_as_float((unsigned)(k + 127) << 23);
+}
+
+// C = alpha * acc / (the two scales), and optionally the largest magnitude of it.  d x d, rows of d.
+template <class TL>
+struct EpiStoreScaled : EpiBase {
+  float* C;
+  const float *inv_a, *inv_b;  // of problem 0
+  unsigned* max_word;          // of problem 0, or null
+  int d;
+  float alpha;
+  static constexpr bool kSwap = true;
+  __device__ __forceinline__ void operator()(floatx4 (&acc)[TL::MB][TL::NB], int batch, int, int, int, int m0, int n0) const {
+    constexpr int kWords = sizeof(SplitScales) / 4;
+    const Frag<TL> f;
+    const float sa = alpha * inv_a[kWords * batch], sb = inv_b[kWords * batch];
+    float* base = C + (int64_t)batch * d * d;
+    unsigned most = 0u;
+#pragma unroll
+    for (int mb = 0; mb < TL::MB; ++mb)
+#pragma unroll
+      for (int nb = 0; nb < TL::NB; ++nb) {
+        const int m = m0 + f.m_row(mb), n = n0 + f.n_quad(nb);
+        if (m < d && n < d) {
+          floatx4 v;
+#pragma unroll
+          for (int r = 0; r < 4; ++r) {
+            v[r] = acc[mb][nb][r] * sa * sb;
+            most = umax(most, abs_bits(v[r]));
+          }
+          *reinterpret_cast<floatx4*>(base + (int64_t)m * d + n) = v;
+        }
+      }
+    if (max_word) workgroup_umax(most, max_word + kWords * batch);
+  }
+};
+
 // ---- Cayley fixed point, in transposed space ---------------------------------------
 // acc = U_k * B^T.  Zt_new = Rt - acc;  U_{k+1} = Rt + Zt_new;
 // delta[it] = max |Zt_new - Zt_old| (bit pattern of a non-negative float, max is
@@ -361,15 +414,16 @@ __device__ __forceinline__ bool cayley_converged(const unsigned* dl, int k, floa
                                k > 1 ? __uint_as_float(dl[k - 2]) : 0.f, k > 1 ? 2 : k, tol);
 }
 
-// Unew is written as fp32, or (Usplit != null) as the [hi | hi | lo] bf16 operand of the
-// three-term bf16 GEMM that runs the next iteration.  As the epilogue of a launch of its own it returns at once when iteration
+// Unew is written as fp32, or (Usplit != null) as the [hi | hi | lo] fp16 operand of the
+// three-term GEMM that runs the next iteration.  As the epilogue of a launch of its own it returns at once when iteration
 // it - 1 or an earlier one has converged.  (cayley_iterate_kernel sets `it` and the two targets.)
 template <class TL>
 struct EpiCayleyIter {
   const float* Rt;
   float* Zt;
   float* Unew;
-  __bf16* Usplit;
+  _Float16* Usplit;
+  const SplitScales* scales = nullptr;  // with Usplit: the product is scaled, Usplit has to be
   unsigned* delta;  // [batch][max_iters]
   int d, it, max_iters;
   float tol;
@@ -385,7 +439,12 @@ struct EpiCayleyIter {
                                              int, int, int m0, int n0) const {
     const Frag<TL> f;
     const int64_t bo = (int64_t)batch * d * d;
-    const float bs = bscale ? bscale[4 * batch + 3] : 1.f;
+    float bs = bscale ? bscale[4 * batch + 3] : 1.f, inv_b = 1.f, us = 1.f;
+    if constexpr (sizeof(typename TL::T) == 2) {
+      us = scales[batch].u;
+      bs *= scales[batch].inv_u;
+      inv_b = scales[batch].inv_b;
+    }
     unsigned dmax = 0u;
 #pragma unroll
     for (int mb = 0; mb < TL::MB; ++mb)
@@ -399,23 +458,24 @@ struct EpiCayleyIter {
           floatx4 z, u;
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
-            z[r] = rt[r] - bs * acc[mb][nb][r];
+            z[r] = rt[r] - (sizeof(typename TL::T) == 2 ? bs * acc[mb][nb][r] * inv_b : bs * acc[mb][nb][r]);
             dmax = umax(dmax, abs_bits(z[r] - zo[r]));
             u[r] = rt[r] + z[r];
           }
           *reinterpret_cast<floatx4*>(Zt + idx) = z;
-          if (Usplit) {
-            typedef __bf16 bf16x4 __attribute__((ext_vector_type(4)));
+          if constexpr (sizeof(typename TL::T) == 2) {
+            typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
             const int64_t so = 3 * bo + (int64_t)m * 3 * d + n;
-            bf16x4 hi, lo;
+            f16x4 hi, lo;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-              hi[r] = (__bf16)u[r];
-              lo[r] = (__bf16)(u[r] - (float)hi[r]);
+              const float x = us * u[r];
+              hi[r] = (_Float16)x;
+              lo[r] = (_Float16)(x - (float)hi[r]);
             }
-            *reinterpret_cast<bf16x4*>(Usplit + so) = hi;
-            *reinterpret_cast<bf16x4*>(Usplit + so + d) = hi;
-            *reinterpret_cast<bf16x4*>(Usplit + so + 2 * d) = lo;
+            *reinterpret_cast<f16x4*>(Usplit + so) = hi;
+            *reinterpret_cast<f16x4*>(Usplit + so + d) = hi;
+            *reinterpret_cast<f16x4*>(Usplit + so + 2 * d) = lo;
           } else {
             *reinterpret_cast<floatx4*>(Unew + idx) = u;
           }

@@ -64,6 +64,13 @@ struct Mma<__bf16> {
 };
 
 template <>
+struct Mma<_Float16> {
+  static __device__ __forceinline__ void run(const intx4& a, const intx4& b, floatx4& c) {
+    asm volatile("v_mfma_f32_16x16x32_f16 %0, %1, %2, %0" : "+a"(c) : "v"(a), "v"(b));
+  }
+};
+
+template <>
 struct Mma<float> {
   static __device__ __forceinline__ void run(const intx4& a, const intx4& b, floatx4& c) {
     const floatx4 fa = __builtin_bit_cast(floatx4, a);
