@@ -118,6 +118,7 @@ using TB_BIG = Tile<bf16, 256, 256, 2, 2>;
 using TB_M128 = Tile<bf16, 128, 256, 1, 4>;  // features on m, d % 256 != 0
 using TB_N128 = Tile<bf16, 256, 128, 4, 1>;  // features on n, d % 256 != 0
 using TB_128 = Tile<bf16, 128, 128, 2, 2>;   // few tiles
+using TB_64 = Tile<bf16, 64, 64, 2, 2>;      // fewer
 using TF = Tile<float, 128, 128, 2, 2>;      // fp32 path, every contraction
 using TH_BIG = Tile<_Float16, 256, 256, 2, 2>;  // retraction, d >= 1024 (split3_kernel)
 using TH_128 = Tile<_Float16, 128, 128, 2, 2>;
@@ -732,6 +733,9 @@ static bool launch_skinny(const bf16* X, int64_t ldx, const TR* R, int64_t ldr, 
 // The 256 x 128 tile of d % 256 != 0 wins in one round over the CUs or two nearly full ones, two 128 x 128 on a CU in any
 // other number: 144 tiles 35.5 / 37.1, 240: 50.7 / 53.1, 288: 68.6 / 59.0, 320: 50.7 / 43.9, 384: 50.6 / 46.0,
 // 432: 72.3 / 73.6, 480: 88.2 / 91.0, 576: 92.2 / 88.1, 1152: 176 / 164.
+// Half the CUs or fewer with a 128 x 128 tile: 64 x 64 ones.  us, 128 / 64: d = 256, n = 200 18.8 / 15.4; 1024, 1000 20.4 / 17.7; 1024, 2000
+// (128 tiles) 24.2 / 23.6; 2048, 200 31.4 / 28.0; 4096, 65 54.3 / 50.2; 4096, 400 (128) 57.6 / 55.1; 4096, 600 (160) 60.0 / 62.7; 2048, 1400
+// (176) 34.2 / 35.9.
 template <typename T, class TL>
 static bool launch_rows_gemm(const T* X, int64_t ldx, int64_t x_batch_stride, const T* R, int64_t ldr, bool in_place, int64_t problems,
                              int64_t rows, int64_t d, float* Y, int64_t y_batch_stride, hipStream_t st) {
@@ -748,6 +752,7 @@ static bool launch_rows_gemm(const T* X, int64_t ldx, int64_t x_batch_stride, co
   if constexpr (sizeof(T) == 4) {
     return with_f32_tile(rows, d, problems, go);
   } else {
+    if (ceil_div(rows, 128) * (d / 128) * problems <= kNumCUs / 2) return go(TB_64{});
     const int64_t tiles = ceil_div(rows, TL::BM) * ceil_div(d, TL::BN) * problems;
     bool small;
     if (TL::BN == 128) small = tiles <= kNumCUs / 2 || (tiles > kNumCUs && (tiles > 2 * kNumCUs || 6 * tiles < 5 * 2 * kNumCUs));

@@ -58,3 +58,16 @@ def test_tiles(batch, d, n, pooled):
         if k is not None:
             assert ((kurt[b].double() - k).abs() <= 1e-4 * k).all()
         assert (dR[b].double() - G).norm() <= 2.0 ** -8 * G.norm()
+
+
+@pytest.mark.parametrize("batch,n,d", [(1, 65, 256), (2, 67, 384), (1, 129, 4096), (1, 500, 1024), (1, 512, 4096), (1, 513, 4096)])
+def test_rotated_rows_of_few_tiles(batch, n, d):
+    """64 x 64 tiles of bf16 rows, on either side of their last size; fp32 sums of d exact products."""
+    g = torch.Generator(device="cuda").manual_seed(n + d)
+    X = torch.randn((batch, n, d + 8), generator=g, device="cuda").bfloat16()[:, :, :d]
+    R = torch.randn((batch, d, d), generator=g, device="cuda") * d ** -0.5
+    Y = torch.full((batch, n, d), float("nan"), device="cuda")
+    kt.kt_rotate_quant_metrics(X, R, Y=Y)
+    for b in range(batch):
+        x, r = X[b].double(), R[b].bfloat16().double()
+        assert ((Y[b].double() - x @ r).abs() <= d * 2.0 ** -24 * (x.abs() @ r.abs())).all()
