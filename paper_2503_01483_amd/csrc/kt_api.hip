@@ -1159,8 +1159,7 @@ static kt_status launch_hadamard_onepass(const bf16* X, int64_t ldx, bf16* Y, in
   return KT_OK;
 }
 
-static kt_status run_hadamard_onepass(const bf16* X, int64_t ldx, bf16* Y, int64_t ldy, const int8_t* signs, int64_t n,
-                                      int64_t d, int m, int kind, int log2j, int logp, hipStream_t st) {
+static HadamardFactor hadamard_factor(int m, int kind, int log2j) {
   HadamardFactor f;
   f.m = m; f.kind = kind; f.log2j = log2j;
   f.h = kind == 2 ? m / 2 : m;
@@ -1168,9 +1167,45 @@ static kt_status run_hadamard_onepass(const bf16* X, int64_t ldx, bf16* Y, int64
   f.squares[0] = f.squares[1] = 0;
   if (kind != 0)
     for (int t = 1; t < f.q; ++t) f.squares[t * t % f.q >> 6] |= 1ull << (t * t % f.q & 63);
+  return f;
+}
+static kt_status run_hadamard_onepass(const bf16* X, int64_t ldx, bf16* Y, int64_t ldy, const int8_t* signs, int64_t n,
+                                      int64_t d, int m, int kind, int log2j, int logp, hipStream_t st) {
+  const HadamardFactor f = hadamard_factor(m, kind, log2j);
   if (d > 16384) return launch_hadamard_onepass<7, 8>(X, ldx, Y, ldy, signs, n, d, f, st);
   return logp == 6 ? launch_hadamard_onepass<6, 4>(X, ldx, Y, ldy, signs, n, d, f, st)
                    : launch_hadamard_onepass<7, 4>(X, ldx, Y, ldy, signs, n, d, f, st);
+}
+
+// fp32 rows with m > 1 in one pass (hadamard_f32_onepass_kernel): LDS for a row and H_m, 0 where two kernels are faster or they do not fit a
+// workgroup.  us, two kernels / one pass: m = 4, 8: d = 8192, 1 row 14.1 / 12.3, 300 19.6 / 11.7, 8000 228 / 195; 16384, 8000 440 / 358; 32768, 16 14.3 /
+// 15.7, 100 21.4 / 16.9, 8000 873 / 730.  m = 108 (13824): 1 51.6 / 51.0, 1000 226 / 177, 8000 1543 / 1376.  m = 12, 20: 5120, 16 15.9 / 11.5, 1000
+// 34.3 / 21.7, 8000 153 / 154; 6144, 8000 149 / 161.  m = 28: 14336, 16 17.4 / 19.1, 100 20.6 / 19.8, 1000 55.4 / 49.1, 8000 391 / 385; 28672, 16 17.8 /
+// 22.1, 8000 775 / 874.
+static size_t hadamard_f32_lds(int64_t n, int64_t d, int m, int kind) {
+  const size_t bytes = ((size_t)ceil_div(d, kHadChunk) * kHadRegion + (size_t)m * m) * 4;
+  if (d > 8 * kHadChunk || bytes > 160 * 1024) return 0;
+  bool faster;
+  if (kind == 0) faster = d <= 4 * kHadChunk || n >= 64;
+  else if (m >= 64) faster = true;
+  else faster = n <= 4 * kNumCUs && (d <= 2 * kHadChunk || (d <= 4 * kHadChunk && n >= 64));
+  return faster ? bytes : 0;
+}
+static kt_status launch_hadamard_f32_onepass(const float* X, int64_t ldx, float* Y, int64_t ldy, const int8_t* signs, int64_t n, int64_t d,
+                                             int m, int p2, int kind, size_t lds, hipStream_t st) {
+  const HadamardFactor f = hadamard_factor(m, kind, 0);
+  int log2p = 0;
+  while ((1 << log2p) < p2) ++log2p;
+  auto go = [&](auto kernel, int waves) -> kt_status {
+    if (!ensure_dynamic_lds(reinterpret_cast<const void*>(kernel), lds))
+      return fail(KT_ERR_DEVICE, "the Hadamard kernel needs %zu bytes of LDS per workgroup", lds);
+    const int64_t wgs = (int64_t)kNumCUs * (160 * 1024 / lds < 2 ? 1 : 2);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(n < wgs ? n : wgs)), dim3(64 * waves), lds, st, X, ldx, Y, ldy, signs, n, (int)d, p2, log2p,
+                       1.0f / sqrtf((float)d), f);
+    if (!launch_ok()) return fail(KT_ERR_DEVICE, "Hadamard launch failed");
+    return KT_OK;
+  };
+  return d <= 4 * kHadChunk ? go(&hadamard_f32_onepass_kernel<4>, 4) : go(&hadamard_f32_onepass_kernel<8>, 8);
 }
 
 template <typename T>
@@ -1181,6 +1216,11 @@ static kt_status run_hadamard(const void* X, int64_t ldx, void* Y, int64_t ldy, 
   int log2j = 0, logp = 0;
   if (sizeof(T) == 2 && m > 1 && hadamard_onepass_plan(n, d, m, p2, kind, &log2j, &logp))
     return run_hadamard_onepass(static_cast<const bf16*>(X), ldx, static_cast<bf16*>(Y), ldy, signs, n, d, m, kind, log2j, logp, st);
+  if constexpr (sizeof(T) == 4) {
+    const size_t lds = m > 1 ? hadamard_f32_lds(n, d, m, kind) : 0;
+    if (lds && (!signs || (reinterpret_cast<uintptr_t>(signs) & 3) == 0))
+      return launch_hadamard_f32_onepass(static_cast<const float*>(X), ldx, static_cast<float*>(Y), ldy, signs, n, d, m, p2, kind, lds, st);
+  }
   const float scale = 1.0f / sqrtf((float)d);
   // the Sylvester factor on the m segments of every row (p2 consecutive elements at a * p2), X -> Y:
   // contiguous rows are one matrix of n * m short rows; otherwise one launch per segment

@@ -467,6 +467,96 @@ __device__ __forceinline__ int hadamard_negative(const HadamardFactor& f, int a,
   return neg;
 }
 
+// ---- fp32 rows of H_m (x) S_p2 in one pass: a workgroup per row, the row in LDS ------------------------
+// The Sylvester factor as in hadamard_rows_kernel (a wave per 4096 elements, the same layout, steps 1 to 3), then H_m straight from
+// LDS to memory as in hadamard_cross_kernel; the loads of the next row are in flight meanwhile.  The order of every sum
+// is that of the two kernels.  Where it is taken it saves a launch and half the traffic; m products per element on the vector ALU, with
+// two workgroups on a CU (the registers of 64 values and of the next row), keep it from HBM's rate (hadamard_f32_lds has the figures).
+// Three workgroups a CU spilled 68 registers and lost 20 to 40 %.
+// Needs d <= 4096 WAVES and LDS for the row (padded, whole blocks of 4096) and H_m as floats.
+template <int WAVES>
+__global__ __launch_bounds__(64 * WAVES) void hadamard_f32_onepass_kernel(const float* X, int64_t ldx, float* Y, int64_t ldy,
+                                                                          const int8_t* __restrict__ signs, int64_t n, int d, int p2,
+                                                                          int log2p, float scale, HadamardFactor f) {
+  constexpr int NT = 64 * WAVES, NLD = 16;  // 16-byte loads per thread for 4096 elements a wave
+  extern __shared__ __align__(16) float row_lds[];
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), m = f.m;
+  const int blocks = (d + kHadChunk - 1) / kHadChunk;
+  float* S = row_lds + blocks * kHadRegion;
+  for (int i = tid; i < m * m; i += NT) S[i] = hadamard_negative(f, i / m, i % m) ? -1.f : 1.f;
+  floatx4 nxt[NLD];
+  auto request = [&](int64_t row) __attribute__((always_inline)) {
+#pragma unroll
+    for (int t = 0; t < NLD; ++t) {
+      const int i = (t * NT + tid) * 4;
+      if (row < n && i < d) nxt[t] = *reinterpret_cast<const floatx4*>(X + row * ldx + i);
+    }
+  };
+  request(blockIdx.x);
+#pragma unroll 1
+  for (int64_t row = blockIdx.x; row < n; row += gridDim.x) {
+#pragma unroll
+    for (int t = 0; t < NLD; ++t) {
+      const int i = (t * NT + tid) * 4;
+      if (i < d) {
+        floatx4 v = nxt[t];
+        if (signs) {
+          const char4 sg = *reinterpret_cast<const char4*>(signs + i);
+          v = floatx4{v[0] * (float)sg.x, v[1] * (float)sg.y, v[2] * (float)sg.z, v[3] * (float)sg.w};
+        }
+        *reinterpret_cast<floatx4*>(row_lds + i + 4 * (i >> 6)) = v;
+      }
+    }
+    __syncthreads();
+    request(row + gridDim.x);
+    if (wave < blocks) {  // (what lies behind the row in its last block never meets the row: other segments)
+      float* lds = row_lds + wave * kHadRegion;
+      float a[64];
+#pragma unroll
+      for (int g = 0; g < 16; ++g) {
+        const floatx4 q = *reinterpret_cast<const floatx4*>(lds + 68 * lane + 4 * g);
+        a[4 * g] = q[0]; a[4 * g + 1] = q[1]; a[4 * g + 2] = q[2]; a[4 * g + 3] = q[3];
+      }
+      had_butterflies<6>(a, 0);
+      had_lds_fence();
+#pragma unroll
+      for (int g = 0; g < 16; ++g)
+        *reinterpret_cast<floatx4*>(lds + 68 * lane + 4 * g) = floatx4{a[4 * g], a[4 * g + 1], a[4 * g + 2], a[4 * g + 3]};
+      had_lds_fence();
+#pragma unroll
+      for (int j = 0; j < 64; ++j) a[j] = lds[lane + 68 * j];
+      static_for<6>([&](auto s_c) __attribute__((always_inline)) {
+        constexpr int s = decltype(s_c)::value;
+        if (6 + s < log2p) had_butterflies<1>(a, s);
+      });
+      had_lds_fence();
+#pragma unroll
+      for (int j = 0; j < 64; ++j) lds[lane + 68 * j] = a[j] * scale;
+    }
+    __syncthreads();
+    // 128 columns of a segment (two per lane) and four outputs at a time
+    const int quads = m >> 2, items = (p2 >> 7) * quads;
+    for (int item = wave; item < items; item += WAVES) {
+      const int g = item / quads, qd = item - g * quads, c = 128 * g + 2 * lane;
+      float acc[4][2] = {{0.f, 0.f}, {0.f, 0.f}, {0.f, 0.f}, {0.f, 0.f}};
+#pragma unroll 4
+      for (int k = 0; k < m; ++k) {
+        const int i = k * p2 + c;
+        const float2 xv = *reinterpret_cast<const float2*>(row_lds + i + 4 * (i >> 6));
+        const floatx4 sv = *reinterpret_cast<const floatx4*>(S + k * m + 4 * qd);
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+          acc[j][0] = fmaf(sv[j], xv.x, acc[j][0]);
+          acc[j][1] = fmaf(sv[j], xv.y, acc[j][1]);
+        }
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) *reinterpret_cast<float2*>(Y + row * ldy + (4 * qd + j) * p2 + c) = make_float2(acc[j][0], acc[j][1]);
+    }
+    __syncthreads();
+  }
+}
+
 // The rows for `signs` that are not all +-1 (0 to drop a channel, say): a sum of M products per lane, its column, and wave,
 // its output, in fp32; the S_P factor across the lanes.  Correct, not fast: x times such a factor is no bf16 number.
 template <int LOGP, int WAVES>

@@ -113,3 +113,24 @@ def test_factors_that_are_not_signs_in_place():
     kt.kt_hadamard_rows(X, signs=f, out=X)
     torch.cuda.synchronize()
     assert torch.equal(X, Y)
+
+
+# fp32 rows: one kernel or two by size (orders 4, 8, 12, 20, 28 and 108, one row to more than two a workgroup, the last block of 4096 partly
+# filled), in place and between wide rows, with signs that are not +-1
+@pytest.mark.parametrize("n,d", [(1, 1536), (1, 5120), (600, 5120), (1025, 1536), (3, 8192), (530, 8192), (2, 13824), (63, 14336), (64, 14336), (2, 16384),
+                                 (63, 32768), (64, 32768)])
+@pytest.mark.parametrize("in_place", [False, True])
+def test_fp32_rows(n, d, in_place):
+    m, p2, kind = oracle.hadamard_factor(d)
+    g = torch.Generator(device="cuda").manual_seed(n + d)
+    X = torch.randn((n, d + 4), generator=g, device="cuda")[:, :d]
+    signs = torch.randint(-1, 2, (d,), generator=g, device="cuda").to(torch.int8)
+    # the columns of H_d from transforms of unit rows are the oracle's business (test_gpu_hadamard.py); here: few rows against it
+    rows = sorted({0, n // 2, n - 1})
+    ref = oracle.hadamard_rows(X[rows].cpu().double().numpy(), signs.cpu().double().numpy())
+    out = X if in_place else torch.full((n, d + 8), float("nan"), device="cuda")[:, :d]
+    kt.kt_hadamard_rows(X, signs=signs, out=out)
+    got = out[rows].cpu().double().numpy()
+    # d values in a tree of depth log2 p2 and a sum of m: 2^-24 of the row's norm per level
+    assert (np.abs(got - ref) <= 1e-5 * np.linalg.norm(ref, axis=1, keepdims=True) + 1e-30).all()
+    assert torch.isfinite(out).all()
