@@ -78,7 +78,8 @@ const char* kt_last_error(void);
 /* Scratch bytes the given operation needs for these sizes (0 on bad sizes).
  * For KT_OP_CAYLEY `n` is ignored.  KT_OP_LOSS_GRAD / KT_OP_POOLED_LOSS_GRAD: the recommended size
  * (with room to keep Y, see kt_kurtosis_loss_grad); KT_OP_LOSS_GRAD_RECOMPUTE /
- * KT_OP_POOLED_LOSS_GRAD_RECOMPUTE: the least those entry points accept.  Host call, launches nothing. */
+ * KT_OP_POOLED_LOSS_GRAD_RECOMPUTE: the least those entry points accept (fp32: the same size, Y lives
+ * where dL/dY goes).  Host call, launches nothing. */
 size_t kt_workspace_bytes(kt_op op, int64_t batch, int64_t n, int64_t d, kt_dtype x_dtype);
 
 /*
@@ -161,7 +162,7 @@ kt_status kt_pooled_kurtosis_loss_grad(const void* X, int64_t ldx, const void* R
  * contracts when (lr/2)||A||_2 < 1 and the library enqueues at most 32 iterations (enough up to
  * about 0.55).  No learning-rate
  * clamp is applied: the caller chooses lr.  For d >= 1024 the d^3 products run on the
- * bf16 matrix cores as three-term bf16 products (about 2^-17 relative per term).
+ * 16-bit matrix cores as three-term fp16 products (heads and tails, 22 bits of a value).
  *
  *  R        [batch][d][d] fp32, in/out (master copy).  d multiple of 128, <= 16384.
  *  dR       [batch][d][d] fp32.  R and dR 16-byte aligned.

@@ -393,7 +393,7 @@ struct EpiStoreScaled : EpiBase {
 //    confirm it, for slow contractions it asks for more than d_k <= tol: what is left of the series then
 //    still matters for max |R^T R - I|;
 //  - the rounding floor: the change is small (within 64 tolerances) and has stopped shrinking over both of
-//    the last two steps (for the three-term bf16 products the floor lies at a few 1e-7 and would never pass
+//    the last two steps (for the three-term products the floor lies at a few 1e-7 and would never pass
 //    a fixed fp32-sized tolerance).
 // d1, d0, d00: changes of iterations k, k-1, k-2; nprev: how many of d0, d00 exist (0, 1 or 2).
 __device__ __forceinline__ bool cayley_converged_hist(float d1, float d0, float d00, int nprev, float tol) {
