@@ -100,8 +100,8 @@ size_t kt_workspace_bytes(kt_op op, int64_t batch, int64_t n, int64_t d, kt_dtyp
  * the workspace handed in has the room (kt_workspace_bytes(KT_OP_LOSS_GRAD) asks for it while Y is at
  * most 64 GiB), the second otherwise (KT_OP_LOSS_GRAD_RECOMPUTE is the smaller size).  Both give the
  * same bits: dL/dY comes from the same fp32 accumulators through the same arithmetic.  dL/dY exists
- * only as the token-minor scratch operand of the last GEMM (which reads X itself in place when X is
- * bf16 and d a multiple of 256, through a token-minor copy otherwise).
+ * only as the token-minor scratch operand of the last GEMM, which reads X itself in place.  fp32 X: Y is
+ * written as rows, dL/dY over it, and the two sizes are one.
  *
  *  X        [batch][n][ldx] row-major, x_dtype (KT_BF16, or KT_F32 for the fp32 path);
  *           d <= ldx <= 2^22, rows 16-byte aligned (ldx % 8 == 0 for bf16, % 4 for fp32).
