@@ -1001,15 +1001,15 @@ static kt_status cayley_run(const CayleyPlan& p, char* ws, float* R, const float
     hipLaunchKernelGGL(split_max_kernel, dim3(256, 2, (unsigned)batch), dim3(256), 0, st, G, R, dd, maxima);
     hipLaunchKernelGGL(split3_kernel, dim3(sb, 2, (unsigned)batch), dim3(256), 0, st, G, R, D, maxima, Us[0], Us[1], scales);
     if (!launch_ok()) return fail(KT_ERR_DEVICE, "split launch failed");
-    auto product = [&](const _Float16* A3, const _Float16* B3, const float* inv_a, const float* inv_b, float* C, unsigned* max_word, float alpha) -> bool {
+    auto product = [&](const _Float16* A3, const _Float16* B3, const int* exp_a, const int* exp_b, float* C, unsigned* max_word, int shift) -> bool {
       return with_f16_tile(d, batch, [&](auto tile_tag) -> bool {
         using TL = decltype(tile_tag);
         EpiStoreScaled<TL> e;
-        e.C = C; e.inv_a = inv_a; e.inv_b = inv_b; e.max_word = max_word; e.d = D; e.alpha = alpha;
+        e.C = C; e.exp_a = exp_a; e.exp_b = exp_b; e.max_word = max_word; e.d = D; e.shift = shift;
         return launch_gemm<TL>(A3, 3 * d, sd, D, B3, 3 * d, sd, D, 3 * d, 0, (int)batch, e, st);
       });
     };
-    if (!product(Us[0], Us[1], &scales->inv_g, &scales->inv_r, Mm, &scales->max_m, 1.f)) return fail(KT_ERR_DEVICE, "dR R^T GEMM launch failed");
+    if (!product(Us[0], Us[1], &scales->g, &scales->r, Mm, &scales->max_m, 0)) return fail(KT_ERR_DEVICE, "dR R^T GEMM launch failed");
     hipLaunchKernelGGL(cayley_setup_kernel, dim3(D / 32, D / 32, (unsigned)batch), dim3(256), 0, st, Mm, R,
                        D, half_coef, (float*)nullptr, Rt, Zt, (float*)nullptr, Bs, Us[0], scales, adam ? adam->sq_part : nullptr, delta,
                        kCayleyMaxIters, control, ncontrol);
@@ -1020,7 +1020,7 @@ static kt_status cayley_run(const CayleyPlan& p, char* ws, float* R, const float
       if (!launch_ok()) return fail(KT_ERR_DEVICE, "Cayley Adam scalar launch failed");
       // M <- S R = (1/2) S (2 Rt)^T: S sits in Bs as [hi|lo|hi], 2 Rt in Us[0] as [hi|hi|lo]; the same three
       // cross terms come out whichever operand carries which layout
-      if (!product(Bs, Us[0], &scales->inv_b, &scales->inv_u, adam->M, nullptr, 0.5f)) return fail(KT_ERR_DEVICE, "momentum projection GEMM launch failed");
+      if (!product(Bs, Us[0], &scales->b, &scales->u, adam->M, nullptr, -1)) return fail(KT_ERR_DEVICE, "momentum projection GEMM launch failed");
     }
     const bool launched = with_f16_tile(d, batch, [&](auto t) { return iterations(t, t, Us[0], Us[1], Bs, 3 * d); });
     if (!launched) return fail(KT_ERR_DEVICE, "Cayley iteration launch failed");

@@ -335,10 +335,11 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
 }
 
 // ---- fp32 products on the 16-bit matrix cores: A B^T ~ A_hi B_hi^T + A_hi B_lo^T + A_lo B_hi^T
-// in fp16 heads and tails, 22 bits of a value, written as ONE GEMM with K tripled: the left operand is stored as [hi | hi | lo]
+// in fp16 heads and tails (split_f16: 22 bits of a value down to 2^-17 of the operand's largest), written as ONE GEMM with K tripled: the left operand is stored as [hi | hi | lo]
 // (3 d wide), the right one as [hi | lo | hi].  Why fp16 and not bf16 (16 bits of a value, no scales): the retraction of a rotation
 // near the identity left max |R^T R - I| at 1e-6 with bf16, from the heads' and tails' own rounding.  fp16 has the range of a
-// matrix's entries only around their largest, so each operand is multiplied by a power of two first (exact).
+// matrix's entries only around their largest, so each operand is multiplied by a power of two first (exact).  What lies 2^-40 below the
+// largest is gone: it shows where a product keeps such rows apart, in the momentum of Cayley Adam at R = I (elsewhere R mixes the rows).
 
 // Largest magnitudes of G (blockIdx.y = 0) and R (1): 256 partial ones each.  grid = (256, 2, problems)
 __global__ __launch_bounds__(256) void split_max_kernel(const float* __restrict__ G, const float* __restrict__ R, int64_t dd,
@@ -371,15 +372,14 @@ __global__ __launch_bounds__(256) void split3_kernel(const float* __restrict__ G
   if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = most;
   __syncthreads();
   most = umax(umax(sh[0], sh[1]), umax(sh[2], sh[3]));
-  const float s = split_scale(most, 15);
+  const int k = split_exponent(most, 15);
   if (blockIdx.x == 0 && threadIdx.x == 0) {
     SplitScales& o = scales[blockIdx.z];
     if (is_r) {
-      o.inv_r = 1.f / s;
-      o.u = split_scale(most, 7);
-      o.inv_u = 1.f / o.u;
+      o.r = k;
+      o.u = split_exponent(most, 7);
     } else {
-      o.inv_g = 1.f / s;
+      o.g = k;
       o.max_m = 0u;
     }
   }
@@ -391,9 +391,10 @@ __global__ __launch_bounds__(256) void split3_kernel(const float* __restrict__ G
     f16x4 hi, lo;
 #pragma unroll
     for (int e = 0; e < 4; ++e) {
-      const float x = v[e] * s;
-      hi[e] = (_Float16)x;
-      lo[e] = (_Float16)(x - (float)hi[e]);
+      _Float16 h, l;
+      split_f16(v[e], k, h, l);
+      hi[e] = h;
+      lo[e] = l;
     }
     _Float16* o = out + r * 3 * d + c;
     *reinterpret_cast<f16x4*>(o) = hi;
@@ -428,15 +429,12 @@ __global__ __launch_bounds__(256) void cayley_setup_kernel(const float* __restri
     for (int i = threadIdx.x; i < ndelta; i += 256) delta[(int64_t)blockIdx.z * ndelta + i] = 0u;
     for (int i = threadIdx.x; i < ncontrol; i += 256) control[(int64_t)blockIdx.z * ncontrol + i] = 0u;
   }
-  float b_scale = 1.f, u_scale = 1.f;
+  int kb = 0, ku = 0;
   if (Bs) {  // |B| <= 2 |half_lr| max |M|
     SplitScales& sc = scales[blockIdx.z];
-    b_scale = split_scale(abs_bits(2.f * half_lr * __uint_as_float(sc.max_m)), 15);
-    u_scale = sc.u;
-    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) {
-      sc.b = b_scale;
-      sc.inv_b = 1.f / b_scale;
-    }
+    kb = split_exponent(abs_bits(half_lr * __uint_as_float(sc.max_m)), 14);
+    ku = sc.u;
+    if (blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) sc.b = kb;
   }
   // load the mirrored tile (rows j0.., cols i0..) of M and of R
 #pragma unroll
@@ -459,11 +457,10 @@ __global__ __launch_bounds__(256) void cayley_setup_kernel(const float* __restri
     Zt[idx] = rt;
     if (Bs) {  // split operands of the three-term GEMM: B as [hi|lo|hi], U as [hi|hi|lo]
       const int64_t so = 3 * bo + (int64_t)(i0 + rr) * 3 * d + j0 + tx;
-      const float x = b * b_scale, y = 2.f * rt * u_scale;
-      _Float16 hi = (_Float16)x, lo = (_Float16)(x - (float)hi);
+      _Float16 hi, lo;
+      split_f16(b, kb, hi, lo);
       Bs[so] = hi; Bs[so + d] = lo; Bs[so + 2 * d] = hi;
-      hi = (_Float16)y;
-      lo = (_Float16)(y - (float)hi);
+      split_f16(2.f * rt, ku, hi, lo);
       Us[so] = hi; Us[so + d] = hi; Us[so + 2 * d] = lo;
     } else {
       Bm[idx] = b;

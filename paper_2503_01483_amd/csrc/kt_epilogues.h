@@ -324,37 +324,40 @@ __device__ __forceinline__ void workgroup_umax(unsigned v, unsigned* word) {
 }
 
 // ---- fp32 products of the retraction from fp16 heads and tails (split3_kernel) --------------------
-// Words of one problem: the operands' scales are powers of two, chosen on the device from their largest magnitudes.
+// Words of one problem.  Every operand is multiplied by a power of two, chosen on the device from its largest magnitude; here are
+// the exponents, so that a product comes back in one exact step (two factors 2^-k one after the other overflow with a gradient of 2^110, and a
+// factor has to end at 2^-126 where a gradient of 2^-120 needs more).
 struct SplitScales {
-  float inv_g, inv_r;  // 1 / scale of the two operands of G R^T
-  unsigned max_m;      // bit pattern of max |G R^T|
-  float u, inv_u;      // scale of U
-  float b, inv_b;      // scale of B
-  float unused;
+  int g, r;        // of the two operands of G R^T
+  unsigned max_m;  // bit pattern of max |G R^T|
+  int u, b;        // of U and B
 };
-// The power of two that takes magnitudes up to that of `bits` (a non-negative float's bit pattern) below 2^exponent; 1 for zero, infinities
-// and NaN, which come out as they are.
-__device__ __forceinline__ float split_scale(unsigned bits, int exponent) {
+// The k with 2^k |x| < 2^exponent for magnitudes up to that of `bits` (a non-negative float's bit pattern); 0 for zero, infinities and
+// NaN, which come out as they are.
+__device__ __forceinline__ int split_exponent(unsigned bits, int exponent) {
   const int e = (int)(bits >> 23);
-  if (bits == 0u || e >= 255) return 1.f;
-  int k = exponent - (e - 126);
-  k = k > 100 ? 100 : k;
-  return __uint_as_float((unsigned)(k + 127) << 23);
+  return bits == 0u || e >= 255 ? 0 : exponent - (e - 126);
+}
+// y = 2^k x -> fp16 head and tail, together within 2^-23 |y| of y while |y| >= 2^-2 and within 2^-25 below: 2^-40 of the operand's
+// largest magnitude with exponent 15, 2^-32 (U) with 7.
+__device__ __forceinline__ void split_f16(float x, int k, _Float16& hi, _Float16& lo) {
+  const float y = ldexpf(x, k);
+  hi = (_Float16)y;
+  lo = (_Float16)(y - (float)hi);
 }
 
-// C = alpha * acc / (the two scales), and optionally the largest magnitude of it.  d x d, rows of d.
+// C = 2^shift * acc / (the two scales), and optionally the largest magnitude of it.  d x d, rows of d.
 template <class TL>
 struct EpiStoreScaled : EpiBase {
   float* C;
-  const float *inv_a, *inv_b;  // of problem 0
-  unsigned* max_word;          // of problem 0, or null
-  int d;
-  float alpha;
+  const int *exp_a, *exp_b;  // of problem 0
+  unsigned* max_word;        // of problem 0, or null
+  int d, shift;
   static constexpr bool kSwap = true;
   __device__ __forceinline__ void operator()(floatx4 (&acc)[TL::MB][TL::NB], int batch, int, int, int, int m0, int n0) const {
     constexpr int kWords = sizeof(SplitScales) / 4;
     const Frag<TL> f;
-    const float sa = alpha * inv_a[kWords * batch], sb = inv_b[kWords * batch];
+    const int e = shift - exp_a[kWords * batch] - exp_b[kWords * batch];
     float* base = C + (int64_t)batch * d * d;
     unsigned most = 0u;
 #pragma unroll
@@ -366,7 +369,7 @@ struct EpiStoreScaled : EpiBase {
           floatx4 v;
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
-            v[r] = acc[mb][nb][r] * sa * sb;
+            v[r] = ldexpf(acc[mb][nb][r], e);
             most = umax(most, abs_bits(v[r]));
           }
           *reinterpret_cast<floatx4*>(base + (int64_t)m * d + n) = v;
@@ -439,11 +442,11 @@ struct EpiCayleyIter {
                                              int, int, int m0, int n0) const {
     const Frag<TL> f;
     const int64_t bo = (int64_t)batch * d * d;
-    float bs = bscale ? bscale[4 * batch + 3] : 1.f, inv_b = 1.f, us = 1.f;
+    const float bs = bscale ? bscale[4 * batch + 3] : 1.f;
+    int ku = 0, kb = 0;
     if constexpr (sizeof(typename TL::T) == 2) {
-      us = scales[batch].u;
-      bs *= scales[batch].inv_u;
-      inv_b = scales[batch].inv_b;
+      ku = scales[batch].u;
+      kb = scales[batch].b;
     }
     unsigned dmax = 0u;
 #pragma unroll
@@ -458,7 +461,7 @@ struct EpiCayleyIter {
           floatx4 z, u;
 #pragma unroll
           for (int r = 0; r < 4; ++r) {
-            z[r] = rt[r] - (sizeof(typename TL::T) == 2 ? bs * acc[mb][nb][r] * inv_b : bs * acc[mb][nb][r]);
+            z[r] = rt[r] - bs * (sizeof(typename TL::T) == 2 ? ldexpf(acc[mb][nb][r], -(ku + kb)) : acc[mb][nb][r]);
             dmax = umax(dmax, abs_bits(z[r] - zo[r]));
             u[r] = rt[r] + z[r];
           }
@@ -469,9 +472,10 @@ struct EpiCayleyIter {
             f16x4 hi, lo;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
-              const float x = us * u[r];
-              hi[r] = (_Float16)x;
-              lo[r] = (_Float16)(x - (float)hi[r]);
+              _Float16 h, l;
+              split_f16(u[r], ku, h, l);
+              hi[r] = h;
+              lo[r] = l;
             }
             *reinterpret_cast<f16x4*>(Usplit + so) = hi;
             *reinterpret_cast<f16x4*>(Usplit + so + d) = hi;
