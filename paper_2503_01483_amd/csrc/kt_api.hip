@@ -163,6 +163,10 @@ constexpr float kCayleyTol = 3e-7f;
 static int g_stamp_next = -1;  // developer build: slot the next GEMM launch records its phase stamps in (-1: none)
 #endif
 
+// A tile is addressed with 32-bit byte offsets from its first row (K along the rows: the tile's rows) or from the first row of a slab (K as the
+// row index: the slab's).  Whether `rows` rows of ld elements can be.
+static bool tile_offsets_fit(int64_t rows, int64_t ld, int64_t esz) { return (rows - 1) * ld * esz + 512 <= (int64_t)UINT32_MAX; }
+
 template <class TL, class Epi, bool ATN = false, bool BTN = false>
 static bool launch_gemm(const void* A, int64_t lda, int64_t bsa, int M, const void* B, int64_t ldb,
                         int64_t bsb, int N, int64_t K, int slabs_per_split, int batch,
@@ -174,10 +178,8 @@ static bool launch_gemm(const void* A, int64_t lda, int64_t bsa, int M, const vo
     else return &gemm_nt_kernel<TL, Epi, ATN, BTN>;
   }();
   constexpr int lds_bytes = TL::LDS_BYTES;
-  // the kernel addresses the rows of a tile with 32-bit byte offsets from the tile's first row
   const int64_t esz = (int64_t)sizeof(typename TL::T);
-  if ((ATN ? 127 : TL::BM - 1) * lda * esz + 512 > (int64_t)UINT32_MAX || (BTN ? 127 : TL::BN - 1) * ldb * esz + 512 > (int64_t)UINT32_MAX)
-    return false;
+  if (!tile_offsets_fit(ATN ? TL::BK : TL::BM, lda, esz) || !tile_offsets_fit(BTN ? TL::BK : TL::BN, ldb, esz)) return false;
   if (ATN && (k_valid < 1 || k_valid > K)) return false;
   if (esz == 4 && ((ATN && M % 4 != 0) || (BTN && N % 4 != 0))) return false;
   if (!ensure_dynamic_lds(reinterpret_cast<const void*>(kern), lds_bytes)) return false;
@@ -206,7 +208,9 @@ static bool launch_gemm(const void* A, int64_t lda, int64_t bsa, int M, const vo
 }
 
 // Whether a row-major fp32 operand can be read in place, K as its row index (16-byte loads).  Otherwise a launch copies it first.
-static bool f32_in_place(const void* p, int64_t ld) { return ((reinterpret_cast<uintptr_t>(p) | (uintptr_t)(ld * 4)) & 15) == 0; }
+static bool f32_in_place(const void* p, int64_t ld) {
+  return ((reinterpret_cast<uintptr_t>(p) | (uintptr_t)(ld * 4)) & 15) == 0 && tile_offsets_fit(TF::BK, ld, 4);
+}
 
 static bool overlap(const void* a, size_t a_bytes, const void* b, size_t b_bytes) {
   const uintptr_t x = reinterpret_cast<uintptr_t>(a), y = reinterpret_cast<uintptr_t>(b);
@@ -234,7 +238,7 @@ template <class TL>
 static bool launch_cayley_iterations(const typename TL::T* U0, const typename TL::T* U1, const typename TL::T* B, int64_t K, int64_t d,
                                      int64_t batch, const EpiCayleyIter<TL>& epi, unsigned* control, hipStream_t stream) {
   auto kern = cayley_iterate_kernel<TL>;
-  if ((TL::BM - 1) * K * (int64_t)sizeof(typename TL::T) + 512 > (int64_t)UINT32_MAX) return false;
+  if (!tile_offsets_fit(TL::BM, K, (int64_t)sizeof(typename TL::T))) return false;
   if (!ensure_dynamic_lds(reinterpret_cast<const void*>(kern), TL::LDS_BYTES)) return false;
   GemmShape g = {};
   g.B = B; g.lda = g.ldb = K; g.batch_stride_a = g.batch_stride_b = d * K;
