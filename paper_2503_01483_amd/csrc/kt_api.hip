@@ -154,9 +154,25 @@ constexpr int64_t kTokenBlock = 4096;
 constexpr int kHadMfmaFrom = 12;  // bf16 Hadamard factors of at least this order run on the matrix cores (measured: the vector kernel wins for 4 and 8)
 constexpr int kSensBlocks = 1024;  // workgroups of the sensitivity sweeps
 constexpr int kCayleyMaxIters = 32;
-// Iterations that are a launch each; a step of usual size converges within them.  Steps, us, all iterations in one launch / the
-// first three by themselves: d = 640 168 / 165, 1152 405 / 364, 1408 663 / 563, 2432 1230 / 926, 3712 3312 / 2964, 3072 with Adam 1399 / 1259.
-constexpr int kCayleyOwnLaunches = 3;
+// Iterations that are a launch each; those behind them share one launch (cayley_iterate_kernel; `tiles` of it per problem, `edge` wide).
+// A launch that finds the iteration converged costs 2 to 3 us.  An iteration inside the kernel costs more than one by itself, by 3 to 10 us
+// up to 128 tiles, by 20 to 40 us at 400 (each tile writes back and drops an L2 that others work from).  A step of usual size takes
+// three iterations, (lr / 2) ||A|| = 0.1, 0.3, 0.5 takes 5, 11, 24.  us, 3 / 8 / 16 / 32 by themselves:
+//   fp32  d = 512 (64 tiles)       3 its 51 / 62 / 84 / 135        11 its 183 / 159 / 152 / 181       23 its 379 / 372 / 333 / 267
+//         d = 768 (144)                  93 / 103 / 121 / 151             294 / 272 / 270 / 300              646 / 622 / 591 / 567
+//         d = 640, 2 problems (200)      84 / 94 / 110 / 140              278 / 251 / 246 / 276              643 / 615 / 573 / 532
+//         d = 896, 2 problems (392)     152 / 162 / 179 / 210             594 / 493 / 443 / 474             1370 / 1264 / 1104 / 934
+//         d = 256, 32 problems (512)     87 / 98 / 114 / 146              377 / 306 / 259 / 290              798 / 728 / 615 / 518
+//         d = 512, 32 problems (512 of 128 x 128; only the 16 of a problem wait for each other)
+//                                       372 / - / 402 / 438              1135 / - / 1115 / 1152             2276 / - / 2295 / 2269
+//   fp16  d = 2048 (256)                307 / 317 / 332 / 362             958 / 875 / 837 / 865             2008 / 1928 / 1799 / 1676
+//         d = 4096 (256)               1580 / 1586 / 1601 / 1632         4128 / 4041 / 4023 / 4042          9237 / 9153 / 9015 / 8911
+static int cayley_own_launches(int64_t tiles, int64_t batch, int edge, bool split) {
+  if (!split && edge == TF::BM) return tiles <= 16 ? 3 : kCayleyMaxIters;
+  if (tiles * batch < kNumCUs / 2) return 3;
+  if (split || tiles * batch < 200) return 8;
+  return tiles * batch <= 400 ? 16 : kCayleyMaxIters;
+}
 constexpr float kCayleyTol = 3e-7f;
 
 #ifdef KT_PHASE_STAMPS
@@ -228,7 +244,7 @@ static bool launch_features_gemm(const typename TL::T* R, int64_t ldr, bool in_p
   return launch_gemm<TL>(R, d, d * d, (int)d, X, ldx, n * ldx, (int)n, d, 0, (int)batch, e, st);
 }
 
-// Iterations kCayleyOwnLaunches, ... of `batch` retractions (cayley_iterate_kernel): U and B are [d][K] in the GEMM dtype.  As many workgroups per
+// Iterations it0, ... of `batch` retractions (cayley_iterate_kernel): U and B are [d][K] in the GEMM dtype.  As many workgroups per
 // problem as the chip holds, at most one per tile.
 template <class TL>
 static int64_t cayley_control_words(int64_t d) {
@@ -236,7 +252,7 @@ static int64_t cayley_control_words(int64_t d) {
 }
 template <class TL>
 static bool launch_cayley_iterations(const typename TL::T* U0, const typename TL::T* U1, const typename TL::T* B, int64_t K, int64_t d,
-                                     int64_t batch, const EpiCayleyIter<TL>& epi, unsigned* control, hipStream_t stream) {
+                                     int64_t batch, const EpiCayleyIter<TL>& epi, unsigned* control, int it0, hipStream_t stream) {
   auto kern = cayley_iterate_kernel<TL>;
   if (!tile_offsets_fit(TL::BM, K, (int64_t)sizeof(typename TL::T))) return false;
   if (!ensure_dynamic_lds(reinterpret_cast<const void*>(kern), TL::LDS_BYTES)) return false;
@@ -250,7 +266,7 @@ static bool launch_cayley_iterations(const typename TL::T* U0, const typename TL
   const int64_t fit = kNumCUs * (160 * 1024 / TL::LDS_BYTES);
   const unsigned wgs = (unsigned)(g.tiles_total < fit ? g.tiles_total : fit);
   hipLaunchKernelGGL(kern, dim3(wgs, (unsigned)batch), dim3(TL::NT), TL::LDS_BYTES, stream, g, epi, U0, U1, control,
-                     cayley_control_words<TL>(d), kCayleyOwnLaunches);
+                     cayley_control_words<TL>(d), it0);
   return launch_ok();
 }
 
@@ -433,6 +449,18 @@ static auto with_f16_tile(int64_t d, int64_t batch, Go go) {
   const int64_t t128 = d / 128 * (d / 128) * batch, t256 = ceil_div(d, 256) * ceil_div(d, 256) * batch, slabs = 3 * d / TH_BIG::BK;
   if (t128 <= kNumCUs / 2) return go(TH_64{});
   return bf16_tile_time(true, t128, slabs, 0, 0.75) < bf16_tile_time(false, t256, slabs, 10, 0) ? go(TH_128{}) : go(TH_BIG{});
+}
+
+// The tile of cayley_iterate_kernel: the same, but 128 x 128 instead of more 64 x 64 ones than there are CUs (what an iteration costs there
+// beyond a launch of its own grows with the tiles).  us, 24 iterations, all but three inside, 64 / 128: d = 1024 (256 tiles of 64) 869 / 933, 1152
+// (324) 1224 / 1062, 1408 (484) 1774 / 1171, 1024, 2 problems (512) 1530 / 1085.  256 instead of 128: 2048 2008 / 3360, 2432 4257 / 4334.
+template <class Go>
+static auto with_f16_iterate_tile(int64_t d, int64_t batch, Go go) {
+  return with_f16_tile(d, batch, [&](auto t) {
+    if constexpr (std::is_same_v<decltype(t), TH_64>)
+      if (d / 64 * (d / 64) * batch > kNumCUs) return go(TH_128{});
+    return go(t);
+  });
 }
 
 static CayleyPlan plan_cayley(int64_t batch, int64_t d, bool split) {
@@ -964,7 +992,7 @@ static kt_status cayley_run(const CayleyPlan& p, char* ws, float* R, const float
   const bool small = small_f32_tiles(d, batch);
   // The control words of the iterations lie where Cayley Adam had its block sums of ||G||^2, cleared by the set-up kernel; a
   // tile grid too large for that room takes that of the sums of ||S||^2, behind the kernel that reads them.
-  const int64_t control_words = p.split ? with_f16_tile(d, batch, [&](auto t) { return cayley_control_words<decltype(t)>(d); })
+  const int64_t control_words = p.split ? with_f16_iterate_tile(d, batch, [&](auto t) { return cayley_control_words<decltype(t)>(d); })
                                         : (small ? cayley_control_words<TF_64>(d) : cayley_control_words<TF>(d));
   const int64_t room = (int64_t)p.g2_blocks * 8 - (p.split ? (int64_t)sizeof(SplitScales) : 0);
   const bool late_control = control_words * 4 > room;
@@ -981,7 +1009,9 @@ static kt_status cayley_run(const CayleyPlan& p, char* ws, float* R, const float
       e.scales = scales;
       return e;
     };
-    for (int it = 0; it < kCayleyOwnLaunches; ++it) {
+    using TL = decltype(tile_tag);
+    const int own = cayley_own_launches(ceil_div(d, TL::BM) * ceil_div(d, TL::BN), batch, TL::BM, p.split);
+    for (int it = 0; it < own; ++it) {
       auto e = epilogue(first_tag);
       auto *from = it & 1 ? U1 : U0, *to = it & 1 ? U0 : U1;
       e.it = it;
@@ -989,9 +1019,9 @@ static kt_status cayley_run(const CayleyPlan& p, char* ws, float* R, const float
       else e.Unew = to;
       if (!launch_gemm<decltype(first_tag)>(from, K, d * K, D, B, K, d * K, D, K, 0, (int)batch, e, st)) return false;
     }
-    using TL = decltype(tile_tag);
+    if (own == kCayleyMaxIters) return true;
     if (late_control) hipLaunchKernelGGL(fill_u32_kernel, dim3(64), dim3(256), 0, st, control, batch * control_words, 0u);
-    return launch_cayley_iterations<TL>(U0, U1, B, K, d, batch, epilogue(tile_tag), control, st);
+    return launch_cayley_iterations<TL>(U0, U1, B, K, d, batch, epilogue(tile_tag), control, own, st);
   };
 
   if (p.split) {
@@ -1026,7 +1056,9 @@ static kt_status cayley_run(const CayleyPlan& p, char* ws, float* R, const float
       // cross terms come out whichever operand carries which layout
       if (!product(Bs, Us[0], &scales->b, &scales->u, adam->M, nullptr, -1)) return fail(KT_ERR_DEVICE, "momentum projection GEMM launch failed");
     }
-    const bool launched = with_f16_tile(d, batch, [&](auto t) { return iterations(t, t, Us[0], Us[1], Bs, 3 * d); });
+    const bool launched = with_f16_tile(d, batch, [&](auto first) {
+      return with_f16_iterate_tile(d, batch, [&](auto t) { return iterations(first, t, Us[0], Us[1], Bs, 3 * d); });
+    });
     if (!launched) return fail(KT_ERR_DEVICE, "Cayley iteration launch failed");
   } else {
   auto product = [&](const float* A, const float* B, float* C) -> bool {  // C = A B^T

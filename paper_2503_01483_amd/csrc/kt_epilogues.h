@@ -506,9 +506,9 @@ constexpr int kCayleyControlWords = 64;  // done[0 .. 31], stop at 32; claim[] b
 // acquired at that scope behind the wait; done[], claim[] and the changes are atomics.
 //
 // Why one launch: the host cannot know when the iteration has converged, so a launch per iteration means all 32 of them, and one
-// that only finds the convergence flag set costs 2 to 5 us.  Why not for the first ones: a release and an acquire per tile write
-// back and drop an XCD's L2 while other workgroups work from it.  Retractions of three iterations, us, all in this launch / the
-// first three by themselves: see kCayleyOwnLaunches.
+// that only finds the convergence flag set costs 2 to 3 us.  Why not for the first ones: a release and an acquire per tile write
+// back and drop an XCD's L2 while other workgroups work from it (cayley_own_launches has the figures; with stores past the L2 in
+// place of the release, large tiles lost more than they gained: d = 4096 9500 / 10500).
 constexpr long long kCayleyWaitTicks = 20ll * 100000000;  // 20 s of the 100 MHz counter
 
 template <class TL>
