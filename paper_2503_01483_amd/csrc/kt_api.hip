@@ -389,9 +389,12 @@ static LossGradPlan plan_loss_grad(int64_t batch, int64_t n, int64_t d, kt_dtype
   Carver c;
   if (p.fp32) {
     // token ranges as for 128 x 128 tiles (also with smaller ones: a quarter of the ranges would be sums four times as long, in
-    // fp32; d = 1024, 16384 tokens: dR off by 8.8e-7 of its norm instead of 6.9e-7), whole blocks of 128 tokens
-    p.slabs_per_split = (int)round_up(choose_slabs_per_split(ceil_div(d, TF::BM) * ceil_div(d, TF::BN) * batch, p.ldt / TF::BK, 4 * kNumCUs), 4);
-    p.split_k = (int)ceil_div(p.ldt / TF::BK, p.slabs_per_split);
+    // fp32; d = 1024, 16384 tokens: dR off by 8.8e-7 of its norm instead of 6.9e-7).  Whole blocks of 128 tokens where 32 x 32 tiles take
+    // them (with_f32_tile on the ranges): four waves share each, so that no sum is longer for it.
+    const int64_t slabs = p.ldt / TF::BK;
+    p.slabs_per_split = choose_slabs_per_split(ceil_div(d, TF::BM) * ceil_div(d, TF::BN) * batch, slabs, 4 * kNumCUs);
+    if (d / 32 * (d / 32) * batch * ceil_div(slabs, p.slabs_per_split) <= 2 * kNumCUs) p.slabs_per_split = (int)round_up(p.slabs_per_split, 4);
+    p.split_k = (int)ceil_div(slabs, p.slabs_per_split);
     p.P = 1;
     p.loss_blocks = (int)(p.ldt / 4 < 2048 ? p.ldt / 4 : 2048);  // workgroups of loss_rows_kernel per problem
     p.o_rt = c.take((size_t)batch * d * d * 4);
