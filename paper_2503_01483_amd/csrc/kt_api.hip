@@ -796,6 +796,45 @@ static bool launch_rows_gemm(const T* X, int64_t ldx, int64_t x_batch_stride, co
   }
 }
 
+// fp32, no gradient: whether Y stays in registers (128 x 128 tiles, features on the rows of the GEMM, row moments in its epilogue, as with
+// bf16) instead of being written as rows and read again, 8 bytes a value that short rows do not hide.  Loss, us, rows / this (tiles of 128):
+//   d = 128: 8192 tokens (64) 16.5 / 18.4, 12000 (94) 20.1 / 18.4, 20000 (157) 25.9 / 18.4, 131072 135 / 46, 64 problems of 4096 253 / 83,
+//            300 of 512 (1200) 111 / 100, of 128 (300, one a problem: the grid rounds up to eight) 61 / 99
+//   d = 256: 4096 (64) 18.5 / 26.2, 8192 (128) 27.6 / 26.8, 12000 (188) 34 / 27, 17000 (266) 45 / 41, 34000 (532) 72 / 59
+//   d = 384: 8192 (192) 37.5 / 35.1, 12000 (282) 50 / 57, 17000 (399) 65 / 58;  512: 9000 (284) 57 / 73, 13000 (408) 75 / 73, 17000 (532) 94 / 105
+//   d = 768, 9000 (426) 100 / 104;  1024, 6000 (376) 110 / 135, 16384 (1024) 269 / 259
+static bool f32_moments(int64_t batch, int64_t n, int64_t d) {
+  const int64_t own = ceil_div(n, TF::BN) * (d / TF::BM), tiles = own * batch;
+  if (own < 4) return false;
+  if (d <= 256) return tiles >= kNumCUs / 2;
+  return d <= 512 ? 4 * tiles >= 3 * round_up(tiles, kNumCUs) : with_f32_tile(n, d, batch, [](auto t) { return std::is_same_v<decltype(t), TF>; });
+}
+static kt_status run_loss_f32(const LossGradPlan& p, const float* X, int64_t ldx, const float* R, int64_t ldr, bool in_place, int64_t batch,
+                              int64_t n, int64_t d, float kappa_target, float* loss, float* row_kurt, char* ws, hipStream_t st,
+                              const PooledArgs* pooled) {
+  // (the room of Y is 4 d bytes a token: 0.25 d of partials, 16 of coefficients, 32 bytes of sums per 256)
+  const int P = (int)(d / TF::BM) * TF::WGM, blocks = (int)ceil_div(n, 256);
+  floatx4* part = reinterpret_cast<floatx4*>(ws + p.o_gt);
+  floatx4* coef = part + batch * P * n;
+  double* sums = reinterpret_cast<double*>(coef + batch * n);
+  {
+    ProfScope prof(0, st);
+    EpiMoments<TF> e;
+    e.part = part; e.n_tokens = (int)n; e.d = (int)d; e.P = P;
+    if (!launch_features_gemm<TF>(R, ldr, in_place, X, ldx, batch, n, d, e, st)) return fail(KT_ERR_DEVICE, "forward GEMM launch failed");
+  }
+  if (pooled) {
+    hipLaunchKernelGGL(pooled_stage1_kernel, dim3(blocks, (unsigned)batch), dim3(256), 0, st, part, P, (int)n, (int)d, pooled->rms_eps, sums);
+    hipLaunchKernelGGL(pooled_stage2_kernel, dim3((unsigned)batch), dim3(256), 0, st, sums, blocks, (int)n, (int)d, kappa_target,
+                       reinterpret_cast<double*>(ws + p.o_gstat), loss, pooled->kappa_out);
+    return launch_ok() ? KT_OK : fail(KT_ERR_DEVICE, "pooled statistics launch failed");
+  }
+  hipLaunchKernelGGL(finalize_rows_kernel, dim3(blocks, (unsigned)batch), dim3(256), 0, st, part, P, (int)n, (int)d, kappa_target, coef,
+                     row_kurt, sums);
+  if (!launch_ok() || !launch_loss_sum(LossSum{sums, blocks, (int)n, (int)batch, loss}, st)) return fail(KT_ERR_DEVICE, "row statistics launch failed");
+  return KT_OK;
+}
+
 // fp32: token-major throughout (kt_rows.h).  Y = X R in the workspace, dL/dY over it, dR = X^T (dL/dY) with K as the row index
 // of both operands.
 static kt_status run_loss_grad_f32(const LossGradPlan& p, const float* X, int64_t ldx, const float* R, int64_t ldr, int64_t batch,
@@ -809,6 +848,8 @@ static kt_status run_loss_grad_f32(const LossGradPlan& p, const float* X, int64_
   float* splitk = reinterpret_cast<float*>(ws + p.o_splitk);
   const bool in_place = f32_in_place(R, ldr);
   if (!in_place && !prep_rt<float>(R, ldr, KT_F32, RT, batch, d, st)) return fail(KT_ERR_DEVICE, "prep_rt launch failed");
+  if (!dR && f32_moments(batch, n, d))
+    return run_loss_f32(p, X, ldx, in_place ? R : RT, ldr, in_place, batch, n, d, kappa_target, loss, row_kurt, ws, st, pooled);
   {
     ProfScope prof(0, st);
     if (!launch_rows_gemm<float, TF>(X, ldx, n * ldx, in_place ? R : RT, ldr, in_place, batch, n, d, Y, p.ldt * d, st))
@@ -817,16 +858,19 @@ static kt_status run_loss_grad_f32(const LossGradPlan& p, const float* X, int64_
   const int wgs = p.loss_blocks;
   {
     ProfScope prof(1, st);
-    auto rows_kernel = d <= 1024 ? loss_rows_kernel<4> : d <= 4096 ? loss_rows_kernel<16> : d <= 8192 ? loss_rows_kernel<32> : loss_rows_kernel<0>;
+    auto rows_kernel = d == 128 ? loss_rows_kernel<1, 32> : d <= 1024 ? loss_rows_kernel<4, 64> : d <= 4096 ? loss_rows_kernel<16, 64>
+                       : d <= 8192 ? loss_rows_kernel<32, 64> : loss_rows_kernel<0, 64>;
     hipLaunchKernelGGL(rows_kernel, dim3(wgs, (unsigned)batch), dim3(256), 0, st, Y, (int)p.ldt, (int)n, (int)d, kappa_target, row_kurt,
                        sums, dR ? 1 : 0, pooled ? pooled->rms_eps : 0.f, part);
     if (!launch_ok()) return fail(KT_ERR_DEVICE, "row statistics launch failed");
     if (pooled) {
       hipLaunchKernelGGL(pooled_stage2_kernel, dim3((unsigned)batch), dim3(256), 0, st, sums, wgs, (int)n, (int)d, kappa_target, gstat,
                          loss, pooled->kappa_out);
-      if (dR)
-        hipLaunchKernelGGL(pooled_grad_rows_kernel, dim3((unsigned)ceil_div(n, 4), (unsigned)batch), dim3(256), 0, st, Y, (int)p.ldt, (int)n,
+      if (dR) {
+        auto grad_kernel = d == 128 ? pooled_grad_rows_kernel<32> : pooled_grad_rows_kernel<64>;
+        hipLaunchKernelGGL(grad_kernel, dim3((unsigned)ceil_div(n, d == 128 ? 8 : 4), (unsigned)batch), dim3(256), 0, st, Y, (int)p.ldt, (int)n,
                            (int)d, pooled->rms_eps, part, gstat);
+      }
       if (!launch_ok()) return fail(KT_ERR_DEVICE, "pooled statistics launch failed");
     }
   }
