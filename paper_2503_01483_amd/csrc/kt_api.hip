@@ -1405,8 +1405,14 @@ kt_status kt_kurtosis_loss_grad(const void* X, int64_t ldx, const void* R, int64
   if (!loss) return fail(KT_ERR_INVALID_ARG, "loss must not be null");
   if (!(kappa_target >= 0.f)) return fail(KT_ERR_INVALID_ARG, "kappa_target must be >= 0");
   LossGradPlan p = plan_loss_grad(batch, n, d, x_dtype);
-  // a workspace of less than kt_workspace_bytes() still serves while one workgroup's partials per problem fit
-  for (int k = p.fused_wgs - 1; p.fused && k >= 1 && workspace_bytes < p.total; --k) p = plan_loss_grad(batch, n, d, x_dtype, false, false, k);
+  if (p.fused && workspace_bytes < p.total) {
+    // A smaller workspace still serves while the loss partials of one workgroup per problem fit: as many workgroups as there is room for
+    // (8 bytes of loss and, from two on, a d x d partial each; the loss partials end at a multiple of 256 bytes).
+    const int64_t room = (int64_t)(workspace_bytes / ((size_t)batch * (8 + d * d * 4)));
+    const int64_t k = room < 1 ? 1 : room < p.fused_wgs ? room : p.fused_wgs - 1;
+    if (k < p.fused_wgs) p = plan_loss_grad(batch, n, d, x_dtype, false, false, k);
+    if (k > 1 && workspace_bytes < p.total) p = plan_loss_grad(batch, n, d, x_dtype, false, false, k - 1);
+  }
   s = check_ws(workspace, workspace_bytes, p.total);
   if (s != KT_OK) return s;
   if (!p.fused && dR) {  // room for Y: keep it instead of recomputing it (same result)
