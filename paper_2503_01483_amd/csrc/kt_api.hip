@@ -336,9 +336,12 @@ static double bf16_tile_time(bool small, int64_t tiles, int64_t slabs, double en
   const int64_t rest = tiles % (2 * kNumCUs);
   return (pair * (double)(tiles / (2 * kNumCUs)) + (rest == 0 ? 0.0 : rest <= kNumCUs ? 0.55 : pair)) * (double)(slabs + 4);
 }
+// From four rounds over the chip on two 128 x 128 tiles take 0.76: the workgroups have drifted apart and the row moments (and kept Y) of
+// twice the tiles meet the loads of others.  Loss alone, us, 256 / 128: d = 512, 2 problems of 131072 tokens (16 rounds) 160 / 176, 64 of 4096 184 / 204, loss +
+// gradient 561 / 585, 712 / 717; 896, 131072 (14) 226 / 210; 1152, 131072 (18), with gradient, 867 / 969.
 static bool small_forward_tiles(int64_t batch, int64_t n, int64_t d) {
-  const int64_t slabs = d / TB_BIG::BK;
-  return bf16_tile_time(true, d / 128 * ceil_div(n, 128) * batch, slabs, 0, 0.7) <
+  const int64_t slabs = d / TB_BIG::BK, tiles = d / 128 * ceil_div(n, 128) * batch;
+  return bf16_tile_time(true, tiles, slabs, 0, tiles < 8 * kNumCUs ? 0.7 : 0.76) <
          bf16_tile_time(false, ceil_div(d, 256) * ceil_div(n, 256) * batch, slabs, 10, 0);
 }
 // dR = X^T G over `slabs` slabs of 64 tokens: tile and slabs per range of tokens, at least eight.  Every range beyond the first
