@@ -103,3 +103,35 @@ def test_row_loss_and_gradient_fp32(batch, n, d, pad, unaligned):
         assert ((kurt[b].double() - kappa[:, 0]).abs() <= 1e-5 * kappa[:, 0]).all()
         assert abs(loss[b].double() - kappa.mean()) <= 1e-5 * kappa.mean()
         assert (dR[b].double() - G).norm() <= 1e-5 * G.norm()
+
+
+@pytest.mark.parametrize("batch,n,d,ldr,offset", [(2, 130, 256, 260, 0), (3, 33, 384, 392, 4), (1, 300, 640, 1024, 8), (2, 700, 512, 516, 0), (2, 20, 1152, 1156, 4),
+                                                  (1, 40000, 128, 136, 0), (2, 9000, 256, 260, 4)])
+def test_wide_aligned_rows_of_rotation(batch, n, d, ldr, offset):
+    """R read in place with rows wider than d, one and several problems (d ldr apart): the same kernels and bits as with rows of d; NaN between
+    the rows.  The last two sizes are past the line where the loss alone takes its row sums in the forward product."""
+    g = torch.Generator(device="cuda").manual_seed(n + d)
+    X = torch.randn((batch, n, d), generator=g, device="cuda") + 0.3
+    R = torch.randn((batch, d, d), generator=g, device="cuda") * d ** -0.5
+    wide = torch.full((batch * d * ldr + offset,), float("nan"), device="cuda")[offset:].view(batch, d, ldr)[:, :, :d]
+    wide.copy_(R)
+    out = []
+    for r in (R, wide):
+        dR, kurt, pooled, kappa = (torch.empty(s, device="cuda") for s in ((batch, d, d), (batch, n), (batch, d, d), (batch,)))
+        only = torch.empty_like(kurt)
+        loss = kt.kt_kurtosis_loss_grad(X, r, row_kurt=kurt, dR=dR)
+        alone = kt.kt_kurtosis_loss_grad(X, r, row_kurt=only)
+        ploss = kt.kt_pooled_kurtosis_loss_grad(X, r, kappa=kappa, dR=pooled)
+        palone = kt.kt_pooled_kurtosis_loss_grad(X, r)
+        scales, err, codes = torch.empty((batch, n), device="cuda"), torch.empty((batch, n, 2), device="cuda"), torch.empty((batch, n, d), dtype=torch.int8, device="cuda")
+        kt.kt_rotate_fakequant_int4(X, r, scales_out=scales, codes=codes, err=err)
+        given = torch.empty_like(codes)
+        kt.kt_rotate_fakequant_int4(X, r, scales_in=scales, codes=given)
+        Y, thr = torch.empty_like(X), torch.empty((batch, n), device="cuda")
+        kt.kt_rotate_quant_metrics(X, r, Y=Y, threshold=thr)
+        out.append((loss, kurt, dR, alone, only, ploss, kappa, pooled, palone, scales, err, codes, given, Y, thr))
+    for a, b in zip(*out):
+        assert torch.equal(a, b)
+    for b in range(batch):
+        A, B = X[b].double(), R[b].double()
+        assert ((out[1][13][b].double() - A @ B).abs() <= _bound(A, B)).all()
