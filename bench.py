@@ -396,8 +396,6 @@ def main():
     if keep and 1 in kern:  # the entry-by-entry kernel: reads Y (fp32), writes dL/dY in the GEMM dtype
         gy_bytes = batch * n * d * (4.0 + (2.0 if bf16 else 4.0))
         breakdown["grad_from_kept_y_gbs"] = round(gy_bytes / (kern[1]["avg_ms"] * 1e-3) / 1e9, 1)
-    if prof[3][1]:
-        breakdown["x_transpose_ms"] = round(prof[3][0] / prof[3][1], 4)
     breakdown["cayley_ms"] = round(prof[4][0] / max(prof[4][1], 1), 4)
     iters = info.cpu().tolist()
     breakdown["cayley_iters_last"] = iters[:4]

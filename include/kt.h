@@ -78,8 +78,12 @@ const char* kt_last_error(void);
 /* Scratch bytes the given operation needs for these sizes (0 on bad sizes).
  * For KT_OP_CAYLEY `n` is ignored.  KT_OP_LOSS_GRAD / KT_OP_POOLED_LOSS_GRAD: the recommended size
  * (with room to keep Y, see kt_kurtosis_loss_grad); KT_OP_LOSS_GRAD_RECOMPUTE /
- * KT_OP_POOLED_LOSS_GRAD_RECOMPUTE: the least those entry points accept (fp32: the same size, Y lives
- * where dL/dY goes).  Host call, launches nothing. */
+ * KT_OP_POOLED_LOSS_GRAD_RECOMPUTE: the smaller size those entry points accept (fp32: the same size, Y lives
+ * where dL/dY goes).  Two calls also take less than the size given here, and then compute in another way:
+ * kt_kurtosis_loss_grad in bf16 with d = 128 sums over as many token ranges as there is room for (dR's fp32 sums come
+ * in another order; at least 8 batch bytes, rounded up to 256), and the Cayley steps with d >= 1024, d % 256 != 0
+ * use fp32 products where only those fit (20 batch d^2 bytes and the scalars, instead of 30).
+ * Host call, launches nothing. */
 size_t kt_workspace_bytes(kt_op op, int64_t batch, int64_t n, int64_t d, kt_dtype x_dtype);
 
 /*
@@ -111,7 +115,8 @@ size_t kt_workspace_bytes(kt_op op, int64_t batch, int64_t n, int64_t d, kt_dtyp
  *  d        multiple of 128, <= 16384.   1 <= n <= 2^22, any value (tail rows are masked).
  *  loss     [batch] fp32, written.
  *  row_kurt [batch][n] fp32 or NULL.
- *  dR       [batch][d][d] fp32 or NULL (NULL: loss only, the backward GEMMs are skipped).
+ *  dR       [batch][d][d] fp32 or NULL (NULL: loss only, the backward GEMMs are skipped; fp32 calls of many rows then take their
+ *           row sums in the forward GEMM's order, and loss and row_kurt can differ in the last bits from those of a call with dR).
  *  A row without spread (m2 <= 1e-10 of its mean square: sigma below 1e-5 of the mean, which fp32
  *  products cannot resolve) counts with kappa = 0 and contributes no gradient.  Above that the row
  *  values carry an error of about 1e-6 |mean| / sigma on top of the path tolerance.
@@ -189,7 +194,7 @@ kt_status kt_cayley_step(float* R, const float* dR, void* R_lowp, int64_t batch,
  *  KT_ERR_NOT_SUPPORTED before anything is enqueued.
  *  All calls on one GPU share that GPU's array: calls that overlap in time on one GPU (different
  *  streams, different host threads) race and must be serialised by the caller.  The array keeps the
- *  previous call's contents; every counter the kernels need at zero is cleared by a fill kernel at the
+ *  previous call's contents; every counter the kernels need at zero is cleared by the kernels at the
  *  start of each call.
  */
 kt_status kt_cayley_step_static(float* R, const float* dR, void* R_lowp, int64_t batch, int64_t d,
@@ -349,9 +354,9 @@ kt_status kt_fuse_rotation(const float* W, int64_t ldw, const float* R, int64_t 
  * benchmark can read per-kernel durations without a profiler attached.  This is the
  * only process-global state the library has; enable/disable/read are host calls and
  * must not run concurrently with other library calls.
- *   kernel ids: 0 forward GEMM + row moments, 1 backward recompute GEMM + dL/dY,
- *               2 gradient GEMM X^T G, 3 token-minor copy of X (fp32, or d not a multiple of 256: bf16 with
- *               d % 256 == 0 reads X as it is),
+ *   kernel ids: 0 forward GEMM (bf16: + row moments; d = 128: the whole loss + gradient pass),
+ *               1 dL/dY (bf16: from the kept Y, or the backward recompute GEMM; fp32: row statistics and dL/dY),
+ *               2 gradient GEMM X^T G, 3 no launch (X is read in place everywhere),
  *               4 every launch of kt_cayley_step, 5 every launch of kt_rotate_fakequant_int4
  * kt_profile_enable(max_records): records up to max_records bracketed launches (0 turns
  *   profiling off and releases the events).

@@ -147,7 +147,7 @@ static auto with_f32_tile(int64_t M, int64_t N, int64_t batch, Go go) {
   return use_small_f32(ceil_div(M, TF::BM) * ceil_div(N, TF::BN) * batch) ? go(TF_64{}) : go(TF{});
 }
 static inline bool small_f32_tiles(int64_t d, int64_t batch) { return use_small_f32(ceil_div(d, 128) * ceil_div(d, 128) * batch); }
-// Token-minor operands (X^T, G^T) are stored in blocks of this many tokens: within a block a
+// Token-minor operands (dL/dY, Y kept for it) are stored in blocks of this many tokens: within a block a
 // feature row is contiguous, blocks follow each other feature-row-set by feature-row-set, so
 // the 256 rows a tile streams together span 2 MiB per block instead of one page per row.
 constexpr int64_t kTokenBlock = 4096;
@@ -187,8 +187,8 @@ template <class TL, class Epi, bool ATN = false, bool BTN = false>
 static bool launch_gemm(const void* A, int64_t lda, int64_t bsa, int M, const void* B, int64_t ldb,
                         int64_t bsb, int N, int64_t K, int slabs_per_split, int batch,
                         const Epi& epi, hipStream_t stream, int64_t k_block = 0,
-                        int64_t block_stride_a = 0, int64_t block_stride_b = 0, int k_valid = 0) {
-  // ATN: A is [K][lda] with the M index along its rows (see gemm_mainloop); K blocking applies to B only.  BTN: B [K][ldb].
+                        int64_t block_stride_b = 0, int k_valid = 0) {
+  // ATN: A is [K][lda] with the M index along its rows (see gemm_mainloop); BTN: B [K][ldb].
   constexpr auto kern = [] {
     if constexpr (std::is_same_v<TL, TF_32>) return &gemm32_kernel<Epi, ATN, BTN>;
     else return &gemm_nt_kernel<TL, Epi, ATN, BTN>;
@@ -210,10 +210,9 @@ static bool launch_gemm(const void* A, int64_t lda, int64_t bsa, int M, const vo
   g.split_k = (int)ceil_div(g.slabs_total, g.slabs_per_split);  // every split non-empty
   g.tiles_total = g.tiles_m * g.tiles_n * g.split_k;
   g.grid_padded = (int)round_up(g.tiles_total, 8);
-  // K blocking: rows hold K in blocks of k_block elements, block b of a row starts
-  // block_stride elements after block b-1 (k_block = 0: ordinary contiguous rows)
+  // K blocking of B: rows hold K in blocks of k_block elements, block b of a row starts
+  // block_stride_b elements after block b-1 (k_block = 0: ordinary contiguous rows)
   g.slabs_per_block = k_block > 0 ? (int)(k_block / TL::BK) : (g.slabs_total > 0 ? g.slabs_total : 1);
-  g.block_bytes_a = block_stride_a * (int64_t)sizeof(typename TL::T);
   g.block_bytes_b = block_stride_b * (int64_t)sizeof(typename TL::T);
   g.k_valid = k_valid;
 #ifdef KT_PHASE_STAMPS
@@ -239,7 +238,7 @@ template <class TL, class Epi>
 static bool launch_features_gemm(const typename TL::T* R, int64_t ldr, bool in_place, const typename TL::T* X, int64_t ldx, int64_t batch,
                                  int64_t n, int64_t d, const Epi& e, hipStream_t st) {
   if constexpr (sizeof(typename TL::T) == 4) {
-    if (in_place) return launch_gemm<TL, Epi, true>(R, ldr, d * ldr, (int)d, X, ldx, n * ldx, (int)n, d, 0, (int)batch, e, st, 0, 0, 0, (int)d);
+    if (in_place) return launch_gemm<TL, Epi, true>(R, ldr, d * ldr, (int)d, X, ldx, n * ldx, (int)n, d, 0, (int)batch, e, st, 0, 0, (int)d);
   }
   return launch_gemm<TL>(R, d, d * d, (int)d, X, ldx, n * ldx, (int)n, d, 0, (int)batch, e, st);
 }
@@ -474,7 +473,7 @@ static CayleyPlan plan_cayley(int64_t batch, int64_t d, bool split) {
   Carver c;
   p.split = split;
   const size_t mat = (size_t)batch * d * d * 4;
-  const size_t smat = (size_t)batch * d * d * 6;  // [d][3d] bf16
+  const size_t smat = (size_t)batch * d * d * 6;  // [d][3d] fp16
   p.o_m = c.take(mat);  // M = dR R^T; in the fp32 path later reused as the second U buffer
   p.o_b = c.take(p.split ? smat : mat);
   p.o_rt = c.take(mat);
@@ -698,7 +697,7 @@ static kt_status run_loss_grad_bf16(const LossGradPlan& p, const void* X, int64_
       e.batch_stride = d * d; e.split_stride = p.split_k > 1 ? batch * d * d : 0;
       e.ldc = d; e.M = (int)d; e.N = (int)d;
       return launch_gemm<TL, EpiStore<TL>, true>(Xp, ldx, n * ldx, (int)d, GT, p.tb, d * p.nblk * p.tb, (int)d, p.ldt,
-                                                 p.slabs_per_split, (int)batch, e, st, p.tb, 0, d * p.tb, (int)n);
+                                                 p.slabs_per_split, (int)batch, e, st, p.tb, d * p.tb, (int)n);
     };
     if (!(p.small_dr ? go(TB_128{}) : go(TB_BIG{}))) return fail(KT_ERR_DEVICE, "gradient GEMM launch failed");
     if (p.split_k > 1 && !launch_splitk_reduce(splitk, batch * d * d, p.split_k, dR, pooled ? LossSum{} : loss_sum, st))
@@ -890,7 +889,7 @@ static kt_status run_loss_grad_f32(const LossGradPlan& p, const float* X, int64_
     e.batch_stride = d * d; e.split_stride = p.split_k > 1 ? batch * d * d : 0;
     e.ldc = d; e.M = (int)d; e.N = (int)d;
     return launch_gemm<TL, EpiStore<TL>, true, true>(X, ldx, n * ldx, (int)d, Y, d, p.ldt * d, (int)d, p.ldt, p.slabs_per_split, (int)batch, e,
-                                                     st, 0, 0, 0, (int)n);
+                                                     st, 0, 0, (int)n);
   };
   if (!with_f32_tile(d, d, batch * p.split_k, go)) return fail(KT_ERR_DEVICE, "gradient GEMM launch failed");
   if (p.split_k > 1 && !launch_splitk_reduce(splitk, batch * d * d, p.split_k, dR, loss_sum, st))
@@ -1494,8 +1493,8 @@ kt_status kt_cayley_step_static(float* R, const float* dR, void* R_lowp, int64_t
                 "(use kt_cayley_step with a workspace)", (long long)batch, (long long)d, need, kStaticScratchBytes);
   void* ws = static_scratch_of_current_device();
   if (!ws) return KT_ERR_DEVICE;
-  // same checks, plan and launches as the workspace form; the fixed point clears its own counters
-  // with a fill kernel, so whatever the previous call left in the array does not matter
+  // same checks, plan and launches as the workspace form; the kernels ahead of the iterations clear their counters,
+  // so whatever the previous call left in the array does not matter
   return kt_cayley_step(R, dR, R_lowp, batch, d, lr, ortho_err, info, ws, kStaticScratchBytes, stream);
 }
 
@@ -1709,7 +1708,7 @@ kt_status kt_fuse_rotation(const float* W, int64_t ldw, const float* R, int64_t 
       EpiStore<TL> e;
       e.C = Wout; e.ldc = ldo; e.batch_stride = 0; e.split_stride = 0; e.M = (int)M; e.N = (int)N;
       return launch_gemm<TL, EpiStore<TL>, decltype(atn_c)::value, decltype(btn_c)::value>(A, lda, 0, (int)M, B, ldb, 0, (int)N, d, 0, 1, e, st,
-                                                                                          0, 0, 0, (int)d);
+                                                                                          0, 0, (int)d);
     };
     return with_f32_tile(M, N, 1, go);
   };

@@ -151,21 +151,18 @@ struct EpiMoments : EpiBase {
 // ---- backward pass: recomputed y -> dL/dy, stored token-minor ---------------------
 // coef[token] = {alpha, mu, beta, m3};  g = alpha * (c (c^2 - beta) - m3), c = y - mu.
 //
-// Layout of GT (and of the token-minor copy of X that meets it in dR = X^T G): rows are
+// Layout of GT (dR = X^T G reads X where it lies, its rows taken in this order): rows are
 // features, and inside every group of 64 tokens the tokens are PERMUTED,
 //     position(t) = (t & 15) * 4 + ((t & 63) >> 4),
 // because the contraction over tokens does not care in which order the tokens come as
 // long as both operands agree.  In the accumulator layout a lane owns tokens
 // t, t+16, t+32, t+48 of a group, so with this order its values for one feature are
 // ADJACENT in memory: one 8-byte store per feature instead of four 2-byte ones, and the 16
-// lanes of a quarter cover 128 contiguous bytes (256 of an fp32 copy).  Tokens in
+// lanes of a quarter cover 128 contiguous bytes (256 of the fp32 Y that is kept).  Tokens in
 // [n_tokens, ldt) are written as zero so the padded K range contributes nothing; ldt is a
 // multiple of 128.
 // Rows are stored in blocks of tb tokens (tb a multiple of 128): position p of feature f
 // lives at  (p / tb) * d * tb + f * tb + p % tb  (one block, tb = ldt, is the plain layout).
-__host__ __device__ __forceinline__ int64_t token_position(int64_t t) {
-  return (t & ~(int64_t)63) + ((t & 15) << 2) + ((t & 63) >> 4);
-}
 
 // dL/dy of one entry from the row's coefficients {alpha, mu, beta, m3}; alpha = 0 (padding tokens, rows
 // without spread) gives 0 by itself as long as y is finite.  One definition for the recompute epilogue and
@@ -263,7 +260,6 @@ struct EpiStore : EpiBase {
   float* C;
   int64_t ldc, batch_stride, split_stride;
   int M, N;
-  float alpha = 1.f;  // C = alpha * acc
   // operands swapped: a lane owns four consecutive columns of one row of every block, so the tile leaves as 16-byte
   // stores straight from the accumulators (a store instruction covers 16 rows x 64 bytes, the block beside it the
   // other half of those 128-byte lines)
@@ -282,7 +278,7 @@ struct EpiStore : EpiBase {
 #pragma unroll
         for (int nb = 0; nb < TL::NB; ++nb) {
           const int n = n0 + f.n_quad(nb);
-          const floatx4 v = alpha * acc[mb][nb];
+          const floatx4 v = acc[mb][nb];
           if (vec) {
             if (n < N) *reinterpret_cast<floatx4*>(row + n) = v;
           } else {
@@ -599,7 +595,7 @@ __global__ __launch_bounds__(TL::NT) void cayley_iterate_kernel(GemmShape g, Epi
       for (int nb = 0; nb < TL::NB; ++nb) acc[mb][nb] = floatx4{0.f, 0.f, 0.f, 0.f};
     settle_all<TL>(acc);
     gemm_mainloop<TL, false, false, true>((k & 1 ? U1 : U0) + (int64_t)batch * g.batch_stride_a, g.lda, g.M, m0, B, g.ldb, g.N, n0, 0,
-                                          g.slabs_total, g.slabs_per_block, 0, 0, acc, lds, 0);
+                                          g.slabs_total, g.slabs_per_block, 0, acc, lds, 0);
     settle_all<TL>(acc);
     EpiCayleyIter<TL> e = epi;
     e.it = k;

@@ -2,8 +2,8 @@
 // (d = 128, bf16) in ONE kernel that reads X exactly once.
 //
 // For many small independent problems (one 128 x 128 rotation per KV head and layer, the
-// R2 learner of "Learning the Rotations") the three-GEMM path is bandwidth-bound: it
-// reads X three times and writes and re-reads two token-minor copies.  Here a workgroup
+// R2 learner of "Learning the Rotations") the path of one product after the other is
+// bandwidth-bound: it reads X twice and writes and re-reads Y and dL/dY.  Here a workgroup
 // walks token tiles of 128 rows of one problem and, per tile,
 //   B. Y = X_tile R            (MFMA; token on the lane, all 128 features of a token in the
 //                               registers of four lanes)

@@ -3,9 +3,9 @@
 // One device-side main loop computes a BM x BN tile of  C = A * B^T  where both
 // operands are stored with the contraction index contiguous ("NT" form):
 //   A [M][lda], B [N][ldb], C[m][n] = sum_k A[m][k] * B[n][k].
-// The loss/gradient step only ever needs this form: the rotation is kept
-// transposed (R^T rows are output features), activations are token-major for the
-// forward passes and feature-major (token-minor) copies feed X^T * G.
+// An operand may also come with K as its row index (ATN, BTN of gemm_mainloop): activations
+// X [token][feature] in X^T G, fp32 R, W and dL/dY as they lie in memory.  The bf16 path keeps
+// R^T (rows are output features) and dL/dY token-minor, which are NT operands.
 //
 // Tiling: 64-wide wavefronts, each wave owns WTM x WTN of the tile as a grid of
 // 16x16 MFMA blocks (v_mfma_f32_16x16x32_bf16, or 4 x v_mfma_f32_16x16x4_f32 per
@@ -191,8 +191,8 @@ struct GemmShape {
   int slabs_per_split;
   int tiles_total;   // tiles_m * tiles_n * split_k
   int grid_padded;   // tiles_total rounded up to a multiple of 8
-  int slabs_per_block;             // K blocking of the operand rows (see gemm_mainloop)
-  int64_t block_bytes_a, block_bytes_b;
+  int slabs_per_block;             // K blocking of the rows of B (see gemm_mainloop)
+  int64_t block_bytes_b;
   int k_valid;                     // ATN: rows of A that exist (K may be padded beyond them)
 #ifdef KT_PHASE_STAMPS
   int stamp_slot;                  // developer build only: which launch record the stamps go to
@@ -277,10 +277,10 @@ constexpr int fragment_read_slot(int r, int base, int spacing) {
 
 // Main loop.  Rows of A beyond M (and of B beyond N) are read from the last valid
 // row, so every load stays inside the operand; the epilogue masks them out.
-// K is addressed in slabs: slab g of an operand row starts at byte
+// K is addressed in slabs: slab g of a row of B starts at byte
 //   (g / slabs_per_block) * block_bytes + (g % slabs_per_block) * 128
-// of the row, which is the plain g * 128 for an ordinary row-major operand
-// (slabs_per_block = number of slabs in a row) and lets the token-minor operands of
+// of the row (of A: at g * 128), which is the plain g * 128 for an ordinary row-major operand
+// (slabs_per_block = number of slabs in a row) and lets the token-minor dL/dY of
 // dR = X^T G be stored in blocks of a few thousand tokens, so that the 256 rows a tile
 // reads at any one time lie within a couple of MiB instead of 256 separate pages.
 // The slab range [slab0, slab0 + k_slabs) must lie inside both operands' rows, and
@@ -311,7 +311,7 @@ constexpr int fragment_read_slot(int r, int base, int spacing) {
 // ATN (bf16): operand A is given with K as its ROW index instead, A[k][lda] with the tile's
 // rows m as consecutive columns (the activations X [token][feature] for dR = X^T G: no
 // token-minor copy of X is needed).  K is walked in the order the other operand stores it
-// (token_position() of the epilogues: position 4a + b of a 64-token group is token a + 16 b), one
+// (EpiGrad's: position 4a + b of a 64-token group is token a + 16 b), one
 // group per slab.  A stage is then 64 tile rows of BM values, columns beyond M read from the last valid ones.  Fragments come from read_tr_operand,
 // two lane quarters at a time reading 32 bytes of rows k .. k+3 and of rows k+8 .. k+11: the 32-byte
 // pieces of a row are XOR-swizzled with 2 (row % 4) + (row / 8) % 2, which puts those eight into
@@ -330,7 +330,7 @@ __device__ __forceinline__ void gemm_mainloop(const typename TL::T* __restrict__
                                               int M, int m0,
                                               const typename TL::T* __restrict__ B, int64_t ldb,
                                               int N, int n0, int slab0, int k_slabs,
-                                              int slabs_per_block, int64_t block_bytes_a,
+                                              int slabs_per_block,
                                               int64_t block_bytes_b,
                                               floatx4 (&acc)[TL::MB][TL::NB], char* lds, int k_valid
                                               KT_STAMP_PARAM) {
@@ -401,13 +401,12 @@ __device__ __forceinline__ void gemm_mainloop(const typename TL::T* __restrict__
 
   // The slabs to request next (A, B) and where they start inside a row: uniform values, advanced slab by slab; past
   // the last one: the last one again.
-  int req_a = slab0, req_b = slab0, in_block_a = slab0 % slabs_per_block, in_block_b = in_block_a;
+  int req_a = slab0, req_b = slab0, in_block_b = slab0 % slabs_per_block;
   const int last_slab = slab0 + k_slabs - 1;
   const char* an = Ab + (ATN ? (int64_t)slab0 * TL::BK * lda * (int64_t)sizeof(T)
-                             : (slab0 / slabs_per_block) * block_bytes_a + (int64_t)in_block_a * kRowBytes);
+                             : (int64_t)slab0 * kRowBytes);
   const char* bn = Bb + (BTN ? (int64_t)slab0 * TL::BK * ldb * (int64_t)sizeof(T)
                              : (slab0 / slabs_per_block) * block_bytes_b + (int64_t)in_block_b * kRowBytes);
-  const int64_t a_wrap = block_bytes_a - (int64_t)(slabs_per_block - 1) * kRowBytes;
   const int64_t b_wrap = block_bytes_b - (int64_t)(slabs_per_block - 1) * kRowBytes;
   sgprx4 rsrc_a, rsrc_b;
   // take the next slab as the one gload() loads
@@ -429,13 +428,7 @@ __device__ __forceinline__ void gemm_mainloop(const typename TL::T* __restrict__
     rsrc_a = raw_buffer(a0);
     if (req_a < last_slab) {
       ++req_a;
-      if constexpr (ATN) {
-        an += (int64_t)TL::BK * lda * (int64_t)sizeof(T);
-      } else {
-        const bool wrap = ++in_block_a == slabs_per_block;
-        if (wrap) in_block_a = 0;
-        an += wrap ? a_wrap : (int64_t)kRowBytes;
-      }
+      an += ATN ? (int64_t)TL::BK * lda * (int64_t)sizeof(T) : (int64_t)kRowBytes;
     }
   };
   auto locate_b = [&]() __attribute__((always_inline)) {
@@ -648,7 +641,7 @@ __global__ __launch_bounds__(TL::NT) void gemm_nt_kernel(GemmShape g, Epi epi) {
   const T* A = static_cast<const T*>(g.A) + (int64_t)batch * g.batch_stride_a;
   const T* B = static_cast<const T*>(g.B) + (int64_t)batch * g.batch_stride_b;
   gemm_mainloop<TL, ATN, BTN, Epi::kSwap>(A, g.lda, g.M, m0, B, g.ldb, g.N, n0, slab0, slabs, g.slabs_per_block,
-                         g.block_bytes_a, g.block_bytes_b, acc, lds, g.k_valid KT_STAMP_ARG);
+                         g.block_bytes_b, acc, lds, g.k_valid KT_STAMP_ARG);
   settle_all<TL>(acc);
   KT_STAMP(g, 2);
   epi(acc, batch, tm, tn, ks, m0, n0);

@@ -6,7 +6,7 @@
 // A step (32 of K) is 32 matrix instructions on 8 KiB of operands, which come through the caches directly in the form the
 // instruction takes them: no LDS round trip, no barrier, three steps in flight.  The four sums meet in LDS in fixed order.
 //
-// Bound: the L2, 32 bytes a cycle and CU, i.e. four times what the 64 x 64 tiles read; those win where they fill the chip.
+// Bound: the L2, 32 bytes a cycle and CU (8 KiB in 256 matrix cycles), twice what the 64 x 64 tiles read; those win where they fill the chip.
 #pragma once
 #include "kt_gemm.h"
 
