@@ -156,22 +156,27 @@ constexpr int kSensBlocks = 1024;  // workgroups of the sensitivity sweeps
 constexpr int kCayleyMaxIters = 32;
 // Iterations that are a launch each; those behind them share one launch (cayley_iterate_kernel; `tiles` of it per problem, `edge` wide).
 // A launch that finds the iteration converged costs 2 to 3 us.  An iteration inside the kernel costs more than one by itself, by 3 to 10 us
-// up to 128 tiles, by 20 to 40 us at 400 (each tile writes back and drops an L2 that others work from).  A step of usual size takes
-// three iterations, (lr / 2) ||A|| = 0.1, 0.3, 0.5 takes 5, 11, 24.  us, 3 / 8 / 16 / 32 by themselves:
-//   fp32  d = 512 (64 tiles)       3 its 51 / 62 / 84 / 135        11 its 183 / 159 / 152 / 181       23 its 379 / 372 / 333 / 267
-//         d = 768 (144)                  93 / 103 / 121 / 151             294 / 272 / 270 / 300              646 / 622 / 591 / 567
-//         d = 640, 2 problems (200)      84 / 94 / 110 / 140              278 / 251 / 246 / 276              643 / 615 / 573 / 532
-//         d = 896, 2 problems (392)     152 / 162 / 179 / 210             594 / 493 / 443 / 474             1370 / 1264 / 1104 / 934
-//         d = 256, 32 problems (512)     87 / 98 / 114 / 146              377 / 306 / 259 / 290              798 / 728 / 615 / 518
+// up to 128 tiles, by up to 40 us at 1000 (each tile drops an L2 that others work from).  A step of usual size takes two or
+// three iterations, (lr / 2) ||A|| = 0.1, 0.3, 0.5 takes 5, 11, 25: the line lies where usual steps pay 10 us or 5 % for the others to be no
+// slower, or a few percent, than a launch for each.  us, 3 / 8 / 16 / 32 by themselves:
+//   fp32  d = 512 (64 tiles)             3 its 53 / 62 / 77 / 107        11 its 184 / 160 / 153 / 183        25 its 408 / 371 / 332 / 268
+//         d = 768 (144)                        95 / 103 / 118 / 147             288 / 268 / 267 / 296              609 / 589 / 556 / 541
+//         d = 640, 2 problems (200)            87 / 96 / 110 / 139              277 / 251 / 244 / 273              625 / 600 / 560 / 520
+//         d = 256, 16 problems (256)           59 / 68 / 83 / 113               179 / 170 / 169 / 199              361 / 353 / 340 / 333
+//         d = 896, 2 problems (392)           162 / 165 / 177 / 207             569 / 485 / 438 / 469             1308 / 1218 / 1076 / 926
+//         d = 512, 8 problems (512)           125 / 133 / 147 / 175             394 / 363 / 345 / 377              831 / 803 / 762 / 716
+//         d = 896, 4 problems (784)           285 / 277 / 293 / 329            1000 / 846 / 763 / 799             2255 / 2098 / 1862 / 1610
+//         d = 256, 64 problems (1024)         148 / 160 / 175 / 210             467 / 430 / 411 / 449              919 / 889 / 838 / 807
 //         d = 512, 32 problems (512 of 128 x 128; only the 16 of a problem wait for each other)
-//                                       372 / - / 402 / 438              1135 / - / 1115 / 1152             2276 / - / 2295 / 2269
-//   fp16  d = 2048 (256)                307 / 317 / 332 / 362             958 / 875 / 837 / 865             2008 / 1928 / 1799 / 1676
-//         d = 4096 (256)               1580 / 1586 / 1601 / 1632         4128 / 4041 / 4023 / 4042          9237 / 9153 / 9015 / 8911
+//                                             372 / - / 402 / 438              1135 / - / 1115 / 1152             2276 / - / 2295 / 2269
+//   fp16  d = 1024 (256)                      129 / 138 / 152 / 182             396 / 361 / 351 / 381              863 / 830 / 777 / 725
+//         d = 2048 (256)                      307 / 317 / 332 / 362             958 / 875 / 837 / 865             2008 / 1928 / 1799 / 1676
+//         d = 4096 (256)                     1580 / 1586 / 1601 / 1632         4128 / 4041 / 4023 / 4042          9237 / 9153 / 9015 / 8911
 static int cayley_own_launches(int64_t tiles, int64_t batch, int edge, bool split) {
   if (!split && edge == TF::BM) return tiles <= 16 ? 3 : kCayleyMaxIters;
   if (tiles * batch < kNumCUs / 2) return 3;
   if (split || tiles * batch < 200) return 8;
-  return tiles * batch <= 400 ? 16 : kCayleyMaxIters;
+  return tiles * batch <= 400 ? 12 : 16;
 }
 constexpr float kCayleyTol = 3e-7f;
 
@@ -252,7 +257,9 @@ static int64_t cayley_control_words(int64_t d) {
 template <class TL>
 static bool launch_cayley_iterations(const typename TL::T* U0, const typename TL::T* U1, const typename TL::T* B, int64_t K, int64_t d,
                                      int64_t batch, const EpiCayleyIter<TL>& epi, unsigned* control, int it0, hipStream_t stream) {
-  auto kern = cayley_iterate_kernel<TL>;
+  auto kern = &cayley_iterate_kernel<TL, false>;
+  if constexpr (TL::BM == 64)
+    if (ceil_div(d, TL::BM) * ceil_div(d, TL::BN) * batch >= 200) kern = &cayley_iterate_kernel<TL, true>;
   if (!tile_offsets_fit(TL::BM, K, (int64_t)sizeof(typename TL::T))) return false;
   if (!ensure_dynamic_lds(reinterpret_cast<const void*>(kern), TL::LDS_BYTES)) return false;
   GemmShape g = {};

@@ -413,6 +413,20 @@ __device__ __forceinline__ bool cayley_converged(const unsigned* dl, int k, floa
                                k > 1 ? __uint_as_float(dl[k - 2]) : 0.f, k > 1 ? 2 : k, tol);
 }
 
+// A store of 8 or 16 bytes, PAST_L2: in units of 8 that are visible to the whole device once they have completed.
+template <bool PAST_L2, class V, class E>
+__device__ __forceinline__ void put(E* p, V v) {
+  if constexpr (PAST_L2) {
+    uint64_t w[sizeof(V) / 8];
+    __builtin_memcpy(w, &v, sizeof(V));
+#pragma unroll
+    for (size_t i = 0; i < sizeof(V) / 8; ++i)
+      __hip_atomic_store(reinterpret_cast<uint64_t*>(p) + i, w[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  } else {
+    *reinterpret_cast<V*>(p) = v;
+  }
+}
+
 // Unew is written as fp32, or (Usplit != null) as the [hi | hi | lo] fp16 operand of the
 // three-term GEMM that runs the next iteration.  As the epilogue of a launch of its own it returns at once when iteration
 // it - 1 or an earlier one has converged.  (cayley_iterate_kernel sets `it` and the two targets.)
@@ -436,6 +450,10 @@ struct EpiCayleyIter {
   }
   __device__ __forceinline__ void operator()(floatx4 (&acc)[TL::MB][TL::NB], int batch, int,
                                              int, int, int m0, int n0) const {
+    apply<false>(acc, batch, m0, n0);
+  }
+  template <bool PAST_L2>
+  __device__ __forceinline__ void apply(floatx4 (&acc)[TL::MB][TL::NB], int batch, int m0, int n0) const {
     const Frag<TL> f;
     const int64_t bo = (int64_t)batch * d * d;
     const float bs = bscale ? bscale[4 * batch + 3] : 1.f;
@@ -461,7 +479,7 @@ struct EpiCayleyIter {
             dmax = umax(dmax, abs_bits(z[r] - zo[r]));
             u[r] = rt[r] + z[r];
           }
-          *reinterpret_cast<floatx4*>(Zt + idx) = z;
+          put<PAST_L2>(Zt + idx, z);
           if constexpr (sizeof(typename TL::T) == 2) {
             typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
             const int64_t so = 3 * bo + (int64_t)m * 3 * d + n;
@@ -473,11 +491,11 @@ struct EpiCayleyIter {
               hi[r] = h;
               lo[r] = l;
             }
-            *reinterpret_cast<f16x4*>(Usplit + so) = hi;
-            *reinterpret_cast<f16x4*>(Usplit + so + d) = hi;
-            *reinterpret_cast<f16x4*>(Usplit + so + 2 * d) = lo;
+            put<PAST_L2>(Usplit + so, hi);
+            put<PAST_L2>(Usplit + so + d, hi);
+            put<PAST_L2>(Usplit + so + 2 * d, lo);
           } else {
-            *reinterpret_cast<floatx4*>(Unew + idx) = u;
+            put<PAST_L2>(Unew + idx, u);
           }
         }
       }
@@ -498,16 +516,19 @@ constexpr int kCayleyControlWords = 64;  // done[0 .. 31], stop at 32; claim[] b
 // that is waited for is in the hands of a running workgroup, whatever else runs on the chip.  (The wait ends after
 // kCayleyWaitTicks all the same; the step then counts as not converged.)
 //
-// The results of a tile become visible with a release at device scope by one thread behind the workgroup's stores, and are
-// acquired at that scope behind the wait; done[], claim[] and the changes are atomics.
+// The results of a tile become visible with a release at device scope by one thread behind the workgroup's stores, or (PAST_L2) are
+// stored past the L2: the stores of a wave are waited for, the barrier gathers the waves, and done[] is raised behind it.  They are
+// acquired at device scope behind the wait; done[], claim[] and the changes are atomics.
 //
 // Why one launch: the host cannot know when the iteration has converged, so a launch per iteration means all 32 of them, and one
 // that only finds the convergence flag set costs 2 to 3 us.  Why not for the first ones: a release and an acquire per tile write
-// back and drop an XCD's L2 while other workgroups work from it (cayley_own_launches has the figures; with stores past the L2 in
-// place of the release, large tiles lost more than they gained: d = 4096 9500 / 10500).
+// back and drop an XCD's L2 while other workgroups work from it (cayley_own_launches has the figures).  PAST_L2 leaves the acquire: better
+// from 200 tiles of 64 x 64 on, 24 iterations, all but three inside, us, release / past the L2: d = 256, 16 problems (256 tiles) 429 / 361, 64 (1024) 1510 / 919,
+// 512, 8 (512) 986 / 831, 896, 2 (392) 1369 / 1308, fp16 1024 (256) 912 / 863; but 256, 1 (16) 268 / 319, 512 (64) 408 / 467, 768 (144) 609 / 657, and
+// 256 x 256 tiles, d = 4096, 9500 / 10500.
 constexpr long long kCayleyWaitTicks = 20ll * 100000000;  // 20 s of the 100 MHz counter
 
-template <class TL>
+template <class TL, bool PAST_L2>
 __global__ __launch_bounds__(TL::NT) void cayley_iterate_kernel(GemmShape g, EpiCayleyIter<TL> epi, const typename TL::T* U0,
                                                                 const typename TL::T* U1, unsigned* control, int64_t control_stride, int it0) {
   extern __shared__ __align__(16) char lds[];
@@ -602,11 +623,11 @@ __global__ __launch_bounds__(TL::NT) void cayley_iterate_kernel(GemmShape g, Epi
     T* next = const_cast<T*>(k & 1 ? U0 : U1);
     if constexpr (sizeof(T) == 2) e.Usplit = next;
     else e.Unew = next;
-    e(acc, batch, tm, tn, 0, m0, n0);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's stores (and its change) have reached the L2
+    e.template apply<PAST_L2>(acc, batch, m0, n0);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");  // this wave's stores (and its change) have reached the L2, or the memory behind it
     __syncthreads();
     if (threadIdx.x == 0) {
-      __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
+      if constexpr (!PAST_L2) __builtin_amdgcn_fence(__ATOMIC_RELEASE, "agent");
       __hip_atomic_fetch_add(done + k, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
     }
   }
