@@ -157,8 +157,8 @@ constexpr int kCayleyMaxIters = 32;
 // Iterations that are a launch each; those behind them share one launch (cayley_iterate_kernel; `tiles` of it per problem, `edge` wide).
 // A launch that finds the iteration converged costs 2 to 3 us.  An iteration inside the kernel costs more than one by itself, by 3 to 10 us
 // up to 128 tiles, by up to 40 us at 1000 (each tile drops an L2 that others work from).  A step of usual size takes two or
-// three iterations, (lr / 2) ||A|| = 0.1, 0.3, 0.5 takes 5, 11, 25: the line lies where usual steps pay 10 us or 5 % for the others to be no
-// slower, or a few percent, than a launch for each.  us, 3 / 8 / 16 / 32 by themselves:
+// three iterations, (lr / 2) ||A|| = 0.1, 0.3, 0.5 takes 5, 11, 25: no more than the first three while 11 iterations are no slower for it than with
+// 32 launches of the former kind (d = 768 163 / 348 / 649, 640, 2 problems 151 / 306 / 595, 896, 2 237 / 548 / 1103), a few more above.  us, 3 / 8 / 16 / 32 by themselves:
 //   fp32  d = 512 (64 tiles)             3 its 53 / 62 / 77 / 107        11 its 184 / 160 / 153 / 183        25 its 408 / 371 / 332 / 268
 //         d = 768 (144)                        95 / 103 / 118 / 147             288 / 268 / 267 / 296              609 / 589 / 556 / 541
 //         d = 640, 2 problems (200)            87 / 96 / 110 / 139              277 / 251 / 244 / 273              625 / 600 / 560 / 520
@@ -174,9 +174,9 @@ constexpr int kCayleyMaxIters = 32;
 //         d = 4096 (256)                     1580 / 1586 / 1601 / 1632         4128 / 4041 / 4023 / 4042          9237 / 9153 / 9015 / 8911
 static int cayley_own_launches(int64_t tiles, int64_t batch, int edge, bool split) {
   if (!split && edge == TF::BM) return tiles <= 16 ? 3 : kCayleyMaxIters;
-  if (tiles * batch < kNumCUs / 2) return 3;
-  if (split || tiles * batch < 200) return 8;
-  return tiles * batch <= 400 ? 12 : 16;
+  if (tiles * batch < (split && edge > 64 ? kNumCUs / 2 : 200) || (split && edge == 64)) return 3;
+  if (split) return 8;
+  return tiles * batch <= 400 ? 6 : 16;
 }
 constexpr float kCayleyTol = 3e-7f;
 

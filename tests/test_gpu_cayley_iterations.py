@@ -1,4 +1,4 @@
-"""Retractions of many iterations: the first 3, 8, 12, 16 or all as launches of their own, the later ones inside one launch (release or stores past the L2), on tile grids on either
+"""Retractions of many iterations: the first 3, 6, 8, 16 or all as launches of their own, the later ones inside one launch (release or stores past the L2), on tile grids on either
 side of each rule, one and several problems; Cayley Adam with both forms of the products and with control words that do not fit
 their first place (d = 5760).  Against the exact transform in 64 bits on the device."""
 import numpy as np
