@@ -382,7 +382,7 @@ def main():
                     "avg_launch_ms": round(kern[0]["avg_ms"], 4), "bytes_per_launch": x_bytes,
                     "mfma_tflops_4nd2": round(2 * flops_launch / (kern[0]["avg_ms"] * 1e-3) / 1e12, 1), "traffic": None}
     else:
-        roofline = {"bound": "mfma", "kernel": ((KERNEL_NAMES_KEEP if keep else KERNEL_NAMES)[dom]) if bf16 else "gemm_nt_kernel<f32 128x128>",
+        roofline = {"bound": "mfma", "kernel": ((KERNEL_NAMES_KEEP if keep else KERNEL_NAMES)[dom]) if bf16 else "fp32 product (gemm32_kernel or gemm_nt_kernel, by size)",
                     "achieved": round(kern[dom]["tflops"], 2), "peak": peak, "unit": "TFLOP/s",
                     "frac": round(kern[dom]["tflops"] / peak, 4), "avg_launch_ms": round(kern[dom]["avg_ms"], 4),
                     "flops_per_launch": flops_launch,
