@@ -26,6 +26,8 @@ KERNEL_NAMES = {0: "gemm_nt_kernel<bf16 256x256, EpiMoments> (forward + row mome
                 2: "gemm_nt_kernel<bf16 256x256, EpiStore> (dR = X^T G)"}
 KERNEL_NAMES_KEEP = {0: "gemm_nt_kernel<bf16 256x256, EpiMomentsKeep> (forward + row moments + Y kept in fp32)",
                      2: "gemm_nt_kernel<bf16 256x256, EpiStore> (dR = X^T G)"}
+KERNEL_NAMES_ONE = {0: "row_sync_kernel<bf16 256x256, RowLossGrad> (forward + row statistics + dL/dY)",
+                    2: "gemm_nt_kernel<bf16 256x256, EpiStore> (dR = X^T G)"}
 # Fabric-side bytes per launch (rocprofv3 --pmc FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0, calibrated on a 1 GiB
 # device copy; see profiles/c3_gemm_counters.md).  Counters need a profiler run of their own, so the
 # figures measured for the default workload are carried here as constants; other workloads report null.
@@ -371,9 +373,10 @@ def main():
         kt.KT_OP_POOLED_LOSS_GRAD if pooled else kt.KT_OP_LOSS_GRAD, batch, n, d, kt.KT_BF16 if bf16 else kt.KT_F32) > \
         kt.kt_workspace_bytes(kt.KT_OP_POOLED_LOSS_GRAD_RECOMPUTE if pooled else kt.KT_OP_LOSS_GRAD_RECOMPUTE, batch, n, d,
                               kt.KT_BF16 if bf16 else kt.KT_F32)
+    one_launch = bf16 and not fused and not pooled and 1 not in kern  # row statistics and dL/dY in the forward product's launch: nothing kept or recomputed
     gemms = [k for k in kern if not (keep and k == 1)]
     dom = max(gemms, key=lambda k: kern[k]["avg_ms"])
-    hw_mult = 4.0 if keep else 6.0   # GEMM flop the step executes, in units of n d^2
+    hw_mult = 4.0 if keep or one_launch else 6.0   # GEMM flop the step executes, in units of n d^2
     if fused:
         x_bytes = 2.0 * batch * n * d
         gbs = x_bytes / (kern[0]["avg_ms"] * 1e-3) / 1e9
@@ -382,15 +385,15 @@ def main():
                     "avg_launch_ms": round(kern[0]["avg_ms"], 4), "bytes_per_launch": x_bytes,
                     "mfma_tflops_4nd2": round(2 * flops_launch / (kern[0]["avg_ms"] * 1e-3) / 1e12, 1), "traffic": None}
     else:
-        roofline = {"bound": "mfma", "kernel": ((KERNEL_NAMES_KEEP if keep else KERNEL_NAMES)[dom]) if bf16 else "fp32 product (gemm32_kernel or gemm_nt_kernel, by size)",
+        roofline = {"bound": "mfma", "kernel": ((KERNEL_NAMES_ONE if one_launch else KERNEL_NAMES_KEEP if keep else KERNEL_NAMES)[dom]) if bf16 else "fp32 product (gemm32_kernel or gemm_nt_kernel, by size)",
                     "achieved": round(kern[dom]["tflops"], 2), "peak": peak, "unit": "TFLOP/s",
                     "frac": round(kern[dom]["tflops"] / peak, 4), "avg_launch_ms": round(kern[dom]["avg_ms"], 4),
                     "flops_per_launch": flops_launch,
                     "traffic": MEASURED_TRAFFIC_BYTES.get(args.config, {}).get("keep" if keep else "recompute", {}).get(dom)
-                    if args.n is None and not pooled else None,
+                    if args.n is None and not pooled and not one_launch else None,
                     "traffic_source": "carried from profiles/c3_gemm_counters.md (rocprofv3 --pmc runs of this command); "
                                       "not measured in this run"}
-    names = {0: "fused_pass_ms" if fused else ("fwd_moments_keep_y_ms" if keep else "fwd_moments_ms"),
+    names = {0: "fused_pass_ms" if fused else "fwd_moments_grad_ms" if one_launch else ("fwd_moments_keep_y_ms" if keep else "fwd_moments_ms"),
              1: "grad_from_kept_y_ms" if keep else "bwd_recompute_ms", 2: "grad_xtg_ms"}
     breakdown = {names[k]: round(kern[k]["avg_ms"], 4) for k in kern}
     if keep and 1 in kern:  # the entry-by-entry kernel: reads Y (fp32), writes dL/dY in the GEMM dtype
@@ -404,11 +407,11 @@ def main():
     alg_tflops = 4.0 * batch * n * d * d * args.steps / elapsed / 1e12
     hw_tflops = hw_mult * batch * n * d * d * args.steps / elapsed / 1e12
 
-    # The form of the step in which Y never reaches HBM (recomputed by a second GEMM in the backward pass; the
+    # Where the pooled loss needs Y again: the form of the step in which it never reaches HBM (recomputed by a second GEMM in the backward pass; the
     # library takes it when handed its smaller workspace), timed beside the default on the same box and state of R.
     recomputed = None
     loss_last = float(loss[0])
-    if keep and args.op == "step":
+    if keep and not one_launch and args.op == "step":
         def step_recompute():
             if pooled:
                 kt.kt_pooled_kurtosis_loss_grad(X, Rw, loss=loss, dR=dR, workspace=ws, recompute=True)
@@ -485,7 +488,8 @@ def main():
                    "global_batch": batch * n, "hidden": d},
         "tflops_algorithmic_4nd2": round(alg_tflops, 2),
         "tflops_hardware": None if fused else round(hw_tflops, 2),
-        "hardware_flop_count": None if fused else ("4 n d^2: Y kept in fp32 scratch by the forward GEMM" if keep else
+        "hardware_flop_count": None if fused else ("4 n d^2: dL/dY in the epilogue of the forward GEMM" if one_launch else
+                                                   "4 n d^2: Y kept in fp32 scratch by the forward GEMM" if keep else
                                                    "6 n d^2: Y recomputed by a second GEMM in the backward pass"),
         "frac_of_bf16_peak_algorithmic": round(alg_tflops / peak, 4),
         "frac_of_bf16_peak_hardware": None if fused else round(hw_tflops / peak, 4),

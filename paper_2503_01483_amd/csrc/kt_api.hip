@@ -16,6 +16,7 @@
 #include "kt_fused_d128.h"
 #include "kt_hadamard.h"
 #include "kt_rows.h"
+#include "kt_rowsync.h"
 #include "kt_skinny.h"
 
 namespace kt {
@@ -248,6 +249,43 @@ static bool launch_features_gemm(const typename TL::T* R, int64_t ldr, bool in_p
   return launch_gemm<TL>(R, d, d * d, (int)d, X, ldx, n * ldx, (int)n, d, 0, (int)batch, e, st);
 }
 
+// ---- row_sync_kernel: features on the rows of the GEMM, one launch for all token tiles of all problems.
+// The tiles of as many whole row blocks as the chip holds are in flight; a block wider than that cannot wait for itself.
+template <class TL>
+static bool row_sync_shape(int64_t batch, int64_t n, int64_t d, RowSync* rs) {
+  const int64_t fit = kNumCUs * (160 * 1024 / TL::LDS_BYTES), cols = ceil_div(d, TL::BM), rows = ceil_div(n, TL::BN) * batch;
+  int64_t at_once = fit / cols;
+  if (at_once > rows) at_once = rows;
+  if (at_once < 1 || cols > 64 || rows * cols > INT32_MAX / 2) return false;  // (RowSync::order)
+  rs->rows = (int)rows;
+  rs->cols = (int)cols;
+  rs->at_once = (int)at_once;
+  rs->per_queue = (int)ceil_div(at_once * cols, 8);
+  rs->items = (int)(ceil_div(rows, at_once) * rs->per_queue);
+  return true;
+}
+template <class TL, class Op>
+static bool launch_row_sync(RowSync& rs, const typename TL::T* RT, const typename TL::T* X, int64_t ldx, int64_t n, int64_t d, const Op& op,
+                            hipStream_t stream) {
+  auto kern = &row_sync_kernel<TL, Op>;
+  static_assert(kNumCUs * (160 * 1024 / TL::LDS_BYTES) <= kRowSyncMost, "all tiles in flight have an entry");
+  rs.arrange();
+  if (!tile_offsets_fit(TL::BM, d, (int64_t)sizeof(typename TL::T)) || !tile_offsets_fit(TL::BN, ldx, (int64_t)sizeof(typename TL::T))) return false;
+  if (!ensure_dynamic_lds(reinterpret_cast<const void*>(kern), TL::LDS_BYTES)) return false;
+  GemmShape g = {};
+  g.A = RT; g.B = X; g.lda = d; g.ldb = ldx;
+  g.batch_stride_a = d * d; g.batch_stride_b = n * ldx;
+  g.M = (int)d; g.N = (int)n;
+  g.tiles_m = rs.cols;
+  g.tiles_n = (int)ceil_div(n, TL::BN);
+  g.slabs_total = g.slabs_per_block = (int)(d / TL::BK);
+#ifdef KT_PHASE_STAMPS
+  g.stamp_slot = -1;
+#endif
+  hipLaunchKernelGGL(kern, dim3((unsigned)(8 * rs.per_queue)), dim3(TL::NT), TL::LDS_BYTES, stream, RowSyncArgs<Op>{g, rs, op});
+  return launch_ok();
+}
+
 // Iterations it0, ... of `batch` retractions (cayley_iterate_kernel): U and B are [d][K] in the GEMM dtype.  As many workgroups per
 // problem as the chip holds, at most one per tile.
 template <class TL>
@@ -366,6 +404,50 @@ static bool small_dr_tiles(int64_t batch, int64_t slabs, int64_t d, int* slabs_p
     }
   }
   return best;
+}
+
+// ---- rows in one launch (kt_rowsync.h): with which tile, or not at all.
+// Time in the unit of bf16_tile_time.  Whole row blocks are in flight, so that the rounds are those of the row blocks; a large tile's ends take 9
+// slabs' time, a pair of small ones 0.82 of the unit (0.63 alone on their CUs) with ends of 4, fitted to 168 calls of d = 256 .. 4096, 1 .. 131072
+// tokens (off by more than 2 % at three of them).
+enum class RowSyncTile { none, small, large };
+template <class TL>
+static double row_sync_time(const RowSync& rs, int64_t slabs) {
+  if (TL::BM == 256) return (double)ceil_div(rs.rows, rs.at_once) * (double)(slabs + 9);
+  const int64_t rest = rs.rows % rs.at_once;
+  auto round = [&](int64_t r) { return r == 0 ? 0.0 : r * rs.cols <= kNumCUs ? 0.63 : 0.82; };
+  return ((double)(rs.rows / rs.at_once) * round(rs.at_once) + round(rest)) * ((double)slabs + 4.0);
+}
+// Loss + gradient, us, three launches (forward product that keeps Y, row statistics, dL/dY) and their better tile / this: d = 256, 16384 tokens 37.7 / 34.9, 131072
+// 136 / 92; 512, 16384 50.7 / 46.0, 131072 279 / 195; 1152, 40000 289 / 262; 2048, 4096 94.6 / 90.8, 16384 285 / 240, 131072 1954 / 1700; 4096, 7000 409 / 392, 131072 6550 / 6070.
+//  - wide rows and up to 256 tokens, or a few of any width, where the launches saved cost less than the wait: d = 2688, 100 55.4 / 56.5, 4096, 256 83.0 /
+//    84.1; but 2048, 256 46.1 / 45.5; 4096, 700 95.0 / 93.9.  One token: 23.7 / 23.6 (256) to 79.1 / 81.2 (4096)
+//  - a second round of large tiles for the last quarter of the row blocks, d > 1408: small ones that drift apart share the CUs better: 1920, 10007 183 / 192,
+//    2048, 10007 192 / 202, 2688, 7000 232 / 241; but 1152, 16384 135 / 133, 1408, 10007 (one round) 116 / 104
+static RowSyncTile loss_row_sync_tile(int64_t batch, int64_t n, int64_t d) {
+  RowSync small, large;
+  if (!row_sync_shape<TB_128>(batch, n, d, &small) || !row_sync_shape<TB_BIG>(batch, n, d, &large)) return RowSyncTile::none;
+  if (batch * n < 64 || (d > 2048 && batch * n <= 256)) return RowSyncTile::none;
+  if (d > 1408 && large.rows > large.at_once && 4 * (int64_t)large.rows <= 5 * (int64_t)large.at_once) return RowSyncTile::none;
+  const int64_t slabs = d / TB_BIG::BK;
+  return row_sync_time<TB_128>(small, slabs) < row_sync_time<TB_BIG>(large, slabs) ? RowSyncTile::small : RowSyncTile::large;
+}
+// Fake-quant, us, staged rows and their best tile / this: d = 256, 16384 tokens 23.6 / 18.3, 131072 80 / 52; 512, 10007 26.6 / 21.4, 131072 166 / 111; 1024, 16384
+// 52.2 / 45.6, 131072 418 / 291; 1920, 16384 151 / 120; 2048, 131072 1174 / 908; 4096, 4096 129 / 125, 16384 468 / 429, 40000 1153 / 1023.
+//  - d <= 640: from about a third of the chip's pairs of small tiles on: 256, 10007 (0.31) 18.2 / 17.6; 512, 4096 (0.25) 16.8 / 18.5; 640, 4096 (0.31) 20.5 / 20.4
+//  - wider rows with large tiles only, where they fill 0.7 of one or two rounds (1024, 7000, 0.44: 32.1 / 40.8; 2048, 10007, 0.62: 118 / 125; 1152, 10007, 0.70: 49.0 /
+//    46.4), or take no round more than the staged product (3072, 16384, four instead of three: 285 / 296)
+static RowSyncTile quant_row_sync_tile(int64_t batch, int64_t n, int64_t d) {
+  RowSync small, large;
+  if (!row_sync_shape<TB_128>(batch, n, d, &small) || !row_sync_shape<TB_BIG>(batch, n, d, &large)) return RowSyncTile::none;
+  const int64_t slabs = d / TB_BIG::BK, rounds = ceil_div(large.rows, large.at_once);
+  if (d <= 640) {
+    if (100 * (int64_t)small.rows * small.cols < 36 * 2 * kNumCUs) return RowSyncTile::none;
+    return row_sync_time<TB_128>(small, slabs) < row_sync_time<TB_BIG>(large, slabs) ? RowSyncTile::small : RowSyncTile::large;
+  }
+  const bool pays = rounds <= 2 ? 10 * (int64_t)large.rows * (d / 128) >= 7 * 2 * kNumCUs * rounds
+                                : rounds > 4 || rounds == ceil_div((int64_t)large.rows * large.cols, kNumCUs);
+  return pays ? RowSyncTile::large : RowSyncTile::none;
 }
 
 // max_fused_wgs: no more workgroups per problem than this on the d = 128 path (a caller's smaller workspace)
@@ -585,15 +667,15 @@ static kt_status check_ws(void* ws, size_t have, size_t need) {
   return KT_OK;
 }
 
-// R (fp32 or bf16, row-major) -> R^T in the GEMM dtype.
+// R (fp32 or bf16, row-major) -> R^T in the GEMM dtype; `zero_words` words at `zero` are cleared on the way.
 template <typename Tout>
 static bool prep_rt(const void* R, int64_t ldr, kt_dtype rdt, Tout* RT, int64_t batch, int64_t d,
-                    hipStream_t st) {
+                    hipStream_t st, unsigned* zero = nullptr, int64_t zero_words = 0) {
   const dim3 grid((unsigned)(d / 64), (unsigned)(d / 64), (unsigned)batch);
   if (rdt == KT_F32)
-    hipLaunchKernelGGL((transpose_kernel<float, Tout>), grid, dim3(256), 0, st, static_cast<const float*>(R), ldr, RT, (int)d);
+    hipLaunchKernelGGL((transpose_kernel<float, Tout>), grid, dim3(256), 0, st, static_cast<const float*>(R), ldr, RT, (int)d, zero, (int)zero_words);
   else
-    hipLaunchKernelGGL((transpose_kernel<bf16, Tout>), grid, dim3(256), 0, st, static_cast<const bf16*>(R), ldr, RT, (int)d);
+    hipLaunchKernelGGL((transpose_kernel<bf16, Tout>), grid, dim3(256), 0, st, static_cast<const bf16*>(R), ldr, RT, (int)d, zero, (int)zero_words);
   return launch_ok();
 }
 
@@ -627,16 +709,43 @@ static kt_status run_loss_grad_bf16(const LossGradPlan& p, const void* X, int64_
   T* GT = reinterpret_cast<T*>(ws + p.o_gt);
   float* splitk = reinterpret_cast<float*>(ws + p.o_splitk);
   const T* Xp = static_cast<const T*>(X);
-  const LossSum loss_sum = {loss_part, p.loss_blocks, (int)n, (int)batch, loss};
+
+  // a1 - a3 in one launch where a row's statistics are all the gradient needs.  Its words are in the room of the row coefficients,
+  // which then stay in the LDS: 8 bytes of loss and a counter per row block and nine counters, 16 bytes per token (packed, they fit in 256 a problem).
+  RowSync rs;
+  const RowSyncTile rs_tile = dR && !pooled ? loss_row_sync_tile(batch, n, d) : RowSyncTile::none;
+  const bool row_sync = rs_tile != RowSyncTile::none;
+  if (row_sync) {
+    (void)(rs_tile == RowSyncTile::small ? row_sync_shape<TB_128>(batch, n, d, &rs) : row_sync_shape<TB_BIG>(batch, n, d, &rs));
+    loss_part = reinterpret_cast<double*>(coef);
+    rs.words = reinterpret_cast<unsigned*>(loss_part + rs.rows);
+    rs.pitch = (size_t)rs.rows * 8 + (size_t)(kRowSyncWords + rs.rows) * kRowSyncPitch * 4 <= p.o_losspart - p.o_coef ? kRowSyncPitch : 1;
+  }
+  const LossSum loss_sum = {loss_part, row_sync ? (int)(rs.rows / batch) : p.loss_blocks, (int)n, (int)batch, loss};
 
   // a0: R -> R^T in the GEMM dtype
-  if (!prep_rt<T>(R, ldr, rdt, RT, batch, d, st)) return fail(KT_ERR_DEVICE, "prep_rt launch failed");
+  if (!prep_rt<T>(R, ldr, rdt, RT, batch, d, st, row_sync ? rs.words : nullptr, row_sync ? (int64_t)(kRowSyncWords + rs.rows) * rs.pitch : 0))
+    return fail(KT_ERR_DEVICE, "prep_rt launch failed");
 
   // go(tile) with the tile of the forward product (features on m, tokens on n)
   auto with_forward_tile = [&](auto go) -> bool {
     return p.small_fwd ? go(TB_128{}) : go(TB_BIG{});
   };
 
+  if (row_sync) {
+    ProfScope prof(0, st);
+    auto go = [&](auto tile_tag) -> bool {
+      using TL = decltype(tile_tag);
+      RowLossGrad<TL> op;
+      op.mom.part = part; op.mom.n_tokens = (int)n; op.mom.d = (int)d; op.mom.P = rs.cols;
+      op.grad.coef = nullptr; op.grad.GT = GT; op.grad.ldt = p.ldt; op.grad.tb = p.tb; op.grad.batch_stride = d * p.nblk * p.tb;
+      op.grad.n_tokens = (int)n; op.grad.d = (int)d;
+      op.kappa_target = kappa_target; op.row_kurt = row_kurt; op.loss_part = loss_part; op.tiles_n = (int)(rs.rows / batch);
+      return launch_row_sync<TL>(rs, RT, Xp, ldx, n, d, op, st);
+    };
+    if (!(rs_tile == RowSyncTile::small ? go(TB_128{}) : go(TB_BIG{}))) return fail(KT_ERR_DEVICE, "forward GEMM launch failed");
+    if (p.split_k == 1 && !launch_loss_sum(loss_sum, st)) return fail(KT_ERR_DEVICE, "loss sum launch failed");
+  } else {
   // a1: forward GEMM with the moment epilogue; with keep_y it also writes Y
   const bool keep = p.keep_y && dR;
   float* YT = reinterpret_cast<float*>(ws + p.o_yt);
@@ -693,6 +802,7 @@ static kt_status run_loss_grad_bf16(const LossGradPlan& p, const void* X, int64_
     });
     if (!ok)
       return fail(KT_ERR_DEVICE, "backward recompute GEMM launch failed");
+  }
   }
   // a4: dR = X^T G, split over tokens
   {
@@ -923,6 +1033,42 @@ static int64_t quant_d128_wgs(int64_t batch, int64_t n) {
   return best;
 }
 
+// Codes straight from the accumulators, the row's maximum taken between the tiles (kt_rowsync.h): no staged Y.
+// KT_ERR_NOT_SUPPORTED: not a size for it.
+static kt_status run_quant_row_sync(const QuantPlan& p, const bf16* X, int64_t ldx, const void* R, int64_t ldr, kt_dtype rdt, int64_t batch,
+                                    int64_t n, int64_t d, float clip, float* scales_out, int8_t* codes, float* err, char* ws, hipStream_t st) {
+  auto go = [&](auto tile_tag) -> kt_status {
+    using TL = decltype(tile_tag);
+    RowSync rs;
+    if (!row_sync_shape<TL>(batch, n, d, &rs)) return KT_ERR_NOT_SUPPORTED;
+    const int64_t tiles = (int64_t)rs.rows * rs.cols, P = rs.cols * TL::WGM;
+    const int64_t counters = kRowSyncWords + 2 * (int64_t)rs.rows;
+    Carver c;  // in the room of the staged rows
+    const size_t o_words = c.take((size_t)counters * kRowSyncPitch * 4), o_links = c.take((size_t)tiles * 4);
+    const size_t o_amax = c.take((size_t)batch * P * n * 4), o_err = c.take(err ? (size_t)batch * P * n * 8 : 0);
+    if (p.o_y + c.off > p.total) return KT_ERR_NOT_SUPPORTED;
+    char* room = ws + p.o_y;
+    rs.words = reinterpret_cast<unsigned*>(room + o_words);
+    rs.pitch = kRowSyncPitch;
+    bf16* RT = reinterpret_cast<bf16*>(ws + p.o_rt);
+    if (!prep_rt<bf16>(R, ldr, rdt, RT, batch, d, st, rs.words, counters * rs.pitch))
+      return fail(KT_ERR_DEVICE, "prep_rt launch failed");
+    RowQuant<TL> op;
+    op.amax.part = reinterpret_cast<float*>(room + o_amax);
+    op.amax.n_tokens = (int)n; op.amax.d = (int)d; op.amax.P = (int)P;
+    op.quant.scales = nullptr; op.quant.codes = codes; op.quant.err_part = err ? reinterpret_cast<float2*>(room + o_err) : nullptr;
+    op.quant.n_tokens = (int)n; op.quant.d = (int)d; op.quant.P = (int)P;
+    op.clip = clip; op.scales_out = scales_out; op.err = reinterpret_cast<float2*>(err);
+    op.links = reinterpret_cast<int*>(room + o_links);
+    op.added = rs.words + (kRowSyncWords + (int64_t)rs.rows) * rs.pitch;
+    op.pitch = rs.pitch;
+    op.cols = rs.cols;
+    return launch_row_sync<TL>(rs, RT, X, ldx, n, d, op, st) ? KT_OK : fail(KT_ERR_DEVICE, "rotation GEMM launch failed");
+  };
+  const RowSyncTile tile = quant_row_sync_tile(batch, n, d);
+  return tile == RowSyncTile::large ? go(TB_BIG{}) : tile == RowSyncTile::small ? go(TB_128{}) : KT_ERR_NOT_SUPPORTED;
+}
+
 template <typename T, class TFWD, class TQ>
 static kt_status run_quant(const QuantPlan& p, const void* X, int64_t ldx, const void* R, int64_t ldr,
                            kt_dtype rdt, int64_t batch, int64_t n, int64_t d, float clip,
@@ -936,6 +1082,12 @@ static kt_status run_quant(const QuantPlan& p, const void* X, int64_t ldx, const
   const bool staged = !scales_in && (codes || err);
   const bool skinny = staged && p.stage_problems == batch && skinny_ok(sizeof(T) == 2 ? KT_BF16 : KT_F32, R, ldr, rdt, n);
   const bool in_place = sizeof(T) == 4 && f32_in_place(R, ldr);
+  if constexpr (sizeof(T) == 2) {
+    if (staged && !skinny) {
+      const kt_status s = run_quant_row_sync(p, Xp, ldx, R, ldr, rdt, batch, n, d, clip, scales_out, codes, err, ws, st);
+      if (s != KT_ERR_NOT_SUPPORTED) return s;
+    }
+  }
   if (!skinny && !in_place && !prep_rt<T>(R, ldr, rdt, RT, batch, d, st)) return fail(KT_ERR_DEVICE, "prep_rt launch failed");
   const T* Rg = in_place ? static_cast<const T*>(R) : RT;
   const int64_t r_stride = in_place ? d * ldr : d * d;

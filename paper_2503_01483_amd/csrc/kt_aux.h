@@ -10,9 +10,13 @@ __device__ __forceinline__ float to_float(Tin v) { return (float)v; }
 
 // R^T in the GEMM dtype: out[c * d + r] = in[r * ldi + c], d a multiple of 128, `out` 16-byte aligned.  64 x 64 tiles through LDS, 16
 // bytes per access on both sides (`in` in single values where its rows are not that aligned).  grid = (d / 64, d / 64, batch)
+// `zero`: words that a later launch counts in, cleared on the way.
 template <typename Tin, typename Tout>
-__global__ __launch_bounds__(256) void transpose_kernel(const Tin* __restrict__ in, int64_t ldi, Tout* __restrict__ out, int d) {
+__global__ __launch_bounds__(256) void transpose_kernel(const Tin* __restrict__ in, int64_t ldi, Tout* __restrict__ out, int d, unsigned* zero,
+                                                        int zero_words) {
   __shared__ float tile[64][65];
+  const int wg = (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x, wgs = gridDim.x * gridDim.y * gridDim.z;
+  for (int i = wg * 256 + threadIdx.x; i < zero_words; i += wgs * 256) zero[i] = 0u;
   constexpr int VI = 16 / (int)sizeof(Tin), VO = 16 / (int)sizeof(Tout);
   typedef Tin vec_in __attribute__((ext_vector_type(VI)));
   typedef Tout vec_out __attribute__((ext_vector_type(VO)));
@@ -65,27 +69,33 @@ __device__ __forceinline__ double block_sum_256(double v, double* sh) {
   return sh[0];
 }
 
+// Sums of (y - mu)^2, ^3, ^4 of one partial (cnt values; {mean, sum c^2, sum c^3, sum c^4} about its own mean) added to M.
+__device__ __forceinline__ void add_partial(const floatx4& v, double cnt, double mu, double (&M)[3]) {
+  const double e = (double)v[0] - mu, e2 = e * e;
+  M[0] += (double)v[1] + cnt * e2;
+  M[1] += (double)v[2] + 3.0 * e * (double)v[1] + cnt * e2 * e;
+  M[2] += (double)v[3] + 4.0 * e * (double)v[2] + 6.0 * e2 * (double)v[1] + cnt * e2 * e2;
+}
+
 // Moments of one token row from the P partials the forward epilogue wrote ({mean_p, sum c^2, sum c^3,
 // sum c^4} about the partial's own mean, d / P features each), merged in fp64 with the shift
 // formulas  sum (c + e)^k = sum c^k + k e sum c^(k-1) + ...  (sum c = 0 inside a partial):
 // mu = row mean, M[0..2] = sums of (y - mu)^2, ^3, ^4 over the row.
-__device__ __forceinline__ void row_central_sums(const floatx4* __restrict__ part, int P, int n, int64_t batch,
-                                                 int token, int d, double& mu, double (&M)[3]) {
+template <class Load>  // load(p): partial p of the row
+__device__ __forceinline__ void row_central_sums_of(Load load, int P, int d, double& mu, double (&M)[3]) {
   const double cnt = (double)d / (double)P;
   double m = 0.0;
-  for (int p = 0; p < P; ++p) m += (double)part[((int64_t)batch * P + p) * n + token][0];
+#pragma unroll 8
+  for (int p = 0; p < P; ++p) m += (double)load(p)[0];
   mu = m / (double)P;
-  double M2 = 0.0, M3 = 0.0, M4 = 0.0;
-  for (int p = 0; p < P; ++p) {
-    const floatx4 v = part[((int64_t)batch * P + p) * n + token];
-    const double e = (double)v[0] - mu, e2 = e * e;
-    M2 += (double)v[1] + cnt * e2;
-    M3 += (double)v[2] + 3.0 * e * (double)v[1] + cnt * e2 * e;
-    M4 += (double)v[3] + 4.0 * e * (double)v[2] + 6.0 * e2 * (double)v[1] + cnt * e2 * e2;
-  }
-  M[0] = M2; M[1] = M3; M[2] = M4;
+  M[0] = M[1] = M[2] = 0.0;
+#pragma unroll 8
+  for (int p = 0; p < P; ++p) add_partial(load(p), cnt, mu, M);
 }
-
+__device__ __forceinline__ void row_central_sums(const floatx4* __restrict__ part, int P, int n, int64_t batch,
+                                                 int token, int d, double& mu, double (&M)[3]) {
+  row_central_sums_of([&](int p) __attribute__((always_inline)) { return part[((int64_t)batch * P + p) * n + token]; }, P, d, mu, M);
+}
 // Central moments of a row (mean and sums of c^2, c^3, c^4) -> {alpha, mu, beta, m3} of its gradient and kappa; its loss
 // term is added to `loss`.
 __device__ __forceinline__ floatx4 row_coefficients(double mu, const double (&M)[3], int n, int d, float kappa_target, double& kappa,

@@ -60,6 +60,20 @@ __device__ __forceinline__ float quarter_pick(int q, float v0, float v1, float v
   return (q & 2) ? b : a;
 }
 
+// A store of 8 or 16 bytes, PAST_L2: in units of 8 that are visible to the whole device once they have completed.
+template <bool PAST_L2, class V, class E>
+__device__ __forceinline__ void put(E* p, V v) {
+  if constexpr (PAST_L2) {
+    uint64_t w[sizeof(V) / 8];
+    __builtin_memcpy(w, &v, sizeof(V));
+#pragma unroll
+    for (size_t i = 0; i < sizeof(V) / 8; ++i)
+      __hip_atomic_store(reinterpret_cast<uint64_t*>(p) + i, w[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  } else {
+    *reinterpret_cast<V*>(p) = v;
+  }
+}
+
 // ---- forward pass: per-token moments of y over the hidden dimension ---------------
 // m = output feature (reduced in registers), n = token (one per lane).
 // part[(batch*P + p)*n_tokens + token] = {mean_p, sum c^2, sum c^3, sum c^4}, c = y - mean_p, over
@@ -67,9 +81,11 @@ __device__ __forceinline__ float quarter_pick(int q, float v0, float v1, float v
 // over the registers), so that a row whose mean is large against its spread loses nothing to
 // cancellation in fp32; the partials of a row are merged in fp64 (row_central_sums in kt_aux.h).
 // bf16, 64 features a wave: the two waves of a token merge theirs, so that a partial is 128 features with every tile.
-template <class TL>
+// PAST_L2: for readers in the same launch (kt_rowsync.h), one partial a tile, P = tiles: what they read goes past the L2 as well.
+template <class TL, bool PAST_L2 = false>
 struct EpiMoments : EpiBase {
   static constexpr bool kMerge = sizeof(typename TL::T) == 2 && TL::WTM == 64;
+  static constexpr bool kExchange = PAST_L2 && !kMerge;
   static_assert(TL::MB % 4 == 0 && TL::NB % 4 == 0, "features and tokens are taken 64 at a time");
   floatx4* part;
   int n_tokens, d, P;
@@ -83,6 +99,7 @@ struct EpiMoments : EpiBase {
     const float inv_cnt = blocks > 0 ? 1.0f / (float)(16 * blocks) : 0.f;
     // 64 tokens (four blocks of columns) at a time: quarter k of the wave ends up with the sums of block k, i.e.
     // lane l with those of token l of the 64
+    floatx4 own = {0.f, 0.f, 0.f, 0.f};  // kExchange: of 64-token group wm
 #pragma unroll
     for (int g = 0; g < TL::NB / 4; ++g) {
       float mean[4], s2[4], s3[4], s4[4];
@@ -128,8 +145,24 @@ struct EpiMoments : EpiBase {
         if (f.wm == 1) return;
         v = merged(v, *other, 64.0);
       }
+      if constexpr (kExchange) {
+        static_assert(!kExchange || (TL::WGM == 2 && TL::NB == 8), "two waves hold the features of 128 tokens");
+        extern __shared__ __align__(16) char lds[];
+        floatx4* sh = reinterpret_cast<floatx4*>(lds) + 64 * (2 * f.wn + g) + f.lane;
+        if (g == 0) __syncthreads();  // (the last fragments have been read)
+        if (f.wm == g) own = v;
+        else *sh = v;
+        if (g == 0) continue;
+        __syncthreads();
+        const floatx4 other = reinterpret_cast<floatx4*>(lds)[64 * (2 * f.wn + f.wm) + f.lane];
+        const int mine = n0 + f.wn * TL::WTN + 64 * f.wm + f.lane;
+        // the last tile of d % 256 = 128 has nothing in its second half
+        v = m0 + TL::WTM < d ? merged(f.wm == 0 ? own : other, f.wm == 0 ? other : own, (double)TL::WTM) : f.wm == 0 ? own : other;
+        if (mine < n_tokens) put<PAST_L2>(&part[((int64_t)batch * P + tm) * n_tokens + mine], v);
+        return;
+      }
       const int pp = kMerge ? tm : p;
-      if (token < n_tokens && pp < P) part[((int64_t)batch * P + pp) * n_tokens + token] = v;
+      if (token < n_tokens && pp < P) put<PAST_L2>(&part[((int64_t)batch * P + pp) * n_tokens + token], v);
     }
   }
   // two partials of cnt values each as one (the shift formulas of row_central_sums)
@@ -182,21 +215,30 @@ struct EpiGrad : EpiBase {
   int n_tokens, d;
   __device__ __forceinline__ void operator()(floatx4 (&acc)[TL::MB][TL::NB], int batch, int,
                                              int, int, int m0, int n0) const {
+    store(acc, batch, m0, n0, [&](int t) __attribute__((always_inline)) {
+      floatx4 c4 = {0.f, 0.f, 0.f, 0.f};  // alpha = 0 zeroes the padding tokens
+      if (n0 + t < n_tokens) c4 = coef[(int64_t)batch * n_tokens + n0 + t];
+      return c4;
+    });
+  }
+  // coef_of(t): the coefficients of token n0 + t
+  template <class CoefOf>
+  __device__ __forceinline__ void store(floatx4 (&acc)[TL::MB][TL::NB], int batch, int m0, int n0, CoefOf coef_of) const {
     typedef T vecT __attribute__((ext_vector_type(4)));
     const Frag<TL> f;
 #pragma unroll
     for (int g = 0; g < TL::NB / 4; ++g) {
       const int group0 = n0 + f.wn * TL::WTN + 64 * g;  // the 64-token group
       if (group0 >= ldt) return;
-      const int64_t pos0 = group0 + (f.l16 << 2);  // the lane's tokens group0 + 16 k + l16 lie at pos0 + k
-      const int64_t blk = pos0 / tb;
-      T* out = GT + (int64_t)batch * batch_stride + blk * d * tb + (pos0 - blk * tb);
+      // the lane's tokens group0 + 16 k + l16 lie at position group0 + 4 l16 + k (a group is in one block): a uniform base and 32 bits a lane
+      const int first = __builtin_amdgcn_readfirstlane(group0), blk = first / (int)tb;
+      char* base = reinterpret_cast<char*>(GT + (int64_t)batch * batch_stride + (int64_t)blk * d * tb + (first - blk * (int)tb) +
+                                           (int64_t)__builtin_amdgcn_readfirstlane(m0 + f.m_block(0)) * tb);
+      const uint32_t lane_off = (uint32_t)(4 * f.q * (int)tb + 4 * f.l16) * (uint32_t)sizeof(T);
       float alpha[4], mu[4], beta[4], m3[4];
 #pragma unroll
       for (int k = 0; k < 4; ++k) {
-        const int token = group0 + 16 * k + f.l16;
-        floatx4 c4 = {0.f, 0.f, 0.f, 0.f};  // alpha = 0 zeroes the padding tokens
-        if (token < n_tokens) c4 = coef[(int64_t)batch * n_tokens + token];
+        const floatx4 c4 = coef_of(group0 - n0 + 16 * k + f.l16);
         alpha[k] = c4[0]; mu[k] = c4[1]; beta[k] = c4[2]; m3[k] = c4[3];
       }
 #pragma unroll
@@ -208,8 +250,7 @@ struct EpiGrad : EpiBase {
 #pragma unroll
             for (int k = 0; k < 4; ++k)  // (the accumulators of padding tokens come from re-read valid rows and are finite)
               v[k] = from_float<T>(grad_value(acc[mb][4 * g + k][r], alpha[k], mu[k], beta[k], m3[k]));
-            const int feat = m0 + f.m_of(mb, r);
-            *reinterpret_cast<vecT*>(out + (int64_t)feat * tb) = v;
+            *reinterpret_cast<vecT*>(base + (int64_t)((16 * mb + r) * (int)tb) * (int64_t)sizeof(T) + lane_off) = v;
           }
         }
       }
@@ -411,20 +452,6 @@ __device__ __forceinline__ bool cayley_converged_now(const unsigned* dl, int k, 
 __device__ __forceinline__ bool cayley_converged(const unsigned* dl, int k, float tol) {
   return cayley_converged_hist(__uint_as_float(dl[k]), k > 0 ? __uint_as_float(dl[k - 1]) : 0.f,
                                k > 1 ? __uint_as_float(dl[k - 2]) : 0.f, k > 1 ? 2 : k, tol);
-}
-
-// A store of 8 or 16 bytes, PAST_L2: in units of 8 that are visible to the whole device once they have completed.
-template <bool PAST_L2, class V, class E>
-__device__ __forceinline__ void put(E* p, V v) {
-  if constexpr (PAST_L2) {
-    uint64_t w[sizeof(V) / 8];
-    __builtin_memcpy(w, &v, sizeof(V));
-#pragma unroll
-    for (size_t i = 0; i < sizeof(V) / 8; ++i)
-      __hip_atomic_store(reinterpret_cast<uint64_t*>(p) + i, w[i], __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  } else {
-    *reinterpret_cast<V*>(p) = v;
-  }
 }
 
 // Unew is written as fp32, or (Usplit != null) as the [hi | hi | lo] fp16 operand of the
@@ -661,7 +688,7 @@ struct EpiOrtho : EpiBase {
 
 // ---- fake-quant pass A: per-token max |y| -----------------------------------------
 // same orientation as EpiMoments; part[(batch*P + p)*n_tokens + token]
-template <class TL>
+template <class TL, bool PAST_L2 = false>
 struct EpiAmax : EpiBase {
   static_assert(TL::MB % 4 == 0 && TL::NB % 4 == 0, "features and tokens are taken 64 at a time");
   float* part;
@@ -685,7 +712,10 @@ struct EpiAmax : EpiBase {
       }
       const float v = quarter_reduce4<OpMax>(a[0], a[1], a[2], a[3]);
       const int token = n0 + f.wn * TL::WTN + 64 * g + f.lane;
-      if (token < n_tokens) part[((int64_t)batch * P + p) * n_tokens + token] = v;
+      if (token < n_tokens && p < P) {
+        if constexpr (PAST_L2) __hip_atomic_store(&part[((int64_t)batch * P + p) * n_tokens + token], v, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        else part[((int64_t)batch * P + p) * n_tokens + token] = v;
+      }
     }
   }
 };
@@ -696,7 +726,7 @@ struct EpiAmax : EpiBase {
 // meet only the other lane quarters, and the codes leave as 16-byte stores (the four lanes of a
 // token exchange packed words over four blocks first).  q = clamp(rint(y * (1/s)), -7, 7) in fp32;
 // pe[(batch*P + p)*n_tokens + token] = {sum (y - q s)^2, sum y^2} over the wave's feature rows.
-template <class TL>
+template <class TL, bool PAST_L2 = false>
 struct EpiQuant : EpiBase {
   static_assert(TL::MB % 4 == 0 && TL::NB % 4 == 0, "features and tokens are taken 64 at a time");
   const float* scales;  // [batch][n_tokens]
@@ -705,6 +735,14 @@ struct EpiQuant : EpiBase {
   int n_tokens, d, P;
   __device__ __forceinline__ void operator()(floatx4 (&acc)[TL::MB][TL::NB], int batch, int tm,
                                              int, int, int m0, int n0) const {
+    apply(acc, batch, tm, m0, n0, [&](int t) __attribute__((always_inline)) {
+      const float s = n0 + t < n_tokens ? scales[(int64_t)batch * n_tokens + n0 + t] : 0.f;
+      return make_float2(s, s > 0.f ? __fdiv_rn(1.0f, s) : 0.f);
+    });
+  }
+  // scale_of(t): the scale of token n0 + t and its reciprocal (0 where the scale is not positive)
+  template <class ScaleOf>
+  __device__ __forceinline__ void apply(floatx4 (&acc)[TL::MB][TL::NB], int batch, int tm, int m0, int n0, ScaleOf scale_of) const {
     const Frag<TL> f;
     const int p = tm * TL::WGM + f.wm;
 #pragma unroll
@@ -714,9 +752,9 @@ struct EpiQuant : EpiBase {
       for (int k = 0; k < 4; ++k) {
         const int token = n0 + f.n_of(4 * g + k);
         const bool tv = token < n_tokens;
-        const float s = tv ? scales[(int64_t)batch * n_tokens + token] : 0.f;
-        const bool live = s > 0.f;
-        const float rinv = live ? __fdiv_rn(1.0f, s) : 0.f;
+        const float2 scale = scale_of(token - n0);
+        const float s = scale.x, rinv = scale.y;
+        const float top = s > 0.f ? 7.f : 0.f;  // a row with scale 0 gets codes 0
         int8_t* crow = codes + ((int64_t)batch * n_tokens + token) * d;
         e2[k] = 0.f; y2[k] = 0.f;
 #pragma unroll
@@ -725,19 +763,20 @@ struct EpiQuant : EpiBase {
             float pk[4];
 #pragma unroll
             for (int i = 0; i < 4; ++i) {
-              unsigned pack = 0u;
+              unsigned t[4];
 #pragma unroll
               for (int e = 0; e < 4; ++e) {
+                // clamp(rint(v)) = rint(clamp(v)) for whole bounds; 1.5 2^23 + v has rint(v) (ties to even) in its low bits
                 const float y = acc[4 * m4 + i][4 * g + k][e];
-                float qv = rintf(__fmul_rn(y, rinv));
-                qv = fminf(fmaxf(qv, -7.f), 7.f);
-                if (!live) qv = 0.f;
-                const float diff = y - qv * s;
+                const float v = __builtin_amdgcn_fmed3f(__fmul_rn(y, rinv), -top, top);
+                const float m = __fadd_rn(v, 12582912.f);
+                t[e] = __float_as_uint(m);
+                const float diff = fmaf(-__fsub_rn(m, 12582912.f), s, y);
                 e2[k] = fmaf(diff, diff, e2[k]);
                 y2[k] = fmaf(y, y, y2[k]);
-                pack |= ((unsigned)(int)qv & 0xffu) << (8 * e);
               }
-              pk[i] = __uint_as_float(pack);
+              const unsigned lo = __builtin_amdgcn_perm(t[1], t[0], 0x0c0c0400u), hi = __builtin_amdgcn_perm(t[3], t[2], 0x04000c0cu);
+              pk[i] = __uint_as_float(lo | hi);
             }
             // word i of quarter c = features 16 i + 4 c .. + 3 of these 64: transposed among the four lanes of the
             // token, quarter c holds all 16 bytes of block c
@@ -754,7 +793,13 @@ struct EpiQuant : EpiBase {
         const float2 v = make_float2(quarter_reduce4<OpAdd>(e2[0], e2[1], e2[2], e2[3]),
                                      quarter_reduce4<OpAdd>(y2[0], y2[1], y2[2], y2[3]));
         const int token = n0 + f.wn * TL::WTN + 64 * g + f.lane;
-        if (token < n_tokens) err_part[((int64_t)batch * P + p) * n_tokens + token] = v;
+        if (token < n_tokens && p < P) {
+          if constexpr (PAST_L2)
+            __hip_atomic_store(reinterpret_cast<uint64_t*>(&err_part[((int64_t)batch * P + p) * n_tokens + token]), __builtin_bit_cast(uint64_t, v),
+                               __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+          else
+            err_part[((int64_t)batch * P + p) * n_tokens + token] = v;
+        }
       }
     }
   }

@@ -135,13 +135,21 @@ __device__ __forceinline__ intx4 read_tr_operand(const char* lds, int addr_lo, i
   return __builtin_bit_cast(intx4, v);
 }
 
+// threadIdx.x, not known to be the same on every call: in a kernel that walks tiles, what follows from it (lane constants of the
+// main loop and of the epilogue) is made anew for each tile instead of being kept, or spilled, across the other's registers.
+__device__ __forceinline__ int thread_id() {
+  int t = threadIdx.x;
+  asm volatile("" : "+v"(t));
+  return t;
+}
+
 // Geometry of one accumulator element, shared by every epilogue.
 template <class TL>
 struct Frag {
   int lane, l16, q, wm, wn;
   __device__ __forceinline__ Frag() {
-    const int wave = threadIdx.x >> 6;
-    lane = threadIdx.x & 63;
+    const int t = thread_id(), wave = t >> 6;
+    lane = t & 63;
     l16 = lane & 15;
     q = lane >> 4;
     wm = wave / TL::WGN;
@@ -353,7 +361,7 @@ __device__ __forceinline__ void gemm_mainloop(const typename TL::T* __restrict__
   static_assert(A_GAP >= 1 && B_GAP >= 1 && load_slot(NLD - 1) - 2 * SLOTS < SLOTS + BAR - 3 && BAR + NB * SPACE1 <= SLOTS && BAR >= 2,
                 "not enough MFMA slots to hide the memory instructions");
 
-  const int tid = threadIdx.x, lane = tid & 63;
+  const int tid = thread_id();
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
   // global addressing: uniform 64-bit base + 32-bit byte offsets.  Load i of a thread fills 16 bytes at
