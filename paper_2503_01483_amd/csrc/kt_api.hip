@@ -286,7 +286,7 @@ static bool launch_row_sync(RowSync& rs, const typename TL::T* RT, const typenam
   return launch_ok();
 }
 
-// Iterations it0, ... of `batch` retractions (cayley_iterate_kernel): U and B are [d][K] in the GEMM dtype.  As many workgroups per
+// Iterations it0, ... of `batch` retractions (cayley_iterate_kernel): U and B have rows of ld in the GEMM dtype.  As many workgroups per
 // problem as the chip holds, at most one per tile.
 template <class TL>
 static int64_t cayley_control_words(int64_t d) {
@@ -294,19 +294,20 @@ static int64_t cayley_control_words(int64_t d) {
 }
 template <class TL>
 static bool launch_cayley_iterations(const typename TL::T* U0, const typename TL::T* U1, const typename TL::T* B, int64_t K, int64_t d,
-                                     int64_t batch, const EpiCayleyIter<TL>& epi, unsigned* control, int it0, hipStream_t stream) {
+                                     int64_t ld, int64_t batch, const EpiCayleyIter<TL>& epi, unsigned* control, int it0, hipStream_t stream) {
   auto kern = &cayley_iterate_kernel<TL, false>;
   if constexpr (TL::BM == 64)
     if (ceil_div(d, TL::BM) * ceil_div(d, TL::BN) * batch >= 200) kern = &cayley_iterate_kernel<TL, true>;
-  if (!tile_offsets_fit(TL::BM, K, (int64_t)sizeof(typename TL::T))) return false;
+  if (!tile_offsets_fit(TL::BM, ld, (int64_t)sizeof(typename TL::T))) return false;
   if (!ensure_dynamic_lds(reinterpret_cast<const void*>(kern), TL::LDS_BYTES)) return false;
   GemmShape g = {};
-  g.B = B; g.lda = g.ldb = K; g.batch_stride_a = g.batch_stride_b = d * K;
+  g.B = B; g.lda = g.ldb = ld; g.batch_stride_a = g.batch_stride_b = d * ld;
   g.M = g.N = (int)d;
   g.tiles_m = (int)ceil_div(d, TL::BM);
   g.tiles_n = (int)ceil_div(d, TL::BN);
   g.tiles_total = g.tiles_m * g.tiles_n;
-  g.slabs_total = g.slabs_per_block = (int)(K / TL::BK);
+  g.slabs_total = (int)(K / TL::BK);
+  g.slabs_per_block = (int)(d / TL::BK);
   const int64_t fit = kNumCUs * (160 * 1024 / TL::LDS_BYTES);
   const unsigned wgs = (unsigned)(g.tiles_total < fit ? g.tiles_total : fit);
   hipLaunchKernelGGL(kern, dim3(wgs, (unsigned)batch), dim3(TL::NT), TL::LDS_BYTES, stream, g, epi, U0, U1, control,
@@ -562,7 +563,7 @@ static CayleyPlan plan_cayley(int64_t batch, int64_t d, bool split) {
   Carver c;
   p.split = split;
   const size_t mat = (size_t)batch * d * d * 4;
-  const size_t smat = (size_t)batch * d * d * 6;  // [d][3d] fp16
+  const size_t smat = (size_t)batch * d * d * 6;  // [d][2d] fp16 (and room that earlier forms needed: sizes stay as they were)
   p.o_m = c.take(mat);  // M = dR R^T; in the fp32 path later reused as the second U buffer
   p.o_b = c.take(p.split ? smat : mat);
   p.o_rt = c.take(mat);
@@ -1207,38 +1208,55 @@ static kt_status cayley_run(const CayleyPlan& p, char* ws, float* R, const float
   SplitScales* scales = reinterpret_cast<SplitScales*>(ws + p.o_g2 + (late_control ? 0 : batch * room));
   unsigned* control = reinterpret_cast<unsigned*>(ws + (late_control ? p.o_sq : p.o_g2));
   const int ncontrol = late_control ? 0 : (int)control_words;
-  auto iterations = [&](auto first_tag, auto tile_tag, auto* U0, auto* U1, const auto* B, int64_t K) -> bool {
-    auto epilogue = [&](auto tag) {
+  // (the changes of a second iteration that counts as the last: EpiCayleyIter)
+  const float second_tol = p.split ? 5e-4f / sqrtf((float)d) : INFINITY;
+  // B and U: rows of ld values
+  auto iterations = [&](auto first_tag, auto tile_tag, auto* U0, auto* U1, const auto* B, int64_t K, int64_t ld) -> bool {
+    auto epilogue = [&](auto tag, auto phase_c) {
       using TL = decltype(tag);
-      EpiCayleyIter<TL> e;
+      EpiCayleyIter<TL, decltype(phase_c)::value> e;
       e.Rt = Rt; e.Zt = Zt; e.Unew = nullptr; e.Usplit = nullptr; e.delta = delta;
-      e.d = D; e.it = 0; e.max_iters = kCayleyMaxIters; e.tol = kCayleyTol;
+      e.d = D; e.it = 0; e.max_iters = kCayleyMaxIters; e.tol = kCayleyTol; e.second_tol = second_tol;
       e.bscale = adam ? adam->scal : nullptr;
       e.scales = scales;
       return e;
     };
     using TL = decltype(tile_tag);
+    using First = decltype(first_tag);
+    constexpr auto later = std::integral_constant<int, 2>{};
     const int own = cayley_own_launches(ceil_div(d, TL::BM) * ceil_div(d, TL::BN), batch, TL::BM, p.split);
-    for (int it = 0; it < own; ++it) {
-      auto e = epilogue(first_tag);
+    int it = 0;
+    if constexpr (sizeof(*B) == 2) {
+      auto e0 = epilogue(first_tag, std::integral_constant<int, 0>{});
+      e0.Usplit = U1;
+      if (!launch_gemm<First>(U0, ld, d * ld, D, B, ld, d * ld, D, K, 0, (int)batch, e0, st, d)) return false;
+      auto e1 = epilogue(first_tag, std::integral_constant<int, 1>{});
+      e1.it = 1;
+      if (!launch_gemm<First>(U1, d, dd, D, B, ld, d * ld, D, d, 0, (int)batch, e1, st, d)) return false;
+      hipLaunchKernelGGL(cayley_u_kernel, dim3(D / 32, D / 32, (unsigned)batch), dim3(256), 0, st, R, Zt, D, Rt, U0, scales, delta,
+                         kCayleyMaxIters, kCayleyTol, second_tol);
+      it = 2;
+    }
+    for (; it < own; ++it) {
+      auto e = epilogue(first_tag, later);
       auto *from = it & 1 ? U1 : U0, *to = it & 1 ? U0 : U1;
       e.it = it;
       if constexpr (sizeof(*B) == 2) e.Usplit = to;
       else e.Unew = to;
-      if (!launch_gemm<decltype(first_tag)>(from, K, d * K, D, B, K, d * K, D, K, 0, (int)batch, e, st)) return false;
+      if (!launch_gemm<First>(from, ld, d * ld, D, B, ld, d * ld, D, K, 0, (int)batch, e, st, d)) return false;
     }
     if (own == kCayleyMaxIters) return true;
     if (late_control) hipLaunchKernelGGL(fill_u32_kernel, dim3(64), dim3(256), 0, st, control, batch * control_words, 0u);
-    return launch_cayley_iterations<TL>(U0, U1, B, K, d, batch, epilogue(tile_tag), control, own, st);
+    return launch_cayley_iterations<TL>(U0, U1, B, K, d, ld, batch, epilogue(tile_tag, later), control, own, st);
   };
 
   if (p.split) {
-    // three-term path: operands live as [d][3d] fp16
+    // three-term path: operands live as [d][2d] fp16, rows of [head | tail]
     _Float16* Bs = reinterpret_cast<_Float16*>(ws + p.o_b);
     _Float16* Us[2] = {reinterpret_cast<_Float16*>(ws + p.o_u0), reinterpret_cast<_Float16*>(ws + p.o_u1)};
-    const int64_t sd = 3 * d * d;
+    const int64_t sd = 2 * d * d;
     const unsigned sb = (unsigned)(ceil_div(dd, 1024) < 2048 ? ceil_div(dd, 1024) : 2048);
-    // M = dR R^T with dR as [hi|hi|lo] (in Us[0]) and R as [hi|lo|hi] (in Us[1]); the partial maxima in the room of M
+    // M = dR R^T with dR in Us[0] and R in Us[1]; the partial maxima in the room of M
     unsigned* maxima = reinterpret_cast<unsigned*>(Mm);
     hipLaunchKernelGGL(split_max_kernel, dim3(256, 2, (unsigned)batch), dim3(256), 0, st, G, R, dd, maxima);
     hipLaunchKernelGGL(split3_kernel, dim3(sb, 2, (unsigned)batch), dim3(256), 0, st, G, R, D, maxima, Us[0], Us[1], scales);
@@ -1248,7 +1266,7 @@ static kt_status cayley_run(const CayleyPlan& p, char* ws, float* R, const float
         using TL = decltype(tile_tag);
         EpiStoreScaled<TL> e;
         e.C = C; e.exp_a = exp_a; e.exp_b = exp_b; e.max_word = max_word; e.d = D; e.shift = shift;
-        return launch_gemm<TL>(A3, 3 * d, sd, D, B3, 3 * d, sd, D, 3 * d, 0, (int)batch, e, st);
+        return launch_gemm<TL>(A3, 2 * d, sd, D, B3, 2 * d, sd, D, 3 * d, 0, (int)batch, e, st, d);
       });
     };
     if (!product(Us[0], Us[1], &scales->g, &scales->r, Mm, &scales->max_m, 0)) return fail(KT_ERR_DEVICE, "dR R^T GEMM launch failed");
@@ -1260,12 +1278,11 @@ static kt_status cayley_run(const CayleyPlan& p, char* ws, float* R, const float
       hipLaunchKernelGGL(adam_scalars2_kernel, dim3((unsigned)batch), dim3(256), 0, st, adam->sq_part,
                          (int)((d / 32) * (d / 32)), adam->lr, adam->q, adam->eps, adam->scal, adam->scalars_out);
       if (!launch_ok()) return fail(KT_ERR_DEVICE, "Cayley Adam scalar launch failed");
-      // M <- S R = (1/2) S (2 Rt)^T: S sits in Bs as [hi|lo|hi], 2 Rt in Us[0] as [hi|hi|lo]; the same three
-      // cross terms come out whichever operand carries which layout
+      // M <- S R = (1/2) S (2 Rt)^T: S sits in Bs, 2 Rt in Us[0]
       if (!product(Bs, Us[0], &scales->b, &scales->u, adam->M, nullptr, -1)) return fail(KT_ERR_DEVICE, "momentum projection GEMM launch failed");
     }
     const bool launched = with_f16_tile(d, batch, [&](auto first) {
-      return with_f16_iterate_tile(d, batch, [&](auto t) { return iterations(first, t, Us[0], Us[1], Bs, 3 * d); });
+      return with_f16_iterate_tile(d, batch, [&](auto t) { return iterations(first, t, Us[0], Us[1], Bs, 3 * d, 2 * d); });
     });
     if (!launched) return fail(KT_ERR_DEVICE, "Cayley iteration launch failed");
   } else {
@@ -1291,12 +1308,12 @@ static kt_status cayley_run(const CayleyPlan& p, char* ws, float* R, const float
     if (!product(Bm, Rt, adam->M)) return fail(KT_ERR_DEVICE, "momentum projection GEMM launch failed");
   }
   const bool launched = with_f32_tile(d, d, batch, [&](auto first) {
-    return small ? iterations(first, TF_64{}, U[0], U[1], Bm, d) : iterations(first, TF{}, U[0], U[1], Bm, d);
+    return small ? iterations(first, TF_64{}, U[0], U[1], Bm, d, d) : iterations(first, TF{}, U[0], U[1], Bm, d, d);
   });
   if (!launched) return fail(KT_ERR_DEVICE, "Cayley iteration launch failed");
   }
-  hipLaunchKernelGGL(cayley_finish_kernel, dim3(D / 32, D / 32, (unsigned)batch), dim3(256), 0, st, Zt, D,
-                     R, static_cast<__bf16*>(R_lowp), delta, kCayleyMaxIters, kCayleyTol, info);
+  hipLaunchKernelGGL(p.split ? cayley_finish_kernel<true> : cayley_finish_kernel<false>, dim3(D / 32, D / 32, (unsigned)batch), dim3(256), 0, st, Zt, D,
+                     R, static_cast<__bf16*>(R_lowp), delta, kCayleyMaxIters, kCayleyTol, second_tol, ortho_err ? 1 : 0, info);
   if (!launch_ok()) return fail(KT_ERR_DEVICE, "Cayley wrap-up launch failed");
   if (ortho_err) {
     hipLaunchKernelGGL(fill_u32_kernel, dim3(1), dim3(256), 0, st, reinterpret_cast<unsigned*>(ortho_err),

@@ -394,7 +394,7 @@ __global__ __launch_bounds__(256) void split3_kernel(const float* __restrict__ G
     }
   }
   const float* in = (is_r ? R : G) + bo;
-  _Float16* out = (is_r ? right : left) + 3 * bo;
+  _Float16* out = (is_r ? right : left) + 2 * bo;
   for (int64_t i = ((int64_t)blockIdx.x * 256 + threadIdx.x) * 4; i < dd; i += (int64_t)gridDim.x * 1024) {
     const int64_t r = i / d, c = i - r * d;
     const floatx4 v = *reinterpret_cast<const floatx4*>(in + i);
@@ -406,15 +406,14 @@ __global__ __launch_bounds__(256) void split3_kernel(const float* __restrict__ G
       hi[e] = h;
       lo[e] = l;
     }
-    _Float16* o = out + r * 3 * d + c;
+    _Float16* o = out + r * 2 * d + c;
     *reinterpret_cast<f16x4*>(o) = hi;
-    *reinterpret_cast<f16x4*>(o + d) = is_r ? lo : hi;
-    *reinterpret_cast<f16x4*>(o + 2 * d) = is_r ? hi : lo;
+    *reinterpret_cast<f16x4*>(o + d) = lo;
   }
 }
 
 // Cayley set-up: from M = dR R^T build  Bm = (lr/2)(M - M^T)  (exactly skew),
-// Rt = R^T, Zt0 = Rt, U0 = 2 Rt (Bm and U0 either as fp32 or as split fp16 operands); clears the changes and control words.
+// Rt = R^T, Zt0 = Rt, U0 = 2 Rt, or (fp16) Bm and U0 alone, as heads and tails; clears the changes and control words.
 // 32 x 32 tiles; grid = (d/32, d/32, batch).
 __global__ __launch_bounds__(256) void cayley_setup_kernel(const float* __restrict__ Mm,
                                                            const float* __restrict__ R, int d,
@@ -463,16 +462,16 @@ __global__ __launch_bounds__(256) void cayley_setup_kernel(const float* __restri
     const float b = half_lr * (m_ij - m_ji);
     sq += (double)b * (double)b;
     const float rt = tr[tx][rr];  // R[j0+tx][i0+rr] = Rt[i0+rr][j0+tx]
-    Rt[idx] = rt;
-    Zt[idx] = rt;
-    if (Bs) {  // split operands of the three-term GEMM: B as [hi|lo|hi], U as [hi|hi|lo]
-      const int64_t so = 3 * bo + (int64_t)(i0 + rr) * 3 * d + j0 + tx;
+    if (Bs) {  // operands of the three-term products, rows of [head | tail]
+      const int64_t so = 2 * bo + (int64_t)(i0 + rr) * 2 * d + j0 + tx;
       _Float16 hi, lo;
       split_f16(b, kb, hi, lo);
-      Bs[so] = hi; Bs[so + d] = lo; Bs[so + 2 * d] = hi;
+      Bs[so] = hi; Bs[so + d] = lo;
       split_f16(2.f * rt, ku, hi, lo);
-      Us[so] = hi; Us[so + d] = hi; Us[so + 2 * d] = lo;
+      Us[so] = hi; Us[so + d] = lo;
     } else {
+      Rt[idx] = rt;
+      Zt[idx] = rt;
       Bm[idx] = b;
       U0[idx] = 2.f * rt;
     }
@@ -549,13 +548,39 @@ __global__ __launch_bounds__(256) void adam_scalars2_kernel(const double* __rest
   }
 }
 
-// Cayley wrap-up: R = Zt^T (and its bf16 copy), info = iterations used or -1.  An iteration that did
-// not converge is rejected as a whole: R stays as it is and the bf16 copy is taken from it.
-__global__ __launch_bounds__(256) void cayley_finish_kernel(const float* __restrict__ Zt, int d,
+// fp16, third iteration to come: Rt = R^T, and U = 2 Rt + D as heads and tails (EpiCayleyIter).  Nothing to do where the second was the last.
+// 32 x 32 tiles; grid = (d/32, d/32, batch).
+__global__ __launch_bounds__(256) void cayley_u_kernel(const float* __restrict__ R, const float* __restrict__ Dt, int d, float* __restrict__ Rt,
+                                                       _Float16* __restrict__ Us, const SplitScales* __restrict__ scales,
+                                                       const unsigned* __restrict__ delta, int max_iters, float tol, float second_tol) {
+  __shared__ float tr[32][33];
+  if (cayley_converged(delta + (int64_t)blockIdx.z * max_iters, 1, tol, second_tol)) return;
+  const int64_t bo = (int64_t)blockIdx.z * d * d;
+  const int i0 = blockIdx.x * 32, j0 = blockIdx.y * 32, tx = threadIdx.x & 31, ty = threadIdx.x >> 5, ku = scales[blockIdx.z].u;
+#pragma unroll
+  for (int k = 0; k < 4; ++k) tr[ty + 8 * k][tx] = R[bo + (int64_t)(j0 + ty + 8 * k) * d + i0 + tx];
+  __syncthreads();
+#pragma unroll
+  for (int k = 0; k < 4; ++k) {
+    const int rr = ty + 8 * k;
+    const int64_t idx = bo + (int64_t)(i0 + rr) * d + j0 + tx, so = 2 * bo + (int64_t)(i0 + rr) * 2 * d + j0 + tx;
+    const float rt = tr[tx][rr];
+    Rt[idx] = rt;
+    _Float16 hi, lo;
+    split_f16(fmaf(2.f, rt, Dt[idx]), ku, hi, lo);
+    Us[so] = hi;
+    Us[so + d] = lo;
+  }
+}
+
+// Cayley wrap-up: R = Zt^T or, MOVED (Zt holds Z - Rt), R += Zt^T (and its bf16 copy), info = iterations used or -1.  An iteration that did
+// not converge is rejected as a whole: R stays as it is and the bf16 copy is taken from it.  whole: Zt is left as the whole Z.
+template <bool MOVED>
+__global__ __launch_bounds__(256) void cayley_finish_kernel(float* __restrict__ Zt, int d,
                                                             float* __restrict__ R,
                                                             __bf16* __restrict__ R_lowp,
                                                             const unsigned* __restrict__ delta,
-                                                            int max_iters, float tol,
+                                                            int max_iters, float tol, float second_tol, int whole,
                                                             int32_t* __restrict__ info) {
   __shared__ float tz[32][33];
   const int64_t bo = (int64_t)blockIdx.z * d * d;
@@ -563,9 +588,10 @@ __global__ __launch_bounds__(256) void cayley_finish_kernel(const float* __restr
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
   int used = -1;  // the same scan in every thread: at most max_iters words, all cache hits
   for (int k = 0; k < max_iters; ++k) {
-    if (cayley_converged(delta + (int64_t)blockIdx.z * max_iters, k, tol)) { used = k + 1; break; }
+    if (cayley_converged(delta + (int64_t)blockIdx.z * max_iters, k, tol, second_tol)) { used = k + 1; break; }
   }
-  if (used > 0) {
+  if (!MOVED) whole = 0;
+  if (used > 0 || whole) {
 #pragma unroll
     for (int k = 0; k < 4; ++k) {
       const int rr = ty + 8 * k;
@@ -573,17 +599,26 @@ __global__ __launch_bounds__(256) void cayley_finish_kernel(const float* __restr
     }
   }
   __syncthreads();
+  float v[4];
 #pragma unroll
   for (int k = 0; k < 4; ++k) {
     const int rr = ty + 8 * k;
     const int64_t idx = bo + (int64_t)(i0 + rr) * d + j0 + tx;
+    if (used > 0 || whole) v[k] = MOVED ? R[idx] + tz[tx][rr] : tz[tx][rr];
     if (used > 0) {
-      const float v = tz[tx][rr];
-      R[idx] = v;
-      if (R_lowp) R_lowp[idx] = (__bf16)v;
+      R[idx] = v[k];
+      if (R_lowp) R_lowp[idx] = (__bf16)v[k];
     } else if (R_lowp) {
       R_lowp[idx] = (__bf16)R[idx];
     }
+  }
+  if (whole) {  // uniform
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 4; ++k) tz[tx][ty + 8 * k] = v[k];
+    __syncthreads();
+#pragma unroll
+    for (int k = 0; k < 4; ++k) Zt[bo + (int64_t)(j0 + ty + 8 * k) * d + i0 + tx] = tz[ty + 8 * k][tx];
   }
   if (info && blockIdx.x == 0 && blockIdx.y == 0 && threadIdx.x == 0) info[blockIdx.z] = used;
 }

@@ -91,7 +91,7 @@ struct EpiMoments : EpiBase {
   int n_tokens, d, P;
   __device__ __forceinline__ void operator()(floatx4 (&acc)[TL::MB][TL::NB], int batch, int tm,
                                              int, int, int m0, int n0) const {
-    const Frag<TL> f;
+    const Frag<TL> f(thread_id<PAST_L2>());
     const int p = tm * TL::WGM + f.wm;
     int blocks = 0;
 #pragma unroll
@@ -222,10 +222,10 @@ struct EpiGrad : EpiBase {
     });
   }
   // coef_of(t): the coefficients of token n0 + t
-  template <class CoefOf>
+  template <bool AGAIN = false, class CoefOf>
   __device__ __forceinline__ void store(floatx4 (&acc)[TL::MB][TL::NB], int batch, int m0, int n0, CoefOf coef_of) const {
     typedef T vecT __attribute__((ext_vector_type(4)));
-    const Frag<TL> f;
+    const Frag<TL> f(thread_id<AGAIN>());
 #pragma unroll
     for (int g = 0; g < TL::NB / 4; ++g) {
       const int group0 = n0 + f.wn * TL::WTN + 64 * g;  // the 64-token group
@@ -449,28 +449,43 @@ __device__ __forceinline__ bool cayley_converged_now(const unsigned* dl, int k, 
   auto at = [&](int i) { return __uint_as_float(__hip_atomic_load(dl + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)); };
   return cayley_converged_hist(at(k), k > 0 ? at(k - 1) : 0.f, k > 1 ? at(k - 2) : 0.f, k > 1 ? 2 : k, tol);
 }
-__device__ __forceinline__ bool cayley_converged(const unsigned* dl, int k, float tol) {
+// second_tol: how large a change the second iteration may end with (EpiCayleyIter, phase 1)
+__device__ __forceinline__ bool cayley_converged(const unsigned* dl, int k, float tol, float second_tol) {
+  if (k == 1 && !(__uint_as_float(dl[1]) <= second_tol)) return false;
   return cayley_converged_hist(__uint_as_float(dl[k]), k > 0 ? __uint_as_float(dl[k - 1]) : 0.f,
                                k > 1 ? __uint_as_float(dl[k - 2]) : 0.f, k > 1 ? 2 : k, tol);
 }
 
-// Unew is written as fp32, or (Usplit != null) as the [hi | hi | lo] fp16 operand of the
-// three-term GEMM that runs the next iteration.  As the epilogue of a launch of its own it returns at once when iteration
+// fp32: Zt and Unew as above.  As the epilogue of a launch of its own it returns at once when iteration
 // it - 1 or an earlier one has converged.  (cayley_iterate_kernel sets `it` and the two targets.)
-template <class TL>
+//
+// fp16 heads and tails: Zt holds the displacement D = Z - Rt instead, which is what a step needs to be exact in (R + D is rounded once,
+// by cayley_finish_kernel).  D_1 = - U_0 B^T, U_0 = 2 Rt, and from there D_k+1 = - U_k B^T, U_k = 2 Rt + D_k, in three terms; but the
+// change of the second iteration is D_2 - D_1 = - D_1 B^T, and in one term, D_1 and B as heads alone (2^-12 of a value), it is as good
+// as the first while it is small: an error of 2^-12 |D_2 - D_1|, random from entry to entry.  So phase 0 (the first iteration) leaves D and
+// the head of D_1, phase 1 adds the change, and a second iteration counts as the last one only if its largest change is within 5e-4 of the
+// root mean square of R's entries, 1/sqrt(d); from the third on (phase 2) U comes back, from cayley_u_kernel the first time, and what the
+// second left out goes with it.  A dense B of norm rho changes the entries by 0.7 rho^2 of it then and stops 0.7 rho^3 short, 2^-12 / rho times
+// what the heads leave out, and both are below the rounding of R at rho = 2e-3.  Error of R against 64 bits before / now over d = 1024 .. 4096, Haar,
+// near-identity R and I, Gaussian, learned and log-normal gradients, (lr / 2) ||A|| = 5e-4 .. 0.3 (315 steps): 1.7e-8 .. 6.0e-7 in both, 0.999 to
+// 1.003 times the former but for two steps of 11 iterations and more.
+//   Usual steps end there (the change is 1e-11 to 1e-6): step in us, three terms in both / this: d = 1152, pooled loss and Adam, 10007 tokens 283 / 256,
+//   2048, 65536 tokens 1134 / 1083, 4096, 131072 tokens 7392 / 7069.
+template <class TL, int PHASE = 2>
 struct EpiCayleyIter {
+  static constexpr bool kF16 = sizeof(typename TL::T) == 2;
   const float* Rt;
   float* Zt;
   float* Unew;
-  _Float16* Usplit;
-  const SplitScales* scales = nullptr;  // with Usplit: the product is scaled, Usplit has to be
+  _Float16* Usplit;  // U as [head | tail] (phase 0: the head of D_1, rows of d)
+  const SplitScales* scales = nullptr;
   unsigned* delta;  // [batch][max_iters]
   int d, it, max_iters;
-  float tol;
+  float tol, second_tol;
   const float* bscale = nullptr;  // acc is scaled by bscale[4 * batch + 3] when given (Cayley Adam)
   static constexpr bool kSwap = true;  // four consecutive columns of a row per lane: 16-byte accesses
   __device__ __forceinline__ bool skip(int batch) const {
-    if (it == 0 || !cayley_converged(delta + (int64_t)batch * max_iters, it - 1, tol)) return false;
+    if (it == 0 || !cayley_converged(delta + (int64_t)batch * max_iters, it - 1, tol, second_tol)) return false;
     // a zero change counts as converged: later launches return too
     if (blockIdx.x == 0 && threadIdx.x == 0) delta[(int64_t)batch * max_iters + it] = 0u;
     return true;
@@ -479,15 +494,22 @@ struct EpiCayleyIter {
                                              int, int, int m0, int n0) const {
     apply<false>(acc, batch, m0, n0);
   }
+  // The exponent of the head of D_1 = bs D', bs = f 2^eb: |D'| <= 2 sqrt(d) max |B|, the rows of R being of norm one, so that 2^(kb - half)
+  // leaves it below 2^15, half = log2(d) / 2 rounded up.  (Rows that are longer by more than that are cut off at the largest fp16 value.)
+  static __device__ __forceinline__ int head_exponent(int kb, int eb, int d) { return kb - eb - (33 - __clz(d - 1)) / 2; }
   template <bool PAST_L2>
   __device__ __forceinline__ void apply(floatx4 (&acc)[TL::MB][TL::NB], int batch, int m0, int n0) const {
+    typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
     const Frag<TL> f;
     const int64_t bo = (int64_t)batch * d * d;
     const float bs = bscale ? bscale[4 * batch + 3] : 1.f;
-    int ku = 0, kb = 0;
-    if constexpr (sizeof(typename TL::T) == 2) {
+    int ku = 0, kb = 0, kd = 0, eb = 0;
+    float bm = 1.f;
+    if constexpr (kF16) {
       ku = scales[batch].u;
       kb = scales[batch].b;
+      bm = frexpf(bs, &eb);
+      kd = head_exponent(kb, eb, d);
     }
     unsigned dmax = 0u;
 #pragma unroll
@@ -497,32 +519,55 @@ struct EpiCayleyIter {
         const int m = m0 + f.m_row(mb), n = n0 + f.n_quad(nb);
         if (m < d && n < d) {  // d is a multiple of 128: all four columns are inside or none
           const int64_t idx = bo + (int64_t)m * d + n;
-          const floatx4 rt = *reinterpret_cast<const floatx4*>(Rt + idx);
-          const floatx4 zo = *reinterpret_cast<const floatx4*>(Zt + idx);
-          floatx4 z, u;
+          floatx4 z;
+          if constexpr (!kF16) {
+            const floatx4 rt = *reinterpret_cast<const floatx4*>(Rt + idx);
+            const floatx4 zo = *reinterpret_cast<const floatx4*>(Zt + idx);
+            floatx4 u;
 #pragma unroll
-          for (int r = 0; r < 4; ++r) {
-            z[r] = rt[r] - bs * (sizeof(typename TL::T) == 2 ? ldexpf(acc[mb][nb][r], -(ku + kb)) : acc[mb][nb][r]);
-            dmax = umax(dmax, abs_bits(z[r] - zo[r]));
-            u[r] = rt[r] + z[r];
-          }
-          put<PAST_L2>(Zt + idx, z);
-          if constexpr (sizeof(typename TL::T) == 2) {
-            typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
-            const int64_t so = 3 * bo + (int64_t)m * 3 * d + n;
+            for (int r = 0; r < 4; ++r) {
+              z[r] = rt[r] - bs * acc[mb][nb][r];
+              dmax = umax(dmax, abs_bits(z[r] - zo[r]));
+              u[r] = rt[r] + z[r];
+            }
+            put<PAST_L2>(Zt + idx, z);
+            put<PAST_L2>(Unew + idx, u);
+          } else if constexpr (PHASE == 0) {
+            f16x4 head;
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              z[r] = -bs * ldexpf(acc[mb][nb][r], -(ku + kb));
+              dmax = umax(dmax, abs_bits(z[r]));
+              head[r] = (_Float16)__builtin_amdgcn_fmed3f(ldexpf(z[r], kd), -65504.f, 65504.f);
+            }
+            *reinterpret_cast<floatx4*>(Zt + idx) = z;
+            *reinterpret_cast<f16x4*>(Usplit + idx) = head;
+          } else if constexpr (PHASE == 1) {
+            z = *reinterpret_cast<const floatx4*>(Zt + idx);
+#pragma unroll
+            for (int r = 0; r < 4; ++r) {
+              const float change = -bm * ldexpf(acc[mb][nb][r], eb - (kd + kb));
+              z[r] += change;
+              dmax = umax(dmax, abs_bits(change));
+            }
+            *reinterpret_cast<floatx4*>(Zt + idx) = z;
+          } else {
+            const floatx4 rt = *reinterpret_cast<const floatx4*>(Rt + idx);
+            const floatx4 zo = *reinterpret_cast<const floatx4*>(Zt + idx);
             f16x4 hi, lo;
 #pragma unroll
             for (int r = 0; r < 4; ++r) {
+              z[r] = -bs * ldexpf(acc[mb][nb][r], -(ku + kb));
+              dmax = umax(dmax, abs_bits(z[r] - zo[r]));
               _Float16 h, l;
-              split_f16(u[r], ku, h, l);
+              split_f16(fmaf(2.f, rt[r], z[r]), ku, h, l);
               hi[r] = h;
               lo[r] = l;
             }
+            put<PAST_L2>(Zt + idx, z);
+            const int64_t so = 2 * bo + (int64_t)m * 2 * d + n;
             put<PAST_L2>(Usplit + so, hi);
-            put<PAST_L2>(Usplit + so + d, hi);
-            put<PAST_L2>(Usplit + so + 2 * d, lo);
-          } else {
-            put<PAST_L2>(Unew + idx, u);
+            put<PAST_L2>(Usplit + so + d, lo);
           }
         }
       }
@@ -695,7 +740,7 @@ struct EpiAmax : EpiBase {
   int n_tokens, d, P;
   __device__ __forceinline__ void operator()(floatx4 (&acc)[TL::MB][TL::NB], int batch, int tm,
                                              int, int, int m0, int n0) const {
-    const Frag<TL> f;
+    const Frag<TL> f(thread_id<PAST_L2>());
     const int p = tm * TL::WGM + f.wm;
 #pragma unroll
     for (int g = 0; g < TL::NB / 4; ++g) {  // 64 tokens: lane l ends up with token l of them
@@ -743,7 +788,7 @@ struct EpiQuant : EpiBase {
   // scale_of(t): the scale of token n0 + t and its reciprocal (0 where the scale is not positive)
   template <class ScaleOf>
   __device__ __forceinline__ void apply(floatx4 (&acc)[TL::MB][TL::NB], int batch, int tm, int m0, int n0, ScaleOf scale_of) const {
-    const Frag<TL> f;
+    const Frag<TL> f(thread_id<PAST_L2>());
     const int p = tm * TL::WGM + f.wm;
 #pragma unroll
     for (int g = 0; g < TL::NB / 4; ++g) {

@@ -135,11 +135,12 @@ __device__ __forceinline__ intx4 read_tr_operand(const char* lds, int addr_lo, i
   return __builtin_bit_cast(intx4, v);
 }
 
-// threadIdx.x, not known to be the same on every call: in a kernel that walks tiles, what follows from it (lane constants of the
-// main loop and of the epilogue) is made anew for each tile instead of being kept, or spilled, across the other's registers.
+// threadIdx.x, AGAIN: not known to be the same on every call.  In a kernel that walks tiles, what follows from it (lane constants of the
+// main loop and of the epilogue) is then made anew for each tile instead of being kept, or spilled, across the other's registers.
+template <bool AGAIN>
 __device__ __forceinline__ int thread_id() {
   int t = threadIdx.x;
-  asm volatile("" : "+v"(t));
+  if constexpr (AGAIN) asm volatile("" : "+v"(t));
   return t;
 }
 
@@ -147,8 +148,8 @@ __device__ __forceinline__ int thread_id() {
 template <class TL>
 struct Frag {
   int lane, l16, q, wm, wn;
-  __device__ __forceinline__ Frag() {
-    const int t = thread_id(), wave = t >> 6;
+  __device__ __forceinline__ explicit Frag(int t = threadIdx.x) {
+    const int wave = t >> 6;
     lane = t & 63;
     l16 = lane & 15;
     q = lane >> 4;
@@ -199,7 +200,7 @@ struct GemmShape {
   int slabs_per_split;
   int tiles_total;   // tiles_m * tiles_n * split_k
   int grid_padded;   // tiles_total rounded up to a multiple of 8
-  int slabs_per_block;             // K blocking of the rows of B (see gemm_mainloop)
+  int slabs_per_block;             // K blocking of the rows of B, the slabs of a term with fp16 (see gemm_mainloop)
   int64_t block_bytes_b;
   int k_valid;                     // ATN: rows of A that exist (K may be padded beyond them)
 #ifdef KT_PHASE_STAMPS
@@ -291,6 +292,8 @@ constexpr int fragment_read_slot(int r, int base, int spacing) {
 // (slabs_per_block = number of slabs in a row) and lets the token-minor dL/dY of
 // dR = X^T G be stored in blocks of a few thousand tokens, so that the 256 rows a tile
 // reads at any one time lie within a couple of MiB instead of 256 separate pages.
+// fp16 (heads and tails, split3_kernel): a row is [head | tail], slabs_per_block slabs each, and K walks head head + head tail + tail head:
+// A head, head, tail, B head, tail, head (and stops after the first of them where there are no more slabs).
 // The slab range [slab0, slab0 + k_slabs) must lie inside both operands' rows, and
 // (BM-1)*lda*sizeof(T) + 128 (same for B) must fit 32 bits (the host checks this).
 //
@@ -333,7 +336,7 @@ constexpr int fragment_read_slot(int r, int base, int spacing) {
 // from the last four valid ones, so M (N) is a multiple of 4; rows of A beyond k_valid as above, B has all of its rows.
 // With copies / in place, us: kt_fuse_rotation, side 1, d = 256, k = 4000: 19.4 / 11.5, d = 1024, k = 1000: 40.5 / 25.7,
 // d = 3072, k = 9000: 1312 / 1240; fp32 fake-quant, d = 1024, 16 tokens: 30.2 / 25.6.
-template <class TL, bool ATN, bool BTN, bool SWAP>
+template <class TL, bool ATN, bool BTN, bool SWAP, bool AGAIN = false>
 __device__ __forceinline__ void gemm_mainloop(const typename TL::T* __restrict__ A, int64_t lda,
                                               int M, int m0,
                                               const typename TL::T* __restrict__ B, int64_t ldb,
@@ -343,7 +346,7 @@ __device__ __forceinline__ void gemm_mainloop(const typename TL::T* __restrict__
                                               floatx4 (&acc)[TL::MB][TL::NB], char* lds, int k_valid
                                               KT_STAMP_PARAM) {
   using T = typename TL::T;
-  constexpr bool F32 = sizeof(T) == 4;
+  constexpr bool F32 = sizeof(T) == 4, F16 = std::is_same_v<T, _Float16>;
   static_assert(!BTN || F32, "BTN: fp32");
   constexpr int EPC = 16 / (int)sizeof(T);  // elements per 16-byte chunk
   constexpr int MB = TL::MB, NB = TL::NB, SLOTS = MB * NB, NFRAG = MB + NB;
@@ -361,7 +364,7 @@ __device__ __forceinline__ void gemm_mainloop(const typename TL::T* __restrict__
   static_assert(A_GAP >= 1 && B_GAP >= 1 && load_slot(NLD - 1) - 2 * SLOTS < SLOTS + BAR - 3 && BAR + NB * SPACE1 <= SLOTS && BAR >= 2,
                 "not enough MFMA slots to hide the memory instructions");
 
-  const int tid = thread_id();
+  const int tid = thread_id<AGAIN>();
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
   // global addressing: uniform 64-bit base + 32-bit byte offsets.  Load i of a thread fills 16 bytes at
@@ -437,6 +440,8 @@ __device__ __forceinline__ void gemm_mainloop(const typename TL::T* __restrict__
     if (req_a < last_slab) {
       ++req_a;
       an += ATN ? (int64_t)TL::BK * lda * (int64_t)sizeof(T) : (int64_t)kRowBytes;
+      if constexpr (F16)
+        if (req_a == slabs_per_block) an -= (int64_t)slabs_per_block * kRowBytes;
     }
   };
   auto locate_b = [&]() __attribute__((always_inline)) {
@@ -445,6 +450,9 @@ __device__ __forceinline__ void gemm_mainloop(const typename TL::T* __restrict__
       ++req_b;
       if constexpr (BTN) {
         bn += (int64_t)TL::BK * ldb * (int64_t)sizeof(T);
+      } else if constexpr (F16) {
+        bn += kRowBytes;
+        if (req_b == 2 * slabs_per_block) bn -= 2 * (int64_t)slabs_per_block * kRowBytes;
       } else {
         const bool wrap = ++in_block_b == slabs_per_block;
         if (wrap) in_block_b = 0;
@@ -458,7 +466,7 @@ __device__ __forceinline__ void gemm_mainloop(const typename TL::T* __restrict__
   const unsigned lds_wave = (unsigned)(size_t)(__attribute__((address_space(3))) char*)lds + wave * 1024u;
   unsigned b_write = 0;  // byte offset of the B stage to fill next
   int b_read = 0;        // ... of the B stage whose fragments are read
-  const Frag<TL> f;
+  const Frag<TL> f(tid);
   // fragment addresses, one per step of a slab: blocks and the A stage are instruction immediates
   const int key = swizzle_key(f.l16);
   int fa_s[2], fb_s[2], fb_now[2];

@@ -164,7 +164,7 @@ __global__ __launch_bounds__(TL::NT, (160 * 1024 / TL::LDS_BYTES)) void row_sync
     settle_all<TL>(acc);
     {
       const GemmShape& g = args().g;
-      gemm_mainloop<TL, false, false, false>(static_cast<const T*>(g.A) + (int64_t)batch * g.batch_stride_a, g.lda, g.M, m0,
+      gemm_mainloop<TL, false, false, false, true>(static_cast<const T*>(g.A) + (int64_t)batch * g.batch_stride_a, g.lda, g.M, m0,
                                              static_cast<const T*>(g.B) + (int64_t)batch * g.batch_stride_b, g.ldb, g.N, n0, 0, g.slabs_total,
                                              g.slabs_per_block, 0, acc, lds, 0);
     }
@@ -269,7 +269,7 @@ struct RowLossGrad {
       if (threadIdx.x == 0) loss_part[row] = s;
     }
     __syncthreads();
-    grad.store(acc, batch, m0, n0, [&](int t) __attribute__((always_inline)) { return coef[t]; });
+    grad.template store<true>(acc, batch, m0, n0, [&](int t) __attribute__((always_inline)) { return coef[t]; });
   }
 };
 
