@@ -432,7 +432,8 @@ __global__ __launch_bounds__(256) void hadamard_cross_mfma_kernel(__bf16* __rest
 // bf16 results -> the same LDS, 16-byte stores.  Four barriers a row; the workgroups that share a CU overlap.
 // LDS rows are 2 P bytes; 64-byte pieces (reads) and 16-byte chunks (results) are XOR-swizzled with the row.
 // Bound: HBM, one read and one write of the rows.  512 MiB of rows, two kernels / this one: d = 14336 491 / 221 us
-// (4.9 TB/s; 16 rows, set-up and all: 15.9 / 8.6), 13824 683 / 223, 8192 547 / 215, 5120 528 / 243, 28672 483 / 288 (eight
+// (4.9 TB/s; 16 rows, set-up and all: 15.9 / 7.2; the first row is requested ahead of the set-up, which makes a row of H_m per thread: with an
+// entry at a time and atomics 16 rows took 8.6, of 13824 21.7 instead of 7.1), 13824 683 / 223, 8192 547 / 215, 5120 528 / 243, 28672 483 / 288 (eight
 // waves of 256 registers, one workgroup per CU: its barriers overlap with nothing), 1536 (one wave of four at work) 778 / 513.
 struct HadamardFactor {
   unsigned long long squares[2];  // bit x: x is a quadratic residue modulo q
@@ -465,6 +466,27 @@ __device__ __forceinline__ int hadamard_negative(const HadamardFactor& f, int a,
     neg = !plus;
   }
   return neg;
+}
+
+// The same for all a at once, bit a.  Off its first row and column the conference matrix is circulant: its row is the first one, rotated.
+typedef unsigned __int128 Bits128;
+__device__ __forceinline__ Bits128 hadamard_negative_row(const HadamardFactor& f, int b) {
+  if (f.kind == 0) {  // m <= 8
+    unsigned row = 0u;
+    for (int a = 0; a < f.m; ++a) row |= (unsigned)(__builtin_popcount(a & b) & 1) << a;
+    return row;
+  }
+  const Bits128 one = 1, ones_q = (one << f.q) - 1;
+  const Bits128 squares = (Bits128)f.squares[1] << 64 | f.squares[0], nonsquares = ones_q & ~squares & ~one;  // (0 is the diagonal)
+  const int v = b < f.h ? b : b - f.h;
+  Bits128 row;
+  if (v == 0) row = f.kind == 1 ? ones_q << 1 : 0;
+  else row = ((nonsquares << (v - 1) | nonsquares >> (f.q - (v - 1))) & ones_q) << 1;
+  if (f.kind == 2) {
+    const Bits128 off = row ^ one << v;
+    row = b < f.h ? row | off << f.h : off | (~row & (ones_q << 1 | one)) << f.h;
+  }
+  return row;
 }
 
 // ---- fp32 rows of H_m (x) S_p2 in one pass: a workgroup per row, the row in LDS ------------------------
@@ -625,13 +647,20 @@ __global__ __launch_bounds__(64 * WAVES, 2) void hadamard_onepass_kernel(const _
     sg[i][0] = sg[i][1] = 0x01010101u;
     if (signs && c < chunks) __builtin_memcpy(sg[i], signs + 8 * c, 8);  // (any alignment)
   }
-  // the signs of H_m as 128-bit rows in LDS: bit a of row b; and a word that is not zero if `signs` holds anything but +-1
+  intx4 nxt[NCH];
+  auto request = [&](int64_t row) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < NCH; ++i) {
+      const int c = tid + NT * i;
+      if (row < n && c < chunks) nxt[i] = *reinterpret_cast<const intx4*>(X + row * ldx + 8 * c);
+    }
+  };
+  if constexpr (!PACKED) request(blockIdx.x);  // (with eight waves the set-up takes all registers)
+  // the signs of H_m as 128-bit rows in LDS, bit a of row b; and behind them a word a wave, not zero if its part of `signs` holds anything but +-1
   unsigned* tab = reinterpret_cast<unsigned*>(had_lds);
-  for (int i = tid; i < 4 * fac.m + 1; i += NT) tab[i] = 0u;
-  __syncthreads();
-  for (int i = tid; i < fac.m * fac.m; i += NT) {
-    const int b = i / fac.m, a = i - b * fac.m;
-    if (hadamard_negative(fac, a, b)) atomicOr(&tab[4 * b + (a >> 5)], 1u << (a & 31));
+  if (tid < fac.m) {
+    const Bits128 row = hadamard_negative_row(fac, tid);
+    *reinterpret_cast<uintx4*>(tab + 4 * tid) = uintx4{(unsigned)row, (unsigned)(row >> 32), (unsigned)(row >> 64), (unsigned)(row >> 96)};
   }
   unsigned other = 0u;  // not zero: this thread has seen a value that is neither 1 nor -1
   unsigned flip8[(NCH + 3) / 4];  // the sign bits of a chunk's eight values, one byte per chunk
@@ -646,9 +675,18 @@ __global__ __launch_bounds__(64 * WAVES, 2) void hadamard_onepass_kernel(const _
     }
     flip8[i / 4] = (i % 4 ? flip8[i / 4] : 0u) | byte << (8 * (i % 4));
   }
-  if (other) atomicOr(&tab[4 * fac.m], 1u);
+  const bool wave_other = __any(other != 0u);
+  if (lane == 0) tab[4 * fac.m + wave] = wave_other;
   __syncthreads();
-  const unsigned any_other = tab[4 * fac.m];
+  unsigned any_other = 0u;
+#pragma unroll
+  for (int w = 0; w < WAVES; ++w) any_other |= tab[4 * fac.m + w];
+  auto sign_words = [](unsigned byte) __attribute__((always_inline)) {  // the sign bits of eight bf16 values
+    intx4 v;
+#pragma unroll
+    for (int e = 0; e < 4; ++e) v[e] = (int)((byte << (15 - 2 * e) & 0x8000u) | (byte << (30 - 2 * e) & 0x80000000u));
+    return v;
+  };
   // this wave's 32 columns of H_M as B operands: lane = output o = 32 wave + l32, 8 inputs i = 16 s + 8 half + e;
   // H_M[i][o] = H_m[i / 2^j][o / 2^j] (-1)^(common bits of i and o below 2^j)
   intx4 hf[KSM];
@@ -659,22 +697,21 @@ __global__ __launch_bounds__(64 * WAVES, 2) void hadamard_onepass_kernel(const _
 #pragma unroll
       for (int w = 0; w < 4; ++w) row[w] = tab[4 * (o >> fac.log2j) + w];
     }
+    // the eight inputs: bits 0 .. 2 of i give one pattern, those above flip all of it
+    const unsigned within = (low & 1 ? 0xaau : 0u) ^ (low & 2 ? 0xccu : 0u) ^ (low & 4 ? 0xf0u : 0u);
 #pragma unroll
     for (int s = 0; s < KSM; ++s) {
       const int i0 = 16 * s + 8 * half, a0 = i0 >> fac.log2j;
       const unsigned word = a0 < 64 ? (a0 < 32 ? row[0] : row[1]) : (a0 < 96 ? row[2] : row[3]);
-      const unsigned bits = word >> (a0 & 31);  // the eight inputs share a word: a0 is a multiple of 8 / 2^j
+      unsigned byte = word >> (a0 & 31);  // the eight inputs share a word: a0 is a multiple of 8 / 2^j, and 2^j of them an entry of H_m
+      if (fac.log2j >= 3) byte = byte & 1u ? 0xffu : 0u;
+      else if (fac.log2j == 2) byte = (byte & 1u ? 0x0fu : 0u) | (byte & 2u ? 0xf0u : 0u);
+      else if (fac.log2j == 1) byte = (byte & 1u) * 0x03u | (byte & 2u) * 0x06u | (byte & 4u) * 0x0cu | (byte & 8u) * 0x18u;
+      byte ^= within ^ (__builtin_popcount(i0 & low) & 1 ? 0xffu : 0u);
+      const intx4 signs8 = sign_words(byte);
 #pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        unsigned v = 0u;
-#pragma unroll
-        for (int e = 0; e < 2; ++e) {
-          const int i = i0 + 2 * w + e;
-          const unsigned neg = ((bits >> ((i >> fac.log2j) - a0)) ^ (unsigned)__builtin_popcount(i & low)) & 1u;
-          v |= ((i < M && o < M) ? 0x3780u | neg << 15 : 0u) << (16 * e);  // bf16 2^-16 is 0x3780
-        }
-        hf[s][w] = (int)v;
-      }
+      for (int w = 0; w < 4; ++w)  // (M is a multiple of 4; bf16 2^-16 is 0x3780)
+        hf[s][w] = i0 + 2 * w < M && o < M ? signs8[w] | 0x37803780 : 0;
       if constexpr (PACKED || LOGP == 6) asm volatile("" : "+v"(hf[s]));  // finished here: half-made words that wait for their end at the loop were spilled
     }
   }
@@ -685,12 +722,6 @@ __global__ __launch_bounds__(64 * WAVES, 2) void hadamard_onepass_kernel(const _
   }
   // the words to XOR a chunk with (PACKED: made from the byte every time)
   intx4 flip[PACKED ? 1 : NCH];
-  auto sign_words = [](unsigned byte) __attribute__((always_inline)) {
-    intx4 v;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) v[e] = (int)((byte << (15 - 2 * e) & 0x8000u) | (byte << (30 - 2 * e) & 0x80000000u));
-    return v;
-  };
 #pragma unroll
   for (int i = 0; i < (PACKED ? 0 : NCH); ++i) flip[i] = sign_words(flip8[i / 4] >> (8 * (i % 4)) & 0xffu);
   // tile rows M .. 16 KS - 1 meet zeros of H_M: they have to be finite
@@ -702,15 +733,7 @@ __global__ __launch_bounds__(64 * WAVES, 2) void hadamard_onepass_kernel(const _
 #pragma unroll
   for (int b = 0; b < NBLK; ++b) tr[b] = tr_row * ROWB + ((b ^ read_key(tr_row)) << 6) + 2 * tr_col;
 
-  intx4 nxt[NCH];
-  auto request = [&](int64_t row) __attribute__((always_inline)) {
-#pragma unroll
-    for (int i = 0; i < NCH; ++i) {
-      const int c = tid + NT * i;
-      if (row < n && c < chunks) nxt[i] = *reinterpret_cast<const intx4*>(X + row * ldx + 8 * c);
-    }
-  };
-  request(blockIdx.x);
+  if constexpr (PACKED) request(blockIdx.x);
 #pragma unroll 1
   for (int64_t row = blockIdx.x; row < n; row += gridDim.x) {
     if constexpr (PACKED) {  // (or the compiler makes all of the words once and spills them)
