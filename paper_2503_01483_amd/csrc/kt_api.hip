@@ -859,7 +859,7 @@ static bool skinny_ok(kt_dtype xdt, const void* R, int64_t ldr, kt_dtype rdt, in
 
 template <typename TR>
 static bool launch_skinny(const bf16* X, int64_t ldx, const TR* R, int64_t ldr, int64_t batch, int64_t n, int64_t d,
-                          char* scratch, size_t rt_bytes, float* Y, hipStream_t st) {
+                          char* scratch, size_t rt_bytes, float* Y, hipStream_t st, const float** parts = nullptr, int* splits = nullptr) {
   // about two workgroups per CU; every row range at least 256 rows (one round of the four waves); partials must fit
   int64_t s = ceil_div(2 * kNumCUs, (d / 64) * batch);
   const int64_t fit = (int64_t)(rt_bytes / ((size_t)batch * n * d * 4));
@@ -877,6 +877,11 @@ static bool launch_skinny(const bf16* X, int64_t ldx, const TR* R, int64_t ldr, 
   else if (n <= 32) go(std::integral_constant<int, 2>{});
   else go(std::integral_constant<int, 4>{});
   if (!launch_ok()) return false;
+  if (parts) {  // the caller adds them
+    *parts = part;
+    *splits = (int)s;
+    return true;
+  }
   return s == 1 || launch_splitk_reduce(part, count, (int)s, Y, LossSum{}, st);
 }
 
@@ -1102,10 +1107,12 @@ static kt_status run_quant(const QuantPlan& p, const void* X, int64_t ldx, const
       for (int64_t t0 = 0; t0 < n; t0 += p.stage_rows) {
         const int64_t nt = n - t0 < p.stage_rows ? n - t0 : p.stage_rows;
         bool ok;
+        const float* parts = Ybuf;
+        int splits = 1;
         if (skinny) {
           const bf16* Xb = reinterpret_cast<const bf16*>(Xp);
-          ok = rdt == KT_F32 ? launch_skinny(Xb, ldx, static_cast<const float*>(R), ldr, batch, n, d, ws + p.o_rt, p.o_amax - p.o_rt, Ybuf, st)
-                             : launch_skinny(Xb, ldx, static_cast<const bf16*>(R), ldr, batch, n, d, ws + p.o_rt, p.o_amax - p.o_rt, Ybuf, st);
+          ok = rdt == KT_F32 ? launch_skinny(Xb, ldx, static_cast<const float*>(R), ldr, batch, n, d, ws + p.o_rt, p.o_amax - p.o_rt, Ybuf, st, &parts, &splits)
+                             : launch_skinny(Xb, ldx, static_cast<const bf16*>(R), ldr, batch, n, d, ws + p.o_rt, p.o_amax - p.o_rt, Ybuf, st, &parts, &splits);
         } else {
           ok = launch_rows_gemm<T, TQ>(Xp + (b0 * n + t0) * ldx, ldx, n * ldx, Rg + b0 * r_stride, ldr, in_place, nb, nt, d, Ybuf, nt * d, st);
         }
@@ -1115,7 +1122,11 @@ static kt_status run_quant(const QuantPlan& p, const void* X, int64_t ldx, const
         int8_t* co = codes ? codes + row0 * d : nullptr;
         float2* eo = err ? reinterpret_cast<float2*>(err) + row0 : nullptr;
         const dim3 grid((unsigned)ceil_div(rows, 4));
-        if (d <= 1024)
+        if (skinny) {
+          auto kern = d <= 4096 ? quant_partials_kernel<1> : d <= 8192 ? quant_partials_kernel<2> : quant_partials_kernel<4>;
+          const int64_t threads = round_up(d / 4, 64) < 1024 ? round_up(d / 4, 64) : 1024;
+          hipLaunchKernelGGL(kern, dim3((unsigned)rows), dim3((unsigned)threads), 0, st, parts, batch * n * d, splits, (int)d, clip, so, co, eo);
+        } else if (d <= 1024)
           hipLaunchKernelGGL((quant_rows_kernel<4, true>), grid, dim3(256), 0, st, Ybuf, rows, (int)d, clip, so, co, eo);
         else if (d <= 4096)
           hipLaunchKernelGGL((quant_rows_kernel<16, true>), grid, dim3(256), 0, st, Ybuf, rows, (int)d, clip, so, co, eo);

@@ -739,6 +739,81 @@ __global__ __launch_bounds__(256) void quant_rows_kernel(const float* __restrict
   }
 }
 
+// The same for the few rows of a decode step, Y still as `splits` partial sums (skinny_rotate_kernel), `stride` apart, added in their order: a
+// workgroup per row, a value of every partial per thread and element, so that all of its loads are in flight at once (with 256 threads, in
+// two rounds of 64 KiB, the kernel took 9 us of a call of 4096 features; that call, with the sums and a wave per row in kernels of
+// their own / this: 19.6 / 16.5 us).  Bound: the latency of a launch and of those loads.  d <= 4 CH blockDim.x; grid = rows.
+template <int CH>
+__global__ __launch_bounds__(1024) void quant_partials_kernel(const float* __restrict__ part, int64_t stride, int splits, int d, float clip,
+                                                              float* __restrict__ scales_out, int8_t* __restrict__ codes, float2* __restrict__ err) {
+  __shared__ float sh[3][16];
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, nt = blockDim.x, waves = nt >> 6;
+  const int64_t row = blockIdx.x;
+  const float* src = part + row * d + 4 * tid;
+  floatx4 v[CH];
+#pragma unroll
+  for (int c = 0; c < CH; ++c) {
+    v[c] = floatx4{0.f, 0.f, 0.f, 0.f};
+    if (4 * (tid + nt * c) < d) {
+      const float* p = src + 4 * nt * c;
+      v[c] = *reinterpret_cast<const floatx4*>(p);
+#pragma unroll 7
+      for (int k = 1; k < splits; ++k) v[c] += *reinterpret_cast<const floatx4*>(p + k * stride);
+    }
+  }
+  float a = 0.f;
+#pragma unroll
+  for (int c = 0; c < CH; ++c)
+#pragma unroll
+    for (int e = 0; e < 4; ++e) a = fmaxf(a, fabsf(v[c][e]));
+#pragma unroll
+  for (int o = 32; o >= 1; o >>= 1) a = fmaxf(a, __shfl_xor(a, o));
+  if (lane == 0) sh[0][wave] = a;
+  __syncthreads();
+  for (int w = 0; w < waves; ++w) a = fmaxf(a, sh[0][w]);
+  const float s = __fdiv_rn(__fmul_rn(clip, a), 7.0f);
+  const bool live = s > 0.f;
+  const float rinv = live ? __fdiv_rn(1.0f, s) : 0.f;
+  float e2 = 0.f, y2 = 0.f;
+#pragma unroll
+  for (int c = 0; c < CH; ++c)
+    if (4 * (tid + nt * c) < d) {
+      unsigned pack = 0u;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        float q = rintf(__fmul_rn(v[c][e], rinv));
+        q = fminf(fmaxf(q, -7.f), 7.f);
+        if (!live) q = 0.f;
+        const float diff = v[c][e] - q * s;
+        e2 = fmaf(diff, diff, e2);
+        y2 = fmaf(v[c][e], v[c][e], y2);
+        pack |= ((unsigned)(int)q & 0xffu) << (8 * e);
+      }
+      if (codes) reinterpret_cast<unsigned*>(codes + row * d)[tid + nt * c] = pack;
+    }
+  if (err) {  // uniform
+#pragma unroll
+    for (int o = 32; o >= 1; o >>= 1) {
+      e2 += __shfl_xor(e2, o);
+      y2 += __shfl_xor(y2, o);
+    }
+    if (lane == 0) {
+      sh[1][wave] = e2;
+      sh[2][wave] = y2;
+    }
+    __syncthreads();
+    if (tid == 0) {
+      e2 = y2 = 0.f;
+      for (int w = 0; w < waves; ++w) {
+        e2 += sh[1][w];
+        y2 += sh[2][w];
+      }
+      err[row] = make_float2(e2, y2);
+    }
+  }
+  if (tid == 0 && scales_out) scales_out[row] = s;
+}
+
 // ---- per-token quantisation-quality figures of a materialised Y = X R ----------------------
 // (max-value "success" of "Evaluation ... on Channel Outliers"; Setup: symmetric per-token
 // quantisation clipped at a quantile, asymmetric quantisation for KV caches; Background:
