@@ -111,7 +111,7 @@ def kt_workspace_bytes(op, batch, n, d, x_dtype):
 
 
 def _ptr(t):
-    return None if t is None else ctypes.c_void_p(t.data_ptr())
+    return None if t is None else t.data_ptr()
 
 
 def _dtype_code(t):
@@ -124,8 +124,9 @@ def _dtype_code(t):
 
 def _stream(stream):
     if stream is None:
-        stream = torch.cuda.current_stream()
-    return ctypes.c_void_p(stream.cuda_stream) if hasattr(stream, "cuda_stream") else ctypes.c_void_p(stream)
+        # torch.cuda.current_stream().cuda_stream without the stream object (of a call of 8 us it took 1.5)
+        return torch._C._cuda_getCurrentRawStream(torch.cuda.current_device())
+    return stream.cuda_stream if hasattr(stream, "cuda_stream") else stream
 
 
 def _check(status):
