@@ -1824,7 +1824,8 @@ kt_status kt_rotate_quant_metrics(const void* X, int64_t ldx, const void* R, int
                            : d < 4096  ? quant_metrics_row_kernel<T, 16, false>
                            : d == 8192 ? quant_metrics_row_kernel<T, 32, true>
                                        : quant_metrics_row_kernel<T, 32, false>;
-        const int64_t row_wgs = ceil_div(nt, 4) < ceil_div(16 * kNumCUs, nb) ? ceil_div(nt, 4) : ceil_div(16 * kNumCUs, nb);
+        // us, 32768 rows, 8 / 16 workgroups a CU: d = 256 71 / 81, 1024 136 / 140, 2048 347 / 342, 4096 987 / 970
+        const int64_t most = ceil_div((d <= 1024 ? 8 : 16) * kNumCUs, nb), row_wgs = ceil_div(nt, 4) < most ? ceil_div(nt, 4) : most;
         hipLaunchKernelGGL(rows_kernel, dim3((unsigned)row_wgs, (unsigned)nb), dim3(256), 0, st, Yb,
                            Xp + row0 * ldx, ldx, n * ldx, (int)nt, (int)d, (double)quantile,
                            amax ? amax + 2 * row0 : nullptr, threshold ? threshold + row0 : nullptr,

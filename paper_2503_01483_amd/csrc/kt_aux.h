@@ -944,8 +944,12 @@ __global__ __launch_bounds__(256, (NV4 <= 4 ? 4 : NV4 <= 16 ? 3 : 2)) void quant
     const double pos = quant * (double)(d - 1);
     const int k = (int)floor(pos);
     const float frac = (float)(pos - (double)k);
-    // a_k = the value of rank k (0-based, ascending) among the |y| bit patterns: radix select in three rounds
-    // on bits 30..20, 19..9 and 8..0, each a histogram of up to 2048 bins kept by this wave in LDS.
+    // a_k = the value of rank k (0-based, ascending) among the |y|.  A histogram of 2048 equal steps up to the largest one, kept by this wave in LDS,
+    // leaves few values in the bin of rank k and the next occupied one: they are gathered and ranked against each other (a multiplication by a
+    // positive constant and a truncation keep the order, so this is exact).  Rows where those bins hold more than 64 (one huge value, many equal
+    // ones), or whose squares overflow, or tiny ones: radix select on the bit patterns in three rounds, bits 30..20, 19..9 and 8..0, a histogram
+    // each.  32768 rows of 4096, us, call with the radix select alone / this: 1054 / 976 (the digits of normal values fall into few bins, whose atomics
+    // wait for each other, and every round looks at every value).
     auto clear_hist = [&]() __attribute__((always_inline)) {
 #pragma unroll
       for (int j = 0; j < 8; ++j) *reinterpret_cast<uint4*>(hist + 256 * j + 4 * lane) = make_uint4(0u, 0u, 0u, 0u);
@@ -1006,6 +1010,61 @@ __global__ __launch_bounds__(256, (NV4 <= 4 ? 4 : NV4 <= 16 ? 3 : 2)) void quant
       return (unsigned)(32 * g0 + __builtin_ctzll(nz3));
     };
     unsigned kk = (unsigned)k, bin, cum, cnt;
+    float ak = 0.f, ak1 = 0.f;
+    bool done = false;
+    if (ar > 1e-30f && y2 < 1e300) {  // (uniform; not with a NaN)
+      const float steps = 2047.f / ar;
+      clear_hist();
+#pragma unroll
+      for (int c = 0; c < NV4; ++c) {
+        if (live(c)) {
+          const float e4[4] = {v[c].x, v[c].y, v[c].z, v[c].w};
+#pragma unroll
+          for (int e = 0; e < 4; ++e) atomicAdd(&hist[(unsigned)__fmul_rn(fabsf(e4[e]), steps)], 1u);
+        }
+      }
+      pick(kk, bin, cum, cnt);
+      const unsigned next = next_bin(), span = next != 0xffffffffu ? next - bin : 0u;
+      const unsigned total = (unsigned)__builtin_amdgcn_readfirstlane((int)(cnt + (next != 0xffffffffu ? hist[next] : 0u)));
+      if (total <= 64u) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();  // the histogram has been read: its room is the list now
+        unsigned have = 0u;
+        float again = steps;  // (the bins are made anew: kept from the histogram they are a register a value)
+        asm volatile("" : "+v"(again));
+#pragma unroll
+        for (int c = 0; c < NV4; ++c) {
+          const float e4[4] = {v[c].x, v[c].y, v[c].z, v[c].w};
+          bool m[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) m[e] = live(c) && (unsigned)__fmul_rn(fabsf(e4[e]), again) - bin <= span;
+          if (!__any((int)(m[0] | m[1] | m[2] | m[3]))) continue;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const unsigned long long mask = __ballot(m[e]);
+            if (m[e]) hist[have + __builtin_amdgcn_mbcnt_hi((unsigned)(mask >> 32), __builtin_amdgcn_mbcnt_lo((unsigned)mask, 0u))] = __float_as_uint(fabsf(e4[e]));
+            have += (unsigned)__builtin_popcountll(mask);
+          }
+        }
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        const unsigned mine = lane < (int)total ? hist[lane] : 0xffffffffu;
+        unsigned rank = 0u;
+        for (unsigned j = 0; j < total; ++j) {
+          const unsigned w = (unsigned)__builtin_amdgcn_readlane((int)mine, (int)j);
+          rank += w < mine || (w == mine && (int)j < lane) ? 1u : 0u;
+        }
+        kk -= cum;
+        const int at = __builtin_ctzll(__ballot(rank == kk && lane < (int)total));
+        ak = ak1 = __uint_as_float((unsigned)__builtin_amdgcn_readlane((int)mine, at));
+        if (kk + 1u < total) {
+          const int at1 = __builtin_ctzll(__ballot(rank == kk + 1u && lane < (int)total));
+          ak1 = __uint_as_float((unsigned)__builtin_amdgcn_readlane((int)mine, at1));
+        }
+        done = true;
+      }
+    }
+    if (!done) {
     // first digit, bits 30..20: every value of the row counts
     clear_hist();
 #pragma unroll
@@ -1076,8 +1135,9 @@ __global__ __launch_bounds__(256, (NV4 <= 4 ? 4 : NV4 <= 16 ? 3 : 2)) void quant
       }
       if (above < 0x80000000u) nxt = above + base;
     }
-    const float ak = __uint_as_float(prefix);
-    const float ak1 = (cnt >= kk + 2u || nxt == 0xffffffffu) ? ak : __uint_as_float(nxt);
+    ak = __uint_as_float(prefix);
+    ak1 = (cnt >= kk + 2u || nxt == 0xffffffffu) ? ak : __uint_as_float(nxt);
+    }
     float inc = __fmul_rn(frac, __fsub_rn(ak1, ak));
     asm volatile("" : "+v"(inc));  // keep the product rounded: no contraction with the add below
     t = __fadd_rn(ak, inc);
