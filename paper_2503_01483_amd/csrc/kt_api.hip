@@ -189,7 +189,7 @@ static int g_stamp_next = -1;  // developer build: slot the next GEMM launch rec
 // row index: the slab's).  Whether `rows` rows of ld elements can be.
 static bool tile_offsets_fit(int64_t rows, int64_t ld, int64_t esz) { return (rows - 1) * ld * esz + 512 <= (int64_t)UINT32_MAX; }
 
-template <class TL, class Epi, bool ATN = false, bool BTN = false>
+template <class TL, class Epi, bool ATN = false, bool BTN = false, bool TWO = false>
 static bool launch_gemm(const void* A, int64_t lda, int64_t bsa, int M, const void* B, int64_t ldb,
                         int64_t bsb, int N, int64_t K, int slabs_per_split, int batch,
                         const Epi& epi, hipStream_t stream, int64_t k_block = 0,
@@ -197,9 +197,11 @@ static bool launch_gemm(const void* A, int64_t lda, int64_t bsa, int M, const vo
   // ATN: A is [K][lda] with the M index along its rows (see gemm_mainloop); BTN: B [K][ldb].
   constexpr auto kern = [] {
     if constexpr (std::is_same_v<TL, TF_32>) return &gemm32_kernel<Epi, ATN, BTN>;
+    else if constexpr (TWO) return &gemm_two_kernel<TL, Epi>;
     else return &gemm_nt_kernel<TL, Epi, ATN, BTN>;
   }();
-  constexpr int lds_bytes = TL::LDS_BYTES;
+  constexpr int lds_bytes = (TWO ? 2 : 1) * TL::LDS_BYTES;
+  static_assert(!TWO || (!ATN && !BTN && lds_bytes <= 160 * 1024), "two groups: both operands along K");
   const int64_t esz = (int64_t)sizeof(typename TL::T);
   if (!tile_offsets_fit(ATN ? TL::BK : TL::BM, lda, esz) || !tile_offsets_fit(BTN ? TL::BK : TL::BN, ldb, esz)) return false;
   if (ATN && (k_valid < 1 || k_valid > K)) return false;
@@ -224,8 +226,23 @@ static bool launch_gemm(const void* A, int64_t lda, int64_t bsa, int M, const vo
 #ifdef KT_PHASE_STAMPS
   g.stamp_slot = g_stamp_next >= 0 && g_stamp_next < kStampSlots ? g_stamp_next++ : -1;
 #endif
-  hipLaunchKernelGGL(kern, dim3(g.grid_padded, batch), dim3(TL::NT), lds_bytes, stream, g, epi);
+  if (TWO && (g.split_k != 1 || g.slabs_total % 2 != 0)) return false;
+  hipLaunchKernelGGL(kern, dim3(g.grid_padded, batch), dim3((TWO ? 2 : 1) * TL::NT), lds_bytes, stream, g, epi);
   return launch_ok();
+}
+
+// An unsplit 16-bit product of 22 slabs or more (before that the second prologue and the sum cost what it gives) whose tiles leave a CU to one workgroup
+// (128 x 128) or two (64 x 64) takes gemm_two_kernel.  us, one group of waves / two: fake-quant, d = 4096: 65 tokens 49.4 / 41.9, 400 52.9 / 49.0, 1000
+// 59.9 / 57.7, 1500 (more tiles) 79.3 / 79.2; 2688: 200 31.8 / 27.2; 2048: 400 27.4 / 24.3; 1408: 400 20.4 / 18.9, 65 16.5 / 16.8; 1152, 1000 (18 slabs) 19.9 /
+// 20.5; 512, 2500 (8) 14.3 / 15.4.  Retractions of two iterations, d = 1024 79.8 / 72.2, 1152 90.8 / 86.7, 1408 112.8 / 103.6, 1664 155.6 / 144.8, 2048 196.6 / 190.1.
+template <class TL, class Epi>
+static bool launch_gemm_few(const void* A, int64_t lda, int64_t bsa, int M, const void* B, int64_t ldb, int64_t bsb, int N, int64_t K, int slabs_per_split,
+                            int batch, const Epi& epi, hipStream_t stream, int64_t k_block = 0) {
+  if constexpr (TL::BM == TL::BN && TL::BM <= 128) {
+    const bool few = ceil_div(M, TL::BM) * ceil_div(N, TL::BN) * batch <= (TL::BM == 64 ? 2 : 1) * kNumCUs;
+    if (few && K / TL::BK >= 22 && slabs_per_split == 0) return launch_gemm<TL, Epi, false, false, true>(A, lda, bsa, M, B, ldb, bsb, N, K, slabs_per_split, batch, epi, stream, k_block);
+  }
+  return launch_gemm<TL>(A, lda, bsa, M, B, ldb, bsb, N, K, slabs_per_split, batch, epi, stream, k_block);
 }
 
 // Whether a row-major fp32 operand can be read in place, K as its row index (16-byte loads).  Otherwise a launch copies it first.
@@ -907,7 +924,8 @@ static bool launch_rows_gemm(const T* X, int64_t ldx, int64_t x_batch_stride, co
       if (in_place)
         return launch_gemm<G, EpiStore<G>, false, true>(X, ldx, x_batch_stride, (int)rows, R, ldr, d * ldr, (int)d, d, 0, (int)problems, e, st);
     }
-    return launch_gemm<G>(X, ldx, x_batch_stride, (int)rows, R, d, d * d, (int)d, d, 0, (int)problems, e, st);
+    if constexpr (sizeof(T) == 2) return launch_gemm_few<G>(X, ldx, x_batch_stride, (int)rows, R, d, d * d, (int)d, d, 0, (int)problems, e, st);
+    else return launch_gemm<G>(X, ldx, x_batch_stride, (int)rows, R, d, d * d, (int)d, d, 0, (int)problems, e, st);
   };
   if constexpr (sizeof(T) == 4) {
     return with_f32_tile(rows, d, problems, go);
@@ -1240,10 +1258,10 @@ static kt_status cayley_run(const CayleyPlan& p, char* ws, float* R, const float
     if constexpr (sizeof(*B) == 2) {
       auto e0 = epilogue(first_tag, std::integral_constant<int, 0>{});
       e0.Usplit = U1;
-      if (!launch_gemm<First>(U0, ld, d * ld, D, B, ld, d * ld, D, K, 0, (int)batch, e0, st, d)) return false;
+      if (!launch_gemm_few<First>(U0, ld, d * ld, D, B, ld, d * ld, D, K, 0, (int)batch, e0, st, d)) return false;
       auto e1 = epilogue(first_tag, std::integral_constant<int, 1>{});
       e1.it = 1;
-      if (!launch_gemm<First>(U1, d, dd, D, B, ld, d * ld, D, d, 0, (int)batch, e1, st, d)) return false;
+      if (!launch_gemm_few<First>(U1, d, dd, D, B, ld, d * ld, D, d, 0, (int)batch, e1, st, d)) return false;
       hipLaunchKernelGGL(cayley_u_kernel, dim3(D / 32, D / 32, (unsigned)batch), dim3(256), 0, st, R, Zt, D, Rt, U0, scales, delta,
                          kCayleyMaxIters, kCayleyTol, second_tol);
       it = 2;
@@ -1254,7 +1272,9 @@ static kt_status cayley_run(const CayleyPlan& p, char* ws, float* R, const float
       e.it = it;
       if constexpr (sizeof(*B) == 2) e.Usplit = to;
       else e.Unew = to;
-      if (!launch_gemm<First>(from, ld, d * ld, D, B, ld, d * ld, D, K, 0, (int)batch, e, st, d)) return false;
+      if constexpr (sizeof(*B) == 2) {
+        if (!launch_gemm_few<First>(from, ld, d * ld, D, B, ld, d * ld, D, K, 0, (int)batch, e, st, d)) return false;
+      } else if (!launch_gemm<First>(from, ld, d * ld, D, B, ld, d * ld, D, K, 0, (int)batch, e, st, d)) return false;
     }
     if (own == kCayleyMaxIters) return true;
     if (late_control) hipLaunchKernelGGL(fill_u32_kernel, dim3(64), dim3(256), 0, st, control, batch * control_words, 0u);
@@ -1277,7 +1297,7 @@ static kt_status cayley_run(const CayleyPlan& p, char* ws, float* R, const float
         using TL = decltype(tile_tag);
         EpiStoreScaled<TL> e;
         e.C = C; e.exp_a = exp_a; e.exp_b = exp_b; e.max_word = max_word; e.d = D; e.shift = shift;
-        return launch_gemm<TL>(A3, 2 * d, sd, D, B3, 2 * d, sd, D, 3 * d, 0, (int)batch, e, st, d);
+        return launch_gemm_few<TL>(A3, 2 * d, sd, D, B3, 2 * d, sd, D, 3 * d, 0, (int)batch, e, st, d);
       });
     };
     if (!product(Us[0], Us[1], &scales->g, &scales->r, Mm, &scales->max_m, 0)) return fail(KT_ERR_DEVICE, "dR R^T GEMM launch failed");

@@ -688,7 +688,7 @@ __global__ __launch_bounds__(TL::NT) void cayley_iterate_kernel(GemmShape g, Epi
       for (int nb = 0; nb < TL::NB; ++nb) acc[mb][nb] = floatx4{0.f, 0.f, 0.f, 0.f};
     settle_all<TL>(acc);
     gemm_mainloop<TL, false, false, true>((k & 1 ? U1 : U0) + (int64_t)batch * g.batch_stride_a, g.lda, g.M, m0, B, g.ldb, g.N, n0, 0,
-                                          g.slabs_total, g.slabs_per_block, 0, acc, lds, 0);
+                                          g.slabs_total, g.slabs_per_block, 0, acc, lds, 0, 0);
     settle_all<TL>(acc);
     EpiCayleyIter<TL> e = epi;
     e.it = k;

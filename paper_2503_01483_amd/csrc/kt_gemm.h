@@ -343,7 +343,8 @@ __device__ __forceinline__ void gemm_mainloop(const typename TL::T* __restrict__
                                               int N, int n0, int slab0, int k_slabs,
                                               int slabs_per_block,
                                               int64_t block_bytes_b,
-                                              floatx4 (&acc)[TL::MB][TL::NB], char* lds, int k_valid
+                                              floatx4 (&acc)[TL::MB][TL::NB], char* lds, int k_valid,
+                                              int first_thread
                                               KT_STAMP_PARAM) {
   using T = typename TL::T;
   constexpr bool F32 = sizeof(T) == 4, F16 = std::is_same_v<T, _Float16>;
@@ -364,7 +365,7 @@ __device__ __forceinline__ void gemm_mainloop(const typename TL::T* __restrict__
   static_assert(A_GAP >= 1 && B_GAP >= 1 && load_slot(NLD - 1) - 2 * SLOTS < SLOTS + BAR - 3 && BAR + NB * SPACE1 <= SLOTS && BAR >= 2,
                 "not enough MFMA slots to hide the memory instructions");
 
-  const int tid = thread_id<AGAIN>();
+  const int tid = thread_id<AGAIN>() - first_thread;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
 
   // global addressing: uniform 64-bit base + 32-bit byte offsets.  Load i of a thread fills 16 bytes at
@@ -414,9 +415,10 @@ __device__ __forceinline__ void gemm_mainloop(const typename TL::T* __restrict__
   // the last one: the last one again.
   int req_a = slab0, req_b = slab0, in_block_b = slab0 % slabs_per_block;
   const int last_slab = slab0 + k_slabs - 1;
+  const int from_a = F16 && slab0 >= slabs_per_block ? slab0 - slabs_per_block : slab0, from_b = F16 && slab0 >= 2 * slabs_per_block ? slab0 - 2 * slabs_per_block : slab0;
   const char* an = Ab + (ATN ? (int64_t)slab0 * TL::BK * lda * (int64_t)sizeof(T)
-                             : (int64_t)slab0 * kRowBytes);
-  const char* bn = Bb + (BTN ? (int64_t)slab0 * TL::BK * ldb * (int64_t)sizeof(T)
+                             : (int64_t)from_a * kRowBytes);
+  const char* bn = Bb + (BTN ? (int64_t)slab0 * TL::BK * ldb * (int64_t)sizeof(T) : F16 ? (int64_t)from_b * kRowBytes
                              : (slab0 / slabs_per_block) * block_bytes_b + (int64_t)in_block_b * kRowBytes);
   const int64_t b_wrap = block_bytes_b - (int64_t)(slabs_per_block - 1) * kRowBytes;
   sgprx4 rsrc_a, rsrc_b;
@@ -657,7 +659,7 @@ __global__ __launch_bounds__(TL::NT) void gemm_nt_kernel(GemmShape g, Epi epi) {
   const T* A = static_cast<const T*>(g.A) + (int64_t)batch * g.batch_stride_a;
   const T* B = static_cast<const T*>(g.B) + (int64_t)batch * g.batch_stride_b;
   gemm_mainloop<TL, ATN, BTN, Epi::kSwap>(A, g.lda, g.M, m0, B, g.ldb, g.N, n0, slab0, slabs, g.slabs_per_block,
-                         g.block_bytes_b, acc, lds, g.k_valid KT_STAMP_ARG);
+                         g.block_bytes_b, acc, lds, g.k_valid, 0 KT_STAMP_ARG);
   settle_all<TL>(acc);
   KT_STAMP(g, 2);
   epi(acc, batch, tm, tn, ks, m0, n0);
@@ -670,6 +672,45 @@ __global__ __launch_bounds__(TL::NT) void gemm_nt_kernel(GemmShape g, Epi epi) {
       g_phase_stamps[((size_t)g.stamp_slot * kStampWgs + wg) * kStampWords + 6] = __builtin_amdgcn_s_getreg((4 << 0) | (0 << 6) | (31 << 11));
   }
 #endif
+}
+
+// The same with K halved between two groups of four waves, each with LDS stages of its own, whose sums meet in the LDS; the first group has the epilogue.
+// For tiles that leave a CU to one or two workgroups: the chain of a slab (barrier, fragments, matrix instructions) is longer than what it
+// keeps busy, and two of them side by side fill it.  An even number of slabs, so that both groups meet at the same barriers.
+template <class TL, class Epi>
+__global__ __launch_bounds__(2 * TL::NT) void gemm_two_kernel(GemmShape g, Epi epi) {
+  extern __shared__ __align__(16) char lds[];
+  using T = typename TL::T;
+  const int batch = blockIdx.y, group = __builtin_amdgcn_readfirstlane(threadIdx.x / TL::NT);
+  int tm, tn, ks;
+  if (!tile_of_block(g, tm, tn, ks)) return;
+  if (epi.skip(batch)) return;
+  const int m0 = tm * TL::BM, n0 = tn * TL::BN, slabs = g.slabs_total / 2;
+  floatx4 acc[TL::MB][TL::NB];
+#pragma unroll
+  for (int mb = 0; mb < TL::MB; ++mb)
+#pragma unroll
+    for (int nb = 0; nb < TL::NB; ++nb) acc[mb][nb] = floatx4{0.f, 0.f, 0.f, 0.f};
+  settle_all<TL>(acc);
+  gemm_mainloop<TL, false, false, Epi::kSwap>(static_cast<const T*>(g.A) + (int64_t)batch * g.batch_stride_a, g.lda, g.M, m0,
+                                              static_cast<const T*>(g.B) + (int64_t)batch * g.batch_stride_b, g.ldb, g.N, n0, group * slabs, slabs,
+                                              g.slabs_per_block, g.block_bytes_b, acc, lds + group * TL::LDS_BYTES, 0, group * TL::NT);
+  settle_all<TL>(acc);
+  __syncthreads();
+  floatx4* other = reinterpret_cast<floatx4*>(lds) + threadIdx.x % TL::NT;
+  if (group == 1) {
+#pragma unroll
+    for (int mb = 0; mb < TL::MB; ++mb)
+#pragma unroll
+      for (int nb = 0; nb < TL::NB; ++nb) other[(mb * TL::NB + nb) * TL::NT] = acc[mb][nb];
+  }
+  __syncthreads();
+  if (group == 1) return;  // (barriers count the waves that are left)
+#pragma unroll
+  for (int mb = 0; mb < TL::MB; ++mb)
+#pragma unroll
+    for (int nb = 0; nb < TL::NB; ++nb) acc[mb][nb] += other[(mb * TL::NB + nb) * TL::NT];
+  epi(acc, batch, tm, tn, 0, m0, n0);
 }
 
 }  // namespace kt

@@ -166,7 +166,7 @@ __global__ __launch_bounds__(TL::NT, (160 * 1024 / TL::LDS_BYTES)) void row_sync
       const GemmShape& g = args().g;
       gemm_mainloop<TL, false, false, false, true>(static_cast<const T*>(g.A) + (int64_t)batch * g.batch_stride_a, g.lda, g.M, m0,
                                              static_cast<const T*>(g.B) + (int64_t)batch * g.batch_stride_b, g.ldb, g.N, n0, 0, g.slabs_total,
-                                             g.slabs_per_block, 0, acc, lds, 0);
+                                             g.slabs_per_block, 0, acc, lds, 0, 0);
     }
     settle_all<TL>(acc);
     if (!again) {

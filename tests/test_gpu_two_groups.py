@@ -1,0 +1,45 @@
+"""16-bit products of few tiles and many slabs of K, whose K is halved between two groups of waves: both tiles, ragged rows, odd halves that begin
+inside a term of the three-term products (d = 1152: 27 slabs of 54), one and several problems.  Against 64 bits on the device."""
+import pytest
+import torch
+
+import paper_2503_01483_amd as kt
+
+pytestmark = pytest.mark.gpu
+
+
+# 64 x 64 and 128 x 128 tiles, the last ones of either rule and the first beyond (d = 1408 has 22 slabs, 1280 has 20)
+@pytest.mark.parametrize("batch,n,d", [(1, 65, 1408), (1, 700, 1408), (2, 129, 1408), (1, 300, 1280), (1, 1500, 2048), (1, 2049, 2048), (1, 1001, 2688)])
+def test_rotated_rows(batch, n, d):
+    g = torch.Generator(device="cuda").manual_seed(d + n)
+    X = torch.randn((batch, n, d + 8), generator=g, device="cuda").bfloat16()[:, :, :d]
+    R = torch.linalg.qr(torch.randn((batch, d, d), generator=g, device="cuda"))[0].contiguous()
+    Y = torch.full((batch, n, d), float("nan"), device="cuda")
+    kt.kt_rotate_quant_metrics(X, R, Y=Y)
+    want = X.double() @ R.bfloat16().double().contiguous()
+    # fp32 sums of d products of entries of order one and 1 / sqrt(d)
+    assert (Y.double() - want).abs().max() <= 2e-6 * d ** 0.5 / 10
+
+
+@pytest.mark.parametrize("batch,d", [(1, 1024), (1, 1152), (2, 1152), (1, 1408), (1, 1664), (1, 2048)])
+def test_retraction(batch, d):
+    g = torch.Generator(device="cuda").manual_seed(d)
+    R = torch.linalg.qr(torch.randn((batch, d, d), generator=g, device="cuda", dtype=torch.float64))[0].float().contiguous()
+    G = torch.randn((batch, d, d), generator=g, device="cuda")
+    M, v = torch.randn((batch, d, d), generator=g, device="cuda"), torch.ones(batch, device="cuda")
+    M0 = M.clone()
+    new, info = R.clone(), torch.zeros(batch, dtype=torch.int32, device="cuda")
+    scal = torch.empty((batch, 3), device="cuda")
+    kt.kt_cayley_adam_step(new, G, M, v, 3, 0.3, info=info, scalars=scal)
+    assert (info >= 1).all()
+    for b in range(batch):
+        m = 0.9 * M0[b].double() + 0.1 * G[b].double()
+        K = m @ R[b].double().T.contiguous()
+        S = 0.5 * (K - K.T)
+        r, alpha = scal[b, 0].double(), scal[b, 1].double()
+        a = alpha / (2 * r) * S
+        want = torch.linalg.solve(torch.eye(d, device="cuda", dtype=torch.float64) + a, R[b].double() - a @ R[b].double())
+        # an accepted iterate is within 3e-7 of the limit entry by entry (a matrix norm of up to 3e-7 d), R is rounded to fp32
+        assert (new[b].double() - want).abs().max() <= 3e-7 + 2.0 ** -24 * want.abs().max()
+        ex = S @ R[b].double()
+        assert (M[b].double() - ex).norm() <= 2e-6 * ex.norm()
