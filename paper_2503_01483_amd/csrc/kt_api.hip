@@ -1210,6 +1210,7 @@ struct AdamArgs {
   float* scal;         // [batch][4] device scalars {r, alpha, ||W||, alpha/(2r)}
   double* sq_part;     // [batch][(d/32)^2] tile partials of ||S||^2
   float* scalars_out;  // [batch][3] {r, alpha, ||W||} for the caller, or null
+  AdamScalars first;   // fp16 operands: taken with them (split3_kernel), and their maxima are there (adam_moment_kernel)
 };
 
 // Shared by the two optimisers.  P = G R^T, S = half_coef (P - P^T), then the Cayley transform
@@ -1234,7 +1235,7 @@ static kt_status cayley_run(const CayleyPlan& p, char* ws, float* R, const float
                                         : (small ? cayley_control_words<TF_64>(d) : cayley_control_words<TF>(d));
   const int64_t room = (int64_t)p.g2_blocks * 8 - (p.split ? (int64_t)sizeof(SplitScales) : 0);
   const bool late_control = control_words * 4 > room;
-  SplitScales* scales = reinterpret_cast<SplitScales*>(ws + p.o_g2 + (late_control ? 0 : batch * room));
+  SplitScales* scales = reinterpret_cast<SplitScales*>(ws + p.o_g2 + batch * room);
   unsigned* control = reinterpret_cast<unsigned*>(ws + (late_control ? p.o_sq : p.o_g2));
   const int ncontrol = late_control ? 0 : (int)control_words;
   // (the changes of a second iteration that counts as the last: EpiCayleyIter)
@@ -1289,8 +1290,9 @@ static kt_status cayley_run(const CayleyPlan& p, char* ws, float* R, const float
     const unsigned sb = (unsigned)(ceil_div(dd, 1024) < 2048 ? ceil_div(dd, 1024) : 2048);
     // M = dR R^T with dR in Us[0] and R in Us[1]; the partial maxima in the room of M
     unsigned* maxima = reinterpret_cast<unsigned*>(Mm);
-    hipLaunchKernelGGL(split_max_kernel, dim3(256, 2, (unsigned)batch), dim3(256), 0, st, G, R, dd, maxima);
-    hipLaunchKernelGGL(split3_kernel, dim3(sb, 2, (unsigned)batch), dim3(256), 0, st, G, R, D, maxima, Us[0], Us[1], scales);
+    if (!adam) hipLaunchKernelGGL(split_max_kernel, dim3(256, 2, (unsigned)batch), dim3(256), 0, st, G, R, dd, maxima);
+    hipLaunchKernelGGL(split3_kernel, dim3(sb, adam ? 3 : 2, (unsigned)batch), dim3(256), 0, st, G, R, D, maxima, Us[0], Us[1], scales,
+                       adam ? adam->first : AdamScalars{});
     if (!launch_ok()) return fail(KT_ERR_DEVICE, "split launch failed");
     auto product = [&](const _Float16* A3, const _Float16* B3, const int* exp_a, const int* exp_b, float* C, unsigned* max_word, int shift) -> bool {
       return with_f16_tile(d, batch, [&](auto tile_tag) -> bool {
@@ -1739,10 +1741,17 @@ kt_status kt_cayley_adam_step(float* R, const float* dR, float* M, float* v, int
   a.scal = reinterpret_cast<float*>(ws + p.o_scal);
   a.sq_part = reinterpret_cast<double*>(ws + p.o_sq);
   double* g2_part = reinterpret_cast<double*>(ws + p.o_g2);
-  hipLaunchKernelGGL(adam_moment_kernel, dim3((unsigned)p.g2_blocks, (unsigned)batch), dim3(256), 0, st, M, dR,
-                     d * d, beta1, g2_part);
-  hipLaunchKernelGGL(adam_scalars1_kernel, dim3((unsigned)batch), dim3(256), 0, st, g2_part, p.g2_blocks, v, beta2,
-                     c1, c2, eps, a.scal);
+  // (with 256 partial sums a problem the SplitScales at the end of their room are clear of them: split3_kernel reads the ones and writes the others)
+  const int blocks = p.split ? 256 : p.g2_blocks;
+  a.first = AdamScalars{g2_part, blocks, v, beta2, c1, c2, eps, a.scal};
+  if (p.split) {
+    hipLaunchKernelGGL(adam_moment_kernel<true>, dim3((unsigned)blocks, (unsigned)batch), dim3(256), 0, st, M, dR, d * d, beta1, g2_part, R,
+                       reinterpret_cast<unsigned*>(ws + p.o_m));
+  } else {
+    hipLaunchKernelGGL(adam_moment_kernel<false>, dim3((unsigned)blocks, (unsigned)batch), dim3(256), 0, st, M, dR, d * d, beta1, g2_part,
+                       (const float*)nullptr, (unsigned*)nullptr);
+    hipLaunchKernelGGL(adam_scalars1_kernel, dim3((unsigned)batch), dim3(256), 0, st, a.first);
+  }
   if (!launch_ok()) return fail(KT_ERR_DEVICE, "Cayley Adam moment launch failed");
   // P = M1 R^T, S = (P - P^T)/2 (= r W for orthogonal R), then the transform with c = alpha/(2r)
   return cayley_run(p, ws, R, M, R_lowp, batch, d, 0.5f, &a, ortho_err, info, st);

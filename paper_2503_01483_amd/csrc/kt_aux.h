@@ -368,12 +368,39 @@ __global__ __launch_bounds__(256) void split_max_kernel(const float* __restrict_
   if (threadIdx.x == 0) part[((int64_t)blockIdx.z * 2 + blockIdx.y) * 256 + blockIdx.x] = umax(umax(sh[0], sh[1]), umax(sh[2], sh[3]));
 }
 
+// v <- beta2 v + (1 - beta2) ||G||_F^2;  scal[4b] = r = c1 sqrt(v / c2 + eps) with the bias
+// corrections c1 = 1 - beta1^k, c2 = 1 - beta2^k taken by the host in double.  One workgroup, problem b.
+struct AdamScalars {
+  const double* g2_part = nullptr;  // [batch][nblk]
+  int nblk = 0;
+  float* v = nullptr;
+  float beta2 = 0.f;
+  double c1 = 0.0, c2 = 0.0;
+  float eps = 0.f;
+  float* scal = nullptr;
+  __device__ __forceinline__ void run(int b) const {
+    __shared__ double sh[256];
+    double s = 0.0;
+    for (int i = threadIdx.x; i < nblk; i += 256) s += g2_part[(int64_t)b * nblk + i];
+    const double g2 = block_sum_256(s, sh);
+    if (threadIdx.x == 0) {
+      const double v1 = (double)beta2 * (double)v[b] + (1.0 - (double)beta2) * g2;
+      v[b] = (float)v1;
+      scal[4 * b] = (float)(c1 * sqrt(v1 / c2 + (double)eps));
+    }
+  }
+};
+
 // G as the left operand (blockIdx.y = 0), R as the right one (1); the problem's scales.  U = R^T + Z^T: the entries of a
 // row are at most its norm, sqrt(d) max |R| <= 2^7 max |R|, and transients of a contracting iteration at most three times that, so
-// 2^7 above max |R| leaves it below 2^16.  grid = (any, 2, problems)
+// 2^7 above max |R| leaves it below 2^16.  grid = (any, 2, problems), with Cayley Adam (any, 3, problems): its scalars ride along.
 __global__ __launch_bounds__(256) void split3_kernel(const float* __restrict__ G, const float* __restrict__ R, int d,
                                                      const unsigned* __restrict__ part, _Float16* __restrict__ left,
-                                                     _Float16* __restrict__ right, SplitScales* __restrict__ scales) {
+                                                     _Float16* __restrict__ right, SplitScales* __restrict__ scales, AdamScalars adam) {
+  if (blockIdx.y == 2) {
+    if (blockIdx.x == 0) adam.run(blockIdx.z);
+    return;
+  }
   typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
   __shared__ unsigned sh[4];
   const int64_t dd = (int64_t)d * d, bo = (int64_t)blockIdx.z * dd;
@@ -485,11 +512,15 @@ __global__ __launch_bounds__(256) void cayley_setup_kernel(const float* __restri
 
 // ---- Cayley Adam: moments and step scalars (the optimiser the paper names; the update rule is
 // that of the cited work on Stiefel-manifold optimisation) --------------------------------------
-// M <- beta1 M + (1 - beta1) G in place; g2_part[batch][gridDim.x] = block partial sums of G^2.
+// M <- beta1 M + (1 - beta1) G in place; g2_part[batch][gridDim.x] = block partial sums of G^2.  MAXIMA: what split_max_kernel gives for M and R
+// as well (256 workgroups a problem), which is then no launch of its own.
+template <bool MAXIMA>
 __global__ __launch_bounds__(256) void adam_moment_kernel(float* __restrict__ M, const float* __restrict__ G,
                                                           int64_t dd, float beta1,
-                                                          double* __restrict__ g2_part) {
+                                                          double* __restrict__ g2_part, const float* __restrict__ R, unsigned* __restrict__ maxima) {
   __shared__ double sh[256];
+  __shared__ unsigned most[2][4];
+  unsigned mm = 0u, mr = 0u;
   const int64_t bo = (int64_t)blockIdx.y * dd;
   double s = 0.0;
   for (int64_t q = (int64_t)blockIdx.x * 256 + threadIdx.x; q < dd / 4; q += (int64_t)gridDim.x * 256) {
@@ -499,28 +530,34 @@ __global__ __launch_bounds__(256) void adam_moment_kernel(float* __restrict__ M,
     for (int e = 0; e < 4; ++e) {
       m[e] = beta1 * m[e] + (1.f - beta1) * g[e];
       s += (double)g[e] * (double)g[e];
+      if (MAXIMA) mm = umax(mm, abs_bits(m[e]));
     }
     *reinterpret_cast<floatx4*>(M + bo + 4 * q) = m;
+    if (MAXIMA) {
+      const floatx4 r = *reinterpret_cast<const floatx4*>(R + bo + 4 * q);
+#pragma unroll
+      for (int e = 0; e < 4; ++e) mr = umax(mr, abs_bits(r[e]));
+    }
+  }
+  if (MAXIMA) {
+    mm = wave_umax(mm);
+    mr = wave_umax(mr);
+    if ((threadIdx.x & 63) == 0) {
+      most[0][threadIdx.x >> 6] = mm;
+      most[1][threadIdx.x >> 6] = mr;
+    }
+    __syncthreads();
+    if (threadIdx.x < 2) {
+      const unsigned* w = most[threadIdx.x];
+      maxima[((int64_t)blockIdx.y * 2 + threadIdx.x) * 256 + blockIdx.x] = umax(umax(w[0], w[1]), umax(w[2], w[3]));
+    }
   }
   const double tot = block_sum_256(s, sh);
   if (threadIdx.x == 0) g2_part[(int64_t)blockIdx.y * gridDim.x + blockIdx.x] = tot;
 }
 
-// v <- beta2 v + (1 - beta2) ||G||_F^2;  scal[4b] = r = c1 sqrt(v / c2 + eps) with the bias
-// corrections c1 = 1 - beta1^k, c2 = 1 - beta2^k taken by the host in double.  grid = batch.
-__global__ __launch_bounds__(256) void adam_scalars1_kernel(const double* __restrict__ g2_part, int nblk,
-                                                            float* __restrict__ v, float beta2, double c1,
-                                                            double c2, float eps, float* __restrict__ scal) {
-  __shared__ double sh[256];
-  double s = 0.0;
-  for (int i = threadIdx.x; i < nblk; i += 256) s += g2_part[(int64_t)blockIdx.x * nblk + i];
-  const double g2 = block_sum_256(s, sh);
-  if (threadIdx.x == 0) {
-    const double v1 = (double)beta2 * (double)v[blockIdx.x] + (1.0 - (double)beta2) * g2;
-    v[blockIdx.x] = (float)v1;
-    scal[4 * blockIdx.x] = (float)(c1 * sqrt(v1 / c2 + (double)eps));
-  }
-}
+// Scalars of the step (AdamScalars), a workgroup per problem.  grid = batch.
+__global__ __launch_bounds__(256) void adam_scalars1_kernel(AdamScalars a) { a.run(blockIdx.x); }
 
 // From the tile partials of ||S||_F^2 (S = (P - P^T)/2, W = S / r):
 // scal[4b+1] = alpha = min(lr, 2 q / (||W|| + eps)), [4b+2] = ||W||_F, [4b+3] = alpha / (2 r), the factor of S
