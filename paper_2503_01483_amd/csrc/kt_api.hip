@@ -1039,7 +1039,8 @@ static kt_status run_loss_grad_f32(const LossGradPlan& p, const float* X, int64_
 }
 
 // ------------------------------------------------------------------ fake-quant ----
-// Workgroups per problem for quant_d128_kernel.  A wave loads all of R^T (32 KiB) before its first tile.
+// Workgroups per problem for quant_d128_kernel.  A workgroup stages all of R before its first tile (the figures are with the copy of R^T that a launch of
+// its own wrote, about 5 us more each).
 //  - While one workgroup per CU holds them: one 16-token tile per wave.  us, one tile / two per wave: 1 problem of 4096 tokens
 //    12.1 / 12.9, of 16384 12.1 / 13.2; two workgroups on a CU with one tile each: 32768 tokens 15.7 against 13.5.
 //  - Beyond: two tiles or more per wave, and as many workgroups as finish first when they start in rounds of 512 (two per
@@ -1776,10 +1777,8 @@ kt_status kt_rotate_fakequant_int4(const void* X, int64_t ldx, const void* R, in
   hipStream_t st = static_cast<hipStream_t>(stream);
   ProfScope prof(5, st);
   if (!p.fp32 && d == 128) {  // one pass over X (kt_fused_d128.h)
-    bf16* RT = reinterpret_cast<bf16*>(ws + p.o_rt);
-    if (!prep_rt<bf16>(R, ldr, r_dtype, RT, batch, d, st)) return fail(KT_ERR_DEVICE, "prep_rt launch failed");
     hipLaunchKernelGGL(quant_d128_kernel, dim3((unsigned)quant_d128_wgs(batch, n), (unsigned)batch), dim3(256), 0, st,
-                       static_cast<const bf16*>(X), ldx, n * ldx, RT, (int)n, clip_ratio, scales_in, scales_out, codes,
+                       static_cast<const bf16*>(X), ldx, n * ldx, R, ldr, r_dtype == KT_BF16 ? 1 : 0, (int)n, clip_ratio, scales_in, scales_out, codes,
                        reinterpret_cast<float2*>(err));
     if (!launch_ok()) return fail(KT_ERR_DEVICE, "d=128 fake-quant launch failed");
     return KT_OK;

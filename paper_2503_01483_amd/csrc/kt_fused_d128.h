@@ -343,7 +343,8 @@ __global__ __launch_bounds__(512) void fused_d128_kernel(const __bf16* __restric
 // The four lanes l, l + 16, l + 32, l + 48 hold a whole rotated token row, so the row maximum, the scale, the codes and the
 // error sums all come out of ONE pass over X (the generic path parks the rotated rows in an fp32
 // staging buffer between the GEMM and a row kernel).
-// Every wave is on its own: 16-token tiles, its rows staged through 4 KiB of private LDS (loads of
+// R is staged in the kernel (stage_rotation; a launch that wrote R^T first was 5 of 101 us of 256 problems and 3 of 11 of a small call).  From there
+// every wave is on its own: 16-token tiles, its rows staged through 4 KiB of private LDS (loads of
 // the next tile in flight), R^T fragments in accumulation registers, no workgroup barrier.
 // 16 x 16 blocks (one token, 32 features per lane) keep a wave under 256 registers, so that two share a SIMD: one wave's
 // loads, matrix instructions and quantiser arithmetic hide behind the other's.  256 problems x 4096 tokens: one wave per
@@ -351,25 +352,19 @@ __global__ __launch_bounds__(512) void fused_d128_kernel(const __bf16* __restric
 // Arithmetic identical to the generic path: s = (clip amax) / 7, q = clamp(rint(y (1/s)), -7, 7).
 // grid = (waves / 4, batch).
 __global__ __launch_bounds__(256, 2) void quant_d128_kernel(const __bf16* __restrict__ X, int64_t ldx,
-                                                         int64_t x_batch_stride, const __bf16* __restrict__ RT,
+                                                         int64_t x_batch_stride, const void* __restrict__ R, int64_t ldr, int r_bf16,
                                                          int n, float clip, const float* __restrict__ scales_in,
                                                          float* __restrict__ scales_out, int8_t* __restrict__ codes,
                                                          float2* __restrict__ err) {
-  __shared__ __align__(16) char lds_all[4 * 16 * 256];
+  __shared__ __align__(16) char lds_all[128 * 256];  // R first, then 4 KiB a wave
   constexpr int D = 128;
   const int b = blockIdx.y, lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int q = lane >> 4, l16 = lane & 15;
   char* lds = lds_all + wave * (16 * 256);
   X += (int64_t)b * x_batch_stride;
-  RT += (int64_t)b * D * D;
+  R = static_cast<const char*>(R) + (int64_t)b * D * ldr * (r_bf16 ? 2 : 4);
   const int tiles = (n + 15) / 16;
   const int wave_id = blockIdx.x * 4 + wave, stride = gridDim.x * 4;
-
-  intx4 rtf[4][8];  // K step, block of 16 features
-#pragma unroll
-  for (int s = 0; s < 4; ++s)
-#pragma unroll
-    for (int mb = 0; mb < 8; ++mb) rtf[s][mb] = *reinterpret_cast<const intx4*>(RT + (mb * 16 + l16) * D + 32 * s + 8 * q);
 
   // chunk i of a lane: tile row q + 4 i, 16-byte column l16
   intx4 nxt[4];
@@ -383,11 +378,23 @@ __global__ __launch_bounds__(256, 2) void quant_d128_kernel(const __bf16* __rest
     }
   };
   request(wave_id);
-  // into accumulation registers, behind all of the requests (a pin behind each one waits for it: 32 times the latency of the L2)
+  // R^T fragments (K step, block of 16 features) from R, rounded and staged by the workgroup, into accumulation registers
+  stage_rotation<256>(R, ldr, r_bf16, lds_all);
+  lds_barrier();
+  intx4 rtf[4][8];
+  const int tr_row = 8 * q + (l16 >> 2), ra = tr_row * 256 + ((((l16 & 3) >> 1) ^ f128_xkey(tr_row)) << 4) + ((l16 & 1) << 3);
+#pragma unroll
+  for (int s = 0; s < 4; ++s)
+#pragma unroll
+    for (int mb = 0; mb < 8; ++mb) {
+      const int at = ra ^ (mb * 32);
+      rtf[s][mb] = read_tr_operand(lds_all, at + s * 32 * 256, (at ^ (4 * 256 + 16)) + s * 32 * 256);
+    }
 #pragma unroll
   for (int s = 0; s < 4; ++s)
 #pragma unroll
     for (int mb = 0; mb < 8; ++mb) asm volatile("" : "+a"(rtf[s][mb]));
+  lds_barrier();  // everybody has its fragments: the room is the waves' own
   for (int tile = wave_id; tile < tiles; tile += stride) {
     asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");  // the previous tile's fragment reads are done
 #pragma unroll
