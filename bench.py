@@ -2,9 +2,9 @@
 """Benchmark of the KurTail rotation-learning step on one MI355X.
 
 A "step" is one pass of the whole hot path over one batch of synthetic calibration
-activations resident in HBM: kt_kurtosis_loss_grad (forward GEMM + row moments, which also keeps
-Y in fp32 scratch; row finalisation; dL/dY from the kept Y; X^T G GEMM) followed by kt_cayley_step.
-With --recompute the library gets its smaller workspace and recomputes Y with a second GEMM instead.
+activations resident in HBM: kt_kurtosis_loss_grad (forward GEMM whose tiles exchange the row moments and write
+dL/dY; X^T G GEMM; with --loss pooled Y is kept in fp32 scratch and dL/dY computed from it) followed by kt_cayley_step.
+With --recompute the library gets its smaller workspace: the pooled loss then recomputes Y with a second GEMM instead.
 Prints ONE JSON line: tokens/s for the whole step, the roofline figures of the dominant
 kernel measured with HIP events inside the timed region, and the fp64 CPU oracle timed on
 a bounded sample of the same workload.

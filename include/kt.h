@@ -98,8 +98,11 @@ size_t kt_workspace_bytes(kt_op op, int64_t batch, int64_t n, int64_t d, kt_dtyp
  *   dL/dy_ij = s_i 4/(n d m2_i^2) [c_ij^3 - m3_i - kappa_i m2_i c_ij],  s_i = f'(kappa_i)
  *   dR = X^T (dL/dY)
  *
- * Y is consumed in the forward GEMM's epilogue (row moments).  For the backward pass it is either
- * KEPT by that epilogue (fp32, token-minor, 4 n d bytes of workspace per problem) and dL/dY computed
+ * Y is consumed in the forward GEMM's epilogue.  bf16, with dR: the tiles of a token row exchange the row's moments inside
+ * that launch and write dL/dY themselves, with either size of workspace.  (The launch makes progress with any number of
+ * compute units to itself; with fewer than a part of a row's tiles, as on a stream of eight units, it waits in vain
+ * once and makes tiles a second time.)  Outside of that (a few tokens, d > 8192 with some sizes), and for the pooled loss,
+ * Y is for the backward pass either KEPT by that epilogue (fp32, token-minor, 4 n d bytes of workspace per problem) and dL/dY computed
  * from it entry by entry, or RECOMPUTED by a second GEMM whose epilogue forms dL/dY: the first when
  * the workspace handed in has the room (kt_workspace_bytes(KT_OP_LOSS_GRAD) asks for it while Y is at
  * most 64 GiB), the second otherwise (KT_OP_LOSS_GRAD_RECOMPUTE is the smaller size).  Both give the
@@ -246,9 +249,9 @@ kt_status kt_cayley_adam_step(float* R, const float* dR, float* M, float* v, int
  *  err        [batch][n][2] fp32 or NULL.
  *  A row with scale 0 gets codes 0.
  *  Workspace: kt_workspace_bytes(KT_OP_FAKEQUANT, ...).  It holds an fp32 staging buffer of at most
- *  1 GiB: when the scales are computed here, y is rotated once, a slice of token rows at a time,
- *  and a row kernel takes the maximum and quantises the staged values (one GEMM pass instead of a
- *  second one that recomputes y).  With scales_in the codes come straight out of the GEMM's registers.
+ *  1 GiB: when the scales are computed here, in fp32 and where bf16 tokens are few, y is rotated once, a slice of token
+ *  rows at a time, and a row kernel takes the maximum and quantises the staged values; else the tiles of a row exchange
+ *  its maximum inside the launch and the codes come straight out of the GEMM's registers.  With scales_in the codes come straight out of the GEMM's registers.
  *  d = 128 in bf16 is a single fused pass with no staging.
  *  Up to 64 bf16 tokens (d > 128, rows of R 16-byte aligned) y is summed in another order when the scales are computed
  *  here: the fp32 rounding of a token's y then depends on n, on batch and on R's alignment, and codes from scales_in, or of
