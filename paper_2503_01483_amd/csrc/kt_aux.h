@@ -15,8 +15,9 @@ template <typename Tin, typename Tout>
 __global__ __launch_bounds__(256) void transpose_kernel(const Tin* __restrict__ in, int64_t ldi, Tout* __restrict__ out, int d, unsigned* zero,
                                                         int zero_words) {
   __shared__ float tile[64][65];
-  const int wg = (blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x, wgs = gridDim.x * gridDim.y * gridDim.z;
-  for (int i = wg * 256 + threadIdx.x; i < zero_words; i += wgs * 256) zero[i] = 0u;
+  // (64 bits: from 2^23 workgroups on, 64 GiB of bf16 R, the threads outnumber 31)
+  const int64_t wg = ((int64_t)blockIdx.z * gridDim.y + blockIdx.y) * gridDim.x + blockIdx.x, wgs = (int64_t)gridDim.x * gridDim.y * gridDim.z;
+  for (int64_t i = wg * 256 + threadIdx.x; i < zero_words; i += wgs * 256) zero[i] = 0u;
   constexpr int VI = 16 / (int)sizeof(Tin), VO = 16 / (int)sizeof(Tout);
   typedef Tin vec_in __attribute__((ext_vector_type(VI)));
   typedef Tout vec_out __attribute__((ext_vector_type(VO)));
