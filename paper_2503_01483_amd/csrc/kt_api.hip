@@ -231,10 +231,10 @@ static bool launch_gemm(const void* A, int64_t lda, int64_t bsa, int M, const vo
   return launch_ok();
 }
 
-// An unsplit 16-bit product of 22 slabs or more (before that the second prologue and the sum cost what it gives) whose tiles leave a CU to one workgroup
-// (128 x 128) or two (64 x 64) takes gemm_two_kernel.  us, one group of waves / two: fake-quant, d = 4096: 65 tokens 49.4 / 41.9, 400 52.9 / 49.0, 1000
-// 59.9 / 57.7, 1500 (more tiles) 79.3 / 79.2; 2688: 200 31.8 / 27.2; 2048: 400 27.4 / 24.3; 1408: 400 20.4 / 18.9, 65 16.5 / 16.8; 1152, 1000 (18 slabs) 19.9 /
-// 20.5; 512, 2500 (8) 14.3 / 15.4.  Retractions of two iterations, d = 1024 79.8 / 72.2, 1152 90.8 / 86.7, 1408 112.8 / 103.6, 1664 155.6 / 144.8, 2048 196.6 / 190.1.
+// A product of a retraction of 22 slabs or more (before that the second prologue and the sum cost what it gives) whose tiles leave a CU to one workgroup
+// (128 x 128) or two (64 x 64) takes gemm_two_kernel.  Retractions of two iterations, us, one group of waves / two: d = 1024 79.8 / 72.2, 1152 90.8 / 86.7, 1408
+// 112.8 / 103.6, 1664 155.6 / 144.8, 2048 196.6 / 190.1.  Not the rotated rows of few tokens, whose y has to come in the order of a larger call's and of
+// one with given scales (kt.h), although fake-quant of 65 tokens of 4096 takes 49.4 us instead of 41.9 for it.
 template <class TL, class Epi>
 static bool launch_gemm_few(const void* A, int64_t lda, int64_t bsa, int M, const void* B, int64_t ldb, int64_t bsb, int N, int64_t K, int slabs_per_split,
                             int batch, const Epi& epi, hipStream_t stream, int64_t k_block = 0) {
@@ -924,8 +924,7 @@ static bool launch_rows_gemm(const T* X, int64_t ldx, int64_t x_batch_stride, co
       if (in_place)
         return launch_gemm<G, EpiStore<G>, false, true>(X, ldx, x_batch_stride, (int)rows, R, ldr, d * ldr, (int)d, d, 0, (int)problems, e, st);
     }
-    if constexpr (sizeof(T) == 2) return launch_gemm_few<G>(X, ldx, x_batch_stride, (int)rows, R, d, d * d, (int)d, d, 0, (int)problems, e, st);
-    else return launch_gemm<G>(X, ldx, x_batch_stride, (int)rows, R, d, d * d, (int)d, d, 0, (int)problems, e, st);
+    return launch_gemm<G>(X, ldx, x_batch_stride, (int)rows, R, d, d * d, (int)d, d, 0, (int)problems, e, st);
   };
   if constexpr (sizeof(T) == 4) {
     return with_f32_tile(rows, d, problems, go);

@@ -126,6 +126,29 @@ def test_own_scales_handed_back(batch, n, d, rdt):
         assert np.all(np.abs(np.abs(v - np.floor(v)) - 0.5)[diff != 0] <= slack[diff != 0])
 
 
+@pytest.mark.parametrize("n,more,d", [(65, 4000, 1408), (700, 3000, 1408), (129, 9000, 2048), (1500, 5000, 2048), (1001, 4100, 2688), (400, 9000, 4096), (1000, 4100, 4096)])
+def test_a_token_has_the_bits_it_has_in_a_larger_call(n, more, d):
+    """From 65 tokens on y, and with it the scale and the codes, does not depend on how many other tokens there are, nor on whose scales are
+    used: every sum over the d products has one order, whatever the tiles."""
+    g = torch.Generator(device="cuda").manual_seed(n + d)
+    X = torch.randn((1, more, d), generator=g, device="cuda").bfloat16()
+    R = torch.linalg.qr(torch.randn((1, d, d), generator=g, device="cuda"))[0].contiguous()
+
+    def rotated(m):
+        Y, scales = torch.empty((1, m, d), device="cuda"), torch.empty((1, m), device="cuda")
+        codes, given = torch.empty((1, m, d), dtype=torch.int8, device="cuda"), torch.empty((1, m, d), dtype=torch.int8, device="cuda")
+        kt.kt_rotate_quant_metrics(X[:, :m], R, Y=Y)
+        kt.kt_rotate_fakequant_int4(X[:, :m], R, scales_out=scales, codes=codes)
+        kt.kt_rotate_fakequant_int4(X[:, :m], R, scales_in=scales, codes=given)
+        return Y, scales, codes, given
+
+    few, many = rotated(n), rotated(more)
+    for a, b in zip(few, many):
+        assert torch.equal(a, b[:, :n])
+    assert torch.equal(few[2], few[3]) and torch.equal(many[2], many[3])
+    assert torch.equal(few[1], few[0].abs().amax(2) / torch.full_like(few[1], 7.0))  # (by a number torch multiplies with its reciprocal)
+
+
 @pytest.mark.parametrize("n,limit", [(16384, 4.6e-7), (8192, 3.2e-7)])
 def test_fp32_gradient_keeps_its_precision_over_many_tokens(n, limit):
     """dR = X^T G sums over the tokens in fp32, in 16 ranges whatever the tile: the relative error of dR is 3.5e-7 and 2.5e-7

@@ -1,5 +1,6 @@
-"""16-bit products of few tiles and many slabs of K, whose K is halved between two groups of waves: both tiles, ragged rows, odd halves that begin
-inside a term of the three-term products (d = 1152: 27 slabs of 54), one and several problems.  Against 64 bits on the device."""
+"""Retractions whose products have few tiles and many slabs of K, halved between two groups of waves: both tiles, odd halves that begin inside a term of
+the three-term products (d = 1152: 27 slabs of 54), one and several problems; and rotated rows of as few tiles, which are not split.  Against 64
+bits on the device."""
 import pytest
 import torch
 
