@@ -420,6 +420,8 @@ struct EpiStoreScaled : EpiBase {
 // acc = U_k * B^T.  Zt_new = Rt - acc;  U_{k+1} = Rt + Zt_new;
 // delta[it] = max |Zt_new - Zt_old| (bit pattern of a non-negative float, max is
 // order independent so the result is deterministic).
+// kHeadCut, the sign bit of a change: the fp16 head of the first iteration's D_1 was cut off (EpiCayleyIter, phase 0).  What is cut off is
+// larger than what is not, so that it goes with the largest magnitude.
 // When an iteration counts as converged.  The map is linear, Z_k+1 - Z_k = -B (Z_k - Z_k-1), so the
 // changes shrink geometrically with the spectral radius rho of B = (lr/2) A and the iterate just written
 // is within d_k rho / (1 - rho) of the fixed point (d_k = max |Z_k - Z_k-1|).  rho is estimated from the
@@ -436,6 +438,7 @@ struct EpiStoreScaled : EpiBase {
 //    the last two steps (for the three-term products the floor lies at a few 1e-7 and would never pass
 //    a fixed fp32-sized tolerance).
 // d1, d0, d00: changes of iterations k, k-1, k-2; nprev: how many of d0, d00 exist (0, 1 or 2).
+constexpr unsigned kHeadCut = 0x80000000u;
 __device__ __forceinline__ bool cayley_converged_hist(float d1, float d0, float d00, int nprev, float tol) {
   if (nprev == 0) return d1 <= tol;
   if (d1 == 0.f) return true;
@@ -446,14 +449,14 @@ __device__ __forceinline__ bool cayley_converged_hist(float d1, float d0, float 
 }
 // (the changes are read past the caches of this XCD: inside cayley_iterate_kernel others have just written them)
 __device__ __forceinline__ bool cayley_converged_now(const unsigned* dl, int k, float tol) {
-  auto at = [&](int i) { return __uint_as_float(__hip_atomic_load(dl + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)); };
+  auto at = [&](int i) { return __uint_as_float(__hip_atomic_load(dl + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & ~kHeadCut); };
   return cayley_converged_hist(at(k), k > 0 ? at(k - 1) : 0.f, k > 1 ? at(k - 2) : 0.f, k > 1 ? 2 : k, tol);
 }
-// second_tol: how large a change the second iteration may end with (EpiCayleyIter, phase 1)
+// second_tol: how large a change the second iteration may end with (EpiCayleyIter, phase 1); not with a head that was cut off.
 __device__ __forceinline__ bool cayley_converged(const unsigned* dl, int k, float tol, float second_tol) {
-  if (k == 1 && !(__uint_as_float(dl[1]) <= second_tol)) return false;
-  return cayley_converged_hist(__uint_as_float(dl[k]), k > 0 ? __uint_as_float(dl[k - 1]) : 0.f,
-                               k > 1 ? __uint_as_float(dl[k - 2]) : 0.f, k > 1 ? 2 : k, tol);
+  auto at = [&](int i) { return __uint_as_float(dl[i] & ~kHeadCut); };
+  if (k == 1 && ((dl[0] & kHeadCut) != 0u || !(at(1) <= second_tol))) return false;
+  return cayley_converged_hist(at(k), k > 0 ? at(k - 1) : 0.f, k > 1 ? at(k - 2) : 0.f, k > 1 ? 2 : k, tol);
 }
 
 // fp32: Zt and Unew as above.  As the epilogue of a launch of its own it returns at once when iteration
@@ -494,9 +497,11 @@ struct EpiCayleyIter {
                                              int, int, int m0, int n0) const {
     apply<false>(acc, batch, m0, n0);
   }
-  // The exponent of the head of D_1 = bs D', bs = f 2^eb: |D'| <= 2 sqrt(d) max |B|, the rows of R being of norm one, so that 2^(kb - half)
-  // leaves it below 2^15, half = log2(d) / 2 rounded up.  (Rows that are longer by more than that are cut off at the largest fp16 value.)
-  static __device__ __forceinline__ int head_exponent(int kb, int eb, int d) { return kb - eb - (33 - __clz(d - 1)) / 2; }
+  // The exponent of the head of D_1 = bs D', bs = f 2^eb: |D'| <= 2 sqrt(d) max |B|, the rows of R being of norm one, and 2^kb |B| < 2^15, so that
+  // 2^(kb - half - 1) leaves it below 2^15, half = log2(d) / 2 rounded up.  Rows longer than two can be cut off at the largest fp16 value: the
+  // change that follows from the head is too small then, and no second iteration counts as the last (kHeadCut; accepted by its own size, a step of
+  // rows of norm 100 and a B of rank two along them ended 4e-6 of its norm off).
+  static __device__ __forceinline__ int head_exponent(int kb, int eb, int d) { return kb - eb - (33 - __clz(d - 1)) / 2 - 1; }
   template <bool PAST_L2>
   __device__ __forceinline__ void apply(floatx4 (&acc)[TL::MB][TL::NB], int batch, int m0, int n0) const {
     typedef _Float16 f16x4 __attribute__((ext_vector_type(4)));
@@ -571,6 +576,7 @@ struct EpiCayleyIter {
           }
         }
       }
+    if (kF16 && PHASE == 0 && !(ldexpf(__uint_as_float(dmax), kd) <= 65504.f)) dmax |= kHeadCut;
     workgroup_umax(dmax, &delta[(int64_t)batch * max_iters + it]);
   }
 };

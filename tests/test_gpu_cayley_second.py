@@ -53,3 +53,25 @@ def test_rows_longer_than_one():
     kt.kt_cayley_step(new, G, lr, info=info)
     assert info.item() >= 1
     assert (new.double() - _exact(R, G, lr)).norm() <= 4e-6 * 1024 ** 0.5
+
+
+@pytest.mark.parametrize("norm", [2.0, 128.0])
+def test_rows_far_longer_than_one(norm):
+    """A B of rank two along a column of R times a Hadamard matrix: every product of D_1 = -2 R B^T has the same sign, so that its head meets its
+    bound, and with rows of norm 128 is cut off.  The change of the second iteration is small enough to end with, were it not for that."""
+    d, half = 1024, 2.0 ** -15
+    H = torch.ones((1, 1), device="cuda", dtype=torch.float64)
+    while len(H) < d:
+        H = torch.cat([torch.cat([H, H], 1), torch.cat([H, -H], 1)], 0)
+    R = (H * (norm / d ** 0.5)).float().contiguous()
+    # G R^T = e_1 1^T: B has 2^-15 in its first row and column.  Powers of two everywhere: the products and their sums are exact
+    K = torch.zeros((d, d), device="cuda", dtype=torch.float64)
+    K[0] = 1.0
+    G = (K @ R.double() / norm ** 2).float().contiguous()
+    new, info = R.clone(), torch.zeros(1, dtype=torch.int32, device="cuda")
+    kt.kt_cayley_step(new, G, 2 * half, info=info)
+    assert info.item() >= 2
+    want = _exact(R, G, 2 * half)
+    # accepted within 3e-7 of the limit, R rounded to fp32 once, 22 bits of U
+    off = (new.double() - want).abs().max().item()
+    assert off <= 3e-7 + 2.0 ** -24 * want.abs().max() + 2.0 ** -21 * (want - R.double()).abs().max(), off
