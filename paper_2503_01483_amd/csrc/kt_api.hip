@@ -1238,8 +1238,8 @@ static kt_status cayley_run(const CayleyPlan& p, char* ws, float* R, const float
   SplitScales* scales = reinterpret_cast<SplitScales*>(ws + p.o_g2 + batch * room);
   unsigned* control = reinterpret_cast<unsigned*>(ws + (late_control ? p.o_sq : p.o_g2));
   const int ncontrol = late_control ? 0 : (int)control_words;
-  // (the changes of a second iteration that counts as the last: EpiCayleyIter)
-  const float second_tol = p.split ? 5e-4f / sqrtf((float)d) : INFINITY;
+  // (fp16: the changes of a second iteration that counts as the last, EpiCayleyIter)
+  const float second_tol = 5e-4f / sqrtf((float)d);
   // B and U: rows of ld values
   auto iterations = [&](auto first_tag, auto tile_tag, auto* U0, auto* U1, const auto* B, int64_t K, int64_t ld) -> bool {
     auto epilogue = [&](auto tag, auto phase_c) {

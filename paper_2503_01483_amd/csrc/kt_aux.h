@@ -592,7 +592,7 @@ __global__ __launch_bounds__(256) void cayley_u_kernel(const float* __restrict__
                                                        _Float16* __restrict__ Us, const SplitScales* __restrict__ scales,
                                                        const unsigned* __restrict__ delta, int max_iters, float tol, float second_tol) {
   __shared__ float tr[32][33];
-  if (cayley_converged(delta + (int64_t)blockIdx.z * max_iters, 1, tol, second_tol)) return;
+  if (cayley_converged<true>(delta + (int64_t)blockIdx.z * max_iters, 1, tol, second_tol)) return;
   const int64_t bo = (int64_t)blockIdx.z * d * d;
   const int i0 = blockIdx.x * 32, j0 = blockIdx.y * 32, tx = threadIdx.x & 31, ty = threadIdx.x >> 5, ku = scales[blockIdx.z].u;
 #pragma unroll
@@ -626,7 +626,7 @@ __global__ __launch_bounds__(256) void cayley_finish_kernel(float* __restrict__ 
   const int tx = threadIdx.x & 31, ty = threadIdx.x >> 5;
   int used = -1;  // the same scan in every thread: at most max_iters words, all cache hits
   for (int k = 0; k < max_iters; ++k) {
-    if (cayley_converged(delta + (int64_t)blockIdx.z * max_iters, k, tol, second_tol)) { used = k + 1; break; }
+    if (cayley_converged<MOVED>(delta + (int64_t)blockIdx.z * max_iters, k, tol, second_tol)) { used = k + 1; break; }
   }
   if (!MOVED) whole = 0;
   if (used > 0 || whole) {

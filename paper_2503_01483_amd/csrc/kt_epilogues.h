@@ -447,15 +447,20 @@ __device__ __forceinline__ bool cayley_converged_hist(float d1, float d0, float 
   if (nprev < 2 || !(d1 <= 64.f * tol)) return false;
   return d1 >= 0.9f * d0 && d1 >= 0.8f * d00;
 }
-// (the changes are read past the caches of this XCD: inside cayley_iterate_kernel others have just written them)
+// The changes of a problem as bits.  F16: the first may carry kHeadCut, and the second iteration ends a step only with a change of at most second_tol
+// that follows from a whole head (EpiCayleyIter, phase 1).  fp32 has neither: the two tests cost its steps 0.4 %, in every launch.
+template <bool F16>
+__device__ __forceinline__ float cayley_change(unsigned bits) { return __uint_as_float(F16 ? bits & ~kHeadCut : bits); }
+// (the changes are read past the caches of this XCD: inside cayley_iterate_kernel others have just written them; not asked for k < 2 with F16)
+template <bool F16>
 __device__ __forceinline__ bool cayley_converged_now(const unsigned* dl, int k, float tol) {
-  auto at = [&](int i) { return __uint_as_float(__hip_atomic_load(dl + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) & ~kHeadCut); };
+  auto at = [&](int i) { return cayley_change<F16>(__hip_atomic_load(dl + i, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT)); };
   return cayley_converged_hist(at(k), k > 0 ? at(k - 1) : 0.f, k > 1 ? at(k - 2) : 0.f, k > 1 ? 2 : k, tol);
 }
-// second_tol: how large a change the second iteration may end with (EpiCayleyIter, phase 1); not with a head that was cut off.
+template <bool F16>
 __device__ __forceinline__ bool cayley_converged(const unsigned* dl, int k, float tol, float second_tol) {
-  auto at = [&](int i) { return __uint_as_float(dl[i] & ~kHeadCut); };
-  if (k == 1 && ((dl[0] & kHeadCut) != 0u || !(at(1) <= second_tol))) return false;
+  auto at = [&](int i) { return cayley_change<F16>(dl[i]); };
+  if (F16 && k == 1 && ((dl[0] & kHeadCut) != 0u || !(at(1) <= second_tol))) return false;
   return cayley_converged_hist(at(k), k > 0 ? at(k - 1) : 0.f, k > 1 ? at(k - 2) : 0.f, k > 1 ? 2 : k, tol);
 }
 
@@ -488,7 +493,7 @@ struct EpiCayleyIter {
   const float* bscale = nullptr;  // acc is scaled by bscale[4 * batch + 3] when given (Cayley Adam)
   static constexpr bool kSwap = true;  // four consecutive columns of a row per lane: 16-byte accesses
   __device__ __forceinline__ bool skip(int batch) const {
-    if (it == 0 || !cayley_converged(delta + (int64_t)batch * max_iters, it - 1, tol, second_tol)) return false;
+    if (it == 0 || !cayley_converged<kF16>(delta + (int64_t)batch * max_iters, it - 1, tol, second_tol)) return false;
     // a zero change counts as converged: later launches return too
     if (blockIdx.x == 0 && threadIdx.x == 0) delta[(int64_t)batch * max_iters + it] = 0u;
     return true;
@@ -622,7 +627,7 @@ __global__ __launch_bounds__(TL::NT) void cayley_iterate_kernel(GemmShape g, Epi
     return (unsigned)__builtin_amdgcn_readfirstlane((int)__hip_atomic_load(p, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
   };
 
-  if (cayley_converged_now(delta, it0 - 1, epi.tol)) return;
+  if (cayley_converged_now<EpiCayleyIter<TL>::kF16>(delta, it0 - 1, epi.tol)) return;
   int it = it0, own = blockIdx.x;  // wave 0: the open iteration, the next of this workgroup's tiles in it
   bool looked = false;           // ... has just found a tile of somebody else's: look for the next one at once
   // tile t of iteration `it`, if nobody has it (wave 0)
@@ -664,7 +669,7 @@ __global__ __launch_bounds__(TL::NT) void cayley_iterate_kernel(GemmShape g, Epi
       }
       looked = false;
       __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
-      if (it + 1 == epi.max_iters || cayley_converged_now(delta, it, epi.tol)) return -1;
+      if (it + 1 == epi.max_iters || cayley_converged_now<EpiCayleyIter<TL>::kF16>(delta, it, epi.tol)) return -1;
       ++it;
       own = blockIdx.x;
     }
