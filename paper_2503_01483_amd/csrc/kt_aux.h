@@ -910,7 +910,11 @@ __global__ __launch_bounds__(256, (NV4 <= 4 ? 4 : NV4 <= 16 ? 3 : 2)) void quant
                                                                 float* __restrict__ err_asym,
                                                                 unsigned long long* __restrict__ success) {
   __shared__ __align__(16) unsigned hist_all[4][2048];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, batch = blockIdx.y;
+  // fp32 rows that do not fill the registers: the wave's number, and all addresses that follow from it, in scalar registers.  Rows of 2048 < d < 4096 spill 10
+  // registers instead of 52, of 4096 < d < 8192 83 instead of 181.  us, kernel, radix select alone / histogram / this: 8192 rows of 2176 63 / 59 / 42, 3072 69 /
+  // 71 / 49, 3968 81 / 89 / 70; 4096 rows of 5120 101 / 97 / 92, 6144 108 / 111 / 105, 7168 118 / 126 / 119.  (bf16 rows of 5120 are slower for it, 91 / 95.)
+  const int tid_wave = threadIdx.x >> 6, wave = sizeof(TX) == 4 && !FULL ? __builtin_amdgcn_readfirstlane(tid_wave) : tid_wave;
+  const int lane = threadIdx.x & 63, batch = blockIdx.y;
   unsigned* hist = hist_all[wave];
   // Rows of this wave whose largest magnitude shrank: one atomic per workgroup, all of them on one word, 10 ns each (per wave / this, us, call of
   // 32768 rows of 256: 231 / 95, of 1024: 291 / 163, of 4096: 1090 / 1054; 4096 rows of 256: 67 / 31).
