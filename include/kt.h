@@ -101,11 +101,11 @@ size_t kt_workspace_bytes(kt_op op, int64_t batch, int64_t n, int64_t d, kt_dtyp
  * Y is consumed in the forward GEMM's epilogue.  bf16, with dR: the tiles of a token row exchange the row's moments inside
  * that launch and write dL/dY themselves, with either size of workspace.  (The launch makes progress with any number of
  * compute units to itself; with fewer than a part of a row's tiles, as on a stream of eight units, it waits in vain
- * once and makes tiles a second time.)  Outside of that (a few tokens, d > 8192 with some sizes), and for the pooled loss,
- * Y is for the backward pass either KEPT by that epilogue (fp32, token-minor, 4 n d bytes of workspace per problem) and dL/dY computed
+ * once and makes tiles a second time.)  Outside of that (fewer than 64 tokens, up to 256 with d > 2048, d > 8192, from d > 1408
+ * on a last round of tiles for few rows), and for the pooled loss, Y is for the backward pass either KEPT by that epilogue (fp32, token-minor, 4 n d bytes of workspace per problem) and dL/dY computed
  * from it entry by entry, or RECOMPUTED by a second GEMM whose epilogue forms dL/dY: the first when
  * the workspace handed in has the room (kt_workspace_bytes(KT_OP_LOSS_GRAD) asks for it while Y is at
- * most 64 GiB), the second otherwise (KT_OP_LOSS_GRAD_RECOMPUTE is the smaller size).  Both give the
+ * most 64 GiB, also for the calls above that leave it unused), the second otherwise (KT_OP_LOSS_GRAD_RECOMPUTE is the smaller size).  Both give the
  * same bits: dL/dY comes from the same fp32 accumulators through the same arithmetic.  dL/dY exists
  * only as the token-minor scratch operand of the last GEMM, which reads X itself in place.  fp32 X: Y is
  * written as rows, dL/dY over it, and the two sizes are one.
@@ -118,8 +118,9 @@ size_t kt_workspace_bytes(kt_op op, int64_t batch, int64_t n, int64_t d, kt_dtyp
  *  d        multiple of 128, <= 16384.   1 <= n <= 2^22, any value (tail rows are masked).
  *  loss     [batch] fp32, written.
  *  row_kurt [batch][n] fp32 or NULL.
- *  dR       [batch][d][d] fp32 or NULL (NULL: loss only, the backward GEMMs are skipped; fp32 calls of many rows then take their
- *           row sums in the forward GEMM's order, and loss and row_kurt can differ in the last bits from those of a call with dR).
+ *  dR       [batch][d][d] fp32 or NULL (NULL: loss only, the backward GEMMs are skipped.  Loss and row_kurt can then differ in the last
+ *           bits from those of a call with dR: fp32 calls of many rows take their row sums in the forward GEMM's order, and bf16
+ *           calls merge the moments of 128 features where one that exchanges them merges those of a tile, 128 or 256).
  *  A row without spread (m2 <= 1e-10 of its mean square: sigma below 1e-5 of the mean, which fp32
  *  products cannot resolve) counts with kappa = 0 and contributes no gradient.  Above that the row
  *  values carry an error of about 1e-6 |mean| / sigma on top of the path tolerance.
@@ -166,11 +167,13 @@ kt_status kt_pooled_kurtosis_loss_grad(const void* X, int64_t ldx, const void* R
  * rho that is estimated from them (over two steps, d_k / d_k-2 = rho^2, once three are there: the
  * even and odd terms of the series can have different patterns), and the iterate is accepted
  * when four times the bound d_k rho / (1 - rho) on its distance to the limit is below 3e-7, or
- * when the changes are small (<= 2e-5) and have stopped shrinking (the rounding floor).  It
+ * when the changes are small (<= 2e-5) and have stopped shrinking (the rounding floor).  For d >= 1024 the second iterate has
+ * to satisfy d_2 <= 5e-4 / sqrt(d) as well, and none of the first displacement may have overflowed fp16 (it can where rows of R are longer than two).  It
  * contracts when (lr/2)||A||_2 < 1 and the library enqueues at most 32 iterations (enough up to
  * about 0.55).  No learning-rate
  * clamp is applied: the caller chooses lr.  For d >= 1024 the d^3 products run on the
- * 16-bit matrix cores as three-term fp16 products (heads and tails, 22 bits of a value).
+ * 16-bit matrix cores as three-term fp16 products (heads and tails, 22 bits of a value); the change of the second iteration,
+ * - (lr/2) A (Z_1 - R), is one of heads alone (11 bits of a change that small; a third iteration takes all of it in three terms again).
  *
  *  R        [batch][d][d] fp32, in/out (master copy).  d multiple of 128, <= 16384.
  *  dR       [batch][d][d] fp32.  R and dR 16-byte aligned.
@@ -280,7 +283,7 @@ kt_status kt_rotate_fakequant_int4(const void* X, int64_t ldx, const void* R, in
  *   Y         [batch][n][d] fp32: receives the rotated activations, or NULL (then they live in
  *             the workspace).  Every output pointer may be NULL.
  * Y is materialised (this is an evaluation tool, not the training step): one GEMM pass, then one
- * wave per token with the row in registers (radix select on the bit patterns for the quantile).
+ * wave per token with the row in registers (the quantile from a histogram and a list of the few values around it; exact).
  * d <= 8192.  The order in which y is summed depends on the call's size as in kt_rotate_fakequant_int4.
  * Workspace: kt_workspace_bytes(KT_OP_QUANT_METRICS, ...) (sized for Y == NULL: the rotated rows then
  * pass through an fp32 staging slice of at most 1 GiB, a few problems or token rows at a time).
