@@ -31,8 +31,7 @@ KERNEL_NAMES_ONE = {0: "row_sync_kernel<bf16 256x256, RowLossGrad> (forward + ro
 # Fabric-side bytes per launch (rocprofv3 --pmc FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0, calibrated on a 1 GiB
 # device copy; see profiles/c3_gemm_counters.md).  Counters need a profiler run of their own, so the
 # figures measured for the default workload are carried here as constants; other workloads report null.
-MEASURED_TRAFFIC_BYTES = {"C3": {"recompute": {0: (6.00 + 0.0625) * 2**30, 1: (6.01 + 1.0) * 2**30, 2: (6.00 + 0.0625) * 2**30},
-                                 "keep": {0: (6.03 + 2.06) * 2**30, 2: (6.00 + 0.0625) * 2**30}}}
+MEASURED_TRAFFIC_BYTES = {"C3": {0: (6.08 + 1.06) * 2**30, 2: (6.10 + 0.0625) * 2**30}}
 CPU_SAMPLE_ROWS = {"C1": 2048, "C2": 32768, "C3": 16384, "C4": 131072, "C5": 4096}
 
 
@@ -303,7 +302,7 @@ def main():
                           "achieved": round(fq_bytes / (ms * 1e-3) / 1e9, 1), "peak": 8000.0, "unit": "GB/s",
                           "frac": round(fq_bytes / (ms * 1e-3) / 1e9 / 8000.0, 4), "bytes_per_launch": fq_bytes,
                           "traffic": None} if (bf16 and d == 128) else
-                         {"bound": "mfma", "kernel": "whole call (gemm_nt_kernel<EpiStore> into the fp32 staging buffer + quant_rows_kernel)",
+                         {"bound": "mfma", "kernel": "whole call (row_sync_kernel<RowQuant>; where that is slower gemm_nt_kernel<EpiStore> into the fp32 staging buffer + quant_rows_kernel)",
                           "achieved": round(flops_call / (ms * 1e-3) / 1e12, 1), "peak": peak_call, "unit": "TFLOP/s",
                           "frac": round(flops_call / (ms * 1e-3) / 1e12 / peak_call, 4), "flops_per_launch": flops_call,
                           "traffic": None}),
@@ -389,8 +388,7 @@ def main():
                     "achieved": round(kern[dom]["tflops"], 2), "peak": peak, "unit": "TFLOP/s",
                     "frac": round(kern[dom]["tflops"] / peak, 4), "avg_launch_ms": round(kern[dom]["avg_ms"], 4),
                     "flops_per_launch": flops_launch,
-                    "traffic": MEASURED_TRAFFIC_BYTES.get(args.config, {}).get("keep" if keep else "recompute", {}).get(dom)
-                    if args.n is None and not pooled and not one_launch else None,
+                    "traffic": MEASURED_TRAFFIC_BYTES.get(args.config, {}).get(dom) if args.n is None and one_launch else None,
                     "traffic_source": "carried from profiles/c3_gemm_counters.md (rocprofv3 --pmc runs of this command); "
                                       "not measured in this run"}
     names = {0: "fused_pass_ms" if fused else "fwd_moments_grad_ms" if one_launch else ("fwd_moments_keep_y_ms" if keep else "fwd_moments_ms"),

@@ -346,8 +346,8 @@ __global__ __launch_bounds__(256) void splitk_reduce_kernel(const float* __restr
 }
 
 // ---- fp32 products on the 16-bit matrix cores: A B^T ~ A_hi B_hi^T + A_hi B_lo^T + A_lo B_hi^T
-// in fp16 heads and tails (split_f16: 22 bits of a value down to 2^-17 of the operand's largest), written as ONE GEMM with K tripled: the left operand is stored as [hi | hi | lo]
-// (3 d wide), the right one as [hi | lo | hi].  Why fp16 and not bf16 (16 bits of a value, no scales): the retraction of a rotation
+// in fp16 heads and tails (split_f16: 22 bits of a value down to 2^-17 of the operand's largest), as ONE GEMM with K tripled: operands are stored as [hi | lo]
+// (2 d wide), and gemm_mainloop walks A hi, hi, lo and B hi, lo, hi.  Why fp16 and not bf16 (16 bits of a value, no scales): the retraction of a rotation
 // near the identity left max |R^T R - I| at 1e-6 with bf16, from the heads' and tails' own rounding.  fp16 has the range of a
 // matrix's entries only around their largest, so each operand is multiplied by a power of two first (exact).  What lies 2^-40 below the
 // largest is gone: it shows where a product keeps such rows apart, in the momentum of Cayley Adam at R = I (elsewhere R mixes the rows).
@@ -891,9 +891,9 @@ __device__ __forceinline__ unsigned block_umin_256(unsigned v, unsigned* red4) {
 // One WAVE per token row, the row in registers (NV4 float4 per lane: d <= 256 NV4; FULL: d = 256 NV4, no
 // bounds tests), no workgroup barrier: the four waves of a workgroup work on four rows independently, all
 // loads of a row are in flight at once, and the reductions are wave shuffles.  The quantile needs two order
-// statistics of |y|: a radix select on the bit patterns (integer work, bit-exact) in three rounds of 11, 11
-// and 9 bits, each a histogram of up to 2048 bins that the wave keeps in LDS (one LDS atomic per value that
-// still matches the bits decided so far; in the later rounds whole 256-value pieces are skipped).
+// statistics of |y|: a histogram of equal steps and a list of the few values around them, or, where that list is too long, a
+// radix select on the bit patterns in three rounds of 11, 11 and 9 bits; exact either way.  Histograms have up to 2048 bins
+// that the wave keeps in LDS (later rounds: one LDS atomic per value that still matches; whole 256-value pieces are skipped).
 // grid = (row workgroups, batch); a wave walks several rows.  Y [batch][n][d] fp32.
 // Error sums: the difference y - q s as one fused multiply-add in fp32 (exact before its single rounding),
 // squares summed four at a time in fp32 and then in fp64; the asymmetric difference, whose terms cancel
